@@ -260,14 +260,16 @@ def _unpack(Z, n):
 
 
 def _pair_masks(n, k, seed):
-    """Rows as a program draws them: (empty, full), then complementary pairs by ascending size. Large members have
-    each player with probability s / n, small ones s players drawn with replacement."""
+    """Rows as a program draws them: (empty, full), then complementary pairs by ascending size of the smaller member,
+    which comes first. Large members have each player with probability s / n, small ones s players drawn with
+    replacement."""
     gen = torch.Generator(device=DEV).manual_seed(seed * 1009 + 5)
     size, w = _plan(n, k)
     W = (n + 63) // 64
     Z = torch.empty((k // 2, 2, W), dtype=torch.int64, device=DEV)
     Z[0, 0] = 0
     full = _pack(torch.ones((1, n), dtype=torch.bool, device=DEV))[0]
+    count = []
     step = max(1, 200_000_000 // n)
     for at in range(0, len(size), step):
         s = torch.from_numpy(size[at:at + step]).to(DEV)
@@ -277,7 +279,11 @@ def _pair_masks(n, k, seed):
         bits[row, torch.randint(n, (len(row),), generator=gen, device=DEV)] = True
         if few < len(s):
             bits[few:] = torch.rand((len(s) - few, n), generator=gen, device=DEV) < (s[few:] / n).float()[:, None]
+        got = bits.sum(1)
+        bits ^= (2 * got > n)[:, None]
+        count.append(torch.minimum(got, n - got))
         Z[1 + at:1 + at + len(s), 0] = _pack(bits)
+    Z[1:, 0] = Z[1:, 0][torch.sort(torch.cat(count), stable=True).indices]
     Z[:, 1] = Z[:, 0] ^ full
     weight = torch.zeros((k // 2, 2), dtype=torch.float32, device=DEV)
     weight[1:] = torch.from_numpy(w).to(DEV)[:, None]
