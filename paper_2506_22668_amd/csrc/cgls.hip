@@ -410,8 +410,319 @@ __global__ void pair_sizes_kernel(const int32_t* sz, int64_t R, int32_t thr, int
   if (r > 0 && sz[2 * (r - 1)] > c) atomicExch((unsigned long long*)&mail[1], 1ull);
 }
 
+// ---- small games: an iteration in two launches ----
+// With a few thousand players and rows an iteration of the loop above is seven launches of 3 to 11 us that each
+// start by finishing the reduction of the one before, so what bounds it is the chain of launches. Here every
+// workgroup redoes the vector work of all n (R) entries itself, straight into the LDS copy that its products gather
+// from (a few dozen KB per workgroup, from L2), and only the owner of a slice writes it back. What is left is
+//   forward: mean and |P s|^2 of the last adjoint, the stopping rule, x and u | d = (rows) u
+//   adjoint: |v|^2 and theta, the residual, h                                 | s = (rows)^T h
+// A kernel never writes what another workgroup of it may still read: u and the residual alternate between two
+// buffers, the scalars between two records (forward reads the adjoint's and writes its own, and the other way
+// round). Every operation, and the order of every sum, is that of the loop above (a sum over a vector goes lane by
+// lane within 64 entries, then 64 by 64 within 256, then over the 256s), so the results are the same to the bit: CGLS
+// turns the last bit of a product into the sixth digit of a score within 200 steps of a badly conditioned game.
+// 3,001 players, 4,000 pairs, 200 iterations: 7.55 -> 3.84 ms (5.68 with the lanes' sums through LDS instead of
+// ds_wave_sum; 7.17 with a workgroup on consecutive rows, whose dense end then sets the time).
+constexpr int kSmallThreads = 1024;
+constexpr int64_t kSmallPlayers = 4096;  // at most this many players ...
+constexpr int64_t kSmallRows = 8192;     // ... and rows of the forward matrix (pairs, or rows): an LDS copy of 65 KB
+constexpr int kSmallPitch = 65;          // doubles per 64-column word of the LDS copy: words start in different banks
+
+enum SmallScalar { kGamma, kTheta, kDone, kIters, kRel, kGamma0, kSumU, kBufU, kSmallScalars };
+
+struct SmallArgs {
+  int n, R;
+  int64_t Wf, stride_f, Wa;        // forward: rows of Z, Wf words of each, stride_f words apart; adjoint: Wa words per row
+  const uint64_t *Z, *Zt;
+  const double *sqw, *t;           // [k]
+  double *x, *s, *d;
+  double *u[2], *r[2];
+  double *rec_f, *rec_a;           // scalar records of the two kernels
+  double tol;
+};
+
+// Sum over a vector of up to N * kSmallThreads entries, entry tid + N' * kSmallThreads in v[N'] (zero past its end), in
+// every thread. part: LDS, 16 N doubles of its own. One barrier.
+template <int N>
+__device__ __forceinline__ double small_sum(const double (&v)[N], double* part) {
+  const int tid = threadIdx.x, lane = tid & 63;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const double a = ds_wave_sum(v[i]);
+    if (lane == 0) part[i * (kSmallThreads / 64) + (tid >> 6)] = a;
+  }
+  __syncthreads();
+  double p = 0.0;
+  if (lane < N * (kSmallThreads / 256)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p += part[4 * lane + i];
+  }
+  return ds_wave_sum(p);
+}
+
+// index of the lowest set bit, 0xffffffff if there is none (what the instruction gives; __ffs adds a select)
+__device__ __forceinline__ uint32_t first_bit(uint32_t x) {
+  uint32_t r;
+  asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(x));
+  return r;
+}
+// Sum of x[j] over the set bits j of w in ascending order; x[64] is zero (the spare entry of the pitch). What bounds the
+// products is the instructions per set bit, so a bit costs one find-first per half, one three-way minimum that sends
+// an empty word to the zero entry, and the 64-bit w & (w - 1); eight LDS reads are in flight.
+__device__ __forceinline__ double small_word_sum(uint64_t w, const double* x) {
+  double a = 0.0;
+  while (w) {
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const uint32_t lo = first_bit((uint32_t)w), hi = first_bit((uint32_t)(w >> 32)) | 32u;
+      const uint32_t bit = lo < hi ? lo : hi;
+      v[q] = x[bit < 64u ? bit : 64u];
+      w &= w - 1;  // 0 stays 0
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) a += v[q];
+  }
+  return a;
+}
+// Sum of xs (pitched in LDS) over the set bits of one row of at most 128 words: a wave, lanes over words; w0 and w1 are
+// the lane's words (word `lane` and word 64 + `lane`, zero past the row's end).
+template <bool TWO>
+__device__ __forceinline__ double small_row_sum(uint64_t w0, uint64_t w1, const double* xs) {
+  const int lane = threadIdx.x & 63;
+  double acc = small_word_sum(w0, xs + lane * kSmallPitch);
+  if (TWO) acc += small_word_sum(w1, xs + (64 + lane) * kSmallPitch);
+  return ds_wave_sum(acc);
+}
+__device__ __forceinline__ uint64_t small_word(const uint64_t* row, int64_t wd, int64_t W, int64_t cols) {
+  if (wd >= W) return 0ull;
+  return row[wd] & (wd == W - 1 && (cols & 63) ? ((1ull << (cols & 63)) - 1ull) : ~0ull);
+}
+
+// mode 0: a step; 1: the first one (u = s, x = 0); 2: only the stopping rule (one workgroup). ub: which u is current.
+template <bool PAIRED, int N>   // N * kSmallThreads >= n
+__global__ __launch_bounds__(kSmallThreads) void small_forward_kernel(SmallArgs a, int ub, int mode) {
+  extern __shared__ double us[];
+  __shared__ double part[3][N * (kSmallThreads / 64)];
+  const int tid = threadIdx.x, lane = tid & 63;
+  // rows ascend by size: a workgroup takes rows a grid apart, so that the dense ones are spread over all of them
+  const int wave0 = (tid >> 6) * (int)gridDim.x + (int)blockIdx.x, waves = (int)gridDim.x * (kSmallThreads / 64);
+  // everything that does not depend on another load is requested first
+  const uint64_t* const row0 = a.Z + (int64_t)(wave0 < a.R ? wave0 : a.R - 1) * a.stride_f;
+  uint64_t w0 = small_word(row0, lane, a.Wf, a.n);
+  double sv[N], uo[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int j = tid + i * kSmallThreads;
+    sv[i] = j < a.n ? a.s[j] : 0.0;
+    uo[i] = j < a.n && mode != 1 ? a.u[ub][j] : 0.0;
+  }
+  if (tid < (int)a.Wf) us[tid * kSmallPitch + 64] = 0.0;
+  const double gamma = a.rec_a[kGamma], theta = a.rec_a[kTheta], gamma0 = a.rec_a[kGamma0];
+  if (a.rec_a[kDone] != 0.0) {
+    if (blockIdx.x == 0 && tid < kSmallScalars) a.rec_f[tid] = a.rec_a[tid];
+    return;
+  }
+  const double mean = small_sum<N>(sv, part[0]) / (double)a.n;
+  double sq[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int j = tid + i * kSmallThreads;
+    sv[i] = sv[i] - mean;
+    sq[i] = j < a.n ? sv[i] * sv[i] : 0.0;
+  }
+  const double g = small_sum<N>(sq, part[1]);
+  const double rel = mode == 1 ? 1.0 : sqrt(g) / sqrt(gamma0);
+  const bool stop = mode == 1 ? !(g > 0.0) : rel <= a.tol;
+  const bool step = mode == 1 || (!stop && mode != 2);   // (u_0 = s_0 is part of the result even if nothing follows)
+  const double beta = mode == 1 || !(gamma > 0.0) ? 0.0 : g / gamma;
+  double U = 0.0;
+  if (step) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int j = tid + i * kSmallThreads;
+      sv[i] = j < a.n ? sv[i] + beta * uo[i] : 0.0;
+      if (j < a.n) us[(j >> 6) * kSmallPitch + (j & 63)] = sv[i];
+    }
+    U = small_sum<N>(sv, part[2]);   // (its barrier also completes us for the products)
+  }
+  if (blockIdx.x == 0 && tid == 0) {
+    a.rec_f[kGamma] = step ? g : gamma;
+    a.rec_f[kTheta] = theta;
+    a.rec_f[kDone] = stop ? 1.0 : 0.0;
+    a.rec_f[kIters] = a.rec_a[kIters] + (mode == 1 ? 0.0 : 1.0);
+    a.rec_f[kRel] = rel;
+    a.rec_f[kGamma0] = mode == 1 ? g : gamma0;
+    a.rec_f[kSumU] = U;
+    a.rec_f[kBufU] = (double)(step ? ub ^ 1 : ub);
+  }
+  if (!step) return;
+  for (int i = wave0; i < a.R; i += waves) {
+    if (i != wave0) w0 = small_word(a.Z + (int64_t)i * a.stride_f, lane, a.Wf, a.n);
+    const double d = small_row_sum<false>(w0, 0ull, us);
+    if (lane == 0) a.d[i] = d;
+  }
+  // the slice of x and u that this workgroup owns
+  const int per = (a.n + (int)gridDim.x - 1) / (int)gridDim.x, own0 = (int)blockIdx.x * per, own1 = own0 + per;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int j = tid + i * kSmallThreads;
+    if (j < a.n && j >= own0 && j < own1) {
+      a.x[j] = mode == 1 ? 0.0 : a.x[j] + theta * uo[i];
+      a.u[ub ^ 1][j] = sv[i];
+    }
+  }
+}
+
+// first: the residual is still the right-hand side's, no step to take off it. rb: which residual is current.
+template <bool PAIRED, int N>   // N * kSmallThreads >= R
+__global__ __launch_bounds__(kSmallThreads) void small_adjoint_kernel(SmallArgs a, int rb, int first) {
+  extern __shared__ double hs[];
+  __shared__ double part[N * (kSmallThreads / 64)];
+  const int tid = threadIdx.x, lane = tid & 63;
+  // rows ascend by size: a workgroup takes rows a grid apart, so that the dense ones are spread over all of them
+  const int wave0 = (tid >> 6) * (int)gridDim.x + (int)blockIdx.x, waves = (int)gridDim.x * (kSmallThreads / 64);
+  const uint64_t* const row0 = a.Zt + (int64_t)(wave0 < a.n ? wave0 : a.n - 1) * a.Wa;
+  uint64_t w0 = small_word(row0, lane, a.Wa, a.R), w1 = small_word(row0, 64 + lane, a.Wa, a.R);
+  if (tid < (int)a.Wa) hs[tid * kSmallPitch + 64] = 0.0;
+  double d[N], w[N], r0[N], r1[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int q = tid + i * kSmallThreads;
+    const bool in = q < a.R;
+    w[i] = in ? a.sqw[PAIRED ? 2 * q : q] : 0.0;
+    d[i] = in && !first ? a.d[q] : 0.0;
+    r1[i] = 0.0;
+    if (first) {
+      r0[i] = in ? w[i] * a.t[PAIRED ? 2 * q : q] : 0.0;
+      if (PAIRED && in) r1[i] = a.sqw[2 * q + 1] * a.t[2 * q + 1];
+    } else {
+      r0[i] = in ? a.r[rb][PAIRED ? 2 * q : q] : 0.0;
+      if (PAIRED && in) r1[i] = a.r[rb][2 * q + 1];
+    }
+  }
+  double theta = 0.0;
+  if (!first) {
+    const double gamma = a.rec_f[kGamma], U = a.rec_f[kSumU];
+    if (a.rec_f[kDone] != 0.0) {
+      if (blockIdx.x == 0 && tid < kSmallScalars) a.rec_a[tid] = a.rec_f[tid];
+      return;
+    }
+    double vv[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const double v0 = w[i] * d[i], v1 = w[i] * (U - d[i]);
+      vv[i] = PAIRED ? v0 * v0 + v1 * v1 : v0 * v0;
+    }
+    const double delta = small_sum<N>(vv, part);
+    const bool null_dir = !(delta > 0.0);   // a direction in the null space ends the iteration with theta = 0
+    theta = null_dir ? 0.0 : gamma / delta;
+    if (blockIdx.x == 0 && tid < kSmallScalars)
+      a.rec_a[tid] = tid == kTheta ? theta : tid == kDone ? (null_dir ? 1.0 : 0.0) : tid == kIters && null_dir ? a.rec_f[tid] + 1.0 : a.rec_f[tid];
+    if (null_dir) return;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      r0[i] -= theta * (w[i] * d[i]);
+      if (PAIRED) r1[i] -= theta * (w[i] * (U - d[i]));
+    }
+  } else if (blockIdx.x == 0 && tid < kSmallScalars) {
+    a.rec_a[tid] = 0.0;
+  }
+  const int per = (a.R + (int)gridDim.x - 1) / (int)gridDim.x, own0 = (int)blockIdx.x * per, own1 = own0 + per;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int q = tid + i * kSmallThreads;
+    if (q < a.R) {
+      hs[(q >> 6) * kSmallPitch + (q & 63)] = w[i] * (PAIRED ? r0[i] - r1[i] : r0[i]);
+      if (q >= own0 && q < own1) {
+        a.r[rb ^ 1][PAIRED ? 2 * q : q] = r0[i];
+        if (PAIRED) a.r[rb ^ 1][2 * q + 1] = r1[i];
+      }
+    }
+  }
+  __syncthreads();
+  for (int j = wave0; j < a.n; j += waves) {
+    if (j != wave0) {
+      const uint64_t* row = a.Zt + (int64_t)j * a.Wa;
+      w0 = small_word(row, lane, a.Wa, a.R);
+      w1 = small_word(row, 64 + lane, a.Wa, a.R);
+    }
+    const double sj = a.Wa > 64 ? small_row_sum<true>(w0, w1, hs) : small_row_sum<false>(w0, 0ull, hs);
+    if (lane == 0) a.s[j] = sj;
+  }
+}
+
+// the last step's x += theta u is folded into the output (theta is 0 if no step was taken)
+__global__ void small_final_kernel(SmallArgs a, const double* rec, const float* y, float* phi) {
+  const int j = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (j >= a.n) return;
+  const double delta = (double)y[1] - (double)y[0];
+  phi[j] = (float)(a.x[j] + rec[kTheta] * a.u[(int)rec[kBufU]][j] + delta / (double)a.n);
+}
+
 constexpr int64_t kHybridMinPlayers = 4096;  // below this the plain bit walk is already cheap
 constexpr int32_t kDenseDiv = 64;            // pair rows with more than n / 64 players are multiplied as bitmaps
+
+// The loop of the small games: see the kernels above. Zt: the transposed copy of the forward matrix's rows.
+template <bool PAIRED>
+int solve_small(ds_ctx* ctx, const SmallArgs& a, int grid, int max_iter, const float* y, float* phi, int* iters_out,
+                double* relres_out, bool* converged_out) {
+  hipStream_t st = ctx->stream;
+  const unsigned lds_f = (unsigned)(a.Wf * kSmallPitch * 8), lds_a = (unsigned)(a.Wa * kSmallPitch * 8);
+  static_assert(kSmallPlayers <= 4 * kSmallThreads && kSmallRows <= 8 * kSmallThreads, "entries per thread");
+  void (*const fwd)(SmallArgs, int, int) = a.n <= 2 * kSmallThreads ? small_forward_kernel<PAIRED, 2> : small_forward_kernel<PAIRED, 4>;
+  void (*const adj)(SmallArgs, int, int) = a.R <= 2 * kSmallThreads   ? small_adjoint_kernel<PAIRED, 2>
+                                           : a.R <= 4 * kSmallThreads ? small_adjoint_kernel<PAIRED, 4>
+                                                                      : small_adjoint_kernel<PAIRED, 8>;
+  if (lds_a > 48 * 1024) DS_HIP(ctx, hipFuncSetAttribute((const void*)adj, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_a));
+  int ub = 0, rb = 0;   // (a run that has stopped leaves both buffers alone: the record says which u is the last)
+  auto adjoint = [&](int first) {
+    hipLaunchKernelGGL(adj, dim3(grid), dim3(kSmallThreads), lds_a, st, a, rb, first);
+    rb ^= 1;
+  };
+  auto forward = [&](int mode) {
+    hipLaunchKernelGGL(fwd, dim3(mode == 2 ? 1 : grid), dim3(kSmallThreads), lds_f, st, a, ub, mode);
+    ub ^= 1;
+  };
+  adjoint(1);
+  forward(1);
+  DS_TRY(ds_kernel_mark(ctx, 3, 0));
+  // The scalars come back every kBurst iterations and are looked at while the next burst is already queued: what runs
+  // after the iteration that stopped only copies them on.
+  constexpr int kBurst = 16;
+  hipEvent_t seen[2] = {ctx->fork2_ev, ctx->join2_ev};
+  int launched = 0, bursts = 0, looked = 0;
+  const double* rec = nullptr;
+  auto look = [&]() -> int {
+    DS_HIP(ctx, hipEventSynchronize(seen[looked & 1]));
+    rec = (const double*)(ctx->h_mail + 16 * (looked & 1));
+    ++looked;
+    return DS_OK;
+  };
+  while (launched < max_iter && !(rec && rec[kDone] != 0.0)) {
+    const int burst = max_iter - launched < kBurst ? max_iter - launched : kBurst;
+    for (int b = 0; b < burst; ++b) {
+      adjoint(0);
+      forward(launched + b + 1 == max_iter ? 2 : 0);   // the last iteration allowed takes no further step
+    }
+    launched += burst;
+    DS_HIP(ctx, hipGetLastError());
+    DS_HIP(ctx, hipMemcpyAsync(ctx->h_mail + 16 * (bursts & 1), a.rec_f, kSmallScalars * 8, hipMemcpyDeviceToHost, st));
+    DS_HIP(ctx, hipEventRecord(seen[bursts & 1], st));
+    ++bursts;
+    if (bursts - looked == 2) DS_TRY(look());
+  }
+  while (looked < bursts) DS_TRY(look());
+  DS_TRY(ds_kernel_mark(ctx, 3, 1));
+  hipLaunchKernelGGL(small_final_kernel, dim3(nblocks(a.n, 256)), dim3(256), 0, st, a, a.rec_f, y, phi);
+  DS_HIP(ctx, hipGetLastError());
+  DS_HIP(ctx, hipStreamSynchronize(st));
+  *iters_out = (int)rec[kIters];
+  *relres_out = rec[kGamma0] > 0.0 ? rec[kRel] : 0.0;
+  *converged_out = rec[kDone] != 0.0;
+  return DS_OK;
+}
 
 }  // namespace
 
@@ -427,7 +738,7 @@ size_t ds_cgls_arena_bytes(int64_t n, int64_t k) {
   const size_t hybrid = 3 * ds_align((size_t)n * KW * 8) + 4 * ds_align((n + 2) * 4) + 2 * ds_align((k + 2) * 4) +
                         ds_align(96 * (size_t)(n > k ? n : k)) + ((size_t)80 << 20) + tile_scratch +
                         4 * ds_scan_arena_bytes(n > k ? n + 1 : k + 1);
-  return hybrid + 2 * ds_align(k * 4) + 7 * ds_align(k * 8) + 4 * ds_align(n * 8) + 131072;
+  return hybrid + 2 * ds_align(k * 4) + 7 * ds_align(k * 8) + 5 * ds_align(n * 8) + 131072;
 }
 
 int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const float* w, const float* y, int paired,
@@ -460,6 +771,41 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
     return ds_fail(ctx, DS_EINTERNAL, "cgls: arena exhausted");
 
   DS_TRY(ds_row_prep(ctx, Z, k, n, w, y, sz, t, sqw, wc));
+
+  // Few players and few rows (from kHybridMinPlayers on the fixed-point products take over; more rows do not fit the
+  // LDS copy): an iteration in two launches.
+  static_assert(kHybridMinPlayers <= kSmallPlayers, "the small kernels hold one word of a forward row per lane");
+  if (n < kHybridMinPlayers && R <= kSmallRows) {
+    uint64_t* Zt = (uint64_t*)ds_arena_alloc(ctx, (size_t)n * RW * 8);
+    double* u1 = (double*)ds_arena_alloc(ctx, n * 8);
+    double* rec = (double*)ds_arena_alloc(ctx, 256);
+    if (!Zt || !u1 || !rec) return ds_fail(ctx, DS_EINTERNAL, "cgls: arena exhausted");
+    DS_TRY(ds_bit_transpose(ctx, Z, R, n, W, 0, paired ? 2 : 1, Zt));
+    DS_HIP(ctx, hipMemsetAsync(rec, 0, 256, st));
+    SmallArgs q;
+    q.n = (int)n; q.R = (int)R;
+    q.Wf = W; q.stride_f = paired ? 2 * W : W; q.Wa = RW;
+    q.Z = Z; q.Zt = Zt;
+    q.sqw = sqw; q.t = t;
+    q.x = a.x; q.s = a.s; q.d = a.d;
+    q.u[0] = a.u; q.u[1] = u1;
+    q.r[0] = a.r; q.r[1] = a.v;
+    q.rec_f = rec; q.rec_a = rec + 16;
+    q.tol = tol;
+    ctx->cgls_bytes_per_iter = 2.0 * (double)R * (double)W * 8.0;
+    const int64_t longest = n > R ? n : R;
+    int64_t grid = (longest + kSmallThreads / 64 - 1) / (kSmallThreads / 64);
+    if (grid > ctx->num_cus) grid = ctx->num_cus;
+    int it = 0;
+    double rel = 0.0;
+    bool converged = false;
+    DS_TRY(paired ? solve_small<true>(ctx, q, (int)grid, max_iter, y, phi, &it, &rel, &converged)
+                  : solve_small<false>(ctx, q, (int)grid, max_iter, y, phi, &it, &rel, &converged));
+    if (iters_out) *iters_out = it;
+    if (relres_out) *relres_out = rel;
+    if (!converged) return ds_fail(ctx, DS_ENOTCONV, "CGLS reached max_iter=%d with relative residual %.3e (tol %.1e)", max_iter, rel, tol);
+    return DS_OK;
+  }
 
   // ---- storage for the two products ----
   // Paired, size-sorted rows of a large game: the small members with at most n/div players become

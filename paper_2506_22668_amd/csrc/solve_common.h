@@ -154,3 +154,32 @@ __device__ __forceinline__ double ds_mm_sum(const int32_t* partial, int64_t rows
 // index lists of the set bits of rows (off = exclusive prefix sums of the row sizes)
 int ds_rows_to_csr(ds_ctx* ctx, const uint64_t* B, int64_t rows, int64_t cols, int64_t stride, int64_t row_first,
                    int64_t row_step, const int32_t* off, int32_t* idx);
+
+// Sum of a over the 64 lanes, the same value in every lane: the additions of `for (o = 32; o > 0; o >>= 1) a +=
+// __shfl_xor(a, o, 64)`, to the bit, without its LDS round trips (two ds_bpermute per step and double, each a wait of
+// some 100 cycles). Lanes 32 and 16 away are reached by the half and row swaps; from there on the values repeat
+// within a row of 16, so that rotations stand in for the lanes 8 and 4 away.
+__device__ __forceinline__ double ds_wave_sum(double a) {
+  auto swapped = [](double v, bool half, double& w) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const u2 l = half ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false) : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const u2 h = half ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false) : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    w = __hiloint2double((int)h.y, (int)l.y);
+    return __hiloint2double((int)h.x, (int)l.x);
+  };
+  double b;
+  a = swapped(a, true, b);    // a, b: the pair {x[l], x[l ^ 32]} in one order or the other
+  a += b;
+  a = swapped(a, false, b);
+  a += b;
+#define DS_DPP_ADD(ctrl)                                                                                              \
+  a += __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(a), ctrl, 0xf, 0xf, false),                     \
+                        __builtin_amdgcn_update_dpp(0, __double2loint(a), ctrl, 0xf, 0xf, false))
+  DS_DPP_ADD(0x128);   // row_ror:8
+  DS_DPP_ADD(0x124);   // row_ror:4
+  DS_DPP_ADD(0x4e);    // quad_perm [2,3,0,1]
+  DS_DPP_ADD(0xb1);    // quad_perm [1,0,3,2]
+#undef DS_DPP_ADD
+  return a;
+}

@@ -327,6 +327,27 @@ def test_cgls_matches_oracle(ctx_tiny, n, ns, paired):
         assert np.abs(got - solve.solve_lstsq(bits, w, y)).max() <= 1e-4 * np.abs(ref).max()
 
 
+# the two-launch iteration of small games: whole words and one column more, the most players it takes (4,095), as many
+# rows as its LDS copy holds (8,192 pairs, or rows) and one pair more (the general loop)
+@pytest.mark.parametrize("n,ns,paired", [(3, 6, 1), (64, 128, 1), (65, 130, 0), (1025, 514, 1), (4095, 300, 1), (4095, 131, 0),
+                                         (130, 16384, 1), (130, 16386, 1), (70, 8192, 0)])
+def test_cgls_small_games_step_by_step(ctx_tiny, n, ns, paired):
+    from paper_2506_22668_amd import Options, DS_SOLVER_CGLS
+    ctx, _ = ctx_tiny
+    Z, w, bits, y = _solve_inputs(n, ns, 300 + n)
+    args = (n, torch.from_numpy(Z.view(np.int64)).cuda(), torch.from_numpy(w).cuda(), torch.from_numpy(y).cuda())
+    for steps in (1, 6, 17):   # (the scalars come back every 16 steps)
+        say(f"cgls n={n} n_samples={ns} paired={paired} steps={steps}")
+        ref, it_ref, rel_ref = solve.solve_cgls(bits, w, y, tol=1e-9, max_iter=steps)
+        phi, rep, _ = ctx.solve(*args, Options(solver=DS_SOLVER_CGLS, tol=1e-9, max_iter=steps, paired=paired),
+                                allow_not_converged=True)
+        assert abs(rep.cgls_iterations - it_ref) <= 1 and rep.cgls_iterations <= steps
+        if it_ref == steps:
+            assert abs(rep.cgls_rel_residual - rel_ref) <= 1e-6 * rel_ref + 1e-12
+        # fp32 scores of an fp64 iteration: half an ulp each, and a step's rounding is far below it
+        assert np.abs(phi.cpu().numpy() - ref).max() <= 3e-7 * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("dense_div", [32, 1024, 65536])
 def test_cgls_dense_row_threshold_leaves_the_solution_alone(ctx_tiny, dense_div):
     """Which pair rows are multiplied as bitmaps on the matrix cores and which as index lists is a tuning choice:
