@@ -254,27 +254,32 @@ constexpr int kMmPlanes = 8;
 constexpr int kMmPlanePitch = kMmChunk + 16;         // LDS pitch of a plane: the eight planes start 16 bytes (4 banks) apart
 constexpr int64_t kMmMaxGroupCols = 1 << 20;         // 2^20 columns * 128 * 2^3 = 2^30: the int32 accumulators cannot overflow
 
-// slot: bit pattern of max |x| over the call (0 on entry; non-negative doubles order like their bit patterns)
-__global__ __launch_bounds__(256) void absmax_kernel(const double* x, int64_t n, unsigned long long* slot) {
+// max_parts[block] = bit pattern of the block's max |x| (non-negative doubles order like their bit patterns)
+__global__ __launch_bounds__(256) void absmax_kernel(const double* x, int64_t n, unsigned long long* max_parts) {
+  __shared__ unsigned long long wm[4];
   unsigned long long m = 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const unsigned long long b = (unsigned long long)__double_as_longlong(x[i]) & 0x7fffffffffffffffull;
     m = b > m ? b : m;
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long t = __shfl_xor(m, o, 64);
-    m = t > m ? t : m;
-  }
-  if ((threadIdx.x & 63) == 0 && m) atomicMax(slot, m);
+  ds_block_max_256(m, wm);
+  if (threadIdx.x == 0) max_parts[blockIdx.x] = m;
 }
 
 // The fixed-point form of a vector: scal[0] = the power of two that turns integer results back into the scale of x
-// (NaN if the vector holds a non-finite value: the products are then NaN everywhere). Two roles per thread:
+// (NaN if the vector holds a non-finite value: the products are then NaN everywhere). max |x| is the largest of the
+// `parts` partial maxima, which every workgroup goes through itself: with one atomic per workgroup on a single slot
+// instead, the kernel that wrote the vector spent 8 us on a thousand atomics. Two roles per thread:
 //  * digit planes of xp[0..n) (npad > 0): one thread per 4 plane positions (i = 0..3: columns 8 apart);
 //  * q64[i] = round(xq[i] * 2^f) for i < qlen (the index-tile products read these): four entries per thread.
-__global__ __launch_bounds__(256) void quantize_kernel(const double* xp, int64_t n, int64_t npad, const unsigned long long* slot,
-                                                       int8_t* D, double* scal, const double* xq, int64_t qlen, long long* q64) {
-  const double mx = __longlong_as_double((long long)*slot);
+__global__ __launch_bounds__(256) void quantize_kernel(const double* xp, int64_t n, int64_t npad, const unsigned long long* max_parts,
+                                                       int parts, int8_t* D, double* scal, const double* xq, int64_t qlen,
+                                                       long long* q64) {
+  __shared__ unsigned long long wm[4];
+  unsigned long long m = 0;
+  for (int i = threadIdx.x; i < parts; i += 256) m = max_parts[i] > m ? max_parts[i] : m;
+  ds_block_max_256(m, wm);
+  const double mx = __longlong_as_double((long long)m);
   const bool finite = mx < __longlong_as_double(0x7ff0000000000000ll);
   int e = 0;
   if (finite && mx > 0.0) frexp(mx, &e);   // mx < 2^e
@@ -443,12 +448,10 @@ __global__ __launch_bounds__(kMmWaves * 64) void bit_spmv_mm_kernel(const uint64
   }
 }
 
-// out[r] = (addend[r] or 0) + scal[0] * sum_d 256^d * (sum over the column groups of digit sum d); clears the
-// maximum slot for the next product if asked to
+// out[r] = (addend[r] or 0) + scal[0] * sum_d 256^d * (sum over the column groups of digit sum d)
 __global__ __launch_bounds__(256) void mm_reduce_kernel(const int32_t* partial, int64_t rows, int groups, const double* scal,
-                                                        const double* addend, double* out, unsigned long long* slot) {
+                                                        const double* addend, double* out) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r == 0 && slot) *slot = 0ull;
   if (r >= rows) return;
   const double val = ds_mm_sum(partial, rows, groups, r) * scal[0];
   out[r] = addend ? addend[r] + val : val;
@@ -591,24 +594,25 @@ int ds_bit_spmv_mm_prepare(ds_ctx* ctx, int64_t rows, int64_t cols, void* ws, ds
   return DS_OK;
 }
 
-int ds_vec_quantize(ds_ctx* ctx, const double* x_all, int64_t len_all, const ds_mm_plan* planes, const double* x_planes,
-                    const double* x_q, int64_t qlen, long long* q64, double* scal, int with_absmax) {
-  unsigned long long* slot = (unsigned long long*)(scal + 1);
-  int64_t mb = (len_all + 2047) / 2048;
-  if (mb > 2 * (int64_t)ctx->num_cus) mb = 2 * (int64_t)ctx->num_cus;
-  if (mb < 1) mb = 1;
-  if (with_absmax) hipLaunchKernelGGL(absmax_kernel, dim3((unsigned)mb), dim3(256), 0, ctx->stream, x_all, len_all, slot);
+int ds_vec_absmax(ds_ctx* ctx, const double* x, int64_t len, unsigned long long* max_parts, int parts) {
+  hipLaunchKernelGGL(absmax_kernel, dim3((unsigned)parts), dim3(256), 0, ctx->stream, x, len, max_parts);
+  DS_HIP(ctx, hipGetLastError());
+  return DS_OK;
+}
+
+int ds_vec_quantize(ds_ctx* ctx, const unsigned long long* max_parts, int parts, const ds_mm_plan* planes, const double* x_planes,
+                    const double* x_q, int64_t qlen, long long* q64, double* scal) {
   const bool with_planes = planes && planes->rows > 0;
   const int64_t npad = with_planes ? planes->npad : 0;
   const int64_t span = npad > qlen ? npad : qlen;
   hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)((span / 4 + 256) / 256)), dim3(256), 0, ctx->stream, x_planes,
-                     with_planes ? planes->cols : 0, npad, slot, with_planes ? planes->D : nullptr, scal, x_q, qlen, q64);
+                     with_planes ? planes->cols : 0, npad, max_parts, parts, with_planes ? planes->D : nullptr, scal, x_q, qlen, q64);
   DS_HIP(ctx, hipGetLastError());
   return DS_OK;
 }
 
 int ds_bit_spmv_mm_product(ds_ctx* ctx, const ds_mm_plan* p, const uint64_t* B, int64_t stride, int64_t row_first,
-                           int64_t row_step, const double* scal, const double* addend, double* out, int clear_slot) {
+                           int64_t row_step, const double* scal, const double* addend, double* out) {
   if (p->rows <= 0) return DS_OK;
   if (row_step * stride * 8 * 16 >= ((int64_t)1 << 32))
     return ds_fail(ctx, DS_EINTERNAL, "matrix-core product: rows of %lld bytes are too far apart", (long long)(row_step * stride * 8));
@@ -616,7 +620,7 @@ int ds_bit_spmv_mm_product(ds_ctx* ctx, const ds_mm_plan* p, const uint64_t* B, 
                      B, p->rows, p->cols, stride, row_first, row_step, p->D, p->npad, p->partial, p->cpg, p->n_chunks);
   if (out)
     hipLaunchKernelGGL(mm_reduce_kernel, dim3((unsigned)((p->rows + 255) / 256)), dim3(256), 0, ctx->stream, p->partial, p->rows,
-                       (int)p->groups, scal, addend, out, clear_slot ? (unsigned long long*)(scal + 1) : (unsigned long long*)nullptr);
+                       (int)p->groups, scal, addend, out);
   DS_HIP(ctx, hipGetLastError());
   return DS_OK;
 }

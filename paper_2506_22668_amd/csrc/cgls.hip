@@ -56,12 +56,12 @@ struct Vecs {
   double *x, *u, *s, *r, *v, *d, *h;  // n, n, n, k, k, R, R
   double* scal;
   double* part;      // [4 * kRed]
-  // fixed-point products only (else null): where the kernel that writes u (h) leaves the bit pattern of max |u| (max |h|)
-  // for the next forward (adjoint) product, which then needs no pass of its own over the vector
-  unsigned long long *slot_u, *slot_h;
+  // fixed-point products only (else null): where the kernel that writes u (h) leaves its workgroups' max |u| (max |h|)
+  // for the next forward (adjoint) product, which then needs no pass of its own over the vector. An iteration that has
+  // stopped leaves vector and maxima alone.
+  unsigned long long *max_u, *max_h;
   // fixed-point products inside the loop (fused != 0): the products leave their integer partial sums, and the loop's
-  // kernel that reads d (s) first adds them up itself, scales them by scal_f[0] (scal_a[0]) and clears the product's
-  // maximum slot. Forward: the rows [0, Rs) come from the tiles, the rest from the matrix cores; adjoint: both parts
+  // kernel that reads d (s) first adds them up itself and scales them by scal_f[0] (scal_a[0]). Forward: the rows [0, Rs) come from the tiles, the rest from the matrix cores; adjoint: both parts
   // cover all n entries and are added, tiles first.
   int fused;
   int64_t Rs;
@@ -105,36 +105,17 @@ __device__ __forceinline__ double adjoint_result(const Vecs& a, double sc, int64
   return a.adj.mm_groups ? tl + mm : tl;
 }
 
-// the workgroup's part of max |x| (bit patterns of non-negative doubles order like the values) into *slot
-// (one atomic per workgroup: every thread of the workgroup must call this)
-__device__ __forceinline__ void publish_absmax(unsigned long long m, unsigned long long* slot) {
+// the workgroup's part of max |x| into max_parts[blockIdx.x] (every thread of the workgroup must call this)
+__device__ __forceinline__ void publish_absmax(unsigned long long m, unsigned long long* max_parts) {
   __shared__ unsigned long long wm[kThreads / 64];
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long t = __shfl_xor(m, o, 64);
-    m = t > m ? t : m;
-  }
-  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < kThreads / 64; ++i) m = wm[i] > m ? wm[i] : m;
-    if (m) atomicMax(slot, m);
-  }
+  static_assert(kThreads == 256, "ds_block_max_256");
+  ds_block_max_256(m, wm);
+  if (threadIdx.x == 0) max_parts[blockIdx.x] = m;
   __syncthreads();
 }
 __device__ __forceinline__ unsigned long long abs_bits(double x) {
   return (unsigned long long)__double_as_longlong(x) & 0x7fffffffffffffffull;
 }
-// (an iteration that has stopped leaves the vector alone, but the products queued behind it still read its maximum)
-__device__ __forceinline__ void publish_absmax_of(const double* x, int64_t len, unsigned long long* slot) {
-  if (!slot) return;
-  unsigned long long m = 0;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < len; i += (int64_t)gridDim.x * kThreads) {
-    const unsigned long long b = abs_bits(x[i]);
-    m = b > m ? b : m;
-  }
-  publish_absmax(m, slot);
-}
-
 // r = sqrt(w) t ; h from r
 __global__ void init_r_kernel(Vecs a, const double* t) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -249,7 +230,6 @@ __global__ __launch_bounds__(kThreads) void loop_make_v_kernel(Vecs a, int parts
     a.scal[0] = a.scal[6];
   }
   const double sc = a.fused ? a.scal_f[0] : 0.0;
-  if (a.fused && blockIdx.x == 0 && threadIdx.x == 0) *a.slot_u = 0ull;
   double acc = 0.0;
   const int sub = threadIdx.x & (T - 1);
   for (int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / T; i < a.R; i += (int64_t)gridDim.x * (kThreads / T)) {
@@ -280,10 +260,7 @@ __global__ __launch_bounds__(kThreads) void loop_update_r_kernel(Vecs a, int par
   const double gamma = a.scal[0];
   const bool null_dir = !(delta > 0.0);
   const double th = null_dir ? 0.0 : gamma / delta;
-  if (done) {
-    publish_absmax_of(a.h, a.R, a.slot_h);
-    return;
-  }
+  if (done) return;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.scal[1] = delta;
     a.scal[2] = th;
@@ -309,7 +286,7 @@ __global__ __launch_bounds__(kThreads) void loop_update_r_kernel(Vecs a, int par
     const unsigned long long b = abs_bits(hn);
     hm = b > hm ? b : hm;
   }
-  if (a.slot_h) publish_absmax(hm, a.slot_h);
+  if (a.max_h) publish_absmax(hm, a.max_h);
 }
 
 template <int T>
@@ -317,7 +294,6 @@ __global__ __launch_bounds__(kThreads) void loop_s_sum_kernel(Vecs a) {
   double s1 = 0;
   if (a.fused) {
     const double sc = a.scal_a[0];
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.slot_h = 0ull;
     const int sub = threadIdx.x & (T - 1);
     for (int64_t j = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / T; j < a.n; j += (int64_t)gridDim.x * (kThreads / T)) {
       const double v = adjoint_result<T>(a, sc, j, sub);
@@ -350,10 +326,7 @@ __global__ __launch_bounds__(kThreads) void loop_s_center_kernel(Vecs a, int par
 // x += theta u, u = s + beta u with the partial sums of the new u
 __global__ __launch_bounds__(kThreads) void loop_update_xu_kernel(Vecs a, int parts_g, double tol, int do_update) {
   const double g = block_sum_partials(a, kPartG, parts_g);
-  if (a.scal[8] != 0.0) {
-    publish_absmax_of(a.u, a.n, a.slot_u);
-    return;
-  }
+  if (a.scal[8] != 0.0) return;
   const double gamma = a.scal[0], gamma0 = a.scal[7];
   const double rel = sqrt(g) / sqrt(gamma0);
   const bool stop = rel <= tol;
@@ -369,10 +342,7 @@ __global__ __launch_bounds__(kThreads) void loop_update_xu_kernel(Vecs a, int pa
       a.scal[6] = g;
     }
   }
-  if (stop || !do_update) {
-    publish_absmax_of(a.u, a.n, a.slot_u);
-    return;
-  }
+  if (stop || !do_update) return;
   double acc = 0;
   unsigned long long um = 0;
   for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < a.n; j += (int64_t)gridDim.x * kThreads) {
@@ -384,7 +354,7 @@ __global__ __launch_bounds__(kThreads) void loop_update_xu_kernel(Vecs a, int pa
     const unsigned long long b = abs_bits(un);
     um = b > um ? b : um;
   }
-  if (a.slot_u) publish_absmax(um, a.slot_u);
+  if (a.max_u) publish_absmax(um, a.max_u);
   double dummy;
   block_reduce2(acc, 0.0, &a.part[kPartU * kRed + blockIdx.x], &dummy);
 }
@@ -738,7 +708,7 @@ size_t ds_cgls_arena_bytes(int64_t n, int64_t k) {
   const size_t hybrid = 3 * ds_align((size_t)n * KW * 8) + 4 * ds_align((n + 2) * 4) + 2 * ds_align((k + 2) * 4) +
                         ds_align(96 * (size_t)(n > k ? n : k)) + ((size_t)80 << 20) + tile_scratch +
                         4 * ds_scan_arena_bytes(n > k ? n + 1 : k + 1);
-  return hybrid + 2 * ds_align(k * 4) + 7 * ds_align(k * 8) + 5 * ds_align(n * 8) + 131072;
+  return hybrid + 2 * ds_align(k * 4) + 7 * ds_align(k * 8) + 5 * ds_align(n * 8) + 131072 + 2 * kRed * 8;
 }
 
 int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const float* w, const float* y, int paired,
@@ -819,7 +789,7 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
   ds_mm_plan mm_f = {}, mm_a = {};   // dense rows: forward (Rd x n) and adjoint (n x Rd) products
   ds_tile_plan tiles = {};           // sparse rows: one entry list for both products
   long long *q64u = nullptr, *q64h = nullptr;   // the vectors of the two products as integers (for the sparse rows)
-  double *scal_f = nullptr, *scal_a = nullptr;  // [0] scale, [1] maximum slot of the forward / adjoint product
+  double *scal_f = nullptr, *scal_a = nullptr;  // [0] scale of the forward / adjoint product's integers
   if (paired && n >= kHybridMinPlayers && n < ((int64_t)1 << 28)) {   // (the matrix-core product addresses rows with 32 bits)
     int32_t* cnt = (int32_t*)ds_arena_alloc(ctx, (R + 1) * 4);
     if (!cnt) return ds_fail(ctx, DS_EINTERNAL, "cgls: arena exhausted");
@@ -846,7 +816,7 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
       void* ws_t = ds_arena_alloc(ctx, ds_tile_ws_bytes(ctx, Rs, n, nnz_s));
       q64u = (long long*)ds_arena_alloc(ctx, n * 8);
       q64h = (long long*)ds_arena_alloc(ctx, (Rs + 1) * 8);
-      scal_f = (double*)ds_arena_alloc(ctx, 256);
+      scal_f = (double*)ds_arena_alloc(ctx, 256 + 2 * kRed * 8);   // scalars, then max_u and max_h
       int32_t* csr_idx = (int32_t*)ds_arena_alloc(ctx, (nnz_s + 1) * 4);   // (index lists; the tile build keeps the memory)
       if (!Ztd || !ws_f || !ws_a || !ws_t || !q64u || !q64h || !scal_f || !csr_idx) return ds_fail(ctx, DS_EINTERNAL, "cgls: arena exhausted");
       scal_a = scal_f + 16;
@@ -871,22 +841,26 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
   // Hybrid layout: the vector is brought into fixed point once per product; the sparse rows' tiles and the dense
   // rows' bitmap are multiplied one after the other (side by side on two streams they only competed for memory
   // bandwidth and the iteration took 8 % longer), the dense product adding the sparse result in the adjoint.
-  a.slot_u = hybrid ? (unsigned long long*)(scal_f + 1) : nullptr;
-  a.slot_h = hybrid ? (unsigned long long*)(scal_a + 1) : nullptr;
-  // with_absmax = 0: the kernel that wrote the vector has left its maximum in the product's slot
+  const unsigned red_n = nblocks(n, kThreads) < (unsigned)kRed ? nblocks(n, kThreads) : (unsigned)kRed;
+  const unsigned red_r = nblocks(R, kThreads) < (unsigned)kRed ? nblocks(R, kThreads) : (unsigned)kRed;
+  a.max_u = hybrid ? (unsigned long long*)(scal_f + 32) : nullptr;
+  a.max_h = hybrid ? a.max_u + kRed : nullptr;
+  // with_absmax = 0: the kernel that wrote the vector has left its workgroups' maxima
   // d (sv) == nullptr: the integer partial sums are left for the loop's kernels
   auto forward = [&](const double* u, double* d, int with_absmax) -> int {  // d = (rows) . u
     if (!hybrid) return ds_bit_spmv(ctx, Z, R, n, W, 0, paired ? 2 : 1, u, d);
-    DS_TRY(ds_vec_quantize(ctx, u, n, &mm_f, u, u, Rs > 0 ? n : 0, q64u, scal_f, with_absmax));
-    if (Rs > 0) DS_TRY(ds_tile_spmv(ctx, &tiles, 0, q64u, scal_f, d, d && Rd == 0 ? 1 : 0));
-    if (Rd > 0) DS_TRY(ds_bit_spmv_mm_product(ctx, &mm_f, Z, W, 2 * Rs, 2, scal_f, nullptr, d ? d + Rs : nullptr, d ? 1 : 0));
+    if (with_absmax) DS_TRY(ds_vec_absmax(ctx, u, n, a.max_u, (int)red_n));
+    DS_TRY(ds_vec_quantize(ctx, a.max_u, (int)red_n, &mm_f, u, u, Rs > 0 ? n : 0, q64u, scal_f));
+    if (Rs > 0) DS_TRY(ds_tile_spmv(ctx, &tiles, 0, q64u, scal_f, d));
+    if (Rd > 0) DS_TRY(ds_bit_spmv_mm_product(ctx, &mm_f, Z, W, 2 * Rs, 2, scal_f, nullptr, d ? d + Rs : nullptr));
     return DS_OK;
   };
   auto adjoint = [&](const double* h, double* sv, int with_absmax) -> int {  // s = (rows)^T . h
     if (!hybrid) return ds_bit_spmv(ctx, Zt, n, R, RW, 0, 1, h, sv);
-    DS_TRY(ds_vec_quantize(ctx, h, R, &mm_a, h + Rs, h, Rs, q64h, scal_a, with_absmax));
-    if (Rs > 0) DS_TRY(ds_tile_spmv(ctx, &tiles, 1, q64h, scal_a, sv, sv && Rd == 0 ? 1 : 0));
-    if (Rd > 0) DS_TRY(ds_bit_spmv_mm_product(ctx, &mm_a, Ztd, RdW, 0, 1, scal_a, sv && Rs > 0 ? sv : nullptr, sv, sv ? 1 : 0));
+    if (with_absmax) DS_TRY(ds_vec_absmax(ctx, h, R, a.max_h, (int)red_r));
+    DS_TRY(ds_vec_quantize(ctx, a.max_h, (int)red_r, &mm_a, h + Rs, h, Rs, q64h, scal_a));
+    if (Rs > 0) DS_TRY(ds_tile_spmv(ctx, &tiles, 1, q64h, scal_a, sv));
+    if (Rd > 0) DS_TRY(ds_bit_spmv_mm_product(ctx, &mm_a, Ztd, RdW, 0, 1, scal_a, sv && Rs > 0 ? sv : nullptr, sv));
     return DS_OK;
   };
   a.fused = hybrid ? 1 : 0;
@@ -902,8 +876,6 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
   DS_HIP(ctx, hipMemsetAsync(a.u, 0, n * 8, st));
   DS_HIP(ctx, hipMemsetAsync(a.scal, 0, 128, st));
 
-  const unsigned red_n = nblocks(n, kThreads) < (unsigned)kRed ? nblocks(n, kThreads) : (unsigned)kRed;
-  const unsigned red_r = nblocks(R, kThreads) < (unsigned)kRed ? nblocks(R, kThreads) : (unsigned)kRed;
   // lanes per entry in the two kernels that add up the products' partial sums: short vectors take 4 or 16, so that
   // enough loads are in flight
   auto lanes_for = [&](int64_t len) { return !hybrid ? 1 : len * 16 <= 262144 ? 16 : len * 4 <= 262144 ? 4 : 1; };

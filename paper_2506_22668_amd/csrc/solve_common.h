@@ -17,10 +17,10 @@ int ds_bit_transpose_blocks(ds_ctx* ctx, const uint64_t* in, int64_t rows, int64
 int ds_bit_spmv(ds_ctx* ctx, const uint64_t* B, int64_t rows, int64_t cols, int64_t stride, int64_t row_first,
                 int64_t row_step, const double* x, double* out);
 // ---- products of the CGLS matrix of a large game in fixed point (exact integer sums) ----
-// Every product starts with ds_vec_quantize: scal[1] (the bit pattern of max |x|, 0 on entry) is found over
-// x_all[0..len_all), scal[0] becomes the power of two that scales integer results back, and the vector is written as
-// digit planes for the matrix-core product (x_planes[0..planes->cols), if `planes` has rows) and/or as 64-bit
-// integers q64[i] = round(x_q[i] * 2^f), i < qlen (if qlen > 0). The product that runs last clears scal[1].
+// Every product starts with ds_vec_quantize: from the partial maxima of |x| (bit patterns, max_parts[0..parts); left by
+// the kernel that wrote x, or by ds_vec_absmax) scal[0] becomes the power of two that scales integer results back, and
+// the vector is written as digit planes for the matrix-core product (x_planes[0..planes->cols), if `planes` has rows)
+// and/or as 64-bit integers q64[i] = round(x_q[i] * 2^f), i < qlen (if qlen > 0).
 //
 // Dense rows on the int8 matrix cores (x split into base-256 digits); out = (addend or 0) + result. A plan fixes
 // the launch shape and the scratch of one (rows, cols) shape: ds_bit_spmv_mm_ws_bytes bytes at `ws`, which
@@ -32,12 +32,12 @@ struct ds_mm_plan {
 };
 size_t ds_bit_spmv_mm_ws_bytes(const ds_ctx* ctx, int64_t rows, int64_t cols);
 int ds_bit_spmv_mm_prepare(ds_ctx* ctx, int64_t rows, int64_t cols, void* ws, ds_mm_plan* plan);
-// with_absmax == 0: the caller's own kernel has left the maximum in scal[1]
-int ds_vec_quantize(ds_ctx* ctx, const double* x_all, int64_t len_all, const ds_mm_plan* planes, const double* x_planes,
-                    const double* x_q, int64_t qlen, long long* q64, double* scal, int with_absmax = 1);
+int ds_vec_absmax(ds_ctx* ctx, const double* x, int64_t len, unsigned long long* max_parts, int parts);
+int ds_vec_quantize(ds_ctx* ctx, const unsigned long long* max_parts, int parts, const ds_mm_plan* planes, const double* x_planes,
+                    const double* x_q, int64_t qlen, long long* q64, double* scal);
 // out == nullptr: the per-group digit sums are left for the caller's own kernel to add up (ds_mm_sum below)
 int ds_bit_spmv_mm_product(ds_ctx* ctx, const ds_mm_plan* plan, const uint64_t* B, int64_t stride, int64_t row_first,
-                           int64_t row_step, const double* scal, const double* addend, double* out, int clear_slot);
+                           int64_t row_step, const double* scal, const double* addend, double* out);
 
 // Sparse rows as 2-D tiles of (row, column) entries: one list serves both products. Built from the index lists of the
 // rows (off = exclusive prefix sums of the row sizes, idx = ascending columns); rows must not hold more than
@@ -57,8 +57,7 @@ int ds_tile_build(ds_ctx* ctx, int64_t rows, int64_t cols, int64_t nnz, int64_t 
 // forward: out[r] = sum of x[c] over the entries of row r (q64 = the 64-bit form of x, cols entries);
 // adjoint: out[c] = sum of x[r] over the entries of column c (q64 of rows entries)
 // out == nullptr: the per-group partial vectors are left for the caller's own kernel to add up (ds_tile_sum below)
-int ds_tile_spmv(ds_ctx* ctx, const ds_tile_plan* plan, int adjoint, const long long* q64, const double* scal, double* out,
-                 int clear_slot);
+int ds_tile_spmv(ds_ctx* ctx, const ds_tile_plan* plan, int adjoint, const long long* q64, const double* scal, double* out);
 
 // Where the integer results of one product lie before they are added up, for kernels that consume them directly
 // (groups == 0: that part of the matrix is empty).
@@ -182,4 +181,16 @@ __device__ __forceinline__ double ds_wave_sum(double a) {
   DS_DPP_ADD(0xb1);    // quad_perm [1,0,3,2]
 #undef DS_DPP_ADD
   return a;
+}
+
+// the largest m of a workgroup of 256 threads, in every thread; wm: four words of LDS of the call's own
+__device__ __forceinline__ void ds_block_max_256(unsigned long long& m, unsigned long long* wm) {
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long t = __shfl_xor(m, o, 64);
+    m = t > m ? t : m;
+  }
+  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) m = wm[i] > m ? wm[i] : m;
 }

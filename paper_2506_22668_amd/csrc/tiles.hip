@@ -221,9 +221,8 @@ __global__ __launch_bounds__(kTileThreads) void tile_spmv_kernel(TileArgs a) {
 // out[i] = scal[0] * 2^sh * sum over the groups of partial[g][i]; the groups are added as two 32-bit halves so that
 // the total may exceed 63 bits
 __global__ __launch_bounds__(256) void tile_reduce_kernel(const long long* partial, int64_t len, int groups, const double* scal, int sh,
-                                                          double* out, unsigned long long* slot) {
+                                                          double* out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0 && slot) *slot = 0ull;
   if (i >= len) return;
   out[i] = ds_tile_sum(partial, len, groups, sh, i) * scal[0];
 }
@@ -333,12 +332,10 @@ int ds_tile_build(ds_ctx* ctx, int64_t rows, int64_t cols, int64_t nnz, int64_t 
   return DS_OK;
 }
 
-int ds_tile_spmv(ds_ctx* ctx, const ds_tile_plan* p, int adjoint, const long long* q64, const double* scal, double* out,
-                 int clear_slot) {
+int ds_tile_spmv(ds_ctx* ctx, const ds_tile_plan* p, int adjoint, const long long* q64, const double* scal, double* out) {
   if (p->rows <= 0) return DS_OK;
   if (p->nnz <= 0) {  // rows without a single entry (the empty coalition of pair 0): a zero result
     if (out) DS_HIP(ctx, hipMemsetAsync(out, 0, (size_t)(adjoint ? p->cols : p->rows) * 8, ctx->stream));
-    if (clear_slot) DS_HIP(ctx, hipMemsetAsync((void*)(scal + 1), 0, 8, ctx->stream));
     return DS_OK;
   }
   TileArgs a;
@@ -354,19 +351,18 @@ int ds_tile_spmv(ds_ctx* ctx, const ds_tile_plan* p, int adjoint, const long lon
   a.q = q64;
   a.partial = p->partial;
   const int lds = 2 * kTileSpan * 8;
-  unsigned long long* slot = clear_slot ? (unsigned long long*)(scal + 1) : (unsigned long long*)nullptr;
   if (!adjoint) {
     a.sh = p->sh_f;
     hipLaunchKernelGGL(tile_spmv_kernel<false>, dim3((unsigned)p->nrb, (unsigned)p->gf), dim3(kTileThreads), lds, ctx->stream, a);
     if (out)
       hipLaunchKernelGGL(tile_reduce_kernel, dim3((unsigned)((p->rows + 255) / 256)), dim3(256), 0, ctx->stream, p->partial,
-                         p->rows, (int)p->gf, scal, p->sh_f, out, slot);
+                         p->rows, (int)p->gf, scal, p->sh_f, out);
   } else {
     a.sh = p->sh_a;
     hipLaunchKernelGGL(tile_spmv_kernel<true>, dim3((unsigned)p->ncb, (unsigned)p->nga), dim3(kTileThreads), lds, ctx->stream, a);
     if (out)
       hipLaunchKernelGGL(tile_reduce_kernel, dim3((unsigned)((p->cols + 255) / 256)), dim3(256), 0, ctx->stream, p->partial,
-                         p->cols, (int)p->nga, scal, p->sh_a, out, slot);
+                         p->cols, (int)p->nga, scal, p->sh_a, out);
   }
   DS_HIP(ctx, hipGetLastError());
   return DS_OK;
