@@ -347,13 +347,13 @@ __global__ __launch_bounds__(kThreads) void masked_gcn_eval_kernel(EvalArgs a) {
 //   * later layers work on per-coalition operands laid out [row][feature][lane] in a global scratch: the
 //     aggregation is cut into (row, 16-feature) items so that all waves stay busy; the dense transform of a
 //     row, (features out x features in) . (features in x 64 coalitions), runs on the matrix cores with the
-//     weight matrix staged in LDS.
+//     weight matrix from L1 and L2.
 // The sixteen waves of the workgroup split nodes, rows and items among them (same 64 coalitions) and
 // meet at barriers between the stages.
 constexpr int kBW = 32;        // mask words per coalition held in LDS (at least; more for wider masks, see the layout)
 constexpr int kBWMax = 192;    // ... up to this many (12,288 players) when the rest of the LDS budget allows
-constexpr int kWBufFloats = 4096;  // the workgroup's staging buffer in LDS: weight-matrix chunks of the dense transforms, and
-                                   // the 64 x 64 tile in which the waves add up a shared row of layer 1
+constexpr int kWBufFloats = 4096;  // the workgroup's staging buffer in LDS: the 64 x 64 tile in which the waves add up a shared
+                                   // row of layer 1
 // entries per matrix-core batch of layer 1: short rows (graphs whose masks fit on chip: 15 entries a row on the
 // 1,010-player config) lose less to a partly filled batch with two (0.34 -> 0.27 ms there); the long shared rows of the
 // external-input mode want four entries' loads in flight (8: 14.9 ms, 4: 14.1 ms, 2: 16.2 ms on the 10^6-player config)
@@ -416,88 +416,82 @@ __device__ const float zero_bias[4096] = {};
 // |V_c| d^2 term): out[t][j][c] = act( sum_f W[f][j] q[t][f][c] + b[j] ) is, for
 // every row t, a (features out x features in) . (features in x coalitions) product and runs on the matrix
 // cores. A wave takes (row, 32 output features, 32 coalitions); with v_mfma_f32_32x32x2f32 lane l supplies
-// W[f + l/32][j0 + l%32] (from the LDS copy of W that the workgroup stages, in row chunks if W is large) and
-// q[t][f + l/32][c0 + l%32], a coalesced load in the [row][feature][coalition] layout. In the bf16
-// configuration both operands are already rounded to bfloat16 (q where the aggregation stored it, W where it is
-// staged) and v_mfma_f32_32x32x8bf16_1k accumulates in fp32.
-template <int kBThreads>
-__device__ __forceinline__ void transform_coalitions(const float* qall, float* nxt, float* Ws, const float* Wg,
-                                                  const float* bias, int rows, int din, int dout, bool relu, bool isbf) {
-  constexpr int kBWaves = kBThreads / 64;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cap = kWBufFloats;
-  int FB = cap / dout;
-  if (FB > din) FB = din;
-  if (FB < din && FB > 8) FB &= ~7;  // whole matrix-core steps per chunk
-  const bool single = FB == din;
-  const int jt = (dout + 31) / 32;
-  const int items = rows * jt * 2;
-  const int nit = (items + kBWaves - 1) / kBWaves;
+// W[f + l/32][j0 + l%32] and q[t][f + l/32][c0 + l%32], both coalesced loads that come from L1 and L2 (neighbouring
+// waves take the same columns of W), requested one step of 16 features ahead. In the bf16 configuration q is
+// already rounded to bfloat16 where the aggregation stored it, W is rounded here, and v_mfma_f32_32x32x8bf16_1k
+// accumulates in fp32. Bound by the latency of those loads; with W staged through LDS between two barriers per
+// 4,096 weights, 2 rows x 128 x 128 of a block of 64 coalitions took 92 us on the four waves of the
+// paired external-input form, now 49 (two workgroups per compute unit).
+template <int kBThreads, bool BF>
+__device__ __forceinline__ void transform_coalitions(const float* qall, float* nxt, const float* Wg, const float* bias, int rows,
+                                                     int din, int dout, bool relu) {
+  constexpr int kBWaves = kBThreads / 64, kStep = 16;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int items = rows * ((dout + 31) / 32) * 2;
   const int half = lane >> 5, r = lane & 31;
   const float* const bl = bias ? bias : zero_bias;
-  for (int it = 0; it < nit; ++it) {
-    const int item = it * kBWaves + wave;
-    const bool live = item < items;
-    const int t = live ? item / (2 * jt) : 0;
-    const int rem = live ? item - t * 2 * jt : 0;
-    const int j0 = (rem >> 1) * 32, c0 = (rem & 1) * 32;
+  struct Ops {
+    float a[kStep / 2], b[kStep / 2];
+  };
+  for (int item = wave; item < items; item += kBWaves) {
+    const int jb = item / (2 * rows), rem = item - jb * 2 * rows;
+    const int t = rem >> 1, j0 = jb * 32, c0 = (rem & 1) * 32;
     const bool jok = j0 + r < dout;
+    const float* const wp = Wg + (jok ? j0 + r : 0);
+    const float* const qp = qall + (size_t)t * din * 64 + c0 + r;
+    // this lane's feature of operand i of the step at fb
+    auto feature = [&](int fb, int i) { return fb + 8 * (i >> 2) + (BF ? 4 * half + (i & 3) : 2 * (i & 3) + half); };
+    auto load = [&](Ops& o, int fb) {   // (unconditional, past the end from the last feature)
+#pragma unroll
+      for (int i = 0; i < kStep / 2; ++i) {
+        const int f = feature(fb, i), fc = f < din ? f : din - 1;
+        o.a[i] = wp[(size_t)fc * dout];
+        o.b[i] = qp[(size_t)fc * 64];
+      }
+    };
     float16_t acc;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-    const float* qp = qall + (size_t)t * din * 64 + c0 + r;
-    for (int fb0 = 0; fb0 < din; fb0 += FB) {
-      const int fcnt = din - fb0 < FB ? din - fb0 : FB;
-      if (!(single && it > 0)) {
-        __syncthreads();
-        for (int i = tid; i < fcnt * dout; i += kBThreads) {
-          const float wv = Wg[(size_t)fb0 * dout + i];
-          Ws[i] = isbf ? bf16_round(wv) : wv;
+    auto use = [&](const Ops& o, int fb) {
+#pragma unroll
+      for (int s = 0; s < kStep / 8; ++s) {
+        float xa[4], xb[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const bool ok = feature(fb, 4 * s + u) < din;
+          xa[u] = (ok && jok) ? o.a[4 * s + u] : 0.f;
+          xb[u] = ok ? o.b[4 * s + u] : 0.f;
         }
-        __syncthreads();
-      }
-      if (live) {
-        const float* wp = Ws + (jok ? j0 + r : 0);
-        // 32 input features per step: their sixteen operand loads are in flight together
-        for (int fb = 0; fb < fcnt; fb += 32) {
-          float xa[4][4], xb[4][4];
+        if (BF) {
+          short4_t av, bv;
 #pragma unroll
-          for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const int f = fb + 8 * s + (isbf ? 4 * half + u : 2 * u + half);
-              const bool ok = f < fcnt;
-              xa[s][u] = (ok && jok) ? wp[f * dout] : 0.f;
-              xb[s][u] = ok ? qp[(size_t)(fb0 + f) * 64] : 0.f;
-            }
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            if (fb + 8 * s >= fcnt) break;
-            if (isbf) {
-              short4_t av, bv;
-#pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                av[u] = (short)(__float_as_uint(xa[s][u]) >> 16);
-                bv[u] = (short)(__float_as_uint(xb[s][u]) >> 16);
-              }
-              acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
-            } else {
-#pragma unroll
-              for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[s][u], xb[s][u], acc, 0, 0, 0);
-            }
+          for (int u = 0; u < 4; ++u) {
+            av[u] = (short)(__float_as_uint(bf16_round(xa[u])) >> 16);
+            bv[u] = (short)(__float_as_uint(xb[u]) >> 16);
           }
+          acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[u], xb[u], acc, 0, 0, 0);
         }
       }
+    };
+    Ops o0, o1;
+    load(o0, 0);
+    for (int fb = 0; fb < din; fb += 2 * kStep) {
+      load(o1, fb + kStep);
+      use(o0, fb);
+      if (fb + kStep >= din) break;
+      load(o0, fb + 2 * kStep);
+      use(o1, fb + kStep);
     }
-    if (live) {
-      // accumulator register i of lane l is out[feature j0 + 8*(i/4) + 4*(l/32) + i%4][coalition c0 + l%32]
+    // accumulator register i of lane l is out[feature j0 + 8*(i/4) + 4*(l/32) + i%4][coalition c0 + l%32]
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int j = j0 + 8 * (i / 4) + 4 * half + (i % 4);
-        if (j < dout) {
-          const float v = acc[i] + bl[j];
-          nxt[((size_t)t * dout + j) * 64 + c0 + r] = relu ? fmaxf(v, 0.f) : v;
-        }
+    for (int i = 0; i < 16; ++i) {
+      const int j = j0 + 8 * (i / 4) + 4 * half + (i % 4);
+      if (j < dout) {
+        const float v = acc[i] + bl[j];
+        nxt[((size_t)t * dout + j) * 64 + c0 + r] = relu ? fmaxf(v, 0.f) : v;
       }
     }
   }
@@ -832,7 +826,7 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
               store_layer1_tile<true>(acc, out, sc0, sc1, relu, a.bias[0], fl, d1);
           } else {
             // the waves add their tiles into one LDS tile, one wave at a time in wave order
-            float* tl = stage_all + (4 * half) * 64 + l32;  // the staging area is idle during layer 1
+            float* tl = stage_all + (4 * half) * 64 + l32;
             for (int w = 0; w < kBWaves; ++w) {
               if (wave == w) {
 #pragma unroll
@@ -915,7 +909,8 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
           }
       }
       __syncthreads();
-      transform_coalitions<kBThreads>(qall, nxt, stage_all, a.Wl[l - 1], a.bias[l - 1], rows, din, dout, relu, a.bf16 != 0);
+      if (a.bf16) transform_coalitions<kBThreads, true>(qall, nxt, a.Wl[l - 1], a.bias[l - 1], rows, din, dout, relu);
+      else transform_coalitions<kBThreads, false>(qall, nxt, a.Wl[l - 1], a.bias[l - 1], rows, din, dout, relu);
       __syncthreads();
       float* tmp = cur; cur = nxt; nxt = tmp;
     }
