@@ -340,8 +340,8 @@ __global__ __launch_bounds__(kThreads) void masked_gcn_eval_kernel(EvalArgs a) {
 // keeps L2 busy instead of the ALUs. Here a workgroup takes 64 coalitions, one per lane, and every
 // loop (over nodes, CSR entries, features) is uniform across the wave:
 //   * the mask words of the 64 coalitions sit in LDS as zs[word][lane]; the local CSR sits in LDS too;
-//   * degrees: for node v, each lane counts the set bits of its coalition among the row's
-//     entries (no atomics), kept as u16 in LDS (or as d^-1/2 in a global scratch for larger graphs);
+//   * degrees: counted player by player with LDS adds, kept as u16 in LDS; for larger graphs each lane counts the set
+//     bits of its coalition among a node's entries and keeps d^-1/2 in a global scratch;
 //   * layer 1, row t: H1[f][c] = sum_e P[src_e][f] * coef[e][c] with coef = bit ? d_src^-1/2 : 0 is a
 //     (features x entries) . (entries x coalitions) product and runs on the matrix cores;
 //   * later layers work on per-coalition operands laid out [row][feature][lane] in a global scratch: the
@@ -580,17 +580,56 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
         zs[w * 64 + lane] = word;
       }
       __syncthreads();
-      // degrees: node v's entries are fetched 64 at a time by the lanes and broadcast one by one
-      for (int v = wave; v < a.V; v += kBWaves) {
-        const int e0 = rp_[v], e1 = rp_[v + 1];
-        int cnt = 1;
-        for (int eb = e0; eb < e1; eb += 64) {
-          const int m = e1 - eb < 64 ? e1 - eb : 64;
-          const int pv = lane < m ? eid_[eb + lane] : 0;
-          for (int i = 0; i < m; ++i) cnt += bit_of(readlane_i(pv, i)) ? 1 : 0;
+      if (DEG_LDS) {
+        // degrees, player by player: lanes 0..31 add the player's bits to the counters of its one end, lanes 32..63 to the
+        // other's, each lane those of two coalitions (one 32-bit LDS add). Four players of one mask word per step: 25
+        // instructions, where counting node by node took 80 per node (1,010 players, 561 nodes: 21 -> 11 us per block of 64
+        // coalitions).
+        uint32_t* const deg2 = (uint32_t*)degs;
+        for (int i = tid; i < a.V * 32; i += kBThreads) deg2[i] = 0x00010001u;   // the self-loop
+        __syncthreads();
+        const int k2 = lane & 31;
+        const bool second = lane >= 32, adds = second || !a.directed;   // (directed: only the receiving end counts)
+        const uint32_t* const zs2 = (const uint32_t*)zs + 4 * k2;
+        // (the end points come by scalar loads, the next step's while this one's counters are added)
+        typedef const __attribute__((address_space(4))) int2* scalar_int2_ptr;
+        const scalar_int2_ptr ends = (scalar_int2_ptr)a.pl;
+        auto end_points = [&](int p0, int2 (&e)[4]) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int p = p0 + u < a.n ? p0 + u : 0;
+            e[u].x = ends[p].x;
+            e[u].y = ends[p].y;
+          }
+        };
+        int2 e[4], ne[4];
+        int p0 = __builtin_amdgcn_readfirstlane(wave) * 4;
+        end_points(p0, e);
+        for (; p0 < a.n; p0 += kBWaves * 4) {
+          end_points(p0 + kBWaves * 4, ne);
+          const uint32_t* zw = zs2 + (p0 >> 6) * 128 + ((p0 >> 5) & 1);
+          const uint32_t w0 = zw[0], w1 = zw[2];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const bool in = p0 + u < a.n;
+            const uint32_t add = __builtin_amdgcn_ubfe(w0, (uint32_t)(p0 + u), in ? 1u : 0u) |
+                                 __builtin_amdgcn_ubfe(w1, (uint32_t)(p0 + u), in ? 1u : 0u) << 16;
+            if (adds) atomicAdd(&deg2[(second ? e[u].y : e[u].x) * 32 + k2], add);
+            e[u] = ne[u];
+          }
         }
-        if (DEG_LDS) degs[v * 64 + lane] = (unsigned short)cnt;
-        else rs[(size_t)v * 64 + lane] = 1.0f / sqrtf((float)cnt);
+      } else {
+        // node v's entries are fetched 64 at a time by the lanes and broadcast one by one
+        for (int v = wave; v < a.V; v += kBWaves) {
+          const int e0 = rp_[v], e1 = rp_[v + 1];
+          int cnt = 1;
+          for (int eb = e0; eb < e1; eb += 64) {
+            const int m = e1 - eb < 64 ? e1 - eb : 64;
+            const int pv = lane < m ? eid_[eb + lane] : 0;
+            for (int i = 0; i < m; ++i) cnt += bit_of(readlane_i(pv, i)) ? 1 : 0;
+          }
+          rs[(size_t)v * 64 + lane] = 1.0f / sqrtf((float)cnt);
+        }
       }
     } else {
       // entry bits of this lane's record (complemented for the second member; bits past the last entry are
@@ -630,6 +669,7 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
       for (int t = 0; t < rows1; ++t) {
         const int e0 = rp_[t], e1 = rp_[t + 1];  // entry e1 stands for the self-loop
         const bool shared = e1 - e0 > kSharedRow;  // the same for every wave
+        if (!EXT && !shared) continue;   // (masks on chip: the ordinary rows follow below)
         if (!shared && (ordinary++ % kBWaves) != wave) continue;
         int s0 = e0, s1 = e1 + 1;
         if (shared) {
@@ -854,6 +894,122 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
           }
         }
       }
+    }
+    if (!EXT) {
+      // The ordinary rows with the masks on chip: (row, 64 features) tasks, dealt to the waves in descending length class
+      // (128 entries, 64, 32, 16), so that no wave is left with two of the long ones. What bounds it is the instructions
+      // that form the coefficients (four matrix-core instructions of 64 cycles each per entry pair): lane (half, j) reads
+      // the key of its entry itself (one broadcast LDS read instead of lane reads and selects), takes the bits of
+      // coalitions j and 32 + j as sign-extended fields that mask the two d^-1/2, and only a row's last step, which holds
+      // the self-loop, tests its entries. The rows of P of the next step are requested before the current one is used.
+      // 40 rows of 20 entries on average: 71 -> 64 us per block of 64 coalitions, of which 33 are the stores of the
+      // result (0.66 MB a block, 3 TB/s over all blocks); six games of 150 to 340 nodes, 256 wide: 14.5 -> 13.5 ms in all,
+      // where five rows x four feature tiles now occupy all sixteen waves. (Steps of eight entries, pipelined across
+      // rows with every key through lane reads: 117 us.)
+      constexpr int SR = 4, Q = SR / 2;   // entries and entry pairs per step
+      const int d1 = a.dims[1], nf = (d1 + 63) / 64, rows1 = a.rows_out[1];
+      const bool relu = a.L > 1;
+      const int half = lane >> 5, l32 = lane & 31;
+      const unsigned char* const zs_lane = smem_raw + 8 * l32;
+      int ord = 0;
+      for (int cls = 4; cls >= 0; --cls)
+        for (int base = 0; base < rows1; base += 64) {
+          const int tl = base + lane;
+          const int len = tl < rows1 ? rp_[tl + 1] - rp_[tl] : kSharedRow + 1;
+          const int c = len >= 128 ? 4 : len >= 64 ? 3 : len >= 32 ? 2 : len >= 16 ? 1 : 0;
+          uint64_t todo = __ballot(len <= kSharedRow && c == cls);
+          for (; todo; todo &= todo - 1) {
+            const int t = base + __ffsll((long long)todo) - 1;
+            for (int f0 = 0; f0 < d1; f0 += 64) {
+              if (ord++ % kBWaves != wave) continue;
+              const int e0 = __builtin_amdgcn_readfirstlane(rp_[t]), e1 = __builtin_amdgcn_readfirstlane(rp_[t + 1]);
+              const bool two = d1 - f0 > 32;
+              // (features past d1 are read from the tile's first column and their results never stored)
+              const int o0 = f0 + (f0 + l32 < d1 ? l32 : 0), o1 = f0 + (f0 + 32 + l32 < d1 ? 32 + l32 : 0);
+              struct Keys {
+                int src[Q], p[Q];
+              };
+              auto load_keys = [&](int eb) {   // past the row's entries: the row itself
+                Keys k;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                  const int e = eb + 2 * q + half;
+                  const int ec = e < e1 ? e : 0;
+                  const int s_ = col_[ec];
+                  k.p[q] = eid_[ec];
+                  k.src[q] = t + (e < e1 ? s_ - t : 0);   // (a select alone would put the read under a branch)
+                }
+                return k;
+              };
+              struct Ops {
+                float av[Q][2];
+              };
+              auto load_ops = [&](const Keys& k) {
+                Ops o;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                  const unsigned at = __umul24((unsigned)k.src[q], (unsigned)d1);   // (fewer than 2^24 nodes, widths to 4096)
+                  o.av[q][0] = a.P[at + (unsigned)o0];
+                  o.av[q][1] = a.P[at + (unsigned)o1];
+                }
+                return o;
+              };
+              float16_t acc[2][2];  // [feature tile][coalition half]
+#pragma unroll
+              for (int i = 0; i < 16; ++i) {
+                acc[0][0][i] = 0.f; acc[0][1][i] = 0.f; acc[1][0][i] = 0.f; acc[1][1][i] = 0.f;
+              }
+              auto use = [&](const Keys& k, const Ops& o, int eb, bool last) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                  const int src = k.src[q], p = k.p[q];
+                  const uint32_t* zw = (const uint32_t*)(zs_lane + ((unsigned)(p & ~63) << 3) + (((unsigned)p >> 3) & 4u));
+                  int m0 = __builtin_amdgcn_sbfe((int)zw[0], p, 1), m1 = __builtin_amdgcn_sbfe((int)zw[64], p, 1);
+                  float r0, r1;
+                  if (DEG_LDS) {
+                    r0 = __frsqrt_rn((float)degs[src * 64 + l32]);
+                    r1 = __frsqrt_rn((float)degs[src * 64 + 32 + l32]);
+                  } else {
+                    r0 = rs[(size_t)src * 64 + l32];
+                    r1 = rs[(size_t)src * 64 + 32 + l32];
+                  }
+                  if (last) {
+                    const int e = eb + 2 * q + half;
+                    m0 = e < e1 ? m0 : e == e1 ? -1 : 0;
+                    m1 = e < e1 ? m1 : e == e1 ? -1 : 0;
+                  }
+                  const float b0 = __int_as_float(__float_as_int(r0) & m0), b1 = __int_as_float(__float_as_int(r1) & m1);
+                  acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][0], b0, acc[0][0], 0, 0, 0);
+                  acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][0], b1, acc[0][1], 0, 0, 0);
+                  if (two) {
+                    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][1], b0, acc[1][0], 0, 0, 0);
+                    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][1], b1, acc[1][1], 0, 0, 0);
+                  }
+                }
+              };
+              Keys k0 = load_keys(e0);
+              Ops x0 = load_ops(k0);
+              int eb = e0;
+              for (; eb + SR <= e1; eb += SR) {
+                const Keys k1 = load_keys(eb + SR);
+                const Ops x1 = load_ops(k1);
+                use(k0, x0, eb, false);
+                k0 = k1;
+                x0 = x1;
+              }
+              use(k0, x0, eb, true);   // 0 to SR - 1 entries and the self-loop
+              const float rst = rs_of(t);
+              const float rst_sw = __shfl_xor(rst, 32, 64);
+              const int fl = f0 + 4 * half;
+              float* out = bufA + ((size_t)t * d1 + fl) * 64 + l32;
+              const float sc0 = half ? rst_sw : rst, sc1 = half ? rst : rst_sw;  // d^-1/2 of row t in coalitions l32, 32 + l32
+              if (a.bias[0] == nullptr && f0 + 64 <= d1)
+                store_layer1_tile<false>(acc, out, sc0, sc1, relu, nullptr, fl, d1);
+              else
+                store_layer1_tile<true>(acc, out, sc0, sc1, relu, a.bias[0], fl, d1);
+            }
+          }
+        }
     }
     __syncthreads();
 
