@@ -227,6 +227,12 @@ int ds_set_gat(ds_ctx* ctx, int32_t num_layers, const int32_t* head_dims, const 
 int ds_explain(ds_ctx* ctx, int64_t target, int64_t n_samples, uint64_t seed, const ds_options* opts,
                float* phi, int64_t* M_inout, int64_t* edge_src, int64_t* edge_dst, ds_report* report);
 
+/* ds_explain of a graph that ds_extract has already built with the same options and model (a caller that sizes its
+ * buffers by ds_cgraph_get_info does not extract twice). Takes over cg: it is released before the call returns,
+ * whatever the status, unless an argument is null. */
+int ds_explain_cgraph(ds_ctx* ctx, ds_cgraph* cg, int64_t n_samples, uint64_t seed, const ds_options* opts, float* phi,
+                      int64_t* M_inout, int64_t* edge_src, int64_t* edge_dst, ds_report* report);
+
 /* Explain T targets (paper's protocol: a set of test nodes per run). Every target gets exactly the result
  * ds_explain would give it; up to eight explanations are in flight at a time (two when the games average more
  * than 4096 players, one above 16384), each on an internal worker context with its own stream, workspace and

@@ -16,7 +16,7 @@ DS_WEIGHT_CLASS_MASS, DS_WEIGHT_UNIFORM = 0, 1
 
 EXPORTED_SYMBOLS = [
     "ds_create", "ds_destroy", "ds_last_error", "ds_set_tuning", "ds_set_graph", "ds_set_features", "ds_set_gcn", "ds_set_gat",
-    "ds_explain", "ds_explain_batch", "ds_extract", "ds_cgraph_get_info", "ds_cgraph_edges",
+    "ds_explain", "ds_explain_cgraph", "ds_explain_batch", "ds_extract", "ds_cgraph_get_info", "ds_cgraph_edges",
     "ds_cgraph_nodes", "ds_cgraph_first_transform", "ds_cgraph_free", "ds_sample_plan", "ds_sample",
     "ds_plan_tables", "ds_plan_tables_ex", "ds_sample_ex", "ds_sample_range", "ds_eval", "ds_eval_pairs", "ds_eval_noalloc", "ds_solve", "ds_fidelity", "ds_copy_probe", "ds_version",
 ]
@@ -93,6 +93,7 @@ def load_library():
         "ds_set_gat": [p, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(p), C.POINTER(p), C.POINTER(p), C.POINTER(p),
                        C.c_float],
         "ds_explain": [p, i64, i64, u64, C.POINTER(Options), p, C.POINTER(i64), p, p, C.POINTER(Report)],
+        "ds_explain_cgraph": [p, p, i64, u64, C.POINTER(Options), p, C.POINTER(i64), p, p, C.POINTER(Report)],
         "ds_explain_batch": [p, C.POINTER(i64), i32, i64, u64, C.POINTER(Options), p, C.POINTER(i64),
                              C.POINTER(i64), p, p, i64, C.POINTER(Report)],
         "ds_extract": [p, i64, C.POINTER(Options), C.POINTER(p)],
@@ -262,10 +263,10 @@ class Context:
                 allow_not_converged=False):
         t = self.torch
         opts = options or Options()
-        if capacity is None:
+        cg = None
+        if capacity is None:  # the buffers are sized by the extracted graph, which the explanation then takes over
             cg = self.extract(target, opts)
             capacity = self.cgraph_info(cg).num_players
-            self.cgraph_free(cg)
         cap = max(int(capacity), 1)
         phi = t.empty(cap, dtype=t.float32, device=self.device)
         es = t.empty(cap, dtype=t.int64, device=self.device) if want_edges else None
@@ -273,10 +274,12 @@ class Context:
         m = C.c_int64(int(capacity))
         rep = Report()
         self._sync_inputs()
-        rc = self._check(self.lib.ds_explain(self.h, int(target), int(n_samples), C.c_uint64(int(seed)),
-                                             C.byref(opts), _ptr(phi), C.byref(m), _ptr(es), _ptr(ed),
-                                             C.byref(rep)),
-                         allow=(DS_ENOTCONV,) if allow_not_converged else ())
+        args = (int(n_samples), C.c_uint64(int(seed)), C.byref(opts), _ptr(phi), C.byref(m), _ptr(es), _ptr(ed), C.byref(rep))
+        if cg is not None:
+            rc = self.lib.ds_explain_cgraph(self.h, cg, *args)
+        else:
+            rc = self.lib.ds_explain(self.h, int(target), *args)
+        self._check(rc, allow=(DS_ENOTCONV,) if allow_not_converged else ())
         n = m.value
         return phi[:n], (es[:n] if want_edges else None), (ed[:n] if want_edges else None), rep, rc
 

@@ -264,6 +264,7 @@ int ds_extract(ds_ctx* ctx, int64_t target, const ds_options* opts, ds_cgraph** 
   if (hops < 1) return ds_fail(ctx, DS_EINVAL, "hops is 0 and no model is set");
   if (ctx->d0 > 0 && ctx->L > 0 && ctx->d0 != ctx->dims[0])
     return ds_fail(ctx, DS_EINVAL, "feature width %d does not match the model's input width %d", ctx->d0, ctx->dims[0]);
+  DS_HIP(ctx, hipEventRecord(ctx->ev[0], ctx->stream));   // an explanation of this graph counts its time from here
   return ds_extract_impl(ctx, target, hops, o.directed ? 1 : 0, out);
 }
 
@@ -283,13 +284,18 @@ __global__ void export_edges_kernel(const int2* pl, const int64_t* node_gid, int
   if (ed) ed[p] = node_gid[e.y];
 }
 
-int ds_cgraph_edges(ds_ctx* ctx, const ds_cgraph* cg, int64_t* edge_src, int64_t* edge_dst) {
-  if (!ctx || !cg) return DS_EINVAL;
+static int export_edges(ds_ctx* ctx, const ds_cgraph* cg, int64_t* edge_src, int64_t* edge_dst) {
   const int64_t n = cg->info.num_players;
   if (n == 0 || (!edge_src && !edge_dst)) return DS_OK;
   hipLaunchKernelGGL(export_edges_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, ctx->stream, cg->pl,
                      cg->node_gid, n, edge_src, edge_dst);
   DS_HIP(ctx, hipGetLastError());
+  return DS_OK;
+}
+
+int ds_cgraph_edges(ds_ctx* ctx, const ds_cgraph* cg, int64_t* edge_src, int64_t* edge_dst) {
+  if (!ctx || !cg) return DS_EINVAL;
+  DS_TRY(export_edges(ctx, cg, edge_src, edge_dst));
   DS_HIP(ctx, hipStreamSynchronize(ctx->stream));
   return DS_OK;
 }
@@ -525,17 +531,26 @@ int ds_explain(ds_ctx* ctx, int64_t target, int64_t n_samples, uint64_t seed, co
   if (!ctx || !M_inout) return DS_EINVAL;
   DS_HIP(ctx, hipSetDevice(ctx->device));
   ds_options o = default_options(opts);
-  hipStream_t st = ctx->stream;
   if (ctx->L < 1) return ds_fail(ctx, DS_EINVAL, "no model is set (ds_set_gcn / ds_set_gat)");
   for (int i = 0; i < 5; ++i) ctx->kev_set[i] = false;
-  DS_HIP(ctx, hipEventRecord(ctx->ev[0], st));
   ds_cgraph* cg = nullptr;
   DS_TRY(ds_extract(ctx, target, &o, &cg));
   return explain_extracted(ctx, cg, target, n_samples, seed, o, phi, M_inout, edge_src, edge_dst, report);
 }
 
-// Everything after the extraction; takes over (and frees) the computational graph. ctx->ev[0] has been recorded
-// before the extraction.
+int ds_explain_cgraph(ds_ctx* ctx, ds_cgraph* cg, int64_t n_samples, uint64_t seed, const ds_options* opts, float* phi,
+                      int64_t* M_inout, int64_t* edge_src, int64_t* edge_dst, ds_report* report) {
+  if (!ctx || !cg || !M_inout) return DS_EINVAL;
+  DS_HIP(ctx, hipSetDevice(ctx->device));
+  if (ctx->L < 1) {
+    ds_cgraph_free(ctx, cg);
+    return ds_fail(ctx, DS_EINVAL, "no model is set (ds_set_gcn / ds_set_gat)");
+  }
+  for (int i = 0; i < 5; ++i) ctx->kev_set[i] = false;
+  return explain_extracted(ctx, cg, cg->info.target, n_samples, seed, default_options(opts), phi, M_inout, edge_src, edge_dst, report);
+}
+
+// Everything after the extraction, which recorded ctx->ev[0]; takes over (and frees) the computational graph.
 static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t n_samples, uint64_t seed, const ds_options& o,
                              float* phi, int64_t* M_inout, int64_t* edge_src, int64_t* edge_dst, ds_report* report) {
   ds_report rep;
@@ -557,7 +572,7 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
     if (report) *report = rep;
     return DS_OK;
   }
-  DS_TRY(ds_cgraph_edges(ctx, cg, edge_src, edge_dst));
+  DS_TRY(export_edges(ctx, cg, edge_src, edge_dst));   // (complete when the call is)
   DS_HIP(ctx, hipEventRecord(ctx->ev[1], st));
 
   const int64_t W = (n + 63) / 64;
@@ -771,7 +786,6 @@ int ds_explain_batch(ds_ctx* ctx, const int64_t* targets, int32_t num_targets, i
   {
     ds_ctx* w0 = ctx->workers[0];
     for (int i = 0; i < 5; ++i) w0->kev_set[i] = false;
-    DS_HIP(ctx, hipEventRecord(w0->ev[0], w0->stream));
     const int rc = ds_extract(w0, targets[0], &o, &first_cg);
     if (rc != DS_OK) {
       strncpy(ctx->err, w0->err, sizeof(ctx->err) - 1);
@@ -798,8 +812,7 @@ int ds_explain_batch(ds_ctx* ctx, const int64_t* targets, int32_t num_targets, i
             cg = first_cg;
           } else {
             for (int i = 0; i < 5; ++i) w->kev_set[i] = false;
-            rc = hipEventRecord(w->ev[0], w->stream) == hipSuccess ? DS_OK : DS_EDEVICE;
-            if (rc == DS_OK) rc = ds_extract(w, targets[t], &o, &cg);
+            rc = ds_extract(w, targets[t], &o, &cg);
           }
           status[t] = rc;
           if (rc != DS_OK) errs[t] = w->err;

@@ -316,3 +316,24 @@ def test_directed_players_and_wider_extraction():
     assert abs(got[pairs.index((2, 3))]) > 1e-4
     assert np.abs(got - ref["phi"]).max() <= 1e-4 * np.abs(ref["phi"]).max() + 1e-7
     ctx.close()
+
+
+def test_explaining_an_extracted_graph_equals_explaining_its_target():
+    """capacity=None sizes the buffers by an extracted graph that the explanation takes over; a given capacity extracts
+    inside the call. Same scores, same players, and the graph is gone afterwards (also after an error)."""
+    from paper_2506_22668_amd import DistShapError
+    from paper_2506_22668_amd.binding import DS_EINVAL
+    w = make_workload("c2_small")
+    say("explain c2_small twice")
+    ctx = make_context(w)
+    a = ctx.explain(w.targets[0], w.n_samples, w.seed)
+    b = ctx.explain(w.targets[0], w.n_samples, w.seed, capacity=a[3].num_players + 5)
+    for x, y in zip(a[:3], b[:3]):
+        assert torch.equal(x, y)
+    assert a[3].num_players == b[3].num_players and a[3].ms_extract > 0 and a[3].pred_class == b[3].pred_class
+    with pytest.raises(DistShapError) as e:
+        ctx.explain(w.targets[0], 2, w.seed)
+    assert e.value.code == DS_EINVAL
+    c = ctx.explain(w.targets[0], w.n_samples, w.seed)
+    assert torch.equal(a[0], c[0])
+    ctx.close()
