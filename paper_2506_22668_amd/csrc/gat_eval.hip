@@ -48,7 +48,8 @@ struct GatArgs {
   int32_t bufH, bufZ, bufS, bufT;  // floats
   int32_t buf_lds;
   const float* h1;      // optional: layer-1 output of every coalition [k][rows_out[1]][dims[1]] (matrix-core path)
-  const int32_t* h1_bad; // device flag: non-zero means h1 was not produced (attention range too wide)
+  const float* z2;      // optional, in the place of h1: layer 2's transformed rows [k][rows_out[1]][zw[1]]
+  const int32_t* h1_bad; // device flag: non-zero means h1 (z2) was not produced (attention range too wide)
 };
 
 __device__ __forceinline__ int readlane_i(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
@@ -213,7 +214,10 @@ __device__ __forceinline__ void masked_gat_eval_body(const GatArgs& a) {
   for (int64_t row = blockIdx.x; row < a.k; row += gridDim.x) {
     const uint64_t* z = a.Z + row * a.W;
     // layer 1: already produced for all coalitions on the matrix cores, or aggregated here
-    if (a.h1 && *a.h1_bad == 0) {
+    const bool have1 = a.h1_bad != nullptr && *a.h1_bad == 0;
+    if (have1 && a.z2) {
+      // (layer 2 starts from its transformed rows)
+    } else if (have1) {
       const int cnt = a.rows_out[1] * a.dims[1];
       const float* src = a.h1 + (size_t)row * cnt;
       for (int i = tid; i < cnt; i += THREADS) bufH[i] = src[i];
@@ -228,6 +232,10 @@ __device__ __forceinline__ void masked_gat_eval_body(const GatArgs& a) {
     for (int l = 2; l <= L; ++l) {
       const int rin = a.rows_out[l - 1], din = a.dims[l - 1], zw = a.zw[l - 1], H = a.heads[l - 1], F = a.fh[l - 1];
       const float* Wm = a.Wl[l - 1];
+      if (l == 2 && have1 && a.z2) {
+        const float* src = a.z2 + (size_t)row * rin * zw;
+        for (int idx = tid; idx < rin * zw; idx += THREADS) bufZ[idx] = src[idx];
+      } else
       for (int idx = tid; idx < rin * zw; idx += THREADS) {
         const int r = idx / zw, j = idx - r * zw;
         const float* hr = bufH + (size_t)r * din;
@@ -343,6 +351,11 @@ struct GatL1Args {
   const uint64_t* Zt;  // optional: transposed masks [n][KW], word blk of row p = bit p of coalitions 64 blk ..
   int64_t KW;
   float* h1;      // [k][R1][zw]
+  // layer 2's transform on the way out (in the place of h1): z2 [k][R1][zw2] = h1 W2, zw2 <= 32
+  const float* W2;
+  float* z2;
+  int32_t zw2;
+  int32_t parts;  // workgroups that share the rows of a block of coalitions
 };
 
 // row maxima M[t][h] over the whole row (self included); one workgroup per needed row t
@@ -410,8 +423,14 @@ __global__ __launch_bounds__(kThreads) void gat_entry_weights_kernel(GatL1Args g
   }
 }
 
-// A workgroup takes 128 coalitions, 32 per wave, and every wave walks all needed rows for its own
-// coalitions, so the waves carry identical work whatever the row lengths are (a hub row is no imbalance).
+// A workgroup takes 128 coalitions, 32 per wave, and every wave walks the workgroup's rows for its own coalitions, so
+// the waves carry identical work whatever the row lengths are. A row is a chain of latencies (operands from L2, then
+// LDS round trips), so the rows of a block of coalitions are dealt to `parts` workgroups until three fill a compute
+// unit, and waves meet at no barrier behind the staging of the mask words. With FUSE the rows go on through layer 2's
+// transform on the matrix cores while they are in LDS, which replaces a round trip of [k][R1][zw] floats through
+// memory (107 MB at 20,000 coalitions of 21 rows of 64) and the transform of one coalition by one wave. 20,000
+// coalitions, 999 players, 820 entries: 259 -> 109 us here (130 with f / F as a division and a reciprocal per column),
+// and 293 -> 69 us in the kernel of the later layers.
 // v_mfma_f32_32x32x2f32: lane l supplies A[m = l%32][k = l/32] and B[k = l/32][n = l%32]; accumulator
 // register i of lane l is D[8*(i/4) + 4*(l/32) + i%4][l%32]. Per row a wave accumulates up to three
 // 32-column tiles of the numerator plus the denominator tile (one row per head).
@@ -419,25 +438,40 @@ __global__ __launch_bounds__(kThreads) void gat_entry_weights_kernel(GatL1Args g
 // coalitions, so the words of the needed entries (staged in LDS once per block of coalitions) serve every
 // lane and no cross-lane traffic is needed: lane l takes bit (32 (wave%2) + l%32) of the word of entry
 // 2q + l/32. The A operand of the next step is loaded while the current step multiplies.
-constexpr int kL1Stage = 16;        // entries per step
-constexpr int kL1Tiles = 3;         // numerator tiles per pass
+constexpr int kL1Stage = 8;         // entries per step
 constexpr int kL1MaxEntries = 4096; // entries of the needed rows whose mask words fit the LDS stage
-constexpr int kL1WaveFloats = 32 * 33 + 32 * 33;
-__global__ __launch_bounds__(kThreads) void masked_gat_layer1_mfma_kernel(GatL1Args g) {
+// LDS accesses of one wave complete in order: between lanes of a wave only the compiler has to keep them so
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+template <bool FUSE, int TILES>   // TILES: numerator tiles per pass
+__global__ __launch_bounds__(kThreads, TILES <= 2 ? 3 : 2) void masked_gat_layer1_mfma_kernel(GatL1Args g) {
   if (*g.bad != 0) return;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_l1[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, l32 = lane & 31;
-  const int wsel_word = wave >> 1, wsel_shift = 32 * (wave & 1) + l32;
+  const int wsel_word = wave >> 1;
   uint64_t* bitsL = (uint64_t*)smem_l1;  // [2][E1 + 2]: mask words of the needed entries, then all-ones, then zero
   const int bstride = g.E1 + 2;
-  float* den_w = (float*)(smem_l1 + (((size_t)2 * bstride * 8 + 15) & ~(size_t)15)) + (size_t)wave * kL1WaveFloats;
-  float* T_w = den_w + 32 * 33;  // one tile [32 coalitions][33]
-  const uint64_t* my_bits = bitsL + (size_t)wsel_word * bstride;
+  float* const w2L = (float*)(smem_l1 + (((size_t)2 * bstride * 8 + 15) & ~(size_t)15));  // FUSE: W2 as [zwr][32], zero-padded
+  float* den_w = w2L + (FUSE ? g.zwr * 32 : 0) + (size_t)wave * (g.H * 33 + 32 * 33);   // [head][33]
+  float* T_w = den_w + g.H * 33;  // one tile [32 coalitions][33]
+  if (FUSE) {
+    for (int i = tid; i < g.zwr * 32; i += kThreads) {
+      const int f = i >> 5, c = i & 31;
+      w2L[i] = f < g.zw && c < g.zw2 ? g.W2[(size_t)f * g.zw2 + c] : 0.f;
+    }
+  }
+  const unsigned head_magic = (unsigned)(0xffffffffu / (unsigned)g.F) + 1u;   // f / F = umulhi(f, .) for F > 1, f < 2^12
+  const uint32_t* my_bits = (const uint32_t*)(bitsL + (size_t)wsel_word * bstride) + (wave & 1);   // every second word
+  const unsigned lane_off = (unsigned)(half * g.zwp + l32);
   const int FT = g.zwr / 32;
   const int64_t blocks = (g.k + 127) / 128;
   const size_t h1_stride = (size_t)g.R1 * g.zw;
-  for (int64_t blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
+  for (int64_t task = blockIdx.x; task < blocks * g.parts; task += gridDim.x) {
+    const int64_t blk = task / g.parts;
+    const int part = (int)(task - blk * g.parts);
     __syncthreads();
     for (int i = tid; i < 2 * g.E1; i += kThreads) {
       const int wd = i >= g.E1 ? 1 : 0, e = i - wd * g.E1;
@@ -450,62 +484,72 @@ __global__ __launch_bounds__(kThreads) void masked_gat_layer1_mfma_kernel(GatL1A
     }
     __syncthreads();
     const int64_t row_base = blk * 128 + wave * 32;
-    for (int t = 0; t < g.R1; ++t) {
-      const int e0 = g.row_ptr[t], e1 = g.row_ptr[t + 1];  // index e1 stands for the self term
-      const size_t self_row = (size_t)(g.E1 + t) * g.zwp;
-      for (int fg = 0; fg < FT; fg += kL1Tiles) {
-        const int nt = FT - fg < kL1Tiles ? FT - fg : kL1Tiles;
-        float16_t num[kL1Tiles], den;
+    for (int t = part; t < g.R1; t += g.parts) {
+      const int e0 = __builtin_amdgcn_readfirstlane(g.row_ptr[t]), e1 = __builtin_amdgcn_readfirstlane(g.row_ptr[t + 1]);
+      // (index e1 stands for the self term)
+      float16_t z2;   // FUSE: the row's transform, [coalition 8*(i/4) + 4*half + i%4][column l32]
+#pragma unroll
+      for (int i = 0; i < 16; ++i) z2[i] = 0.f;
+      for (int fg = 0; fg < FT; fg += TILES) {
+        const int nt = FT - fg < TILES ? FT - fg : TILES;
+        float16_t num[TILES], den;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           den[i] = 0.f;
 #pragma unroll
-          for (int j = 0; j < kL1Tiles; ++j) num[j][i] = 0.f;
+          for (int j = 0; j < TILES; ++j) num[j][i] = 0.f;
         }
-        const float* az = g.Az + l32;
-        float an[kL1Stage / 2][kL1Tiles], ad[kL1Stage / 2];
-#pragma unroll
-        for (int q = 0; q < kL1Stage / 2; ++q) {  // rows past the end are clamped to the self row and masked by B = 0
-          const int ee = e0 + 2 * q + half;
-          const float* ap = az + (ee < e1 ? (size_t)ee * g.zwp : self_row);
-#pragma unroll
-          for (int j = 0; j < kL1Tiles; ++j) an[q][j] = ap[(fg + (j < nt ? j : 0)) * 32];
-          ad[q] = ap[g.zwr];
-        }
-        for (int eb = e0; eb <= e1; eb += kL1Stage) {
-          float an2[kL1Stage / 2][kL1Tiles], ad2[kL1Stage / 2];
-#pragma unroll
-          for (int q = 0; q < kL1Stage / 2; ++q) {
-            const int ee = eb + kL1Stage + 2 * q + half;
-            const float* ap = az + (ee < e1 ? (size_t)ee * g.zwp : self_row);
-#pragma unroll
-            for (int j = 0; j < kL1Tiles; ++j) an2[q][j] = ap[(fg + (j < nt ? j : 0)) * 32];
-            ad2[q] = ap[g.zwr];
-          }
+        // A step of kL1Stage entries: the operands of the next step are requested before the current one is multiplied. Full
+        // steps are addressed from a scalar base and test nothing; the last one holds the self term and what is past it.
+        struct Ops {
+          float n[kL1Stage / 2][TILES], d[kL1Stage / 2];
+        };
+        auto load = [&](Ops& o, int eb, bool last) {
 #pragma unroll
           for (int q = 0; q < kL1Stage / 2; ++q) {
             const int ee = eb + 2 * q + half;
-            const uint64_t wsel = my_bits[ee < e1 ? ee : (ee == e1 ? g.E1 : g.E1 + 1)];
-            const float bq = (float)((uint32_t)(wsel >> wsel_shift) & 1u);
-            den = __builtin_amdgcn_mfma_f32_32x32x2f32(ad[q], bq, den, 0, 0, 0);
-            num[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(an[q][0], bq, num[0], 0, 0, 0);
-            if (nt > 1) num[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(an[q][1], bq, num[1], 0, 0, 0);
-            if (nt > 2) num[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(an[q][2], bq, num[2], 0, 0, 0);
+            // (rows past the end are the self row's, masked by B = 0)
+            const float* ap = last ? g.Az + (unsigned)(ee < e1 ? ee : g.E1 + t) * (unsigned)g.zwp + l32
+                                   : g.Az + (size_t)(eb + 2 * q) * g.zwp + lane_off;
+#pragma unroll
+            for (int j = 0; j < TILES; ++j) o.n[q][j] = ap[(fg + (j < nt ? j : 0)) * 32];
+            o.d[q] = ap[g.zwr];
           }
+        };
+        auto use = [&](const Ops& o, int eb, bool last) {
 #pragma unroll
           for (int q = 0; q < kL1Stage / 2; ++q) {
-            ad[q] = ad2[q];
+            const int ee = eb + 2 * q + half;
+            const int at = !last || ee < e1 ? ee : ee == e1 ? g.E1 : g.E1 + 1;
+            const float bq = __int_as_float(__builtin_amdgcn_sbfe((int)my_bits[2 * at], (uint32_t)l32, 1) & 0x3f800000);   // 0 or 1
+            den = __builtin_amdgcn_mfma_f32_32x32x2f32(o.d[q], bq, den, 0, 0, 0);
 #pragma unroll
-            for (int j = 0; j < kL1Tiles; ++j) an[q][j] = an2[q][j];
+            for (int j = 0; j < TILES; ++j)
+              if (TILES < 3 || nt > j) num[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.n[q][j], bq, num[j], 0, 0, 0);
           }
+        };
+        {
+          Ops cur, nxt;
+          int eb = e0;
+          load(cur, eb, eb + kL1Stage > e1);
+          for (; eb + kL1Stage <= e1; eb += kL1Stage) {
+            if (eb + 2 * kL1Stage <= e1) load(nxt, eb + kL1Stage, false);
+            else load(nxt, eb + kL1Stage, true);
+            use(cur, eb, false);
+            cur = nxt;
+          }
+          use(cur, eb, true);
         }
         // denominators to LDS as [head][coalition], so that every column finds its head's
-        __syncthreads();
+        wave_lds_fence();
 #pragma unroll
-        for (int i = 0; i < 16; ++i) den_w[(8 * (i / 4) + 4 * half + (i % 4)) * 33 + l32] = den[i];
-        __syncthreads();
+        for (int i = 0; i < 16; ++i) {
+          const int h = 8 * (i / 4) + 4 * half + (i % 4);
+          if (h < g.H) den_w[h * 33 + l32] = __frcp_rn(den[i]);
+        }
+        wave_lds_fence();
 #pragma unroll
-        for (int j = 0; j < kL1Tiles; ++j) {
+        for (int j = 0; j < TILES; ++j) {
           if (j < nt) {
             const int ft = fg + j;
 #pragma unroll
@@ -514,7 +558,8 @@ __global__ __launch_bounds__(kThreads) void masked_gat_layer1_mfma_kernel(GatL1A
               const int f = ft * 32 + fl;
               float v = 0.f;
               if (f < g.zw) {
-                v = num[j][i] * __frcp_rn(den_w[(f / g.F) * 33 + l32]);
+                const int h = g.F > 1 ? (int)__umulhi((unsigned)f, head_magic) : f;
+                v = num[j][i] * den_w[h * 33 + l32];
                 if (g.concat_elu) {
                   v += g.bias ? g.bias[f] : 0.f;
                   v = v > 0.f ? v : __expf(v) - 1.f;
@@ -522,17 +567,28 @@ __global__ __launch_bounds__(kThreads) void masked_gat_layer1_mfma_kernel(GatL1A
               }
               T_w[l32 * 33 + fl] = v;
             }
-          }
-          __syncthreads();
-          if (j < nt && ft_in_range(fg + j, l32, g.zw)) {
+            wave_lds_fence();
+            if (FUSE) {
+#pragma unroll
+              for (int u = 0; u < 16; ++u) 
+                z2 = __builtin_amdgcn_mfma_f32_32x32x2f32(T_w[l32 * 33 + 2 * u + half], w2L[(ft * 32 + 2 * u + half) * 32 + l32], z2, 0, 0, 0);
+            } else if (ft_in_range(ft, l32, g.zw)) {
 #pragma unroll 4
-            for (int cc = 0; cc < 16; ++cc) {
-              const int c = 2 * cc + half;  // coalition of this wave
-              const int64_t rw = row_base + c;
-              if (rw < g.k) g.h1[(size_t)rw * h1_stride + (size_t)t * g.zw + (fg + j) * 32 + l32] = T_w[c * 33 + l32];
+              for (int cc = 0; cc < 16; ++cc) {
+                const int c = 2 * cc + half;  // coalition of this wave
+                const int64_t rw = row_base + c;
+                if (rw < g.k) g.h1[(size_t)rw * h1_stride + (size_t)t * g.zw + ft * 32 + l32] = T_w[c * 33 + l32];
+              }
             }
+            wave_lds_fence();
           }
-          __syncthreads();
+        }
+      }
+      if (FUSE && l32 < g.zw2) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int64_t rw = row_base + 8 * (i / 4) + 4 * half + (i % 4);
+          if (rw < g.k) g.z2[((size_t)rw * g.R1 + t) * g.zw2 + l32] = z2[i];
         }
       }
     }
@@ -593,7 +649,8 @@ GatLayout gat_layout(const ds_ctx* ctx, const ds_cgraph* cg, int64_t k, int thre
 
 // the matrix-core path for layer 1 applies to models with at least two layers and enough coalitions
 struct GatL1Layout {
-  bool use, transpose;
+  bool use, transpose, fuse;
+  int parts;
   int32_t R1, E1, zwr, zwp;
   int64_t KW;
   size_t az_bytes, h1_bytes, zt_bytes, lds_bytes;
@@ -622,10 +679,21 @@ GatL1Layout gat_l1_layout(const ds_ctx* ctx, const ds_cgraph* cg, int64_t k) {
   q.transpose = true;
   if ((size_t)k * W * 8 > ((size_t)1 << 30) || q.E1 > kL1MaxEntries) return q;
   q.zt_bytes = (size_t)cg->info.num_players * q.KW * 8;
-  q.lds_bytes = (((size_t)2 * (q.E1 + 2) * 8 + 15) & ~(size_t)15) + (size_t)kWaves * kL1WaveFloats * 4;
+  // layer 2's transform rides along where its columns fit one matrix-core tile and its weights LDS
+  q.fuse = ctx->gat.zw[1] <= 32 && q.zwr <= 256;
+  if (q.fuse) q.h1_bytes = (size_t)k * q.R1 * ctx->gat.zw[1] * 4;   // z2 in its place
+  q.lds_bytes = (((size_t)2 * (q.E1 + 2) * 8 + 15) & ~(size_t)15) + (q.fuse ? (size_t)q.zwr * 128 : 0) +
+                (size_t)kWaves * (ctx->gat.heads[0] * 33 + 32 * 33) * 4;
+  // as many workgroups as fit (registers: three waves a SIMD up to 64 columns, else two; LDS), the rows of a block of coalitions shared accordingly
   const int64_t blocks = (k + 127) / 128;
-  const int64_t cap = (int64_t)ctx->num_cus * 2;
-  q.grid = (int)(blocks < cap ? blocks : cap);
+  int64_t occ = (int64_t)((160 * 1024 - 512) / q.lds_bytes);
+  const int waves = q.zwr <= 64 ? 3 : 2;   // per SIMD
+  occ = occ > waves ? waves : occ < 1 ? 1 : occ;
+  const int64_t cap = (int64_t)ctx->num_cus * occ;
+  int64_t parts = (2 * cap + blocks - 1) / blocks;
+  if (parts > q.R1) parts = q.R1;
+  q.parts = (int)(parts < 1 ? 1 : parts);
+  q.grid = (int)(blocks * q.parts < 0x7fffffffLL ? blocks * q.parts : 0x7fffffffLL);
   q.use = true;
   return q;
 }
@@ -760,9 +828,11 @@ int ds_gat_eval_impl(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, i
     l1.row_ptr = a.row_ptr; l1.col = a.col; l1.eid = a.eid;
     l1.P = a.P; l1.att1 = a.att1; l1.bias = a.bias[0]; l1.slope = a.slope;
     l1.Az = Az; l1.bad = bad; l1.h1 = h1;
+    l1.W2 = a.Wl[1]; l1.z2 = h1; l1.zw2 = a.zw[1]; l1.parts = q.parts;   // (z2 or h1: one buffer)
     l1.rowmax = rowmax; l1.Zt = Zt; l1.KW = q.KW;
     Zt_w = Zt;
-    a.h1 = h1;
+    if (q.fuse) a.z2 = h1;
+    else a.h1 = h1;
     a.h1_bad = bad;
   }
   DS_TRY(ds_kernel_mark(ctx, 0, 0));
@@ -772,9 +842,12 @@ int ds_gat_eval_impl(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, i
     hipLaunchKernelGGL(gat_entry_weights_kernel, dim3((q.E1 + q.R1 + kWaves - 1) / kWaves), dim3(kThreads), 0, ctx->stream, l1);
     DS_HIP(ctx, hipGetLastError());
     if (q.transpose) DS_TRY(ds_bit_transpose(ctx, Z, k, cg->info.num_players, a.W, 0, 1, Zt_w));
+    void (*const kern)(GatL1Args) = q.zwr <= 32   ? (q.fuse ? masked_gat_layer1_mfma_kernel<true, 1> : masked_gat_layer1_mfma_kernel<false, 1>)
+                                    : q.zwr <= 64 ? (q.fuse ? masked_gat_layer1_mfma_kernel<true, 2> : masked_gat_layer1_mfma_kernel<false, 2>)
+                                                  : (q.fuse ? masked_gat_layer1_mfma_kernel<true, 3> : masked_gat_layer1_mfma_kernel<false, 3>);
     if (q.lds_bytes > 48 * 1024)
-      DS_HIP(ctx, hipFuncSetAttribute((const void*)masked_gat_layer1_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)q.lds_bytes));
-    hipLaunchKernelGGL(masked_gat_layer1_mfma_kernel, dim3(q.grid), dim3(kThreads), q.lds_bytes, ctx->stream, l1);
+      DS_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)q.lds_bytes));
+    hipLaunchKernelGGL(kern, dim3(q.grid), dim3(kThreads), q.lds_bytes, ctx->stream, l1);
     DS_HIP(ctx, hipGetLastError());
   }
   DS_TRY(gat_launch(ctx, a, g, g.grid));

@@ -88,6 +88,19 @@ def test_masked_gat_shapes(heads, widths):
     _eval_case(w, model, len(heads), False, 0, 270, rng)
 
 
+# the second layer's transform inside the first one's kernel: at most 32 columns behind at most 256 (a column, a tile
+# and one more, three tiles a pass and a second pass), and just outside of both limits
+@pytest.mark.parametrize("heads,widths", [((1, 1), (1, 1)), ((3, 1), (11, 32)), ((3, 1), (11, 33)), ((8, 2), (12, 16)),
+                                          ((5, 1), (13, 7)), ((2, 3), (49, 5)), ((32, 1), (8, 3)), ((32, 1), (9, 3))])
+def test_masked_gat_second_transform_on_the_way_out(heads, widths):
+    w = make_workload("gat_small")
+    say(f"gat second transform heads={heads} widths={widths}")
+    rng = np.random.default_rng(11)
+    model = _gat_model(rng, w.features.shape[1], heads, widths)
+    biases = [0.1 * rng.standard_normal(o).astype(np.float32) for o in (heads[0] * widths[0], widths[1])]
+    _eval_case(w, model, 2, False, 1, 257, rng, biases)   # two blocks of 128 coalitions and one row
+
+
 def test_masked_gat_wide_attention_range_falls_back_to_the_running_maximum():
     """Attention vectors scaled up until the logits of one row span more than exp() can hold in fp32 relative
     to the row maximum: the matrix-core path for layer 1 must step aside (its weights would underflow) and the
