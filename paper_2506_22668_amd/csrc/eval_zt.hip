@@ -33,7 +33,7 @@ constexpr int kZThreads = 256;
 constexpr int kZWaves = kZThreads / 64;
 
 struct ZtArgs {
-  int32_t V, L, score, bf16;
+  int32_t V, L, score, bf16, directed;
   int32_t paired;      // rows 2r, 2r+1 are complementary: T holds the even rows only, block 2j = the stored members of pairs
                        // 64j .. 64j+63, block 2j+1 = their complements (the same words inverted)
   int32_t dims[DS_MAX_LAYERS + 1];
@@ -107,6 +107,11 @@ __global__ __launch_bounds__(kZThreads) void zt_degrees_kernel(ZtArgs a) {
 // operands of four steps are requested together. Rows are short (20 entries on the hub workload), so a task is mostly
 // the chain row bounds -> entries -> words -> operands: four workgroups a compute unit (the accumulators in ordinary
 // registers, 117 in all) hide it better than two (29 -> 19 ms there).
+// The next layer reads this row only in the coalitions in which one of its entries towards a row of that layer is
+// active (or the row is one of that layer's itself): only those coalitions' tiles are formed and stored. Blocks of
+// sparse members are half of all blocks and need few of them; the stores are what bounds the kernel (50,021 players,
+// 10,000 coalitions: 12.5 GB if all were stored; 5.33 -> 4.00 ms). Not where entries have a direction: the entry that reads
+// this row is then another player's.
 __global__ __launch_bounds__(kZThreads, 4) void zt_layer1_kernel(ZtArgs a, float* out) {
   const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
   const int64_t wave = ((int64_t)blockIdx.x * kZThreads + threadIdx.x) >> 6, nwaves = ((int64_t)gridDim.x * kZThreads) >> 6;
@@ -119,8 +124,22 @@ __global__ __launch_bounds__(kZThreads, 4) void zt_layer1_kernel(ZtArgs a, float
     uint64_t inv;
     const uint64_t* Tb = block_words(a, a.blk0 + cbi, &inv);
     const float* rsb = a.rs + (size_t)cbi * a.V * 64;
-    const int e0 = a.row_ptr[t], e1 = a.row_ptr[t + 1];  // entry e1 stands for the self-loop
-    const float rst0 = rsb[(size_t)t * 64 + l32], rst1 = rsb[(size_t)t * 64 + 32 + l32];
+    const int e0 = __builtin_amdgcn_readfirstlane(a.row_ptr[t]), e1 = __builtin_amdgcn_readfirstlane(a.row_ptr[t + 1]);
+    // (entry e1 stands for the self-loop)
+    uint64_t need = ~0ull;   // coalitions in which the next layer reads this row
+    if (a.L > 1 && !a.directed && t >= a.rows_out[2]) {
+      need = 0ull;
+      for (int eb = e0; eb < e1 && ~need; eb += 64) {
+        const int e = eb + lane;
+        const bool up = e < e1 && a.col[e < e1 ? e : e0] < a.rows_out[2];
+        const uint64_t word = up ? Tb[a.eid[e]] ^ inv : 0ull;
+        for (unsigned long long m = __ballot(word != 0ull); m; m &= m - 1ull) {
+          const int i = __ffsll((long long)m) - 1;
+          need |= ((uint64_t)rl((uint32_t)(word >> 32), i) << 32) | rl((uint32_t)word, i);
+        }
+      }
+      if (need == 0ull) continue;
+    }
     for (int f0 = 0; f0 < d1; f0 += 64) {
       float16_t acc[2][2];
 #pragma unroll
@@ -139,6 +158,7 @@ __global__ __launch_bounds__(kZThreads, 4) void zt_layer1_kernel(ZtArgs a, float
         } else if (e == e1) {
           word = ~0ull;
         }
+        word &= need;
         const uint32_t wlo = (uint32_t)word, whi = (uint32_t)(word >> 32);
         // only entries that are active in some coalition of the block take a step (in a block of sparse stored members
         // most are not): their lanes are taken from the ballot, eight at a time = four steps of two entries
@@ -205,6 +225,7 @@ __global__ __launch_bounds__(kZThreads, 4) void zt_layer1_kernel(ZtArgs a, float
           const float4 rt4 = *(const float4*)(rp + 32 * nb + 8 * g);
           const float rt[4] = {rt4.x, rt4.y, rt4.z, rt4.w};
           float* og = o + (size_t)(32 * nb + 8 * g) * cs;
+          const uint32_t m4 = (uint32_t)(need >> (32 * nb + 8 * g)) >> (4 * half);   // bit j: coalition j of the group
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             float v0 = rt[j] * acc[0][nb][4 * g + j] + bias0, v1 = rt[j] * acc[1][nb][4 * g + j] + bias1;
@@ -212,8 +233,9 @@ __global__ __launch_bounds__(kZThreads, 4) void zt_layer1_kernel(ZtArgs a, float
               v0 = fmaxf(v0, 0.f) * rt[j];
               v1 = fmaxf(v1, 0.f) * rt[j];
             }
-            if (ok0) og[0] = v0;
-            if (ok1) og[32] = v1;
+            const bool st = (m4 >> j) & 1u;
+            if (ok0 && st) og[0] = v0;
+            if (ok1 && st) og[32] = v1;
             og += cs;
           }
         }
@@ -282,16 +304,21 @@ __global__ __launch_bounds__(kZThreads) void zt_aggregate_kernel(ZtArgs a, int l
 }
 
 // Dense transform of a later layer on the matrix cores, per coalition: nxt[t][j] = act( sum_f q[t][f] W[f][j] + b[j] ), a
-// (rows x features in) . (features in x features out) product. One wave per (coalition, 32 rows, 32 output features):
-// lane l supplies q[t0 + l%32][f + l/32] (eight consecutive f of its row per load pair) and W[f + l/32][j0 + l%32]
-// (v_mfma_f32_32x32x2f32); in the bfloat16 configuration both operands are rounded to bfloat16 (q already is) and
-// v_mfma_f32_32x32x8bf16_1k accumulates in fp32, lane l supplying f = 4*(l/32) .. +3. A layer that another one follows
-// is stored times d_t^-1/2.
+// (rows x features in) . (features in x features out) product. One wave per (coalition, 32 rows, 32 output features).
+// Which feature an operand's k-index stands for is free as long as q and W agree: of every 32 features lanes 0..31
+// take the first half and lanes 32..63 the last, so that a lane's part of its row of q is four 16-byte loads of one
+// piece and a step uses whole cache lines (four-byte loads of 32 rows 256 bytes apart each touch 32 of them: 2.21 -> 1.72 ms at 10,000 coalitions x 579 rows x 64 x 64).
+// A step is requested while the one before is multiplied; W comes from L1. v_mfma_f32_32x32x2f32;
+// in the bfloat16 configuration both operands are rounded to bfloat16 (q already is) and v_mfma_f32_32x32x8bf16_1k
+// accumulates in fp32. A layer that another one follows is stored times d_t^-1/2. VEC: rows of q are 16-byte aligned
+// (a multiple of four features).
+template <bool BF, bool VEC>
 __global__ __launch_bounds__(kZThreads) void zt_transform_kernel(ZtArgs a, int l, const float* q, float* nxt) {
+  constexpr int kStep = 32, kMine = kStep / 2;
   const int lane = threadIdx.x & 63, half = lane >> 5, r = lane & 31;
   const int64_t wave = ((int64_t)blockIdx.x * kZThreads + threadIdx.x) >> 6, nwaves = ((int64_t)gridDim.x * kZThreads) >> 6;
   const int din = a.dims[l - 1], dout = a.dims[l], rows = a.rows_out[l];
-  const bool last = l == a.L, isbf = a.bf16 != 0;
+  const bool last = l == a.L;
   const float* Wg = a.Wl[l - 1];
   const float* bias = a.bias[l - 1];
   const int jt = (dout + 31) / 32, tt = (rows + 31) / 32;
@@ -307,35 +334,63 @@ __global__ __launch_bounds__(kZThreads) void zt_transform_kernel(ZtArgs a, int l
     const int tr = t0 + r < rows ? t0 + r : rows - 1;   // rows past the end read the last one and are not stored
     const float* qp = q + ((size_t)cl * rows + tr) * din;
     const float* wp = Wg + (jok ? j0 + r : 0);
+    struct Ops {
+      float q[kMine], w[kMine];   // features fb + kMine * half + i; past the end: any valid ones
+    };
+    auto load = [&](Ops& o, int fb) {
+      const int f0 = fb + kMine * half;
+#pragma unroll
+      for (int h = 0; h < kMine / 4; ++h) {
+        const int f = f0 + 4 * h;
+        if (VEC) {
+          const float4 v = *(const float4*)(qp + (f < din ? f : 0));
+          o.q[4 * h + 0] = v.x;
+          o.q[4 * h + 1] = v.y;
+          o.q[4 * h + 2] = v.z;
+          o.q[4 * h + 3] = v.w;
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) o.q[4 * h + u] = qp[f + u < din ? f + u : 0];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kMine; ++i) o.w[i] = wp[(size_t)(f0 + i < din ? f0 + i : 0) * dout];
+    };
     float16_t acc;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-    for (int fb = 0; fb < din; fb += 8) {
-      if (isbf) {
-        short4_t av, bv;
+    auto use = [&](const Ops& o, int fb) {
+      float xa[kMine], xb[kMine];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int f = fb + 4 * half + u;
-          const bool ok = f < din;
-          const float qv = qp[ok ? f : 0], wv = wp[(size_t)(ok ? f : 0) * dout];
-          av[u] = (short)(__float_as_uint(ok ? qv : 0.f) >> 16);
-          bv[u] = (short)(__float_as_uint((ok && jok) ? zt_bf16_round(wv) : 0.f) >> 16);
-        }
-        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
-      } else {
-        float xa[4], xb[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int f = fb + 2 * u + half;
-          const bool ok = f < din;
-          const float qv = qp[ok ? f : 0], wv = wp[(size_t)(ok ? f : 0) * dout];
-          xa[u] = ok ? qv : 0.f;
-          xb[u] = (ok && jok) ? wv : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (fb + 2 * u < din) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[u], xb[u], acc, 0, 0, 0);
+      for (int i = 0; i < kMine; ++i) {
+        const bool ok = fb + kMine * half + i < din;
+        xa[i] = ok ? o.q[i] : 0.f;
+        xb[i] = (ok && jok) ? o.w[i] : 0.f;
       }
+      if (BF) {
+#pragma unroll
+        for (int s = 0; s < kMine / 4; ++s) {
+          short4_t av, bv;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            av[u] = (short)(__float_as_uint(xa[4 * s + u]) >> 16);
+            bv[u] = (short)(__float_as_uint(zt_bf16_round(xb[4 * s + u])) >> 16);
+          }
+          acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i], xb[i], acc, 0, 0, 0);
+      }
+    };
+    Ops o0, o1;
+    load(o0, 0);
+    for (int fb = 0; fb < din; fb += 2 * kStep) {
+      load(o1, fb + kStep);
+      use(o0, fb);
+      if (fb + kStep >= din) break;
+      load(o0, fb + 2 * kStep);
+      use(o1, fb + kStep);
     }
     // accumulator register i of lane l is out[row t0 + 8*(i/4) + 4*(l/32) + i%4][feature j0 + l%32]
 #pragma unroll
@@ -458,6 +513,7 @@ int ds_eval_zt(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, int sco
   a.score = score;
   a.bf16 = ctx->transform_dtype == DS_BF16_IN_F32_ACC;
   a.paired = paired;
+  a.directed = cg->info.directed;
   for (int i = 0; i <= ctx->L; ++i) {
     a.dims[i] = ctx->dims[i];
     a.rows_out[i] = p.rows_out[i];
@@ -492,7 +548,11 @@ int ds_eval_zt(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, int sco
       if (agg_grid > 0x7fffffffLL) return ds_fail(ctx, DS_EINTERNAL, "eval: too many aggregation workgroups");
       hipLaunchKernelGGL(zt_aggregate_kernel, dim3((unsigned)agg_grid), dim3(kZThreads), 0, ctx->stream, a, l, (const float*)cur, q,
                          wg_per_coalition);
-      hipLaunchKernelGGL(zt_transform_kernel, dim3((unsigned)grid_for_waves(ctx, (int64_t)a.nblk * 64 * tt * jt)), dim3(kZThreads), 0,
+      const bool vec = (a.dims[l - 1] & 3) == 0;
+      void (*const transform)(ZtArgs, int, const float*, float*) =
+          a.bf16 ? (vec ? zt_transform_kernel<true, true> : zt_transform_kernel<true, false>)
+                 : (vec ? zt_transform_kernel<false, true> : zt_transform_kernel<false, false>);
+      hipLaunchKernelGGL(transform, dim3((unsigned)grid_for_waves(ctx, (int64_t)a.nblk * 64 * tt * jt)), dim3(kZThreads), 0,
                          ctx->stream, a, l, (const float*)q, nxt);
       cur = nxt;
     }
