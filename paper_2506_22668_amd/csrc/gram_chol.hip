@@ -1092,115 +1092,97 @@ __global__ __launch_bounds__(kThreads) void chol_update_wide_kernel(double* M, i
 }
 
 
-// L^T psi = y (y = row n of M after the factorisation), block by block from the end, using the stored
-// inverses of the diagonal blocks. One launch per block: every workgroup recomputes the 64 unknowns of
-// the block, psi_c = sum_{r >= c} Linv[r][c] y_r (cheap; workgroup 0 stores them), and removes their
-// contribution from its own slice of the earlier entries, y_j -= sum_r L[j0+r][j] psi_r.
-__global__ __launch_bounds__(kThreads) void chol_back_step_kernel(const double* M, int64_t ld, int64_t j0, int nb,
-                                                                  const double* linv, double* yv, double* psi) {
-  __shared__ double xs[NB];
-  __shared__ double part[kThreads / NB][NB];
-  const int tid = threadIdx.x;
-  {
-    const int c = tid & (NB - 1), q = tid / NB;  // four partial sums per unknown, added in a fixed order
-    double s = 0.0;
-    for (int r = c + q; r < nb; r += kThreads / NB) s += linv[r * NB + c] * yv[j0 + r];
-    part[q][c] = s;
-  }
-  __syncthreads();
-  if (tid < NB) {
-    double s = 0.0;
-#pragma unroll
-    for (int q = 0; q < kThreads / NB; ++q) s += part[q][tid];
-    xs[tid] = s;
-    if (blockIdx.x == 0 && tid < nb) psi[j0 + tid] = s;
-  }
-  __syncthreads();
-  const int64_t j = (int64_t)blockIdx.x * kThreads + tid;
-  if (j < j0) {  // all NB loads of the column are in flight together (rows past a short block are skipped)
-    double mv[NB];
-#pragma unroll
-    for (int r = 0; r < NB; ++r) mv[r] = r < nb ? M[(j0 + r) * ld + j] : 0.0;
-    double s = 0.0;
-#pragma unroll
-    for (int r = 0; r < NB; ++r) s += mv[r] * xs[r];
-    yv[j] -= s;
-  }
-}
-
-// The same back substitution for small systems (n <= kBackSmallMax) in ONE launch: a single workgroup of
-// 512 threads keeps the right-hand side in LDS and walks the blocks from the end; per block the 64 unknowns
-// come from the stored inverse (8 partial sums each, added in a fixed order), then every earlier entry
-// drops their contribution. At this size the chain of per-block launches costs more than the arithmetic.
-constexpr int kBackSmallMax = 2048;
+// L^T psi = y (y = row n of M after the factorisation, worked on in place), 256 unknowns per launch from the end, phi =
+// psi + (y1 - y0)/n. Every workgroup solves the launch's unknowns itself, 64 at a time from the stored inverses of the
+// diagonal blocks (psi_c = sum_{r >= c} Linv[r][c] y_r, then their contribution leaves the entries of the 64s below),
+// and removes the contribution of all 256 from its own 64 of the earlier entries. What bounds it is latency: a chain
+// of launches, and four dependent 64 x 64 products in each, whose operands are therefore requested one product ahead.
+// (One launch per 64 unknowns: 6,007 unknowns 787 us, now 323; a single workgroup for all of up to 2,048: 1,010 unknowns 111 us,
+// now 50.) Sums have a fixed order.
 constexpr int64_t kFuseMaxRows = 2048;
-constexpr int kBackThreads = 512;
-__global__ __launch_bounds__(kBackThreads) void chol_back_small_kernel(const double* M, int64_t ld, int64_t n, int nblk,
-                                                                       const double* linv, const float* y01, float* phi) {
-  __shared__ double ys[kBackSmallMax];
-  __shared__ double xs[NB];
-  __shared__ double part[kBackThreads / NB][NB];
-  const int tid = threadIdx.x;
-  for (int j = tid; j < n; j += kBackThreads) ys[j] = M[n * ld + j];
+constexpr int kBackBlocks = 4;                    // diagonal blocks per launch
+constexpr int kBackPer = NB * NB / kThreads;      // entries of a 64 x 64 block per thread
+__global__ __launch_bounds__(kThreads) void chol_back_kernel(double* M, int64_t ld, int64_t n, int64_t J, int blocks,
+                                                             const double* linv, const float* y01, float* phi) {
+  constexpr int kParts = kThreads / NB;           // rows of a block go to the threads of a column in turn
+  __shared__ double ys[kBackBlocks * NB];         // right-hand side of the launch's blocks, then their unknowns
+  __shared__ double part[kParts][kBackBlocks * NB];
+  const int tid = threadIdx.x, c = tid & (NB - 1), g = tid / NB;
+  double* const y = M + n * ld;
   const double shift = ((double)y01[1] - (double)y01[0]) / (double)n;
-  __syncthreads();
-  // entries of the block inverse this thread multiplies: column c, rows c + q + 16 i (fetched one block ahead,
-  // so that the only memory wait inside a step is the update's own)
-  constexpr int kLi = NB / (kBackThreads / NB);
-  const int c = tid & (NB - 1), q = tid / NB;
-  double lv[kLi];
-  auto fetch_li = [&](int bk) {
-    const double* li = linv + (size_t)bk * NB * NB;
+  // a thread's entries of a block with rows r0 .. and columns c0 .. (rows past n are read from row n - 1 and meet zeros)
+  auto fetch = [&](double (&v)[kBackPer], int64_t r0, int64_t c0) {
 #pragma unroll
-    for (int i = 0; i < kLi; ++i) {
-      const int r = c + q + (kBackThreads / NB) * i;
-      lv[i] = r < NB ? li[r * NB + c] : 0.0;  // rows past a short last block are skipped in the product
+    for (int i = 0; i < kBackPer; ++i) {
+      const int64_t r = r0 + g + kParts * i;
+      v[i] = M[(r < n ? r : n - 1) * ld + c0 + c];
     }
   };
-  fetch_li(nblk - 1);
-  for (int bk = nblk - 1; bk >= 0; --bk) {
-    const int j0 = bk * NB;
-    const int nb = (int)(n - j0 < NB ? n - j0 : NB);
-    {
-      double s = 0.0;
+  auto fetch_inverse = [&](double (&v)[kBackPer], int b) {
+    const double* li = linv + (size_t)(J / NB + b) * NB * NB;
 #pragma unroll
-      for (int i = 0; i < kLi; ++i) {
-        const int r = c + q + (kBackThreads / NB) * i;
-        if (r < nb) s += lv[i] * ys[j0 + r];
-      }
-      part[q][c] = s;
-    }
-    if (bk > 0) fetch_li(bk - 1);
+    for (int i = 0; i < kBackPer; ++i) v[i] = li[(g + kParts * i) * NB + c];   // (identity-padded, zero above the diagonal)
+  };
+  auto dot = [&](const double (&v)[kBackPer], const double* x) {
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < kBackPer; ++i) s += v[i] * x[g + kParts * i];
+    return s;
+  };
+  // this workgroup's 64 of the earlier entries (workgroup 0 of a launch without any: none)
+  const int64_t j0 = (int64_t)blockIdx.x * NB;
+  const bool earlier = j0 < J;
+  double li[kBackPer], lo[kBackBlocks - 1][kBackPer];
+  fetch_inverse(li, blocks - 1);
+  if (tid < blocks * NB) ys[tid] = J + tid < n ? y[J + tid] : 0.0;
+  __syncthreads();
+  for (int b = blocks - 1; b >= 0; --b) {
+#pragma unroll
+    for (int k = 0; k < kBackBlocks - 1; ++k)
+      if (k < b) fetch(lo[k], J + b * NB, J + k * NB);
+    part[g][c] = dot(li, ys + b * NB);
+    if (b > 0) fetch_inverse(li, b - 1);
     __syncthreads();
     if (tid < NB) {
       double s = 0.0;
 #pragma unroll
-      for (int qq = 0; qq < kBackThreads / NB; ++qq) s += part[qq][tid];
-      xs[tid] = s;
-      if (tid < nb) phi[j0 + tid] = (float)(s + shift);
+      for (int q = 0; q < kParts; ++q) s += part[q][tid];
+      ys[b * NB + tid] = s;
+      const int64_t at = J + b * NB + tid;
+      if (blockIdx.x == 0 && at < n) phi[at] = (float)(s + shift);
     }
     __syncthreads();
-    for (int j = tid; j < j0; j += kBackThreads) {
-      double s = 0.0;
-      const double* mp = M + (size_t)j0 * ld + j;
-#pragma unroll 32
-      for (int r = 0; r < NB; ++r) s += (r < nb ? mp[(size_t)r * ld] : 0.0) * xs[r];
-      ys[j] -= s;
+    if (b > 0) {
+#pragma unroll
+      for (int k = 0; k < kBackBlocks - 1; ++k)
+        if (k < b) part[g][k * NB + c] = dot(lo[k], ys + b * NB);
+      __syncthreads();
+      if (tid < b * NB) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < kParts; ++q) s += part[q][tid];
+        ys[tid] -= s;
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
-}
-
-__global__ void copy_row_kernel(const double* M, int64_t ld, int64_t n, double* yv) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n) yv[j] = M[n * ld + j];
-}
-
-__global__ void finish_phi_kernel(const double* psi, const float* y01, int64_t n, float* phi) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const double delta = (double)y01[1] - (double)y01[0];
-  phi[j] = (float)(psi[j] + delta / (double)n);
+  if (!earlier) return;
+  double s = 0.0;
+  for (int b = 0; b < blocks; b += 2) {   // two blocks' loads in flight
+    double v0[kBackPer], v1[kBackPer];
+    fetch(v0, J + b * NB, j0);
+    if (b + 1 < blocks) fetch(v1, J + (b + 1) * NB, j0);
+    s += dot(v0, ys + b * NB);
+    if (b + 1 < blocks) s += dot(v1, ys + (b + 1) * NB);
+  }
+  part[g][c] = s;
+  __syncthreads();
+  if (tid < NB) {
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < kParts; ++q) t += part[q][tid];
+    y[j0 + tid] -= t;
+  }
 }
 
 inline float dense_fraction(const ds_ctx* ctx) {
@@ -1284,10 +1266,9 @@ int ds_gram_begin(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const fl
   gs->sqw = (double*)ds_arena_alloc(ctx, k * 8);
   gs->gc = (double*)ds_arena_alloc(ctx, R * 8);
   gs->c = (double*)ds_arena_alloc(ctx, n * 8);
-  gs->yv = (double*)ds_arena_alloc(ctx, n * 8);
   gs->flag = (int*)ds_arena_alloc(ctx, 64);
   if (!gs->Zt || !Gp || !gs->M || !gs->linv || !gs->panel[0] || !gs->panel[1] || !gw || !wu || !uni || !m || !stats || !Zc || !keep || !wq || !gscale || !gs->sz || !gs->wc || !gs->t ||
-      !gs->sqw || !gs->gc || !gs->c || !gs->yv || !gs->flag)
+      !gs->sqw || !gs->gc || !gs->c || !gs->flag)
     return ds_fail(ctx, DS_EINTERNAL, "gram: arena exhausted");
   hipLaunchKernelGGL(used_row_weights_kernel, dim3(nblocks(R, 256)), dim3(256), 0, st, w, R, paired, gw);
   DS_TRY(ds_bit_transpose(ctx, Z, R, n, W, 0, paired ? 2 : 1, gs->Zt));
@@ -1405,18 +1386,12 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
     j0 += nb;
   }
   DS_TRY(ds_kernel_mark(ctx, 2, 1));
-  if (n <= kBackSmallMax) {
-    hipLaunchKernelGGL(chol_back_small_kernel, dim3(1), dim3(kBackThreads), 0, st, M, ld, n, (int)gs->nblk, linv, y, phi);
-  } else {
-  hipLaunchKernelGGL(copy_row_kernel, dim3(nblocks(n, 256)), dim3(256), 0, st, M, ld, n, gs->yv);
-  for (int64_t bk = gs->nblk - 1; bk >= 0; --bk) {
-    const int64_t j0 = bk * NB;
-    const int nb = (int)(n - j0 < NB ? n - j0 : NB);
-    const unsigned wgs = j0 > 0 ? nblocks(j0, kThreads) : 1;
-    hipLaunchKernelGGL(chol_back_step_kernel, dim3(wgs), dim3(kThreads), 0, st, M, ld, j0, nb,
-                       linv + (size_t)bk * NB * NB, gs->yv, gs->c);  // c is free again: it receives psi
-  }
-  hipLaunchKernelGGL(finish_phi_kernel, dim3(nblocks(n, 256)), dim3(256), 0, st, gs->c, y, n, phi);
+  for (int64_t last = gs->nblk; last > 0;) {   // blocks J / NB .. last - 1 per launch
+    const int64_t first = (last - 1) / kBackBlocks * kBackBlocks;
+    const int64_t J = first * NB;
+    hipLaunchKernelGGL(chol_back_kernel, dim3((unsigned)(first > 0 ? first : 1)), dim3(kThreads), 0, st, M, ld, n, J,
+                       (int)(last - first), linv, y, phi);
+    last = first;
   }
   DS_HIP(ctx, hipGetLastError());
   if (defer_check) return DS_OK;  // the caller reads gs->flag back with its own results
