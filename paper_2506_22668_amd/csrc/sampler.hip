@@ -26,29 +26,65 @@ constexpr int kThreads = 256;
 constexpr int kBins = 4096;
 constexpr int kCandMax = 2048;
 
-__device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                              uint32_t k0, uint32_t k1, uint32_t out[4]) {
+// x ^ y ^ z in one instruction (the compiler makes two of it)
+__device__ __forceinline__ uint32_t xor3(uint32_t x, uint32_t y, uint32_t z) { return __builtin_amdgcn_bitop3_b32(x, y, z, 0x96); }
+
+// rounds FIRST .. 9 on the counter (c0, c1, c2, c3)
+template <int FIRST>
+__device__ __forceinline__ void philox_rounds(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
+                                              uint32_t out[4]) {
   const uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
 #pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    if (r > 0) {
-      k0 += 0x9E3779B9u;
-      k1 += 0xBB67AE85u;
-    }
+  for (int r = FIRST; r < 10; ++r) {
+    const uint32_t kr0 = k0 + (uint32_t)r * 0x9E3779B9u, kr1 = k1 + (uint32_t)r * 0xBB67AE85u;
     // one 32 x 32 -> 64 multiply per product (as a high and a low multiply the generator ran 18 % slower)
     unsigned long long p0, p1;
     asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(p0) : "v"(c0), "s"(M0) : "vcc");
     asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(p1) : "v"(c2), "s"(M1) : "vcc");
     const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0, hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-    c0 = hi1 ^ c1 ^ k0;
+    c0 = xor3(hi1, c1, kr0);
     c1 = lo1;
-    c2 = hi0 ^ c3 ^ k1;
+    c2 = xor3(hi0, c3, kr1);
     c3 = lo0;
   }
   out[0] = c0;
   out[1] = c1;
   out[2] = c2;
   out[3] = c3;
+}
+__device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
+                                              uint32_t out[4]) {
+  philox_rounds<0>(c0, c1, c2, c3, k0, k1, out);
+}
+
+// The generator along a row: the counter words 1 to 3 and the key are the row's, so that of the first two rounds only one
+// product each depends on the column (with the counter c0 = column / 4, whose product with M0 moves by M0 from one
+// call to the next). The rest is formed once per row, in scalar registers.
+struct PhiloxRow {
+  uint32_t after1, xor1, xor2, low2;   // round 1: c0, and what c2 is xored with; round 2: what c2 and c3 come from
+  uint32_t low1, k0, k1;
+};
+__device__ __forceinline__ PhiloxRow philox_row(uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1) {
+  const uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
+  PhiloxRow w;
+  const unsigned long long p1 = (unsigned long long)M1 * c2;
+  w.after1 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
+  w.low1 = (uint32_t)p1;
+  w.xor1 = c3 ^ k1;
+  const unsigned long long q0 = (unsigned long long)M0 * w.after1;
+  w.xor2 = (uint32_t)(q0 >> 32) ^ (k1 + 0xBB67AE85u);
+  w.low2 = (uint32_t)q0;
+  w.k0 = k0;
+  w.k1 = k1;
+  return w;
+}
+__device__ __forceinline__ unsigned long long philox_first_product(uint32_t c0) { return (unsigned long long)0xD2511F53u * c0; }
+// p0: philox_first_product of the call's counter
+__device__ __forceinline__ void philox_along_row(const PhiloxRow& w, unsigned long long p0, uint32_t out[4]) {
+  const uint32_t M1 = 0xCD9E8D57u;
+  unsigned long long p1;
+  asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(p1) : "v"((uint32_t)(p0 >> 32) ^ w.xor1), "s"(M1) : "vcc");
+  philox_rounds<2>(xor3((uint32_t)(p1 >> 32), w.low1, w.k0 + 0x9E3779B9u), (uint32_t)p1, (uint32_t)p0 ^ w.xor2, w.low2, w.k0, w.k1, out);
 }
 
 // Smallest bin whose inclusive prefix count reaches `want` (1-based rank); returns the bin and the
@@ -394,7 +430,7 @@ __global__ __launch_bounds__(kFastThreads) void sample_pairs_fast_kernel(SampleA
     const int64_t list_off = listing ? a.list_cum[s] + (r - a.b[s - 1] - 1) * (int64_t)s : 0;
     uint32_t* const lst = a.list + list_off;
     if (!give_up) {
-      const uint32_t r_lo = (uint32_t)r, r_hi = (uint32_t)((uint64_t)r >> 32);
+      const PhiloxRow gen = philox_row((uint32_t)r, (uint32_t)((uint64_t)r >> 32), a.tag, a.seed_lo, a.seed_hi);
       for (int i = t; i < kWinBins; i += kFastThreads) whist[i] = 0;
       if (t == 0) {
         cand_count = 0;
@@ -409,10 +445,11 @@ __global__ __launch_bounds__(kFastThreads) void sample_pairs_fast_kernel(SampleA
         const uint32_t valid = c0 + 32 <= n ? 0xffffffffu : (c0 < n ? (1u << (uint32_t)(n - c0)) - 1u : 0u);
         uint32_t word = 0;
         if (valid) {
+          unsigned long long p0 = philox_first_product((uint32_t)(d * 8));   // (counters of a word do not wrap: 8 divides 2^32)
 #pragma unroll 2
-          for (int i = 0; i < 8; ++i) {
+          for (int i = 0; i < 8; ++i, p0 += 0xD2511F53u) {
             uint32_t key[4];
-            philox4x32_10((uint32_t)(d * 8 + i), r_lo, r_hi, a.tag, a.seed_lo, a.seed_hi, key);
+            philox_along_row(gen, p0, key);
             // the common case without a branch per key: a key below the window shifts a one into the word (first column
             // ends up in the top bit: reversed once at the end); key - k_lo <= width (unsigned: a key below k_lo wraps
             // to more than width, because k_lo + width < 2^32) marks a key inside the window, and the four tests of a
