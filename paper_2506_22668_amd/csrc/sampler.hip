@@ -22,7 +22,7 @@
 
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kParts = 256;         // partial sums of a histogram
 constexpr int kBins = 4096;
 constexpr int kCandMax = 2048;
 
@@ -92,11 +92,13 @@ __device__ __forceinline__ void philox_along_row(const PhiloxRow& w, unsigned lo
 // scans the 256 partial sums with shuffles, and one lane walks the at most 4 + 16 remaining entries.
 __device__ void select_bin(const uint32_t* hist, uint32_t* part, uint32_t want, uint32_t* res) {
   const int t = threadIdx.x;
-  constexpr int kPer = kBins / kThreads;  // 16
-  uint32_t s = 0;
+  constexpr int kPer = kBins / kParts;  // 16
+  if (t < kParts) {
+    uint32_t s = 0;
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) s += hist[t * kPer + i];
-  part[t] = s;
+    for (int i = 0; i < kPer; ++i) s += hist[t * kPer + i];
+    part[t] = s;
+  }
   __syncthreads();
   if (t < 64) {
     const uint32_t v0 = part[4 * t], v1 = part[4 * t + 1], v2 = part[4 * t + 2], v3 = part[4 * t + 3];
@@ -147,9 +149,13 @@ struct SampleArgs {
   int64_t list_max;
 };
 
-__global__ __launch_bounds__(kThreads) void sample_pairs_kernel(SampleArgs a) {
+// THREADS: 256 where every pair comes here (short rows), 1024 for the pairs that the one-pass kernel hands on: those are a
+// few per compute unit or fewer, so that the time is that of one row (400,013 players, 20,000 pairs, 60 of them handed
+// on: 368 -> 171 us)
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void sample_pairs_kernel(SampleArgs a) {
   __shared__ uint32_t hist[kBins];
-  __shared__ uint32_t part[kThreads];
+  __shared__ uint32_t part[kParts];
   __shared__ uint32_t res[2];
   __shared__ unsigned long long cand[kCandMax];
   __shared__ uint32_t cand_count;
@@ -169,7 +175,7 @@ __global__ __launch_bounds__(kThreads) void sample_pairs_kernel(SampleArgs a) {
     uint64_t* row_small = a.Z + (2 * (r - a.pair_begin)) * W;
     uint64_t* row_big = row_small + W;
     if (r == 0) {  // (empty, full): the two constraint rows
-      for (int64_t wd = t; wd < W; wd += kThreads) {
+      for (int64_t wd = t; wd < W; wd += THREADS) {
         row_small[wd] = 0ull;
         row_big[wd] = (wd == W - 1) ? tail_mask : ~0ull;
       }
@@ -194,7 +200,7 @@ __global__ __launch_bounds__(kThreads) void sample_pairs_kernel(SampleArgs a) {
       // x, t elements still to choose after it), skip x while j >= c. c follows x and t by exact integer updates:
       // C(m-1, t) = c (m-t) / m and C(m-1, t-1) = c t / m (c <= K, so the products stay below 2^63 for the sizes
       // the host admits).
-      for (int64_t wd = t; wd < W; wd += kThreads) {
+      for (int64_t wd = t; wd < W; wd += THREADS) {
         row_small[wd] = 0ull;
         row_big[wd] = (wd == W - 1) ? tail_mask : ~0ull;
       }
@@ -241,13 +247,13 @@ __global__ __launch_bounds__(kThreads) void sample_pairs_kernel(SampleArgs a) {
       win_hi = pred + delta < (uint32_t)kBins - 1u ? pred + delta : (uint32_t)kBins - 1u;
     }
     // pass A: histogram of the top 12 key bits; keys in the window are kept
-    for (int i = t; i < kBins; i += kThreads) hist[i] = 0;
+    for (int i = t; i < kBins; i += THREADS) hist[i] = 0;
     if (t == 0) {
       cand_count = 0;
       window_count = 0;
     }
     __syncthreads();
-    for (int64_t q = t; q < nq; q += kThreads) {
+    for (int64_t q = t; q < nq; q += THREADS) {
       uint32_t key[4];
       philox4x32_10((uint32_t)q, r_lo, r_hi, a.tag, a.seed_lo, a.seed_hi, key);
       const int64_t j0 = q << 2;
@@ -273,7 +279,7 @@ __global__ __launch_bounds__(kThreads) void sample_pairs_kernel(SampleArgs a) {
     if (in_window) {
       // the keys of the threshold bin are among the kept ones: move them to the candidate list
       const uint32_t wc = window_count;
-      for (uint32_t i = t; i < wc; i += kThreads) {
+      for (uint32_t i = t; i < wc; i += THREADS) {
         const unsigned long long c = window[i];
         if ((uint32_t)(c >> 52) == bin1) {
           const uint32_t pos = atomicAdd(&cand_count, 1u);
@@ -289,9 +295,9 @@ __global__ __launch_bounds__(kThreads) void sample_pairs_kernel(SampleArgs a) {
     }
     if (!have_candidates) {
       // pass B: next 12 bits among keys in bin1
-      for (int i = t; i < kBins; i += kThreads) hist[i] = 0;
+      for (int i = t; i < kBins; i += THREADS) hist[i] = 0;
       __syncthreads();
-      for (int64_t q = t; q < nq; q += kThreads) {
+      for (int64_t q = t; q < nq; q += THREADS) {
         uint32_t key[4];
         philox4x32_10((uint32_t)q, r_lo, r_hi, a.tag, a.seed_lo, a.seed_hi, key);
         const int64_t j0 = q << 2;
@@ -305,7 +311,7 @@ __global__ __launch_bounds__(kThreads) void sample_pairs_kernel(SampleArgs a) {
       want3 = want2 - res[1];  // 1-based rank among the candidates
       __syncthreads();
       // pass C: list the keys sharing the 24-bit prefix, as (key, column) composites
-      for (int64_t q = t; q < nq; q += kThreads) {
+      for (int64_t q = t; q < nq; q += THREADS) {
         uint32_t key[4];
         philox4x32_10((uint32_t)q, r_lo, r_hi, a.tag, a.seed_lo, a.seed_hi, key);
         const int64_t j0 = q << 2;
@@ -323,7 +329,7 @@ __global__ __launch_bounds__(kThreads) void sample_pairs_kernel(SampleArgs a) {
       if (t == 0) atomicExch(a.error_flag, 1);
       nc = kCandMax;
     }
-    for (uint32_t i = t; i < nc; i += kThreads) {
+    for (uint32_t i = t; i < nc; i += THREADS) {
       const unsigned long long me = cand[i];
       uint32_t rank = 0;
       for (uint32_t o = 0; o < nc; ++o) rank += (cand[o] < me) ? 1u : 0u;
@@ -334,7 +340,7 @@ __global__ __launch_bounds__(kThreads) void sample_pairs_kernel(SampleArgs a) {
 
     // pass D: emit. Each wave covers 4 words (256 columns) per step: lane l owns
     // the quad of columns 4l..4l+3 of that span.
-    for (int64_t span = wave; span * 4 < W; span += kThreads / 64) {
+    for (int64_t span = wave; span * 4 < W; span += THREADS / 64) {
       const int64_t q = span * 64 + lane;
       uint32_t nib = 0;
       if (q < nq) {
@@ -704,10 +710,10 @@ int ds_sample_launch(ds_ctx* ctx, const ds_plan& plan, uint64_t seed, uint32_t t
       hipLaunchKernelGGL(sample_pairs_fast_kernel, dim3((unsigned)fblocks), dim3(kFastThreads), 0, ctx->stream, a);
       const int64_t rblocks = blocks < (int64_t)ctx->num_cus * 4 ? blocks : (int64_t)ctx->num_cus * 4;
       if (a.window_cap > 4096) a.window_cap = 4096;   // (the multi-pass kernel holds more static LDS)
-      hipLaunchKernelGGL(sample_pairs_kernel, dim3((unsigned)rblocks), dim3(kThreads), (size_t)a.window_cap * 8, ctx->stream, a);
+      hipLaunchKernelGGL(sample_pairs_kernel<1024>, dim3((unsigned)rblocks), dim3(1024), (size_t)a.window_cap * 8, ctx->stream, a);
     } else {
       if (a.window_cap > 4096) a.window_cap = 4096;
-      hipLaunchKernelGGL(sample_pairs_kernel, dim3((unsigned)blocks), dim3(kThreads), (size_t)a.window_cap * 8, ctx->stream, a);
+      hipLaunchKernelGGL(sample_pairs_kernel<256>, dim3((unsigned)blocks), dim3(256), (size_t)a.window_cap * 8, ctx->stream, a);
     }
   }
   DS_HIP(ctx, hipGetLastError());
