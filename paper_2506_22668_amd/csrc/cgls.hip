@@ -740,7 +740,7 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
   if (!sz || !wc || !t || !sqw || !a.r || !a.v || !a.d || !a.h || !a.x || !a.u || !a.s || !a.scal || !a.part)
     return ds_fail(ctx, DS_EINTERNAL, "cgls: arena exhausted");
 
-  DS_TRY(ds_row_prep(ctx, Z, k, n, w, y, sz, t, sqw, wc));
+  DS_TRY(ds_row_prep(ctx, Z, k, n, paired, w, y, sz, t, sqw, wc));
 
   // Few players and few rows (from kHybridMinPlayers on the fixed-point products take over; more rows do not fit the
   // LDS copy): an iteration in two launches.

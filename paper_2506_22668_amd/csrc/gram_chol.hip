@@ -1312,7 +1312,7 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
   const int64_t n = gs->n, k = gs->k, R = gs->R, RW = gs->RW, ld = gs->ld;
   double* M = gs->M;
   double* linv = gs->linv;
-  DS_TRY(ds_row_prep(ctx, Z, k, n, w, y, gs->sz, gs->t, gs->sqw, gs->wc));
+  DS_TRY(ds_row_prep(ctx, Z, k, n, gs->paired, w, y, gs->sz, gs->t, gs->sqw, gs->wc));
   hipLaunchKernelGGL(used_row_rhs_kernel, dim3(nblocks(R, 256)), dim3(256), 0, st, gs->wc, gs->t, R, gs->paired, gs->gc);
   DS_TRY(ds_bit_spmv(ctx, gs->Zt, n, R, RW, 0, 1, gs->gc, gs->c));  // c_j = sum over the rows containing j of gc
   hipLaunchKernelGGL(build_rhs_kernel, dim3(1), dim3(kThreads), 0, st, gs->c, n, ld, M);

@@ -3,8 +3,9 @@
 #include "internal.h"
 
 // sz[i] = |S_i|, t[i] = y_i - y_0 - ((y_1-y_0)/n)|S_i| (0 for the two constraint rows),
-// sqw[i] = sqrt(w_i), wc[i] = w_i (both 0 for the two constraint rows)
-int ds_row_prep(ds_ctx* ctx, const uint64_t* Z, int64_t k, int64_t n, const float* w, const float* y, int32_t* sz,
+// sqw[i] = sqrt(w_i), wc[i] = w_i (both 0 for the two constraint rows); paired (k even): row 2r+1 is row 2r's complement
+// and is not read
+int ds_row_prep(ds_ctx* ctx, const uint64_t* Z, int64_t k, int64_t n, int paired, const float* w, const float* y, int32_t* sz,
                 double* t, double* sqw, float* wc);
 // out[cols x ceil(rows/64)] = transpose of the rows row_first + i*row_step (i < rows) of `in`
 int ds_bit_transpose(ds_ctx* ctx, const uint64_t* in, int64_t rows, int64_t cols, int64_t in_stride, int64_t row_first,
