@@ -392,7 +392,9 @@ struct BatchedArgs {
 
 // One wave's 64 x 64 (feature x coalition) result tile of a first-layer row: accumulator register i of lane l is
 // [feature 8*(i/4) + 4*(l/32) + i%4][coalition l%32]; `out` points at this lane's feature 4*(l/32) and coalition l%32.
-template <bool GENERAL>
+// INTERLEAVED: the two feature tiles are the even and the odd features of the 64 instead of its halves
+// (`out` then points at feature 8*(l/32)).
+template <bool GENERAL, bool INTERLEAVED = false>
 __device__ __forceinline__ void store_layer1_tile(const float16_t (&acc)[2][2], float* out, float sc0, float sc1, bool relu,
                                                   const float* bias, int fl, int d1) {
 #pragma unroll
@@ -401,7 +403,7 @@ __device__ __forceinline__ void store_layer1_tile(const float16_t (&acc)[2][2], 
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const int fo = ft * 32 + 8 * (i / 4) + (i % 4);
+        const int m = 8 * (i / 4) + (i % 4), fo = INTERLEAVED ? 2 * m + ft : ft * 32 + m;
         if (!GENERAL || fl + fo < d1) {
           float v = (nb ? sc1 : sc0) * acc[ft][nb][i];
           if (GENERAL && bias) v += bias[fl + fo];
@@ -694,60 +696,87 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
             pv_next = key_[s0 + lane];
             sv_next = col_[s0 + lane];
           }
-          if (EXT && PAIRED && e1 > e0) {
-            // A row's (or, of a shared row, this wave's) entries, two steps deep: the keys of step j + 2 and the operands of step j + 1 (rows of P, the
-            // pair's degree, the source's full degree) are requested before the matrix cores get step j. Every load of the
-            // loop is issued unconditionally (indices clamped into the row, which has at least one entry), so
-            // that the wait before a step's operands is a count of younger loads and not a wait for all of them.
-            constexpr int SRP = 8;   // entries per step here
+          if (EXT && PAIRED) {
+            // A row's (or, of a shared row, this wave's) entries, two steps deep: the keys of step j + 2 and the operands of
+            // step j + 1 (rows of P, the pair's degree, the source's full degree) are requested before the matrix cores get
+            // step j. Every load of the loop is issued unconditionally (indices clamped), so that the wait before a step's operands is a count of younger loads and not a wait for all of
+            // them. The member's and the complement's factor are masked with the sign-extended bit and its inverse; only the
+            // last step tests its entries. Bound by the number of loads a step issues: two of keys, four times a row of P, a
+            // degree and a full degree (block of 64 coalitions, 1,700 entries x 128: 228 us with two loads per row of P and
+            // keys selected between lane reads, which had become a branch per key; 250 with every lane loading its own
+            // keys; 198 now).
+            constexpr int SRP = 8, QP = SRP / 2;   // entries and entry pairs per step here
+            const int lim = s1 < e1 ? s1 : e1;     // real entries of the piece: s0 .. lim - 1; entry e1 (the self-loop) if s1 > e1
+            struct Keys {
+              int src, p;   // lane i < SRP: entry i of the step
+            };
             struct Ops {
-              float av[SRP / 2][2];
-              int d[SRP / 2], f[SRP / 2], p[SRP / 2];
+              float av[QP][2];
+              int d[QP], f[QP], p[QP];
             };
-            auto load_keys = [&](int eb, int& pk, int& sk) {
-              const int e = eb + (lane < SRP ? lane : 0);
-              const bool real = e < s1 && e < e1;
-              const int ec = real ? e : e1 - 1;
-              const int k_ = key_[ec], c_ = col_[ec];
-              pk = real ? k_ : 0;
-              sk = real ? c_ : t;
+            const int second = -half;   // all ones in the lanes that take the second entry of a pair
+            // the lane's two features of a row of P, f0 + 2 l32 and the next, in one load (the first alone at the end of an
+            // odd width; past it whatever the row's first two are: not stored)
+            typedef float float2_a4 __attribute__((ext_vector_type(2), aligned(4)));
+            const bool odd_end = f0 + 2 * l32 + 1 == d1 && d1 > 1;
+            const int fo = odd_end ? d1 - 2 : f0 + 2 * l32 < d1 ? f0 + 2 * l32 : 0;
+            auto load_keys = [&](Keys& k, int eb) {
+              const int e = eb + (lane & (SRP - 1));
+              const int ec = e < lim ? e : 0;
+              const int c_ = col_[ec];
+              k.p = key_[ec];
+              k.src = t + (e < lim ? c_ - t : 0);   // (a select alone would put the load under a branch)
             };
-            auto load_ops = [&](Ops& o, int pk, int sk) {
+            // the pair's key in the lane's half, without the branch that a select between two lane reads becomes
+            auto mine = [&](int v, int q) {
+              const int a0 = readlane_i(v, 2 * q), a1 = readlane_i(v, 2 * q + 1);
+              return a0 + (second & (a1 - a0));
+            };
+            auto load_ops = [&](Ops& o, const Keys& k) {
 #pragma unroll
-              for (int q = 0; q < SRP / 2; ++q) {
-                const int src = half ? readlane_i(sk, 2 * q + 1) : readlane_i(sk, 2 * q);
-                o.p[q] = half ? readlane_i(pk, 2 * q + 1) : readlane_i(pk, 2 * q);
-                const float* pr = a.P + (size_t)src * d1 + f0;
-                o.av[q][0] = pr[f0 + l32 < d1 ? l32 : 0];
-                o.av[q][1] = pr[f0 + 32 + l32 < d1 ? 32 + l32 : 0];
-                o.d[q] = ext_deg_lane[(size_t)src << b.ext_lr];
+              for (int q = 0; q < QP; ++q) {
+                const unsigned src = (unsigned)mine(k.src, q), at = __umul24(src, (unsigned)d1);   // (at most 65,000 nodes, widths to 4096)
+                o.p[q] = mine(k.p, q);
+                const float2_a4 v = *(const float2_a4*)(a.P + (at + (unsigned)fo));
+                o.av[q][0] = odd_end ? v.y : v.x;
+                o.av[q][1] = v.y;
+                o.d[q] = ext_deg_lane[src << b.ext_lr];
                 o.f[q] = (int)b.fdeg2[src];
               }
             };
-            const bool fok0 = f0 + l32 < d1, fok1 = f0 + 32 + l32 < d1;
-            Ops cur, nxt;
-            int pk1, sk1;
-            load_keys(s0, pk1, sk1);
-            load_ops(cur, pk1, sk1);
-            load_keys(s0 + SRP, pk1, sk1);
-            for (int eb = s0; eb < s1; eb += SRP) {
-              const int cnt = s1 - eb < SRP ? s1 - eb : SRP;
-              load_ops(nxt, pk1, sk1);
-              load_keys(eb + 2 * SRP, pk1, sk1);
+            auto use = [&](const Ops& o, int eb, bool last) {
 #pragma unroll
-              for (int q = 0; q < SRP / 2; ++q) {
-                const int ei = 2 * q + half, p = cur.p[q];
-                const bool ok = ei < cnt, self = eb + ei == e1;
-                const bool bit = (ebs[(p >> 5) * 32 + l32] >> (p & 31)) & 1u;
-                const float b0 = (ok && (self || bit)) ? __frsqrt_rn((float)cur.d[q]) : 0.f;              // the members
-                const float b1 = (ok && (self || !bit)) ? __frsqrt_rn((float)(cur.f[q] - cur.d[q])) : 0.f;  // the complements
-                const float a0 = (ok && fok0) ? cur.av[q][0] : 0.f, a1 = (ok && fok1) ? cur.av[q][1] : 0.f;
-                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
+              for (int q = 0; q < QP; ++q) {
+                const int p = o.p[q];
+                int m0 = __builtin_amdgcn_sbfe((int)ebs[(p >> 5) * 32 + l32], (uint32_t)p, 1), m1 = ~m0;
+                if (last) {
+                  const int e = eb + 2 * q + half;
+                  const int self = e == e1 && e < s1 ? -1 : 0;
+                  m0 = e < lim ? m0 : self;
+                  m1 = e < lim ? m1 : self;
+                }
+                const float b0 = __int_as_float(__float_as_int(__frsqrt_rn((float)o.d[q])) & m0);               // the members
+                const float b1 = __int_as_float(__float_as_int(__frsqrt_rn((float)(o.f[q] - o.d[q]))) & m1);    // the complements
+                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][0], b0, acc[0][0], 0, 0, 0);
+                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][0], b1, acc[0][1], 0, 0, 0);
+                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][1], b0, acc[1][0], 0, 0, 0);
+                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][1], b1, acc[1][1], 0, 0, 0);
               }
-              cur = nxt;
+            };
+            if (s0 < s1) {
+              Keys k1;
+              Ops x0, x1;
+              load_keys(k1, s0);
+              load_ops(x0, k1);
+              load_keys(k1, s0 + SRP);
+              int eb = s0;
+              for (; eb + SRP <= lim; eb += SRP) {
+                load_ops(x1, k1);
+                load_keys(k1, eb + 2 * SRP);
+                use(x0, eb, false);
+                x0 = x1;
+              }
+              if (eb < s1) use(x0, eb, true);
             }
           } else
           for (int eb = s0; eb < s1; eb += kStageRows) {
@@ -769,36 +798,9 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
               av[q][0] = (ok && f0 + l32 < d1) ? pr[0] : 0.f;
               av[q][1] = (ok && f0 + 32 + l32 < d1) ? pr[32] : 0.f;
             }
-            if (EXT && PAIRED) {
-              // Lane (half, j) feeds the matrix cores the coefficients of entry 2q + half for coalition j (the stored
-              // member of pair j) and coalition 32 + j (its complement): both come from one degree of the source and one
-              // bit of the member's row, which this lane reads itself -- no value crosses lanes, and an entry costs one
-              // degree load for the pair instead of one per member.
-              float b0v[kStageRows / 2], b1v[kStageRows / 2];
-#pragma unroll
-              for (int q = 0; q < kStageRows / 2; ++q) {
-                const int ei = 2 * q + half;
-                const int p = half ? readlane_i(pv, 2 * q + 1) : readlane_i(pv, 2 * q);
-                const int src = half ? readlane_i(sv, 2 * q + 1) : readlane_i(sv, 2 * q);
-                const bool ok = ei < cnt, self = eb + ei == e1;
-                const bool bit = (ebs[(p >> 5) * 32 + l32] >> (p & 31)) & 1u;
-                const int d = ext_deg_lane[(size_t)src << b.ext_lr];
-                const int f = (int)b.fdeg2[src];
-                b0v[q] = (ok && (self || bit)) ? __frsqrt_rn((float)d) : 0.f;         // coalitions 0..31: the members
-                b1v[q] = (ok && (self || !bit)) ? __frsqrt_rn((float)(f - d)) : 0.f;  // coalitions 32..63: the complements
-              }
-#pragma unroll
-              for (int q = 0; q < kStageRows / 2; ++q) {
-                if (2 * q < cnt) {
-                  acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[q][0], b0v[q], acc[0][0], 0, 0, 0);
-                  acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[q][0], b1v[q], acc[0][1], 0, 0, 0);
-                  acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[q][1], b0v[q], acc[1][0], 0, 0, 0);
-                  acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[q][1], b1v[q], acc[1][1], 0, 0, 0);
-                }
-              }
-            } else if (!EXT) {
-              // the same without external inputs: lane (half, j) takes the bits of coalitions j and 32 + j from their
-              // mask words and the two degrees from where this kernel keeps them
+            if (!EXT) {
+              // lane (half, j) feeds the matrix cores the coefficients of entry 2q + half for coalitions j and 32 + j: it takes
+              // their bits from their mask words and the two degrees from where this kernel keeps them
               float b0v[kStageRows / 2], b1v[kStageRows / 2];
 #pragma unroll
               for (int q = 0; q < kStageRows / 2; ++q) {
@@ -858,19 +860,19 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
           // accumulator register i of lane l is D[feature 8*(i/4) + 4*(l/32) + i%4][coalition l%32]
           if (!shared) {
             // a full tile without a bias (the usual case) is stored without a test or a load per element
-            const int fl = f0 + 4 * half;
+            const int fl = f0 + (PAIRED ? 8 : 4) * half;
             float* out = bufA + ((size_t)t * d1 + fl) * 64 + l32;
             const float sc0 = half ? rst_sw : rst, sc1 = half ? rst : rst_sw;  // d^-1/2 of row t in coalitions l32, 32 + l32
             if (a.bias[0] == nullptr && f0 + 64 <= d1)
-              store_layer1_tile<false>(acc, out, sc0, sc1, relu, nullptr, fl, d1);
+              store_layer1_tile<false, PAIRED>(acc, out, sc0, sc1, relu, nullptr, fl, d1);
             else
-              store_layer1_tile<true>(acc, out, sc0, sc1, relu, a.bias[0], fl, d1);
+              store_layer1_tile<true, PAIRED>(acc, out, sc0, sc1, relu, a.bias[0], fl, d1);
           } else {
             // The waves' tiles are added in wave order: each wave leaves its own in LDS and all threads add them up, or, where
             // LDS does not hold a tile per wave beside a second workgroup, one wave at a time adds to a single tile
             // (2 x 3 shared rows of a block of 64 coalitions and 128 features, four waves: 242 -> 228 us with the layer).
             const bool own = EXT && PAIRED && b.wave_tiles;
-            float* tl = stage_all + (own ? wave * kWBufFloats : 0) + (4 * half) * 64 + l32;
+            float* tl = stage_all + (own ? wave * kWBufFloats : 0) + ((PAIRED ? 8 : 4) * half) * 64 + l32;
             for (int w = 0; w < (own ? 1 : kBWaves); ++w) {
               if (own || wave == w) {
 #pragma unroll
@@ -879,7 +881,8 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
                   for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                      float* dst = tl + (ft * 32 + 8 * (i / 4) + (i % 4)) * 64 + nb * 32;
+                      const int m = 8 * (i / 4) + (i % 4);
+                      float* dst = tl + (PAIRED ? 2 * m + ft : ft * 32 + m) * 64 + nb * 32;
                       *dst = w == 0 ? acc[ft][nb][i] : *dst + acc[ft][nb][i];
                     }
               }

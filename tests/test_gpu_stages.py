@@ -264,6 +264,30 @@ def test_masked_inference_matches_oracle(key, hops, directed, score, with_bias, 
     _eval_case(w, hops, directed, score, biases, 320, rng, layers=layers)
 
 
+# widths around the 32- and 64-feature tiles and 4-feature pieces of the kernels, odd ones among them; rows of every
+# length class of the masks-on-chip kernel (a hub of 300 entries, which the waves share, 130, 70, 33, 17 and single
+# entries), and a directed graph, whose first-layer rows are read through other players than their own entries
+@pytest.mark.parametrize("dims,directed", [((6, 1, 3), False), ((6, 33, 5, 4), False), ((6, 64, 36, 3), False), ((6, 65, 63, 3), False),
+                                           ((6, 131, 17, 2), False), ((6, 66, 5, 4), True)])
+def test_masked_inference_widths_and_row_lengths(dims, directed):
+    from synth import csr_from_undirected_edges
+    from synth.workloads import Workload, glorot_uniform
+    rng = np.random.default_rng(41)
+    src, dst, at = [], [], 7
+    for i, kids in enumerate((300, 130, 70, 33, 17, 1)):
+        src += [0] + [1 + i] * kids
+        dst += [1 + i] + list(range(at, at + kids))
+        at += kids
+    src += [1, 1, 2, 8, 9]                       # and a few edges within the shells
+    dst += [2, 3, 4, 400, 410]
+    rp, ci = csr_from_undirected_edges(at, src, dst)
+    w = Workload("row_lengths", at, rp, ci, rng.standard_normal((at, dims[0]), dtype=np.float32), dims,
+                 [glorot_uniform(rng, dims[i], dims[i + 1]) for i in range(len(dims) - 1)], [0], 0, 0, "gram_chol")
+    biases = [0.1 * rng.standard_normal(d).astype(np.float32) for d in dims[1:]]
+    say(f"masked inference dims={dims} directed={directed}")
+    _eval_case(w, len(dims) - 1, directed, 1, biases, 322, rng)
+
+
 def test_masked_inference_all_enumerated_rows_tiny(ctx_tiny):
     ctx, w = ctx_tiny
     say("eval c1 all 4096 rows")
