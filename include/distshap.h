@@ -223,7 +223,8 @@ int ds_set_gat(ds_ctx* ctx, int32_t num_layers, const int32_t* head_dims, const 
  *   edge_src, edge_dst: int64[capacity] out or NULL, global ids of the players
  *   report:    [host] out or NULL
  * n == 0 is a success with *M_inout = 0. n_samples < 4 is DS_EINVAL when n >= 2.
- * DS_ECAPACITY writes the needed n to *M_inout and touches no output buffer. */
+ * DS_ECAPACITY writes the needed n to *M_inout; it and a refused argument touch no output buffer.
+ * Whatever the status, no work on the caller's buffers is under way when the call returns. */
 int ds_explain(ds_ctx* ctx, int64_t target, int64_t n_samples, uint64_t seed, const ds_options* opts,
                float* phi, int64_t* M_inout, int64_t* edge_src, int64_t* edge_dst, ds_report* report);
 

@@ -557,10 +557,18 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   ds_report rep;
   memset(&rep, 0, sizeof(rep));
   hipStream_t st = ctx->stream;
+  // queued: work of this call may still be under way on the main stream (whatever the status, the caller's buffers are
+  // its own again when the call returns)
   struct Guard {
-    ds_ctx* c; ds_cgraph* g;
-    ~Guard() { (void)hipStreamSynchronize(c->side); c->lists = ds_pair_lists{}; ds_cgraph_free(c, g); ds_arena_reset(c); }
-  } guard{ctx, cg};
+    ds_ctx* c; ds_cgraph* g; hipStream_t st; bool queued;
+    ~Guard() {
+      if (queued) (void)hipStreamSynchronize(st);
+      (void)hipStreamSynchronize(c->side);
+      c->lists = ds_pair_lists{};
+      ds_cgraph_free(c, g);
+      ds_arena_reset(c);
+    }
+  } guard{ctx, cg, st, false};
   const int64_t n = cg->info.num_players;
   rep.num_players = n;
   rep.num_nodes = cg->info.num_nodes;
@@ -573,7 +581,6 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
     if (report) *report = rep;
     return DS_OK;
   }
-  DS_TRY(export_edges(ctx, cg, edge_src, edge_dst));   // (complete when the call is)
   DS_HIP(ctx, hipEventRecord(ctx->ev[1], st));
 
   const int64_t W = (n + 63) / 64;
@@ -587,6 +594,8 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
     DS_TRY(ds_make_plan(ctx, n, n_samples, &plan, o.weighting, o.saturate ? 1 : 0));
     k = plan.k;
   }
+  guard.queued = true;   // (the arguments have all been looked at: a refused one has left the output buffers alone)
+  DS_TRY(export_edges(ctx, cg, edge_src, edge_dst));
   rep.num_rows = k;
   rep.enumerated = n >= 2 ? plan.enumerate : 1;
   // workspace: Z, w, sz, y live for the whole call; stage temporaries follow them
@@ -688,6 +697,7 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   DS_HIP(ctx, hipGetLastError());
   DS_HIP(ctx, hipMemcpyAsync(ctx->h_mail + 32, ctx->d_mail + 32, 5 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
   DS_HIP(ctx, hipStreamSynchronize(st));
+  guard.queued = false;
   if (n >= 2 && ctx->h_mail[35] != 0)
     return ds_fail(ctx, DS_EINTERNAL, "sampler: candidate list overflow (too many keys share a 24-bit prefix)");
   if (direct && *(int*)(ctx->h_mail + 36) != 0) {
@@ -696,6 +706,7 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
     // rank-deficient: the minimum-norm solve instead
     int iters = 0;
     double rel = 0.0;
+    guard.queued = true;
     rc = ds_solve_cgls_impl(ctx, n, k, Z, w, y, 1, o.tol, o.max_iter, phi, &iters, &rel);
     rep.solver_used = DS_SOLVER_CGLS;
     rep.cgls_iterations = iters;
@@ -703,6 +714,7 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
     if (rc != DS_OK && rc != DS_ENOTCONV) return rc;
     DS_HIP(ctx, hipEventRecord(ctx->ev[4], st));
     DS_HIP(ctx, hipStreamSynchronize(st));
+    guard.queued = false;
   }
   rep.f_empty = f01[0];
   rep.f_full = f01[1];

@@ -337,3 +337,30 @@ def test_explaining_an_extracted_graph_equals_explaining_its_target():
     c = ctx.explain(w.targets[0], w.n_samples, w.seed)
     assert torch.equal(a[0], c[0])
     ctx.close()
+
+
+def test_a_refused_explanation_leaves_the_output_buffers_alone():
+    """Every argument that is only looked at after the extraction (number of samples, weighting, saturation), through
+    each of the three entry points: the output buffers hold what the caller put there, also once the device is idle."""
+    import ctypes as C
+    from paper_2506_22668_amd import Options
+    from paper_2506_22668_amd.binding import DS_EINVAL, Report, _ptr
+    w = make_workload("c2_small")
+    ctx = make_context(w)
+    target = w.targets[0]
+    n = ctx.explain(target, w.n_samples, w.seed)[3].num_players
+    phi = torch.full((2 * n,), -7.0, dtype=torch.float32, device="cuda")
+    es, ed = (torch.full((2 * n,), -7, dtype=torch.int64, device="cuda") for _ in range(2))
+    torch.cuda.synchronize()
+    for ns, opts in ((2, Options()), (w.n_samples, Options(weighting=9)), (w.n_samples, Options(weighting=1, saturate=1))):
+        say(f"refused explanations n_samples={ns} weighting={opts.weighting} saturate={opts.saturate}")
+        m, rep, o = C.c_int64(n), Report(), C.byref(opts)
+        tail = (_ptr(phi), C.byref(m), _ptr(es), _ptr(ed), C.byref(rep))
+        assert ctx.lib.ds_explain(ctx.h, target, ns, w.seed, o, *tail) == DS_EINVAL
+        assert ctx.lib.ds_explain_cgraph(ctx.h, ctx.extract(target, opts), ns, w.seed, o, *tail) == DS_EINVAL
+        M, off, reps = (C.c_int64 * 2)(), (C.c_int64 * 3)(), (Report * 2)()
+        assert ctx.lib.ds_explain_batch(ctx.h, (C.c_int64 * 2)(target, target), 2, ns, w.seed, o, _ptr(phi), M, off,
+                                        _ptr(es), _ptr(ed), 2 * n, reps) == DS_EINVAL
+        torch.cuda.synchronize()
+        assert bool((phi == -7).all()) and bool((es == -7).all()) and bool((ed == -7).all())
+    ctx.close()
