@@ -230,7 +230,8 @@ int ds_explain(ds_ctx* ctx, int64_t target, int64_t n_samples, uint64_t seed, co
 
 /* ds_explain of a graph that ds_extract has already built with the same options and model (a caller that sizes its
  * buffers by ds_cgraph_get_info does not extract twice). Takes over cg: it is released before the call returns,
- * whatever the status, unless a required argument is null or cg belongs to another context (DS_EINVAL). */
+ * whatever the status, unless a required argument is null or cg is not a live graph of this context (one released
+ * before, by ds_cgraph_free or an earlier call of this function, or another context's): DS_EINVAL, nothing is released. */
 int ds_explain_cgraph(ds_ctx* ctx, ds_cgraph* cg, int64_t n_samples, uint64_t seed, const ds_options* opts, float* phi,
                       int64_t* M_inout, int64_t* edge_src, int64_t* edge_dst, ds_report* report);
 

@@ -1,6 +1,7 @@
 // C ABI entry points: argument checks, workspace, and the end-to-end explanation.
 #include "internal.h"
 
+#include <algorithm>
 #include <string>
 #include <condition_variable>
 #include <mutex>
@@ -541,7 +542,9 @@ int ds_explain(ds_ctx* ctx, int64_t target, int64_t n_samples, uint64_t seed, co
 int ds_explain_cgraph(ds_ctx* ctx, ds_cgraph* cg, int64_t n_samples, uint64_t seed, const ds_options* opts, float* phi,
                       int64_t* M_inout, int64_t* edge_src, int64_t* edge_dst, ds_report* report) {
   if (!ctx || !cg || !M_inout) return DS_EINVAL;
-  if (cg->owner != ctx) return ds_fail(ctx, DS_EINVAL, "the computational graph belongs to another context");
+  // (the handle is looked up before it is followed: one that was released points at freed memory)
+  if (std::find(ctx->graphs.begin(), ctx->graphs.end(), cg) == ctx->graphs.end())
+    return ds_fail(ctx, DS_EINVAL, "the computational graph is not a live graph of this context (released, or another context's)");
   DS_HIP(ctx, hipSetDevice(ctx->device));
   if (ctx->L < 1) {
     ds_cgraph_free(ctx, cg);

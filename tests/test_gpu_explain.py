@@ -364,3 +364,65 @@ def test_a_refused_explanation_leaves_the_output_buffers_alone():
         torch.cuda.synchronize()
         assert bool((phi == -7).all()) and bool((es == -7).all()) and bool((ed == -7).all())
     ctx.close()
+
+
+def test_an_explained_graph_is_taken_over_once():
+    """ds_explain_cgraph releases its graph whatever the status, and refuses a handle that is not a live graph of its
+    context: one it has taken over, one released by ds_cgraph_free, another context's (which stays usable)."""
+    import ctypes as C
+    from paper_2506_22668_amd import Context, Options
+    from paper_2506_22668_amd.binding import DS_EINVAL, DS_OK, Report, _ptr
+    w = make_workload("c2_small")
+    rng = np.random.default_rng(5)
+    # wide features: a graph's block is several hundred kilobytes, so that a leaked one shows in the free memory
+    w.features = rng.standard_normal((w.num_nodes, 512), dtype=np.float32)
+    w.weights = [rng.standard_normal((512, w.weights[0].shape[1])).astype(np.float32) / 16] + list(w.weights[1:])
+    target, ns, opts = w.targets[0], w.n_samples, Options()
+    ctx, other = make_context(w), make_context(w)
+    cap = 4096
+    phi = torch.empty(cap, dtype=torch.float32, device="cuda")
+
+    def run(c, cg, samples=ns):
+        m = C.c_int64(cap)
+        return c.lib.ds_explain_cgraph(c.h, cg, samples, w.seed, C.byref(opts), _ptr(phi), C.byref(m), None, None, C.byref(Report()))
+
+    say("handles: twice, after a free, another context's")
+    cg = ctx.extract(target, opts)
+    assert run(ctx, cg) == DS_OK
+    want = phi.clone()
+    assert run(ctx, cg) == DS_EINVAL and b"live" in ctx.lib.ds_last_error(ctx.h)
+    cg = ctx.extract(target, opts)
+    assert run(ctx, cg, 2) == DS_EINVAL and run(ctx, cg) == DS_EINVAL
+    cg = ctx.extract(target, opts)
+    ctx.cgraph_free(cg)
+    assert run(ctx, cg) == DS_EINVAL
+    theirs = other.extract(target, opts)
+    assert run(ctx, theirs) == DS_EINVAL
+    phi.zero_()
+    torch.cuda.synchronize()
+    n = other.cgraph_info(theirs).num_players
+    assert run(other, theirs) == DS_OK and torch.equal(phi[:n], want[:n])
+    other.close()
+
+    say("handle of a context without a model")
+    bare = Context("cuda:0")
+    bare.set_graph(w.row_ptr, w.col)
+    bare.set_features(w.features)
+    cg = bare.extract(target, Options(hops=3))
+    assert run(bare, cg) == DS_EINVAL and b"model" in bare.lib.ds_last_error(bare.h)
+    assert run(bare, cg) == DS_EINVAL and b"live" in bare.lib.ds_last_error(bare.h)
+    bare.close()
+
+    say("free memory over failing and succeeding calls")
+    for _ in range(2):                                   # (the workspace and the spare block are kept)
+        assert run(ctx, ctx.extract(target, opts)) == DS_OK
+    info = ctx.extract(target, opts)
+    block = ctx.cgraph_info(info).num_nodes * 512 * 4
+    ctx.cgraph_free(info)
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    for i in range(24):
+        assert run(ctx, ctx.extract(target, opts), ns if i % 2 else 2) == (DS_OK if i % 2 else DS_EINVAL)
+    torch.cuda.synchronize()
+    assert block > 200_000 and free0 - torch.cuda.mem_get_info()[0] < 4 * block
+    ctx.close()
