@@ -749,18 +749,21 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
               for (int q = 0; q < QP; ++q) {
                 const int p = o.p[q];
                 int m0 = __builtin_amdgcn_sbfe((int)ebs[(p >> 5) * 32 + l32], (uint32_t)p, 1), m1 = ~m0;
-                if (last) {
+                float a0 = o.av[q][0], a1 = o.av[q][1];
+                if (last) {   // (a slot past the end multiplies zeros: the row it has loaded, this one, may hold an infinity)
                   const int e = eb + 2 * q + half;
                   const int self = e == e1 && e < s1 ? -1 : 0;
                   m0 = e < lim ? m0 : self;
                   m1 = e < lim ? m1 : self;
+                  a0 = e < lim || self ? a0 : 0.f;
+                  a1 = e < lim || self ? a1 : 0.f;
                 }
                 const float b0 = __int_as_float(__float_as_int(__frsqrt_rn((float)o.d[q])) & m0);               // the members
                 const float b1 = __int_as_float(__float_as_int(__frsqrt_rn((float)(o.f[q] - o.d[q]))) & m1);    // the complements
-                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][0], b0, acc[0][0], 0, 0, 0);
-                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][0], b1, acc[0][1], 0, 0, 0);
-                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][1], b0, acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][1], b1, acc[1][1], 0, 0, 0);
+                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
+                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
+                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
+                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
               }
             };
             if (s0 < s1) {
@@ -985,17 +988,20 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
                     r0 = rs[(size_t)src * 64 + l32];
                     r1 = rs[(size_t)src * 64 + 32 + l32];
                   }
-                  if (last) {
+                  float a0 = o.av[q][0], a1 = o.av[q][1];
+                  if (last) {   // (a slot past the end multiplies zeros: the row it has loaded, this one, may hold an infinity)
                     const int e = eb + 2 * q + half;
                     m0 = e < e1 ? m0 : e == e1 ? -1 : 0;
                     m1 = e < e1 ? m1 : e == e1 ? -1 : 0;
+                    a0 = e <= e1 ? a0 : 0.f;
+                    a1 = e <= e1 ? a1 : 0.f;
                   }
                   const float b0 = __int_as_float(__float_as_int(r0) & m0), b1 = __int_as_float(__float_as_int(r1) & m1);
-                  acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][0], b0, acc[0][0], 0, 0, 0);
-                  acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][0], b1, acc[0][1], 0, 0, 0);
+                  acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
+                  acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
                   if (two) {
-                    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][1], b0, acc[1][0], 0, 0, 0);
-                    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.av[q][1], b1, acc[1][1], 0, 0, 0);
+                    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
+                    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
                   }
                 }
               };

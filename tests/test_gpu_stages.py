@@ -288,6 +288,33 @@ def test_masked_inference_widths_and_row_lengths(dims, directed):
     _eval_case(w, len(dims) - 1, directed, 1, biases, 322, rng)
 
 
+# a row's own term stays what it is where the row's features are infinite: the slots that fill up the last step of a row
+# (steps of 2, 4 and 8 entries) must not multiply it by a zero. One layer, so that no other row reads the target's.
+@pytest.mark.parametrize("leaves", [1, 2, 3, 4, 5, 6, 7, 8, 9, 21, 260, 301])
+def test_infinite_features_of_the_target_stay_infinite(leaves):
+    from paper_2506_22668_amd import Options, Tuning
+    from synth import csr_from_undirected_edges
+    from synth.workloads import Workload
+    rng = np.random.default_rng(leaves)
+    rp, ci = csr_from_undirected_edges(leaves + 1, [0] * leaves, list(range(1, leaves + 1)))
+    X = rng.standard_normal((leaves + 1, 5), dtype=np.float32)
+    X[0, 0] = np.inf
+    W1 = rng.uniform(0.5, 1.0, (5, 3)).astype(np.float32) * np.array([-1, 1, -1], dtype=np.float32)
+    w = Workload("inf", leaves + 1, rp, ci, X, (5, 3), [W1], [0], 0, 0, "gram_chol")
+    ctx = make_context(w)
+    cg = ctx.extract(0, Options(hops=1))
+    bits = rng.random((258, leaves)) < rng.random((258, 1))
+    bits[1::2] = ~bits[0::2]
+    Z = torch.from_numpy(sampling.pack_rows(bits).view(np.int64)).cuda()
+    for path, pairs in ((0, False), (1, False), (2, False), (3, False), (0, True), (3, True)):
+        say(f"infinite features leaves={leaves} path={path} pairs={pairs}")
+        ctx.set_tuning(Tuning(eval_path=path))
+        y, pc = ctx.eval(cg, Z, 1, pairs=pairs)
+        assert pc == 1 and bool((y == np.inf).all())
+    ctx.cgraph_free(cg)
+    ctx.close()
+
+
 def test_masked_inference_all_enumerated_rows_tiny(ctx_tiny):
     ctx, w = ctx_tiny
     say("eval c1 all 4096 rows")
