@@ -679,8 +679,9 @@ GatL1Layout gat_l1_layout(const ds_ctx* ctx, const ds_cgraph* cg, int64_t k) {
   q.transpose = true;
   if ((size_t)k * W * 8 > ((size_t)1 << 30) || q.E1 > kL1MaxEntries) return q;
   q.zt_bytes = (size_t)cg->info.num_players * q.KW * 8;
-  // layer 2's transform rides along where its columns fit one matrix-core tile and its weights LDS
-  q.fuse = ctx->gat.zw[1] <= 32 && q.zwr <= 256;
+  // layer 2's transform rides along where its columns fit one matrix-core tile and its weights LDS, and where what it
+  // hands on is no larger than the first layer's output, by which the workspace was admitted above
+  q.fuse = ctx->gat.zw[1] <= 32 && q.zwr <= 256 && ctx->gat.zw[1] <= ctx->gat.zw[0];
   if (q.fuse) q.h1_bytes = (size_t)k * q.R1 * ctx->gat.zw[1] * 4;   // z2 in its place
   q.lds_bytes = (((size_t)2 * (q.E1 + 2) * 8 + 15) & ~(size_t)15) + (q.fuse ? (size_t)q.zwr * 128 : 0) +
                 (size_t)kWaves * (ctx->gat.heads[0] * 33 + 32 * 33) * 4;

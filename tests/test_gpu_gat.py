@@ -101,6 +101,34 @@ def test_masked_gat_second_transform_on_the_way_out(heads, widths):
     _eval_case(w, model, 2, False, 1, 257, rng, biases)   # two blocks of 128 coalitions and one row
 
 
+def test_masked_gat_workspace_follows_the_narrower_layer():
+    """What the first layer's kernel hands on ([k][rows][columns]) is never larger than the first layer's own output,
+    which the 2 GiB limit of that path is tested against: a narrow first layer in front of many classes keeps it small."""
+    w = make_workload("gat_small")
+    rng = np.random.default_rng(3)
+    model = _gat_model(rng, w.features.shape[1], (1, 1), (4, 32))
+    ctx = _context(w, model)
+    from paper_2506_22668_amd import Options
+    cg = ctx.extract(w.targets[0], Options(hops=2))
+    info = ctx.cgraph_info(cg)
+    n, r1, k = info.num_players, info.ball[1], 1 << 16
+    bits = _random_rows(n, 512, rng)
+    Z = torch.from_numpy(sampling.pack_rows(bits).view(np.int64)).cuda().repeat(k // 512, 1).contiguous()
+    y512, _ = ctx.eval(cg, Z[:512])
+    spare = torch.empty(k, dtype=torch.float32, device="cuda")   # (the allocator then has the output's memory)
+    del spare
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    y, _ = ctx.eval(cg, Z)
+    used = free0 - torch.cuda.mem_get_info()[0]
+    h1, masks = k * r1 * 4 * 4, k * ((n + 63) // 64) * 8
+    say(f"gat workspace n={n} rows={r1} k={k}: {used >> 20} MiB, first layer {h1 >> 20} MiB, masks {masks >> 20} MiB")
+    assert used <= h1 + 2 * masks + (8 << 20) < k * r1 * 32 * 4
+    assert torch.equal(y.view(-1, 512), y512.expand(k // 512, 512))
+    ctx.cgraph_free(cg)
+    ctx.close()
+
+
 def test_masked_gat_wide_attention_range_falls_back_to_the_running_maximum():
     """Attention vectors scaled up until the logits of one row span more than exp() can hold in fp32 relative
     to the row maximum: the matrix-core path for layer 1 must step aside (its weights would underflow) and the
