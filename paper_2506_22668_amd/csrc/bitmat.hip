@@ -2,6 +2,7 @@
 // regression targets and the bit-matrix transpose.
 #include "internal.h"
 #include "solve_common.h"
+#include "mm_split.h"
 
 namespace {
 constexpr int kThreads = 256;
@@ -554,34 +555,9 @@ static void mm_shape(const ds_ctx* ctx, int64_t rows, int64_t cols, ds_mm_plan* 
   p->row_groups = (rows + kMmRows - 1) / kMmRows;
   p->n_chunks = (cols + kMmChunk - 1) / kMmChunk;
   p->npad = p->n_chunks * kMmChunk;
-  // Column groups: two workgroups fit a compute unit (registers), so a launch runs in rounds of up to 2 x CUs of them.
-  // Every split is priced, in us as measured on this card, and the cheapest taken: a round of w workgroups spends
-  // 0.9 + 0.0054 w on each chunk of its groups (the first term is the latency that a workgroup alone waits for, the
-  // second the memory's rate), and a group's digit sums are written and read once more by whoever adds them up.
-  // 8,000 dense rows x 300,000 columns: 84.8 -> 85 forward, 120 -> 94 adjoint, and the kernels that add up 9.8 -> 7.6
-  // and 14.1 -> 8.6; 10,000 x 100,000: 48.4 -> 36.5, 65 -> 42, 8.6 -> 6.4, 14.8 -> 8.5 (before: whichever split gave 3 to
-  // 10 rounds with the least idle in the last one, which on matrices this small means groups of two chunks).
-  const int64_t cap = 2 * (int64_t)ctx->num_cus, rg = p->row_groups > 0 ? p->row_groups : 1;
-  const int64_t max_cpg = kMmMaxGroupCols / kMmChunk;
-  int64_t g_hi = (10 * cap + rg - 1) / rg;
-  if (g_hi > p->n_chunks) g_hi = p->n_chunks;
-  double best = -1.0;
-  p->cpg = p->n_chunks > 0 ? p->n_chunks : 1;
-  p->groups = 1;
-  for (int64_t g = 1; g <= g_hi; ++g) {
-    int64_t cpg = (p->n_chunks + g - 1) / g;
-    if (cpg > max_cpg) cpg = max_cpg;
-    if (cpg < 1) cpg = 1;
-    const int64_t groups = (p->n_chunks + cpg - 1) / cpg;
-    const int64_t wgs = rg * groups, rounds = wgs / cap, rest = wgs % cap;
-    auto round_us = [&](int64_t w) { return w > 0 ? (double)cpg * (0.9 + 0.0054 * (double)w * 512.0 / (double)cap) : 0.0; };
-    const double us = (double)rounds * round_us(cap) + round_us(rest) + (double)groups * (double)rows * (kMmPlanes * 4) * 1.5e-6;
-    if (best < 0.0 || us < best) {
-      best = us;
-      p->cpg = cpg;
-      p->groups = groups;
-    }
-  }
+  const ds_mm_split c = ds_mm_choose_split(ctx->num_cus, rows, p->row_groups, p->n_chunks, kMmMaxGroupCols / kMmChunk, kMmPlanes * 4);
+  p->cpg = c.cpg;
+  p->groups = c.groups;
 }
 
 size_t ds_bit_spmv_mm_ws_bytes(const ds_ctx* ctx, int64_t rows, int64_t cols) {

@@ -1,0 +1,42 @@
+// How the matrix-core product of the bit-packed rows (bitmat.hip) is cut into column groups. Host code only.
+#pragma once
+#include <stdint.h>
+
+struct ds_mm_split {
+  int64_t cpg, groups;   // chunks per column group; column groups
+};
+
+// Two workgroups fit a compute unit (registers), so a launch runs in rounds of up to 2 x CUs of them. Every split is
+// priced, in us as measured on this card, and the cheapest taken. A round costs, per chunk of its groups, 2.6 with two
+// workgroups on a unit, also where only some units hold two, and 1.6 with at most one on each: a workgroup waits for the
+// latency of its loads and, where two share a unit, for the other. A group's digit sums (`sum_bytes` a row) are written
+// and read once more by whoever adds them up: 1 us per MB. The three figures are fitted to sweeps of the number of
+// groups over both products of ten games (matrices of 9 MB to 7.2 GB; inside and outside of the Infinity Cache they
+// differ less than the fit is off). us per CGLS iteration, against a price that grew with the number of workgroups in
+// flight and took digit sums for 1.5 times as dear (dense rows x columns of the forward product):
+//   34,267 x 99,981  335.0 -> 322.9 (428 MB; 3 and 1 groups instead of 7 and 5 left a fifth of the places empty)
+//   32,409 x 200,003 558.4 -> 537.7    15,121 x 500,009 618.7 -> 613.4    7,906 x 20,011 76.1 -> 72.7
+//   3,425 x 100,428 86.5 -> 86.9; 57,572 x 1,000,175, 9,424 x 300,007, 18,176 x 50,021 and 10,280 x 99,981: same splits
+inline ds_mm_split ds_mm_choose_split(int64_t num_cus, int64_t rows, int64_t row_groups, int64_t n_chunks, int64_t max_cpg,
+                                      int64_t sum_bytes) {
+  const int64_t cap = 2 * num_cus, rg = row_groups > 0 ? row_groups : 1;
+  int64_t g_hi = (10 * cap + rg - 1) / rg;
+  if (g_hi > n_chunks) g_hi = n_chunks;
+  ds_mm_split best = {n_chunks > 0 ? n_chunks : 1, 1};
+  double best_us = -1.0;
+  for (int64_t g = 1; g <= g_hi; ++g) {
+    int64_t cpg = (n_chunks + g - 1) / g;
+    if (cpg > max_cpg) cpg = max_cpg;
+    if (cpg < 1) cpg = 1;
+    const int64_t groups = (n_chunks + cpg - 1) / cpg;
+    const int64_t wgs = rg * groups, rest = wgs % cap;
+    const double per_chunk = 2.6 * (double)(wgs / cap) + (rest == 0 ? 0.0 : rest <= num_cus ? 1.6 : 2.6);
+    const double us = (double)cpg * per_chunk + (double)groups * (double)rows * (double)sum_bytes * 1.0e-6;
+    if (best_us < 0.0 || us < best_us) {
+      best_us = us;
+      best.cpg = cpg;
+      best.groups = groups;
+    }
+  }
+  return best;
+}
