@@ -107,6 +107,7 @@ int ds_create(ds_ctx** out, int device, void* stream) {
   ctx->h_stage = nullptr;
   ctx->h_stage_bytes = 0;
   ctx->stage_busy = false;
+  ctx->timed = nullptr;
   if (hipEventCreate(&ctx->stage_ev) != hipSuccess) { delete ctx; return DS_EDEVICE; }
   if (hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming) != hipSuccess ||
@@ -256,17 +257,32 @@ static ds_options default_options(const ds_options* in) {
   return o;
 }
 
-int ds_extract(ds_ctx* ctx, int64_t target, const ds_options* opts, ds_cgraph** out) {
-  if (!ctx || !out) return DS_EINVAL;
+// The time of the last extraction by ds_extract, from the context's events into its graph, before they are recorded again.
+static void settle_extraction_time(ds_ctx* ctx) {
+  if (!ctx->timed) return;
+  if (hipEventSynchronize(ctx->ev[5]) != hipSuccess || hipEventElapsedTime(&ctx->timed->ms_extract, ctx->ev[0], ctx->ev[5]) != hipSuccess)
+    (void)hipGetLastError();
+  ctx->timed = nullptr;
+}
+
+static int extract_checked(ds_ctx* ctx, int64_t target, const ds_options& o, ds_cgraph** out) {
   *out = nullptr;
   DS_HIP(ctx, hipSetDevice(ctx->device));
-  ds_options o = default_options(opts);
   int hops = o.hops > 0 ? o.hops : ctx->L;
   if (hops < 1) return ds_fail(ctx, DS_EINVAL, "hops is 0 and no model is set");
   if (ctx->d0 > 0 && ctx->L > 0 && ctx->d0 != ctx->dims[0])
     return ds_fail(ctx, DS_EINVAL, "feature width %d does not match the model's input width %d", ctx->d0, ctx->dims[0]);
-  DS_HIP(ctx, hipEventRecord(ctx->ev[0], ctx->stream));   // an explanation of this graph counts its time from here
+  settle_extraction_time(ctx);
+  DS_HIP(ctx, hipEventRecord(ctx->ev[0], ctx->stream));   // an explanation that goes on with the graph counts from here
   return ds_extract_impl(ctx, target, hops, o.directed ? 1 : 0, out);
+}
+
+int ds_extract(ds_ctx* ctx, int64_t target, const ds_options* opts, ds_cgraph** out) {
+  if (!ctx || !out) return DS_EINVAL;
+  DS_TRY(extract_checked(ctx, target, default_options(opts), out));
+  if (hipEventRecord(ctx->ev[5], ctx->stream) == hipSuccess) ctx->timed = *out;   // (read when ds_explain_cgraph asks for it)
+  else (void)hipGetLastError();
+  return DS_OK;
 }
 
 int ds_cgraph_get_info(const ds_cgraph* cg, ds_cgraph_info* info) {
@@ -325,6 +341,7 @@ int ds_cgraph_first_transform(ds_ctx* ctx, ds_cgraph* cg, float* out) {
 int ds_cgraph_free(ds_ctx* ctx, ds_cgraph* cg) {
   if (!cg) return DS_OK;
   if (!ctx) ctx = cg->owner;
+  if (ctx->timed == cg) ctx->timed = nullptr;
   for (size_t i = 0; i < ctx->graphs.size(); ++i)
     if (ctx->graphs[i] == cg) {
       ctx->graphs.erase(ctx->graphs.begin() + i);
@@ -535,7 +552,7 @@ int ds_explain(ds_ctx* ctx, int64_t target, int64_t n_samples, uint64_t seed, co
   if (ctx->L < 1) return ds_fail(ctx, DS_EINVAL, "no model is set (ds_set_gcn / ds_set_gat)");
   for (int i = 0; i < 5; ++i) ctx->kev_set[i] = false;
   ds_cgraph* cg = nullptr;
-  DS_TRY(ds_extract(ctx, target, &o, &cg));
+  DS_TRY(extract_checked(ctx, target, o, &cg));
   return explain_extracted(ctx, cg, target, n_samples, seed, o, phi, M_inout, edge_src, edge_dst, report);
 }
 
@@ -551,10 +568,18 @@ int ds_explain_cgraph(ds_ctx* ctx, ds_cgraph* cg, int64_t n_samples, uint64_t se
     return ds_fail(ctx, DS_EINVAL, "no model is set (ds_set_gcn / ds_set_gat)");
   }
   for (int i = 0; i < 5; ++i) ctx->kev_set[i] = false;
+  // the clock starts here; the extraction's own time is added to it, what the caller did in between is not
+  settle_extraction_time(ctx);
+  if (hipEventRecord(ctx->ev[0], ctx->stream) != hipSuccess) {
+    (void)hipGetLastError();
+    ds_cgraph_free(ctx, cg);
+    return ds_fail(ctx, DS_EDEVICE, "cannot record an event");
+  }
   return explain_extracted(ctx, cg, cg->info.target, n_samples, seed, default_options(opts), phi, M_inout, edge_src, edge_dst, report);
 }
 
-// Everything after the extraction, which recorded ctx->ev[0]; takes over (and frees) the computational graph.
+// Everything after the extraction; ctx->ev[0] has been recorded before it (or, with the extraction's time in the graph,
+// after it). Takes over (and frees) the computational graph.
 static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t n_samples, uint64_t seed, const ds_options& o,
                              float* phi, int64_t* M_inout, int64_t* edge_src, int64_t* edge_dst, ds_report* report) {
   ds_report rep;
@@ -728,6 +753,8 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   hipEventElapsedTime(&rep.ms_eval, ctx->ev[2], ctx->ev[3]);
   hipEventElapsedTime(&rep.ms_solve, ctx->ev[3], ctx->ev[4]);
   hipEventElapsedTime(&rep.ms_total, ctx->ev[0], ctx->ev[4]);
+  rep.ms_extract += cg->ms_extract;   // (0 unless ds_extract built the graph)
+  rep.ms_total += cg->ms_extract;
   kernel_times(ctx, &rep);
   rep.num_pairs = k / 2 - 1;
   {
@@ -802,7 +829,7 @@ int ds_explain_batch(ds_ctx* ctx, const int64_t* targets, int32_t num_targets, i
   {
     ds_ctx* w0 = ctx->workers[0];
     for (int i = 0; i < 5; ++i) w0->kev_set[i] = false;
-    const int rc = ds_extract(w0, targets[0], &o, &first_cg);
+    const int rc = extract_checked(w0, targets[0], o, &first_cg);
     if (rc != DS_OK) {
       strncpy(ctx->err, w0->err, sizeof(ctx->err) - 1);
       return rc;
@@ -828,7 +855,7 @@ int ds_explain_batch(ds_ctx* ctx, const int64_t* targets, int32_t num_targets, i
             cg = first_cg;
           } else {
             for (int i = 0; i < 5; ++i) w->kev_set[i] = false;
-            rc = ds_extract(w, targets[t], &o, &cg);
+            rc = extract_checked(w, targets[t], o, &cg);
           }
           status[t] = rc;
           if (rc != DS_OK) errs[t] = w->err;

@@ -426,3 +426,33 @@ def test_an_explained_graph_is_taken_over_once():
     torch.cuda.synchronize()
     assert block > 200_000 and free0 - torch.cuda.mem_get_info()[0] < 4 * block
     ctx.close()
+
+
+def test_times_of_an_explanation_are_its_own():
+    """What the caller does between ds_extract and ds_explain_cgraph (other extractions and explanations, waiting) is in
+    none of the report's times; the graph's own extraction is."""
+    import ctypes as C
+    import time
+    from paper_2506_22668_amd import Options
+    from paper_2506_22668_amd.binding import DS_OK, Report
+    w = make_workload("c2_small")
+    ctx = make_context(w)
+    opts, phi = Options(), torch.empty(4096, dtype=torch.float32, device="cuda")
+    ctx.explain(w.targets[0], w.n_samples, w.seed)
+
+    def run(cg):
+        m, rep = C.c_int64(4096), Report()
+        assert ctx.lib.ds_explain_cgraph(ctx.h, cg, w.n_samples, w.seed, C.byref(opts), C.c_void_p(phi.data_ptr()), C.byref(m),
+                                         None, None, C.byref(rep)) == DS_OK
+        return rep
+
+    say("times of two extracted graphs")
+    first = ctx.extract(w.targets[0], opts)
+    time.sleep(0.25)
+    second = ctx.extract(w.targets[0], opts)
+    time.sleep(0.25)
+    ctx.explain(w.targets[0], w.n_samples, w.seed, capacity=4096)   # (an explanation that extracts for itself)
+    for rep in (run(first), run(second), ctx.explain(w.targets[0], w.n_samples, w.seed)[3]):
+        assert 0 < rep.ms_extract < rep.ms_total < 200
+        assert abs(rep.ms_extract + rep.ms_sample + rep.ms_eval + rep.ms_solve - rep.ms_total) <= 0.02
+    ctx.close()
