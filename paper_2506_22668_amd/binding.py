@@ -263,22 +263,28 @@ class Context:
                 allow_not_converged=False):
         t = self.torch
         opts = options or Options()
+        target, n_samples, seed = int(target), int(n_samples), C.c_uint64(int(seed))
         cg = None
         if capacity is None:  # the buffers are sized by the extracted graph, which the explanation then takes over
             cg = self.extract(target, opts)
-            capacity = self.cgraph_info(cg).num_players
-        cap = max(int(capacity), 1)
-        phi = t.empty(cap, dtype=t.float32, device=self.device)
-        es = t.empty(cap, dtype=t.int64, device=self.device) if want_edges else None
-        ed = t.empty(cap, dtype=t.int64, device=self.device) if want_edges else None
-        m = C.c_int64(int(capacity))
-        rep = Report()
-        self._sync_inputs()
-        args = (int(n_samples), C.c_uint64(int(seed)), C.byref(opts), _ptr(phi), C.byref(m), _ptr(es), _ptr(ed), C.byref(rep))
+        try:
+            capacity = int(capacity) if cg is None else self.cgraph_info(cg).num_players
+            cap = max(capacity, 1)
+            phi = t.empty(cap, dtype=t.float32, device=self.device)
+            es = t.empty(cap, dtype=t.int64, device=self.device) if want_edges else None
+            ed = t.empty(cap, dtype=t.int64, device=self.device) if want_edges else None
+            m = C.c_int64(capacity)
+            rep = Report()
+            self._sync_inputs()
+            args = (n_samples, seed, C.byref(opts), _ptr(phi), C.byref(m), _ptr(es), _ptr(ed), C.byref(rep))
+        except BaseException:  # (no memory for the buffers, say: the graph has not been handed over)
+            if cg is not None:
+                self.lib.ds_cgraph_free(self.h, cg)
+            raise
         if cg is not None:
             rc = self.lib.ds_explain_cgraph(self.h, cg, *args)
         else:
-            rc = self.lib.ds_explain(self.h, int(target), *args)
+            rc = self.lib.ds_explain(self.h, target, *args)
         self._check(rc, allow=(DS_ENOTCONV,) if allow_not_converged else ())
         n = m.value
         return phi[:n], (es[:n] if want_edges else None), (ed[:n] if want_edges else None), rep, rc
