@@ -288,6 +288,38 @@ def test_masked_inference_widths_and_row_lengths(dims, directed):
     _eval_case(w, len(dims) - 1, directed, 1, biases, 322, rng)
 
 
+# graphs past the limits of the smaller ones above: degrees outside of LDS (more than 640 nodes), with the local CSR in LDS
+# and without, and more than 4,096 first-layer entries, where the waves of the paired external-input form add up a
+# shared row in a single tile; an odd width and one above 64 of each, two layers (as many shared rows as children above
+# 256) and three
+@pytest.mark.parametrize("kids,dims", [((420, 130, 70, 33, 17, 1), (6, 33, 3)), ((420, 130, 70, 33, 17, 1), (6, 131, 5, 4)),
+                                       ((1800, 1500, 1200, 900, 600, 300, 70, 33, 17, 1), (6, 33, 3)),
+                                       ((1800, 1500, 1200, 900, 600, 300, 70, 33, 17, 1), (6, 131, 3)),
+                                       ((1800, 1500, 1200, 900, 600, 300, 70, 33, 17, 1), (6, 66, 5, 4))])
+def test_masked_inference_beyond_the_on_chip_limits(kids, dims):
+    from synth import csr_from_undirected_edges
+    from synth.workloads import Workload, glorot_uniform
+    rng = np.random.default_rng(43)
+    m = len(kids)
+    src, dst, at = [], [], 1 + m
+    for i, c in enumerate(kids):
+        src += [0] + [1 + i] * c
+        dst += [1 + i] + list(range(at, at + c))
+        at += c
+    src += [1, 1, 2, m + 3, m + 4]
+    dst += [2, 3, 4, m + 500, m + 510]
+    rp, ci = csr_from_undirected_edges(at, src, dst)
+    w = Workload("limits", at, rp, ci, rng.standard_normal((at, dims[0]), dtype=np.float32), dims,
+                 [glorot_uniform(rng, dims[i], dims[i + 1]) for i in range(len(dims) - 1)], [0], 0, 0, "gram_chol")
+    lengths, entries = np.diff(rp), int(rp[1 + m])          # (rows 0 .. m are within one hop)
+    assert at > 640 and int((lengths[:1 + m] > 256).sum()) == sum(c > 256 for c in kids)
+    if sum(kids) > 4096:   # neither the CSR (12 bytes an entry pair, beside the masks) nor a tile per wave fits
+        assert entries > 4096 and 8 * len(ci) + 512 * (len(ci) // 128) > 160 * 1024 - 16384
+    biases = [0.1 * rng.standard_normal(d).astype(np.float32) for d in dims[1:]]
+    say(f"masked inference nodes={at} first-layer entries={entries} dims={dims}")
+    _eval_case(w, len(dims) - 1, False, 1, biases, 322, rng)
+
+
 # a row's own term stays what it is where the row's features are infinite: the slots that fill up the last step of a row
 # (steps of 2, 4 and 8 entries) must not multiply it by a zero. One layer, so that no other row reads the target's.
 @pytest.mark.parametrize("leaves", [1, 2, 3, 4, 5, 6, 7, 8, 9, 21, 260, 301])
