@@ -354,9 +354,11 @@ constexpr int kBW = 32;        // mask words per coalition held in LDS (at least
 constexpr int kBWMax = 192;    // ... up to this many (12,288 players) when the rest of the LDS budget allows
 constexpr int kWBufFloats = 4096;  // the workgroup's staging buffer in LDS: the 64 x 64 tile in which the waves add up a shared
                                    // row of layer 1
-// entries per matrix-core batch of layer 1: short rows (graphs whose masks fit on chip: 15 entries a row on the
-// 1,010-player config) lose less to a partly filled batch with two (0.34 -> 0.27 ms there); the long shared rows of the
-// external-input mode want four entries' loads in flight (8: 14.9 ms, 4: 14.1 ms, 2: 16.2 ms on the 10^6-player config)
+// entries per matrix-core batch in the general loop of layer 1. External inputs that are not pairs take it for every row,
+// four entries' loads in flight (10^6 players, when pairs took it too: 8 entries 14.9 ms, 4 14.1, 2 16.2). With the masks on
+// chip only rows that the waves share (more than kSharedRow entries) still do; their two dates from when short rows did as
+// well (15 entries a row on 1,010 players lose less to a partly filled batch: 0.34 -> 0.27 ms) and has not been swept for
+// shared rows alone. Pairs and the ordinary rows on chip have loops of their own, with their own steps.
 template <bool EXT> constexpr int stage_rows() { return EXT ? 4 : 2; }
 // Waves that share the 64 coalitions of a workgroup. With the masks on chip only one workgroup fits a compute unit's LDS
 // and the stages are latency chains per wave, so sixteen waves shorten them (against eight: 0.39 -> 0.32 ms on 1,010
@@ -653,26 +655,27 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
 
     // layer 1 on the matrix cores: for row t, H1[f][c] = sum_e P[src_e][f] * coef[e][c] is a product
     // (features x entries) . (entries x coalitions). With v_mfma_f32_32x32x2f32 lane l supplies
-    // A[m = l%32][k = l/32] = P[src of entry 2q + l/32][feature tile + l%32] (a plain coalesced
-    // load, nothing is broadcast) and B[k = l/32][n = l%32] = coefficient of entry 2q + l/32 for
-    // coalition n, which lives in another lane's register and comes over with one cross-half
-    // shuffle per entry pair. The accumulator holds D[feature][coalition], so its stores are
-    // 128-byte runs of consecutive coalitions.
+    // A[m = l%32][k = l/32] = P[src of entry 2q + l/32][feature tile + l%32] (a plain coalesced load, nothing is
+    // broadcast; pairs: features 2m and 2m + 1 of the 64 in one load, for the two tiles) and B[k = l/32][n = l%32] =
+    // coefficient of entry 2q + l/32 for coalition n. With the masks on chip and with pairs the lane forms that
+    // coefficient itself; on unpaired external inputs it lives in the lane of its coalition and comes over with one
+    // cross-half shuffle per entry pair. The accumulator holds D[feature][coalition], so its stores are 128-byte runs
+    // of consecutive coalitions.
     {
       const int d1 = a.dims[1];
       const bool relu = a.L > 1;
       const int half = lane >> 5, l32 = lane & 31;
       const float* const bias1 = a.bias[0] ? a.bias[0] : zero_bias;
       const int rows1 = a.rows_out[1];
-      // One loop over the rows layer 1 produces. A row of ordinary length belongs to one wave (round-robin). A long
-      // row (a hub within L-1 hops of the target) is shared: the waves split its entries, leave their partial
-      // tiles in the workgroup's scratch and add them up in wave order (a fixed order: results do not depend on
-      // timing).
+      // The rows layer 1 produces; with the masks on chip only the long ones (the ordinary ones follow below). On
+      // external inputs a row of ordinary length belongs to one wave (round-robin). A long row (a hub within L-1 hops
+      // of the target) is shared: the waves split its entries and their partial tiles are added up in LDS in wave
+      // order (a fixed order: results do not depend on timing).
       int ordinary = 0;
       for (int t = 0; t < rows1; ++t) {
         const int e0 = rp_[t], e1 = rp_[t + 1];  // entry e1 stands for the self-loop
         const bool shared = e1 - e0 > kSharedRow;  // the same for every wave
-        if (!EXT && !shared) continue;   // (masks on chip: the ordinary rows follow below)
+        if (!EXT && !shared) continue;
         if (!shared && (ordinary++ % kBWaves) != wave) continue;
         int s0 = e0, s1 = e1 + 1;
         if (shared) {
@@ -692,7 +695,7 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
             acc[0][0][i] = 0.f; acc[0][1][i] = 0.f; acc[1][0][i] = 0.f; acc[1][1][i] = 0.f;
           }
           int pv_next = 0, sv_next = t;  // sources and keys of the step's entries, fetched one step ahead
-          if (lane < kStageRows && s0 + lane < s1 && s0 + lane < e1) {
+          if (!PAIRED && lane < kStageRows && s0 + lane < s1 && s0 + lane < e1) {
             pv_next = key_[s0 + lane];
             sv_next = col_[s0 + lane];
           }
@@ -922,7 +925,7 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
       // where five rows x four feature tiles now occupy all sixteen waves. (Steps of eight entries, pipelined across
       // rows with every key through lane reads: 117 us.)
       constexpr int SR = 4, Q = SR / 2;   // entries and entry pairs per step
-      const int d1 = a.dims[1], nf = (d1 + 63) / 64, rows1 = a.rows_out[1];
+      const int d1 = a.dims[1], rows1 = a.rows_out[1];
       const bool relu = a.L > 1;
       const int half = lane >> 5, l32 = lane & 31;
       const unsigned char* const zs_lane = smem_raw + 8 * l32;
