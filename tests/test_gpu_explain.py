@@ -320,7 +320,8 @@ def test_directed_players_and_wider_extraction():
 
 def test_explaining_an_extracted_graph_equals_explaining_its_target():
     """capacity=None sizes the buffers by an extracted graph that the explanation takes over; a given capacity extracts
-    inside the call. Same scores, same players, and the graph is gone afterwards (also after an error)."""
+    inside the call. Same scores and same players, also after a refused call (what becomes of the graph is
+    test_an_explained_graph_is_taken_over_once)."""
     from paper_2506_22668_amd import DistShapError
     from paper_2506_22668_amd.binding import DS_EINVAL
     w = make_workload("c2_small")
