@@ -93,8 +93,8 @@ typedef struct ds_options {
 } ds_options;
 
 /* What an explanation did (all [host]). Times are wall-clock milliseconds measured
- * with HIP events on the context's stream; of a graph that ds_extract built before, its own
- * extraction counts and what lay between the two calls does not. */
+ * with HIP events on the context's stream; of a graph that ds_extract built before, the time of
+ * that call (host clock) counts and what lay between the two calls does not. */
 typedef struct ds_report {
   int64_t num_players;    /* n */
   int64_t num_nodes;      /* |V_c| */

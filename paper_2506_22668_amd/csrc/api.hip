@@ -2,6 +2,7 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <chrono>
 #include <string>
 #include <condition_variable>
 #include <mutex>
@@ -107,7 +108,6 @@ int ds_create(ds_ctx** out, int device, void* stream) {
   ctx->h_stage = nullptr;
   ctx->h_stage_bytes = 0;
   ctx->stage_busy = false;
-  ctx->timed = nullptr;
   if (hipEventCreate(&ctx->stage_ev) != hipSuccess) { delete ctx; return DS_EDEVICE; }
   if (hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming) != hipSuccess ||
@@ -257,14 +257,6 @@ static ds_options default_options(const ds_options* in) {
   return o;
 }
 
-// The time of the last extraction by ds_extract, from the context's events into its graph, before they are recorded again.
-static void settle_extraction_time(ds_ctx* ctx) {
-  if (!ctx->timed) return;
-  if (hipEventSynchronize(ctx->ev[5]) != hipSuccess || hipEventElapsedTime(&ctx->timed->ms_extract, ctx->ev[0], ctx->ev[5]) != hipSuccess)
-    (void)hipGetLastError();
-  ctx->timed = nullptr;
-}
-
 static int extract_checked(ds_ctx* ctx, int64_t target, const ds_options& o, ds_cgraph** out) {
   *out = nullptr;
   DS_HIP(ctx, hipSetDevice(ctx->device));
@@ -272,16 +264,15 @@ static int extract_checked(ds_ctx* ctx, int64_t target, const ds_options& o, ds_
   if (hops < 1) return ds_fail(ctx, DS_EINVAL, "hops is 0 and no model is set");
   if (ctx->d0 > 0 && ctx->L > 0 && ctx->d0 != ctx->dims[0])
     return ds_fail(ctx, DS_EINVAL, "feature width %d does not match the model's input width %d", ctx->d0, ctx->dims[0]);
-  settle_extraction_time(ctx);
-  DS_HIP(ctx, hipEventRecord(ctx->ev[0], ctx->stream));   // an explanation that goes on with the graph counts from here
   return ds_extract_impl(ctx, target, hops, o.directed ? 1 : 0, out);
 }
 
 int ds_extract(ds_ctx* ctx, int64_t target, const ds_options* opts, ds_cgraph** out) {
   if (!ctx || !out) return DS_EINVAL;
+  // (the call ends behind a wait, so the host's clock has its time; two more events took 2 % of a 12-player explanation)
+  const auto t0 = std::chrono::steady_clock::now();
   DS_TRY(extract_checked(ctx, target, default_options(opts), out));
-  if (hipEventRecord(ctx->ev[5], ctx->stream) == hipSuccess) ctx->timed = *out;   // (read when ds_explain_cgraph asks for it)
-  else (void)hipGetLastError();
+  (*out)->ms_extract = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - t0).count();
   return DS_OK;
 }
 
@@ -341,7 +332,6 @@ int ds_cgraph_first_transform(ds_ctx* ctx, ds_cgraph* cg, float* out) {
 int ds_cgraph_free(ds_ctx* ctx, ds_cgraph* cg) {
   if (!cg) return DS_OK;
   if (!ctx) ctx = cg->owner;
-  if (ctx->timed == cg) ctx->timed = nullptr;
   for (size_t i = 0; i < ctx->graphs.size(); ++i)
     if (ctx->graphs[i] == cg) {
       ctx->graphs.erase(ctx->graphs.begin() + i);
@@ -552,6 +542,7 @@ int ds_explain(ds_ctx* ctx, int64_t target, int64_t n_samples, uint64_t seed, co
   if (ctx->L < 1) return ds_fail(ctx, DS_EINVAL, "no model is set (ds_set_gcn / ds_set_gat)");
   for (int i = 0; i < 5; ++i) ctx->kev_set[i] = false;
   ds_cgraph* cg = nullptr;
+  DS_HIP(ctx, hipEventRecord(ctx->ev[0], ctx->stream));
   DS_TRY(extract_checked(ctx, target, o, &cg));
   return explain_extracted(ctx, cg, target, n_samples, seed, o, phi, M_inout, edge_src, edge_dst, report);
 }
@@ -568,18 +559,12 @@ int ds_explain_cgraph(ds_ctx* ctx, ds_cgraph* cg, int64_t n_samples, uint64_t se
     return ds_fail(ctx, DS_EINVAL, "no model is set (ds_set_gcn / ds_set_gat)");
   }
   for (int i = 0; i < 5; ++i) ctx->kev_set[i] = false;
-  // the clock starts here; the extraction's own time is added to it, what the caller did in between is not
-  settle_extraction_time(ctx);
-  if (hipEventRecord(ctx->ev[0], ctx->stream) != hipSuccess) {
-    (void)hipGetLastError();
-    ds_cgraph_free(ctx, cg);
-    return ds_fail(ctx, DS_EDEVICE, "cannot record an event");
-  }
   return explain_extracted(ctx, cg, cg->info.target, n_samples, seed, default_options(opts), phi, M_inout, edge_src, edge_dst, report);
 }
 
-// Everything after the extraction; ctx->ev[0] has been recorded before it (or, with the extraction's time in the graph,
-// after it). Takes over (and frees) the computational graph.
+// Everything after the extraction; ctx->ev[0] has been recorded before it, unless the graph holds the extraction's time
+// (it was built by ds_extract, and what the caller has done since is not counted). Takes over (and frees) the
+// computational graph.
 static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t n_samples, uint64_t seed, const ds_options& o,
                              float* phi, int64_t* M_inout, int64_t* edge_src, int64_t* edge_dst, ds_report* report) {
   ds_report rep;
@@ -748,13 +733,14 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   rep.f_full = f01[1];
   rep.pred_class = *(int32_t*)(ctx->h_mail + 34);
   cg->pred_class = rep.pred_class;
-  hipEventElapsedTime(&rep.ms_extract, ctx->ev[0], ctx->ev[1]);
+  const bool apart = cg->ms_extract > 0.f;   // (the clock then starts with ev[1])
+  if (apart) rep.ms_extract = cg->ms_extract;
+  else hipEventElapsedTime(&rep.ms_extract, ctx->ev[0], ctx->ev[1]);
   hipEventElapsedTime(&rep.ms_sample, ctx->ev[1], ctx->ev[2]);
   hipEventElapsedTime(&rep.ms_eval, ctx->ev[2], ctx->ev[3]);
   hipEventElapsedTime(&rep.ms_solve, ctx->ev[3], ctx->ev[4]);
-  hipEventElapsedTime(&rep.ms_total, ctx->ev[0], ctx->ev[4]);
-  rep.ms_extract += cg->ms_extract;   // (0 unless ds_extract built the graph)
-  rep.ms_total += cg->ms_extract;
+  hipEventElapsedTime(&rep.ms_total, ctx->ev[apart ? 1 : 0], ctx->ev[4]);
+  if (apart) rep.ms_total += cg->ms_extract;
   kernel_times(ctx, &rep);
   rep.num_pairs = k / 2 - 1;
   {
@@ -829,6 +815,7 @@ int ds_explain_batch(ds_ctx* ctx, const int64_t* targets, int32_t num_targets, i
   {
     ds_ctx* w0 = ctx->workers[0];
     for (int i = 0; i < 5; ++i) w0->kev_set[i] = false;
+    DS_HIP(ctx, hipEventRecord(w0->ev[0], w0->stream));
     const int rc = extract_checked(w0, targets[0], o, &first_cg);
     if (rc != DS_OK) {
       strncpy(ctx->err, w0->err, sizeof(ctx->err) - 1);
@@ -855,7 +842,8 @@ int ds_explain_batch(ds_ctx* ctx, const int64_t* targets, int32_t num_targets, i
             cg = first_cg;
           } else {
             for (int i = 0; i < 5; ++i) w->kev_set[i] = false;
-            rc = extract_checked(w, targets[t], o, &cg);
+            rc = hipEventRecord(w->ev[0], w->stream) == hipSuccess ? DS_OK : DS_EDEVICE;
+            if (rc == DS_OK) rc = extract_checked(w, targets[t], o, &cg);
           }
           status[t] = rc;
           if (rc != DS_OK) errs[t] = w->err;

@@ -36,7 +36,7 @@ struct ds_cgraph {
   int32_t pred_class;     // host copy, -1 until fetched
   int32_t d0, d1;
   int64_t ball_entries[8]; // row_ptr[ball[h]]: CSR entries of the rows within h hops
-  float ms_extract;        // what the extraction took, once it has been read from the context's events
+  float ms_extract;        // built by ds_extract: what the call took; 0: extracted inside an explanation
   int32_t att_heads;       // heads the `att` array was sized for (0: extracted for a GCN)
 };
 
@@ -95,7 +95,6 @@ struct ds_ctx {
   hipEvent_t kev[10];  // begin/end pairs: 0 masked inference, 1 Gram, 2 Cholesky, 3 CGLS loop, 4 mask-streaming kernel
   bool kev_set[5];
   std::vector<ds_cgraph*> graphs;
-  ds_cgraph* timed;    // the graph whose extraction ran between ev[0] and ev[5], or nullptr
   // one released computational-graph block is kept for the next extraction (no malloc/free per explanation)
   void* cg_spare;
   size_t cg_spare_bytes;
