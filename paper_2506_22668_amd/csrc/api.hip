@@ -493,6 +493,7 @@ int ds_solve(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const float* 
   for (int i = 0; i < 5; ++i) ctx->kev_set[i] = false;
   int rc = solve_dispatch(ctx, n, k, Z, w, y, o, o.paired ? 1 : 0, phi, report);
   hipStreamSynchronize(ctx->stream);
+  if (rc != DS_OK) hipStreamSynchronize(ctx->side);   // (a solve that failed half-way has not joined its side stream)
   ds_arena_reset(ctx);
   if (report) {
     kernel_times(ctx, report);

@@ -1033,16 +1033,17 @@ __global__ void copy_panel_kernel(const double* M, int64_t ld, int64_t rows_tota
   if (r < rows_total) P[r * NB + c] = j0 + c < n ? M[r * ld + j0 + c] : 0.0;
 }
 
-// Trailing update of a whole super-panel: A22 -= L21 L21^T with L21 = the kw (a multiple of 64) columns
-// starting at J, on the lower 64x64 tiles of the matrix from row/column `base` = J + kw on. The tile stays in
-// registers across the kw/64 column chunks, so it is read and written once per super-panel instead of once
-// per 64 columns; the next chunk of the two operands is fetched into registers while the matrix cores work on
-// the current one.
-template <int KW>  // columns of the super-panel: known at compile time, so that the chunk loop unrolls (column offsets
-                   // become immediates and the accumulators stay where the matrix cores want them)
-__global__ __launch_bounds__(kThreads) void chol_update_wide_kernel(double* M, int64_t ld, int64_t rows_total, int64_t n,
-                                                                    int64_t J, int64_t base) {
-  constexpr int kw = KW;
+// Trailing update of a whole super-panel: A22 -= L21 L21^T with L21 = the KW columns starting at J, on the lower part of
+// the matrix from row/column `base` = J + KW on. A tile stays in registers across the columns of the super-panel, so it
+// is read and written once per super-panel instead of once per 64 columns. Two kernels share it.
+//
+// The next super-panel's own columns: 64x64 tiles (block columns 0 .. gridDim.x - 1), which fill the GPU, and the
+// workgroup of the first one goes on to factorise it, as in chol_update_kernel<true>. The next chunk of the two operands is
+// fetched into registers while the matrix cores work on the current one.
+template <int KW>  // known at compile time, so that the chunk loop unrolls (column offsets become immediates and the
+                   // accumulators stay where the matrix cores want them)
+__global__ __launch_bounds__(kThreads) void chol_update_next_kernel(double* M, int64_t ld, int64_t rows_total, int64_t n, int64_t J,
+                                                                    int64_t base, double* linv_next, int* flag) {
   const int ti = blockIdx.y, tj = blockIdx.x;
   if (tj > ti) return;
   __shared__ double Li[kTile][NB + 1];
@@ -1075,7 +1076,7 @@ __global__ __launch_bounds__(kThreads) void chol_update_wide_kernel(double* M, i
     for (int j = 0; j < 2; ++j) acc[i][j] = double4_t{0.0, 0.0, 0.0, 0.0};
   fetch(0);
 #pragma unroll
-  for (int kc = 0; kc < kw; kc += NB) {
+  for (int kc = 0; kc < KW; kc += NB) {
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
@@ -1084,11 +1085,184 @@ __global__ __launch_bounds__(kThreads) void chol_update_wide_kernel(double* M, i
       Lj[r][c] = pj[u];
     }
     __syncthreads();
-    if (kc + NB < kw) fetch(kc + NB);
+    if (kc + NB < KW) fetch(kc + NB);
     tile_nt_mfma(Li, Lj, acc);
+  }
+  if (ti == 0) {   // the next diagonal block (the super-panels leave at least 64 columns)
+    double4_t mt[2][2];
+    load_diag_block(M, ld, base, NB, mt);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) mt[i][j] -= acc[i][j];
+    __syncthreads();   // every wave has read Li and Lj
+    chol_diag_body(M, ld, base, NB, linv_next, flag, nullptr, Li, Lj, mt);
+    return;
   }
   const int wave = tid >> 6;
   tile_sub_store<2, 2>(M, ld, rows_total, n, i0, c0, (wave >> 1) * 32, (wave & 1) * 32, acc, nullptr);
+}
+
+// The rest of the matrix, 128x128 tiles from row/column `base` on (T rows of tiles), a 32x64 piece of one to each of
+// eight waves. One workgroup fills a compute unit, so the kernel pipelines on its own: the operands' next step is on its
+// way while the matrix cores work on the current one, the tile's old values under the last step, the next tile's first
+// step under this tile's stores. A tile takes 37 us, 30 of them the products (the matrix cores alone need 28.5), the rest
+// is the tile's way in and out: 51 TFLOP/s over 946 tiles on 256 compute units, against 44 of 64 x 64 tiles. Two workgroups
+// of four waves on a unit reach more (30 us a tile), but the diagonal block's lone wave beside them then takes six times
+// as long; a whole unit to a workgroup leaves kWideSpare units to the chain.
+constexpr int kWideThreads = 512;
+constexpr int kWideTile = 128;
+constexpr int kWideK = 32;                 // columns per step, two buffers
+constexpr int kWidePitch = kWideK + 2;     // doubles per LDS row: the 32 lanes of half a wave read from all 64 banks
+constexpr int kWidePut = 24;               // column of a step after which the next one's operands go to LDS
+constexpr int kWideSpare = 32;             // compute units left to the chain on the side stream
+constexpr int kWideStrip = 4;              // tile rows walked together
+
+// the p-th lower tile of T rows of tiles, in strips of kWideStrip rows, column by column inside a strip: workgroups with
+// neighbouring p share operands
+__device__ __forceinline__ void wide_tile_of(int p, int T, int& ti, int& tj) {
+  int r0 = 0, h = 0;
+  for (;; r0 += kWideStrip) {
+    h = T - r0 < kWideStrip ? T - r0 : kWideStrip;
+    const int count = h * (r0 + 1) + h * (h - 1) / 2;
+    if (p < count) break;
+    p -= count;
+  }
+  if (p < h * (r0 + 1)) {
+    tj = p / h;
+    ti = r0 + p % h;
+    return;
+  }
+  p -= h * (r0 + 1);
+  int j = 1;
+  for (; p >= h - j; ++j) p -= h - j;
+  tj = r0 + j;
+  ti = r0 + j + p;
+}
+
+template <int KW>
+__global__ __launch_bounds__(kWideThreads, 2) void chol_update_wide_kernel(double* M, int64_t ld, int64_t rows_total, int64_t n,
+                                                                           int64_t J, int64_t base, int T, int tiles) {
+  __shared__ __align__(16) double Ls[2][2][kWideTile * kWidePitch];   // [buffer][rows, columns of the tile]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, lk = lane >> 4;
+  const int wi = (wave >> 1) * 32, wj = (wave & 1) * 64;
+  typedef double pair_t __attribute__((ext_vector_type(2)));
+  constexpr int kPer = kWideTile * kWideK / 2 / kWideThreads;   // 16-byte pieces per thread and operand
+  constexpr int kRowsPer = kWideThreads / (kWideK / 2);         // rows per pass
+  const int pr = tid / (kWideK / 2), pc = (tid % (kWideK / 2)) * 2;
+  int64_t i0, c0;
+  int ti, tj;
+  const char *basei, *basej;   // one base per operand and 32-bit offsets from it
+  uint32_t offi[kPer], offj[kPer];
+  pair_t pi[kPer], pj[kPer];
+  auto fetch = [&](int kc) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      pi[u] = *(const pair_t*)(basei + (offi[u] + (uint32_t)kc * 8u));
+      pj[u] = *(const pair_t*)(basej + (offj[u] + (uint32_t)kc * 8u));
+    }
+  };
+  auto put = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      *(pair_t*)&Ls[buf][0][(pr + u * kRowsPer) * kWidePitch + pc] = pi[u];
+      *(pair_t*)&Ls[buf][1][(pr + u * kRowsPer) * kWidePitch + pc] = pj[u];
+    }
+  };
+  auto start = [&](int p) {   // the p-th tile, its first step requested
+    wide_tile_of(p, T, ti, tj);
+    i0 = base + (int64_t)ti * kWideTile;
+    c0 = base + (int64_t)tj * kWideTile;
+    basei = (const char*)(M + i0 * ld + J);
+    // (a last tile that holds the right-hand-side row only has no columns of its own; it is not stored)
+    const int64_t cs = c0 < n ? c0 : n - 1;
+    basej = (const char*)(M + cs * ld + J);
+    const int last_i = (int)(rows_total - 1 - i0 < kWideTile ? rows_total - 1 - i0 : kWideTile);
+    const int last_j = (int)(n - 1 - cs < kWideTile ? n - 1 - cs : kWideTile);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {   // (rows past the end: as in chol_update_next_kernel)
+      const int r = pr + u * kRowsPer;
+      offi[u] = ((uint32_t)(r < last_i ? r : last_i) * (uint32_t)ld + (uint32_t)pc) * 8u;
+      offj[u] = ((uint32_t)(r < last_j ? r : last_j) * (uint32_t)ld + (uint32_t)pc) * 8u;
+    }
+    fetch(0);
+  };
+  // consecutive workgroups go to the eight XCDs in turn: each XCD takes a run of neighbouring tiles
+  const int G = (int)gridDim.x, bid = (int)blockIdx.x;
+  int p = (G & 7) == 0 ? (bid & 7) * (G >> 3) + (bid >> 3) : bid;
+  if (p >= tiles) return;
+  start(p);
+  for (;;) {
+    double4_t acc[2][4], cur[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = double4_t{0.0, 0.0, 0.0, 0.0};
+    const bool live = ti != tj || wj < wi + 32;   // (a piece above the diagonal has nothing to do)
+    put(0);   // (every wave is past the barrier that ended the tile before)
+    __syncthreads();
+#pragma unroll
+    for (int kc = 0; kc < KW; kc += kWideK) {
+      const int buf = (kc / kWideK) & 1;
+      const bool last = kc + kWideK >= KW;
+      if (!last) {
+        fetch(kc + kWideK);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4) {
+            const int64_t r = i0 + wi + 16 * i + 4 * r4 + lk, rs = r < rows_total ? r : rows_total - 1;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const int64_t c = c0 + wj + 16 * j + l16;
+              cur[i][j][r4] = M[rs * ld + (c < n ? c : n - 1)];
+            }
+          }
+      }
+      const double* pa = &Ls[buf][0][(wi + l16) * kWidePitch + lk];
+      const double* pb = &Ls[buf][1][(wj + l16) * kWidePitch + lk];
+      double av[2][2], bv[2][4];
+      auto operands = [&](int k0) {
+        const int q = (k0 >> 2) & 1;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) av[q][i] = pa[i * 16 * kWidePitch + k0];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bv[q][j] = pb[j * 16 * kWidePitch + k0];
+      };
+      operands(0);
+#pragma unroll
+      for (int k0 = 0; k0 < kWideK; k0 += 4) {
+        const int q = (k0 >> 2) & 1;
+        if (k0 + 4 < kWideK) operands(k0 + 4);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[q][i], bv[q][j], acc[i][j], 0, 0, 0);
+        if (k0 == kWidePut && !last) put(buf ^ 1);
+      }
+      __syncthreads();
+    }
+    const int64_t si = i0 + wi, sj = c0 + wj;
+    p += G;
+    const bool more = p < tiles;
+    if (more) start(p);
+    if (live) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const int64_t r = si + 16 * i + 4 * r4 + lk;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int64_t c = sj + 16 * j + l16;
+            if (r < rows_total && c < n && c <= r) M[r * ld + c] = cur[i][j][r4] - acc[i][j][r4];
+          }
+        }
+    }
+    if (!more) return;
+  }
 }
 
 
@@ -1323,6 +1497,12 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
   // inside it the updates reach only the super-panel's own columns, and the rest of the trailing matrix is
   // updated once with all 256 columns. Below kFuseMaxRows trailing rows: one block per step, the update
   // factorising the next diagonal block on the way.
+  // The super-panels run one ahead on the side stream: the columns of the next super-panel are updated first and its
+  // chain of small launches (panels, narrow updates with the diagonal blocks: a few workgroups each) goes on behind
+  // them, while the main stream updates the rest of the matrix. Every tile still meets the super-panels in their order:
+  // the next super-panel's columns wait for the rest of the update before (join_ev), the rest for them (fork_ev).
+  hipStream_t chain = st;
+  bool rest_queued = false;   // an update of the rest is under way on the main stream, join_ev behind it
   bool diag_done = true;  // the first diagonal block was factorised with the system matrix (ds_gram_begin)
   bool panel_ready = false;  // gs->panel[pbuf] holds the rows of the current panel (fused steps only)
   int pbuf = 0;
@@ -1330,26 +1510,42 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
   while (j0 < n) {
     const bool super = rows_total - j0 - kSuperCols > kFuseMaxRows && n - j0 >= kSuperCols + NB;
     if (super) {
+      if (chain == st) {   // the first one
+        chain = ctx->side;
+        DS_HIP(ctx, hipEventRecord(ctx->fork_ev, st));
+        DS_HIP(ctx, hipStreamWaitEvent(chain, ctx->fork_ev, 0));
+      }
       for (int b = 0; b < kSuperCols / NB; ++b) {
         const int64_t jb = j0 + (int64_t)b * NB;
         double* li = linv + (size_t)(jb / NB) * NB * NB;
-        // inside the super-panel the narrow update factorises the next diagonal block on the way
-        if (b == 0 && jb > 0) hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(kThreads), 0, st, M, ld, jb, NB, li, gs->flag);
+        // the update before has factorised the diagonal block on the way
         const int64_t rest = rows_total - jb - NB;
         const unsigned tt = nblocks(rest, kTile);
-        hipLaunchKernelGGL(chol_panel_kernel, dim3(tt), dim3(kThreads), 0, st, M, ld, rows_total, jb, NB, li);
+        hipLaunchKernelGGL(chol_panel_kernel, dim3(tt), dim3(kThreads), 0, chain, M, ld, rows_total, jb, NB, li);
         const unsigned inside = (unsigned)(kSuperCols / NB - 1 - b);  // block columns of the super-panel still ahead
         if (inside > 0)
-          hipLaunchKernelGGL(chol_update_kernel<true>, dim3(inside, tt), dim3(kThreads), 0, st, M, ld, rows_total, n, jb,
+          hipLaunchKernelGGL(chol_update_kernel<true>, dim3(inside, tt), dim3(kThreads), 0, chain, M, ld, rows_total, n, jb,
                              NB, li + (size_t)NB * NB, gs->flag);
       }
       const int64_t base = j0 + kSuperCols;
-      const unsigned tw = nblocks(rows_total - base, kTile);
-      hipLaunchKernelGGL(chol_update_wide_kernel<(int)kSuperCols>, dim3(tw, tw), dim3(kThreads), 0, st, M, ld, rows_total, n,
-                         j0, base);
+      if (rest_queued) DS_HIP(ctx, hipStreamWaitEvent(chain, ctx->join_ev, 0));
+      hipLaunchKernelGGL(chol_update_next_kernel<(int)kSuperCols>, dim3((unsigned)(kSuperCols / NB), nblocks(rows_total - base, kTile)),
+                         dim3(kThreads), 0, chain, M, ld, rows_total, n, j0, base, linv + (size_t)(base / NB) * NB * NB, gs->flag);
+      DS_HIP(ctx, hipEventRecord(ctx->fork_ev, chain));
+      DS_HIP(ctx, hipStreamWaitEvent(st, ctx->fork_ev, 0));
+      const int64_t tw = (rows_total - base - kSuperCols + kWideTile - 1) / kWideTile;   // (kFuseMaxRows rows are left at least)
+      const int64_t tiles = tw * (tw + 1) / 2, slots = ctx->num_cus > 2 * kWideSpare ? ctx->num_cus - kWideSpare : ctx->num_cus;
+      hipLaunchKernelGGL(chol_update_wide_kernel<(int)kSuperCols>, dim3((unsigned)(tiles < slots ? tiles : slots)), dim3(kWideThreads), 0, st,
+                         M, ld, rows_total, n, j0, base + kSuperCols, (int)tw, (int)tiles);
+      DS_HIP(ctx, hipEventRecord(ctx->join_ev, st));
+      rest_queued = true;
       j0 += kSuperCols;
-      diag_done = false;
-      continue;
+      continue;   // (diag_done stays true)
+    }
+    if (chain != st) {   // behind the last super-panel everything is on the main stream again
+      DS_HIP(ctx, hipEventRecord(ctx->fork_ev, chain));
+      DS_HIP(ctx, hipStreamWaitEvent(st, ctx->fork_ev, 0));
+      chain = st;
     }
     const int nb = (int)(n - j0 < NB ? n - j0 : NB);
     double* li = linv + (size_t)(j0 / NB) * NB * NB;

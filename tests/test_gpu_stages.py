@@ -501,6 +501,26 @@ def test_gram_cholesky_mid_size_crosses_every_factorisation_regime(ctx_tiny):
     assert err <= 1e-4 * np.abs(ref).max()
 
 
+# The 128 x 128 tiles of the wide update start at row 512: 2,304 leaves a last row of tiles that holds nothing but the
+# right-hand side, 2,305 one of a single column, 2,431 a whole last tile less the right-hand side; 2,561 runs two
+# super-panels, the second one's columns updated ahead of the rest.
+@pytest.mark.parametrize("n", [2304, 2305, 2431, 2561])
+def test_gram_cholesky_at_the_edges_of_the_wide_update(ctx_tiny, n):
+    from paper_2506_22668_amd import Options, DS_SOLVER_GRAM_CHOL
+    ctx, _ = ctx_tiny
+    ns = 9000
+    say(f"gram+chol wide n={n}")
+    Z, w, bits, y = _solve_inputs(n, ns, 500 + n)
+    ref = solve.solve_lstsq(bits, w, y)
+    args = (n, torch.from_numpy(Z.view(np.int64)).cuda(), torch.from_numpy(w).cuda(), torch.from_numpy(y).cuda())
+    got = [ctx.solve(*args, Options(solver=DS_SOLVER_GRAM_CHOL, paired=1))[0].cpu().numpy() for _ in range(3)]
+    # a system of condition 1e3 at most (eigenvalues 5e-3 .. 5.3) solved in fp64: what is left is the rounding of the
+    # scores to float32, 6e-8 of the largest
+    assert np.abs(got[0].astype(np.float64) - ref).max() <= 1e-6 * np.abs(ref).max()
+    for g in got[1:]:   # the two streams of the factorisation meet the same tiles in the same order every time
+        assert np.array_equal(g, got[0])
+
+
 def test_rank_deficient_gram_is_reported_and_auto_falls_back(ctx_tiny):
     from paper_2506_22668_amd import Options, DistShapError, DS_SOLVER_GRAM_CHOL, DS_SOLVER_CGLS, DS_ESINGULAR
     ctx, _ = ctx_tiny
