@@ -523,14 +523,6 @@ __device__ __forceinline__ double fast_rsqrt(double p) {
   return r;
 }
 
-// 1/p for 1e-30 < p < 1e30: hardware seed (about 24 bits), two Newton steps x += x (1 - p x)
-__device__ __forceinline__ double fast_rcp(double p) {
-  double x = __builtin_amdgcn_rcp(p);
-  x = fma(x, fma(-p, x, 1.0), x);
-  x = fma(x, fma(-p, x, 1.0), x);
-  return x;
-}
-
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
 // acc (+)= A[64 x 64] * B[64 x 64]^T for 64x64 tiles held in LDS with row pitch NB+1, on the fp64
@@ -564,6 +556,22 @@ __device__ __forceinline__ void tile_nt_mfma(const double (*A)[NB + 1], const do
     a1 = na1;
     b0 = nb0;
     b1 = nb1;
+  }
+}
+
+// acc[j] = A[64 x 64] * L[64 x 64]^T for a lower triangular L (both in LDS), subtile (wave, j) of 16 x 16: column block j takes
+// the k up to its own end only, and a wave owns a row of subtiles, so that the waves have the same 40 of 64 products.
+__device__ __forceinline__ void tile_nt_lower_mfma(const double (*A)[NB + 1], const double (*L)[NB + 1], double4_t (&acc)[4]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l16 = lane & 15, lk = lane >> 4;
+  const double* pa = &A[16 * wave + l16][lk];
+  const double* pl = &L[l16][lk];
+#pragma unroll
+  for (int k0 = 0; k0 < NB; k0 += 4) {
+    const double av = pa[k0];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (16 * j + 15 >= k0) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, pl[16 * j * (NB + 1) + k0], acc[j], 0, 0, 0);
   }
 }
 
@@ -642,11 +650,13 @@ constexpr int kSub = 16;  // sub-block of the diagonal block: one matrix-core ti
 // can be done elsewhere: no square root, no pivot check, no stores to global memory.
 // Lane l < 16 keeps row l of D (columns up to l matter), lane 16 + l keeps column l of the inverse (the upper half
 // of the wave repeats the lower). With d the pivot of column j and p = 1/d, L[i][j] L[k][j] = S[i][j] S[k][j] p:
-// lane i subtracts (S[i][j] p) col[k] from its entry of column k > j, where col[] is column j as updated so far,
-// which every lane has put into LDS (entry j of it is the pivot's own lane's); the same column moves the forward substitution L X = I on,
-// X[k][c] -= col[k] (X[j][c] p), so one multiply-add per k serves both halves. The pivot reaches all lanes through
-// scalar registers; the column travels through LDS (two buffers; reads of one address by all lanes are a
-// broadcast) under the updates of the step before. I16 is a 16 x 16 identity.
+// lane i subtracts (S[i][j] p) col[k] from its entry of column k > j, where col[] is column j as updated so far;
+// the same column moves the forward substitution L X = I on, X[k][c] -= col[k] (X[j][c] p), so one multiply-add per k
+// serves both halves. What bounds the loop is the chain from pivot to pivot: reciprocal, p, the next column's entry.
+// The two values it needs, the pivot and col[j + 1], reach all lanes through scalar registers; the rest of the column
+// travels through LDS (two buffers; reads of one address by all lanes are a broadcast), which takes longer than a step, so
+// the updates with it are a step late: they fill the wait for the next reciprocal. (With every update waiting for its
+// column: 2,500 cycles a block; now 2,360.) I16 is a 16 x 16 identity.
 __device__ __forceinline__ void eliminate_sub_block(double (*S)[NB + 1], int o, double (*XT)[kSub + 1],
                                                     const double (*I16)[kSub + 1], double* col) {
   const int lane = threadIdx.x & 63, l = lane & 15, slot = lane & 31;
@@ -656,8 +666,8 @@ __device__ __forceinline__ void eliminate_sub_block(double (*S)[NB + 1], int o, 
   double v[kSub];
 #pragma unroll
   for (int k = 0; k < kSub; ++k) v[k] = init[k];
-  // The column's store and loads are written as instructions: the loads of the next column have to be issued right
-  // behind its store, so that they return under the remaining updates of this column, and the compiler's scheduler
+  // The column's store and loads are written as instructions: the loads of a column have to be issued right
+  // behind its store, so that they return under the step that follows, and the compiler's scheduler
   // puts them next to their first use instead. LDS answers a wave in order, so the compiler's own counting of its
   // LDS accesses stays on the safe side. Between a load and the wait below its destination registers are in flight,
   // which the compiler does not know: tests/test_isa_lds_reads.py checks the generated code for any use in between.
@@ -668,32 +678,41 @@ __device__ __forceinline__ void eliminate_sub_block(double (*S)[NB + 1], int o, 
   asm volatile("ds_write_b64 %0, %1" ::"v"(slot_lds), "v"(v[0]) : "memory");
 #pragma unroll
   for (int h = 0; h < kSub / 2; ++h) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(q[h]) : "v"(col_lds), "n"(16 * h));
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(q[4]), "+v"(q[5]), "+v"(q[6]), "+v"(q[7]));
-  double c[kSub];
-#pragma unroll
-  for (int h = 0; h < kSub / 2; ++h) {
-    c[2 * h] = q[h].x;
-    c[2 * h + 1] = q[h].y;
-  }
+  // The order below is the order of issue (sched_barrier): the late updates go where the chain waits.
+#define DS_HERE __builtin_amdgcn_sched_barrier(0)
+  double c[kSub];      // column j - 1, whose updates of the columns from j + 1 on are still to be made, and ...
+  double late = 0.0;   // ... its p
 #pragma unroll
   for (int j = 0; j + 1 < kSub; ++j) {
-    const double p = v[j] * fast_rcp(wave_bcast(v[j], j));
-    v[j + 1] = fma(-p, c[j + 1], v[j + 1]);
-    if (j + 2 < kSub) {  // the next column is complete: send it on its way before the other updates
-      asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(slot_lds), "v"(v[j + 1]), "n"(((j + 1) & 1) * 256) : "memory");
+    int at = j + 1;    // next late update
+    auto update = [&](int count) {
+      if (j > 0) {
 #pragma unroll
-      for (int h = (j + 2) / 2; h < kSub / 2; ++h)
-        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(q[h]) : "v"(col_lds), "n"(((j + 1) & 1) * 256 + 16 * h));
-    }
-#pragma unroll
-    for (int k = j + 2; k < kSub; ++k) v[k] = fma(-p, c[k], v[k]);
-    // pin the updates to this step: left to itself the compiler defers the updates of a column until the column's
-    // own step and holds every earlier column in registers for them
-#pragma unroll
-    for (int k = j + 2; k < kSub; ++k) asm volatile("" : "+v"(v[k]));
+        for (int i = 0; i < count; ++i)
+          if (at < kSub) {
+            v[at] = fma(-late, c[at], v[at]);
+            ++at;
+          }
+      }
+      DS_HERE;
+    };
+    const double d = wave_bcast(v[j], j);
+    double x = __builtin_amdgcn_rcp(d);   // 1/d for 1e-30 < d < 1e30: seed (about 24 bits), then x (1 + e + e^2) with e = 1 - d x
+    DS_HERE;
+    const double next = wave_bcast(v[j], j + 1);
+    update(3);
+    double e = fma(-d, x, 1.0);
+    update(1);
+    e = fma(e, e, e);
+    update(1);
+    x = fma(x, e, x);
+    update(1);
+    const double p = v[j] * x;
+    update(1);
+    v[j + 1] = fma(-p, next, v[j + 1]);
+    update(kSub);
     if (j + 2 < kSub) {
-      // q[h] for h below (j + 2) / 2 were not loaded again and pass through unchanged
+      // column j is here (q[h] for h below (j + 2) / 2 were not loaded and pass through unchanged)
       asm volatile("s_waitcnt lgkmcnt(0)"
                    : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(q[4]), "+v"(q[5]), "+v"(q[6]), "+v"(q[7]));
 #pragma unroll
@@ -701,8 +720,17 @@ __device__ __forceinline__ void eliminate_sub_block(double (*S)[NB + 1], int o, 
         c[2 * h] = q[h].x;
         c[2 * h + 1] = q[h].y;
       }
+      late = p;
     }
+    if (j + 3 < kSub) {  // column j + 1 is complete: send it on its way
+      asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(slot_lds), "v"(v[j + 1]), "n"(((j + 1) & 1) * 256) : "memory");
+#pragma unroll
+      for (int h = (j + 2) / 2; h < kSub / 2; ++h)
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(q[h]) : "v"(col_lds), "n"(((j + 1) & 1) * 256 + 16 * h));
+    }
+    DS_HERE;
   }
+#undef DS_HERE
   asm volatile("" ::: "memory");
 #pragma unroll
   for (int k = 0; k < kSub; ++k) mine[k] = v[k];
@@ -741,56 +769,78 @@ __device__ __forceinline__ void sub_block_store(double (*T)[NB + 1], int r0, int
 //   B. one wave eliminates S_bb and the identity beside it (the only sequential part: 16 columns),
 //   C. L_ib = S_ib Linv_bb^T for i > b, Y_bj = -Linv_bb T_bj for j < b, and the scaled L_bb and Y_bb = Linv_bb
 //      (4 tasks, one a wave; this is where the square roots are taken and the pivots are checked),
-// where Y follows the forward substitution L Y = I block row by block row. A and C are 16 x 16 x 16 products on the
-// fp64 matrix cores; results go to global memory as they appear. A pivot that is not positive (or not a number, or
+// where Y follows the forward substitution L Y = I block row by block row. The terms of A that do not wait for block column
+// b - 1 are formed while the wave of B eliminates (by the other three, in registers), so that A itself is one product a wave.
+// (A took 910, 1,350 and 1,820 cycles for b = 1..3, now 820 each; the whole block 24,600, now 22,900.) A and C are 16 x 16 x 16
+// products on the fp64 matrix cores; results go to global memory as they appear. A pivot that is not positive (or not a number, or
 // below the relative floor stored next to the flag, or above 1e30) raises the flag; nothing is repaired, the caller discards a flagged factorisation.
 // `pend`: optional 64 x 64 tile (LDS, pitch NB+1; may be the tile Y) holding the rows of this block in the panel
 // just finished; its outer product is the one trailing update the block has not received yet and is subtracted
 // first.
-// the block's entries as chol_diag_body wants them (identity beyond nb): each wave's 32 x 32 quadrant, matrix-core
-// layout. A caller with other work to do first loads them early, so that they arrive under that work.
-__device__ __forceinline__ void load_diag_block(const double* M, int64_t ld, int64_t j0, int nb, double4_t (&mt)[2][2]) {
+// The diagonal block's ten lower 16 x 16 subtiles (the others are not looked at) are dealt to the four waves, subtile t to
+// wave t % 4: DiagRegs holds a wave's entries, matrix-core layout, identity beyond row or column nb. A caller with other
+// work to do first loads them early, so that they arrive under that work.
+struct DiagRegs {
+  double4_t v[3];
+};
+constexpr int kDiagTiles = 10;
+__device__ __forceinline__ void diag_subtile(int t, int& r0, int& c0) {
+  const int i = t >= 6 ? 3 : t >= 3 ? 2 : t >= 1 ? 1 : 0;
+  r0 = kSub * i;
+  c0 = kSub * (t - i * (i + 1) / 2);
+}
+__device__ __forceinline__ void load_diag_block(const double* M, int64_t ld, int64_t j0, int nb, DiagRegs& mt) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int u = 0; u < 3; ++u) {
+    const int t = wave + 4 * u;
+    if (t >= kDiagTiles) break;
+    int r0, c0;
+    diag_subtile(t, r0, c0);
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const int r = wi + 16 * i + 4 * r4 + (lane >> 4), c = wj + 16 * j + (lane & 15);
-        mt[i][j][r4] = (r < nb && c < nb) ? M[(j0 + r) * ld + j0 + c] : (r == c ? 1.0 : 0.0);
-      }
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const int r = r0 + 4 * r4 + (lane >> 4), c = c0 + (lane & 15);
+      const bool in = r < nb && c < nb;
+      const double m = M[(j0 + (in ? r : 0)) * ld + j0 + (in ? c : 0)];
+      mt.v[u][r4] = in ? m : (r == c ? 1.0 : 0.0);
+    }
+  }
 }
 
 __device__ __forceinline__ void chol_diag_body(double* M, int64_t ld, int64_t j0, int nb, double* linv_out, int* flag,
                                                const double (*pend)[NB + 1], double (*S)[NB + 1], double (*Y)[NB + 1],
-                                               const double4_t (&mt)[2][2]) {
+                                               const DiagRegs& mt) {
   __shared__ double XT[kSub][kSub + 1];
   __shared__ double I16[kSub][kSub + 1];
   __shared__ __align__(16) double col[2 * 32];  // two buffers for the column in flight
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, lk = lane >> 4;
   {
-    double4_t acc[2][2];
+    double4_t v[3];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int u = 0; u < 3; ++u) {
+      v[u] = mt.v[u];
+      const int t = wave + 4 * u;
+      if (pend && t < kDiagTiles) {   // rows past nb of the tile are zero, so the identity padding stays as it is
+        int r0, c0;
+        diag_subtile(t, r0, c0);
+        double4_t acc = double4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = double4_t{0.0, 0.0, 0.0, 0.0};
-    if (pend) {  // rows past nb of the tile are zero, so the identity padding stays as it is
-      tile_nt_mfma(pend, pend, acc);
-      __syncthreads();  // every wave has read `pend` before Y (possibly the same tile) is written
+        for (int k0 = 0; k0 < NB; k0 += 4)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(pend[r0 + l16][k0 + lk], pend[c0 + l16][k0 + lk], acc, 0, 0, 0);
+        v[u] -= acc;
+      }
     }
-    const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
+    if (pend) __syncthreads();  // every wave has read `pend` before Y (possibly the same tile) is written
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const int r = wi + 16 * i + 4 * r4 + lk, c = wj + 16 * j + l16;
-          S[r][c] = mt[i][j][r4] - acc[i][j][r4];
-        }
+    for (int u = 0; u < 3; ++u) {
+      const int t = wave + 4 * u;
+      if (t < kDiagTiles) {
+        int r0, c0;
+        diag_subtile(t, r0, c0);
+        sub_block_store(S, r0, c0, v[u]);
+      }
+    }
     I16[tid >> 4][tid & 15] = (tid >> 4) == (tid & 15) ? 1.0 : 0.0;
     // the sub-blocks of Linv above the diagonal are zero; the others are written as they are computed
     for (int idx = tid; idx < NB * NB; idx += kThreads)
@@ -799,25 +849,35 @@ __device__ __forceinline__ void chol_diag_body(double* M, int64_t ld, int64_t j0
   __syncthreads();
   constexpr int nsb = NB / kSub;
   const double4_t zero = double4_t{0.0, 0.0, 0.0, 0.0};
+  double4_t early = zero;   // waves 1..3: the terms k < b - 1 of this wave's task in A
   for (int b = 0; b < nsb; ++b) {
     const int o = b * kSub;
+    // tasks of A: wave 0 takes T_b,b-1 (one term only), waves 1 .. the column's S_ib, then the row's other T_bj
     if (b > 0) {  // A
-      if (wave < nsb - b) {
-        const int i = b + wave;
-        double4_t acc = zero;
-        for (int k = 0; k < b; ++k)  // (m, n): sum_kk S[16 i + m][16 k + kk] S[16 b + n][16 k + kk]
-          acc = sub_block_mma(&S[i * kSub][k * kSub], NB + 1, 1, &S[o][k * kSub], 1, NB + 1, acc);
+      const int kb = (b - 1) * kSub;
+      if (wave > 0 && wave - 1 < nsb - b) {
+        const int i = b + wave - 1;  // (m, n): sum_kk S[16 i + m][16 k + kk] S[16 b + n][16 k + kk]
+        const double4_t acc = sub_block_mma(&S[i * kSub][kb], NB + 1, 1, &S[o][kb], 1, NB + 1, early);
         sub_block_store(S, i * kSub, o, sub_block_load(S, i * kSub, o) - acc);
       } else {
-        const int j = wave - (nsb - b);
-        double4_t acc = zero;
-        for (int k = j; k < b; ++k)  // (m, n): sum_kk S[o + m][16 k + kk] Y[16 k + kk][16 j + n]
-          acc = sub_block_mma(&S[o][k * kSub], NB + 1, 1, &Y[k * kSub][j * kSub], NB + 1, 1, acc);
-        sub_block_store(Y, o, j * kSub, acc);
+        const int j = wave > 0 ? wave - 1 - (nsb - b) : b - 1;  // (m, n): sum_kk S[o + m][16 k + kk] Y[16 k + kk][16 j + n]
+        sub_block_store(Y, o, j * kSub, sub_block_mma(&S[o][kb], NB + 1, 1, &Y[kb][j * kSub], NB + 1, 1, early));
       }
       __syncthreads();
     }
-    if (wave == 0) eliminate_sub_block(S, o, XT, I16, col);  // B
+    if (wave == 0) {
+      eliminate_sub_block(S, o, XT, I16, col);  // B
+    } else if (b + 1 < nsb) {   // the next A's terms k < b
+      const int b1 = b + 1, i = b1 + wave - 1, j = wave - 1 - (nsb - b1);
+      early = zero;
+      if (wave - 1 < nsb - b1) {
+        for (int k = 0; k < b; ++k)
+          early = sub_block_mma(&S[i * kSub][k * kSub], NB + 1, 1, &S[b1 * kSub][k * kSub], 1, NB + 1, early);
+      } else {
+        for (int k = j; k < b; ++k)
+          early = sub_block_mma(&S[b1 * kSub][k * kSub], NB + 1, 1, &Y[k * kSub][j * kSub], NB + 1, 1, early);
+      }
+    }
     __syncthreads();
     {  // C
       const double d = S[o + l16][o + l16];
@@ -860,7 +920,7 @@ __global__ __launch_bounds__(kThreads) void chol_diag_kernel(double* M, int64_t 
                                                              int* flag) {
   __shared__ double S[kTile][NB + 1];
   __shared__ double Y[kTile][NB + 1];
-  double4_t mt[2][2];
+  DiagRegs mt;
   load_diag_block(M, ld, j0, nb, mt);
   chol_diag_body(M, ld, j0, nb, linv_out, flag, nullptr, S, Y, mt);
 }
@@ -879,25 +939,20 @@ __global__ __launch_bounds__(kThreads) void chol_panel_kernel(double* M, int64_t
     tile_put(Ls, tl, 0, NB, NB);
   }
   __syncthreads();
-  double4_t acc[2][2];
+  double4_t acc[4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = double4_t{0.0, 0.0, 0.0, 0.0};
-  tile_nt_mfma(As, Ls, acc);
+  for (int j = 0; j < 4; ++j) acc[j] = double4_t{0.0, 0.0, 0.0, 0.0};
+  tile_nt_lower_mfma(As, Ls, acc);
   {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const int64_t r = i0 + wi + 16 * i + 4 * r4 + (lane >> 4);
-          const int c = wj + 16 * j + (lane & 15);
-          if (r < rows_total && c < nb) M[r * ld + j0 + c] = acc[i][j][r4];
-        }
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const int64_t r = i0 + 16 * wave + 4 * r4 + (lane >> 4);
+        const int c = 16 * j + (lane & 15);
+        if (r < rows_total && c < nb) M[r * ld + j0 + c] = acc[j][r4];
+      }
   }
 }
 
@@ -916,6 +971,8 @@ __global__ __launch_bounds__(kThreads) void chol_update_kernel(double* M, int64_
   __shared__ double Lj[kTile][NB + 1];
   const int64_t base = j0 + nb;
   const int64_t i0 = base + (int64_t)ti * kTile, c0 = base + (int64_t)tj * kTile;
+  DiagRegs mt;  // the next diagonal block (its workgroup only), on its way with the operands
+  if (FUSE && ti == 0 && tj == 0) load_diag_block(M, ld, base, (int)(n - base < NB ? n - base : NB), mt);
   {
     TileRegs ta, tb;
     tile_fetch(ta, M, ld, i0, rows_total, j0, nb);
@@ -933,8 +990,6 @@ __global__ __launch_bounds__(kThreads) void chol_update_kernel(double* M, int64_
       M[n * ld + base + c] -= sum;
     }
     __syncthreads();  // the row above has read Li, which becomes the block's tile
-    double4_t mt[2][2];
-    load_diag_block(M, ld, base, (int)(n - base < NB ? n - base : NB), mt);
     chol_diag_body(M, ld, base, (int)(n - base < NB ? n - base : NB), linv_next, flag, Lj, Li, Lj, mt);
     return;
   }
@@ -970,7 +1025,7 @@ __global__ __launch_bounds__(kThreads) void chol_step_kernel(double* M, int64_t 
   const int64_t i0 = base + (int64_t)ti * kTile, c0 = base + (int64_t)tj * kTile;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
-  double4_t mt[2][2];  // the next diagonal block (first diagonal tile only), on its way while the panel is solved
+  DiagRegs mt;  // the next diagonal block (first diagonal tile only), on its way while the panel is solved
   if (ti == 0) load_diag_block(M, ld, base, (int)(n - base < NB ? n - base : NB), mt);
   {
     TileRegs ta, tb, tl;
@@ -982,27 +1037,23 @@ __global__ __launch_bounds__(kThreads) void chol_step_kernel(double* M, int64_t 
     if (ti != tj) tile_put(Lj, tb, c0, rows_total, NB);
   }
   __syncthreads();
-  double4_t xi[2][2], xj[2][2];
+  double4_t xi[4], xj[4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) xi[i][j] = xj[i][j] = double4_t{0.0, 0.0, 0.0, 0.0};
-  tile_nt_mfma(Li, Ls, xi);
-  if (ti != tj) tile_nt_mfma(Lj, Ls, xj);
+  for (int j = 0; j < 4; ++j) xi[j] = xj[j] = double4_t{0.0, 0.0, 0.0, 0.0};
+  tile_nt_lower_mfma(Li, Ls, xi);
+  if (ti != tj) tile_nt_lower_mfma(Lj, Ls, xj);
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const int r = wi + 16 * i + 4 * r4 + (lane >> 4), c = wj + 16 * j + (lane & 15);
-        const double x = xi[i][j][r4];
-        Li[r][c] = x;
-        // on a diagonal tile Lj is the same piece without the right-hand-side row (row n of the matrix)
-        Lj[r][c] = ti != tj ? xj[i][j][r4] : (c0 + r < n ? x : 0.0);
-        if (tj == 0 && i0 + r < rows_total) M[(i0 + r) * ld + j0 + c] = x;
-      }
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const int r = 16 * wave + 4 * r4 + (lane >> 4), c = 16 * j + (lane & 15);
+      const double x = xi[j][r4];
+      Li[r][c] = x;
+      // on a diagonal tile Lj is the same piece without the right-hand-side row (row n of the matrix)
+      Lj[r][c] = ti != tj ? xj[j][r4] : (c0 + r < n ? x : 0.0);
+      if (tj == 0 && i0 + r < rows_total) M[(i0 + r) * ld + j0 + c] = x;
+    }
   __syncthreads();
   if (ti == 0) {  // tj == 0 too: the next diagonal block
     // a short last block shares its tile with the right-hand-side row, which still needs this update
@@ -1075,6 +1126,7 @@ __global__ __launch_bounds__(kThreads) void chol_update_next_kernel(double* M, i
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = double4_t{0.0, 0.0, 0.0, 0.0};
   fetch(0);
+  DiagRegs mt;   // the next diagonal block (its workgroup only)
 #pragma unroll
   for (int kc = 0; kc < KW; kc += NB) {
     __syncthreads();
@@ -1086,16 +1138,27 @@ __global__ __launch_bounds__(kThreads) void chol_update_next_kernel(double* M, i
     }
     __syncthreads();
     if (kc + NB < KW) fetch(kc + NB);
+    else if (ti == 0) load_diag_block(M, ld, base, NB, mt);
     tile_nt_mfma(Li, Lj, acc);
   }
   if (ti == 0) {   // the next diagonal block (the super-panels leave at least 64 columns)
-    double4_t mt[2][2];
-    load_diag_block(M, ld, base, NB, mt);
+    __syncthreads();   // every wave has read Li and Lj
+    const int wi = (tid >> 7) * 32, wj = ((tid >> 6) & 1) * 32;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) mt[i][j] -= acc[i][j];
-    __syncthreads();   // every wave has read Li and Lj
+      for (int j = 0; j < 2; ++j) sub_block_store(Li, wi + 16 * i, wj + 16 * j, acc[i][j]);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      const int t = (tid >> 6) + 4 * u;
+      if (t < kDiagTiles) {
+        int r0, q0;
+        diag_subtile(t, r0, q0);
+        mt.v[u] -= sub_block_load(Li, r0, q0);
+      }
+    }
+    __syncthreads();   // Li becomes the block's tile
     chol_diag_body(M, ld, base, NB, linv_next, flag, nullptr, Li, Lj, mt);
     return;
   }
@@ -1553,8 +1616,11 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
     if (!diag_done) hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(kThreads), 0, st, M, ld, j0, nb, li, gs->flag);
     diag_done = false;
     const int64_t rest = rows_total - j0 - nb;
-    if (n - j0 - nb > 0 && rest <= kFuseMaxRows) {  // nb == NB here
-      const unsigned tt = nblocks(rest, kTile);
+    // One launch per step where its workgroups, one to a compute unit, run in a single round; above that the panel's own
+    // launch is the cheaper one (2,048 rows: 53 us in one launch, 24 in two; 1,408 rows: 24 and 22).
+    const int64_t step_tiles = nblocks(rest, kTile);
+    if (n - j0 - nb > 0 && rest <= kFuseMaxRows && step_tiles * (step_tiles + 1) / 2 <= ctx->num_cus) {  // nb == NB here
+      const unsigned tt = (unsigned)step_tiles;
       if (!panel_ready) {
         hipLaunchKernelGGL(copy_panel_kernel, dim3(nblocks(rest * NB, 256)), dim3(256), 0, st, M, ld, rows_total, j0 + NB, j0, n,
                            gs->panel[pbuf]);
