@@ -49,6 +49,9 @@ struct GatArgs {
   int32_t buf_lds;
   const float* h1;      // optional: layer-1 output of every coalition [k][rows_out[1]][dims[1]] (matrix-core path)
   const float* z2;      // optional, in the place of h1: layer 2's transformed rows [k][rows_out[1]][zw[1]]
+  const float* z2_lanes; // ... or, for masked_gat_last_layer_kernel, [block of 64 coalitions][rows_out[1]][zw[1]][64]
+  const uint64_t* Zt;   // with z2_lanes: the transposed masks, word blk of player p = its bits in the block's coalitions
+  int64_t KW;
   const int32_t* h1_bad; // device flag: non-zero means h1 (z2) was not produced (attention range too wide)
 };
 
@@ -303,6 +306,129 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 8))) void
   masked_gat_eval_body<64>(a);
 }
 
+// The last layer of a two-layer model on the rows that layer 1's kernel has already transformed (z2_lanes): only the
+// target's row is left. One coalition per lane, so that a feature column of a node is one coalesced load and an entry's
+// mask bits are one word of the transposed masks; the four waves of a workgroup take the entries of the target's row in
+// turn (a wave alone would be a chain of one L2 latency per entry) and wave 0 merges their running soft-maxima in wave
+// order. A wave per coalition with lanes over columns had ten of 64 lanes at work on ten classes: 20,000 coalitions, 999
+// players 69 us, now 12. F: columns of a head, at most NC. Raised flag: layer 1 was not produced, the general body does all.
+template <int NC>
+__global__ __launch_bounds__(kThreads) void masked_gat_last_layer_kernel(GatArgs a) {
+  if (*a.h1_bad != 0) {
+    masked_gat_eval_body<kThreads>(a);
+    return;
+  }
+  __shared__ float part[kWaves - 1][NC + 2][64];
+  __shared__ float att[2][32 * NC];   // attention vectors, NC to a head, zero from F on
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int H = a.heads[1], F = a.fh[1], zw = a.zw[1], R1 = a.rows_out[1];   // (H F <= 32)
+  for (int i = threadIdx.x; i < H * NC; i += kThreads) {
+    const int h = i / NC, c = i - h * NC;
+    att[0][i] = c < F ? a.asrc[1][h * F + c] : 0.f;
+    att[1][i] = c < F ? a.adst[1][h * F + c] : 0.f;
+  }
+  __syncthreads();
+  const int e1 = a.row_ptr[1];   // (the target is node 0)
+  const int64_t blocks = (a.k + 63) / 64;
+  for (int64_t blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
+    const float* zb = a.z2_lanes + (size_t)blk * R1 * zw * 64 + lane;
+    float out[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) out[c] = 0.f;
+    for (int h = 0; h < H; ++h) {
+      const float *as = att[0] + h * NC, *ad = att[1] + h * NC;
+      auto load = [&](int node, float (&z)[NC]) {
+        const float* zr = zb + (size_t)(node * zw + h * F) * 64;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const float v = zr[(c < F ? c : 0) * 64];
+          z[c] = c < F ? v : 0.f;
+        }
+      };
+      auto dot = [&](const float* w, const float (&z)[NC]) {
+        float s = 0.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) s += w[c] * z[c];
+        return s;
+      };
+      float acc[NC], m = -INFINITY, l = 0.f;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c] = 0.f;
+      float z[NC], zn[NC];
+      load(0, z);
+      const float sd = dot(ad, z);
+      if (wave == 0) {   // the self term starts the running soft-max
+        m = lrelu(dot(as, z) + sd, a.slope);
+        l = 1.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[c] = z[c];
+      }
+      int e = wave;
+      if (e < e1) load(a.col[e], z);
+      for (; e < e1; e += kWaves) {
+        const uint64_t word = a.Zt[(size_t)a.eid[e] * a.KW + blk];
+        if (e + kWaves < e1) load(a.col[e + kWaves], zn);
+        const float ee = lrelu(dot(as, z) + sd, a.slope);
+        if ((word >> lane) & 1ull) {
+          // of the two factors exp(m - max) and exp(e - max) one is always 1
+          const float d = ee - m, x = __expf(-fabsf(d));
+          const float sc = d > 0.f ? x : 1.f, pe = d > 0.f ? 1.f : x;
+          l = l * sc + pe;
+#pragma unroll
+          for (int c = 0; c < NC; ++c) acc[c] = acc[c] * sc + pe * z[c];
+          m = fmaxf(m, ee);
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) z[c] = zn[c];
+      }
+      if (wave > 0) {
+        part[wave - 1][NC][lane] = m;
+        part[wave - 1][NC + 1][lane] = l;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) part[wave - 1][c][lane] = acc[c];
+      }
+      __syncthreads();
+      if (wave == 0) {
+        float mm = m;
+#pragma unroll
+        for (int w = 0; w < kWaves - 1; ++w) mm = fmaxf(mm, part[w][NC][lane]);
+        const float s0 = __expf(m - mm);
+        l *= s0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[c] *= s0;
+#pragma unroll
+        for (int w = 0; w < kWaves - 1; ++w) {
+          const float sw = __expf(part[w][NC][lane] - mm);   // (exp(-inf) = 0 for a wave that saw nothing)
+          l += part[w][NC + 1][lane] * sw;
+#pragma unroll
+          for (int c = 0; c < NC; ++c) acc[c] += part[w][c][lane] * sw;
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) out[c] += acc[c] / l;
+      }
+      __syncthreads();
+    }
+    const int64_t row = blk * 64 + lane;
+    if (wave == 0 && row < a.k) {   // heads averaged, bias, score
+      const int pred = *a.pred_ptr;
+      float top = -INFINITY, zc = 0.f;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        if (c < F) {
+          out[c] = out[c] / (float)H + (a.bias[1] ? a.bias[1][c] : 0.f);
+          top = fmaxf(top, out[c]);
+          zc = c == pred ? out[c] : zc;
+        }
+      }
+      float s = 0.f;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        if (c < F) s += expf(out[c] - top);
+      a.y[row] = a.score == DS_SCORE_LOGIT ? zc : expf(zc - top) / s;
+    }
+  }
+}
+
 // s_src[v, h] = a_src^h . z_v^h and s_dst[v, h] = a_dst^h . z_v^h for the shared first transform
 __global__ void gat_att_scalars_kernel(const float* P, const float* asrc, const float* adst, int V, int H, int F,
                                        float* out) {
@@ -351,7 +477,7 @@ struct GatL1Args {
   const uint64_t* Zt;  // optional: transposed masks [n][KW], word blk of row p = bit p of coalitions 64 blk ..
   int64_t KW;
   float* h1;      // [k][R1][zw]
-  // layer 2's transform on the way out (in the place of h1): z2 [k][R1][zw2] = h1 W2, zw2 <= 32
+  // layer 2's transform on the way out (in the place of h1): z2 = h1 W2, zw2 <= 32, laid out as FUSE says
   const float* W2;
   float* z2;
   int32_t zw2;
@@ -430,7 +556,7 @@ __global__ __launch_bounds__(kThreads) void gat_entry_weights_kernel(GatL1Args g
 // transform on the matrix cores while they are in LDS, which replaces a round trip of [k][R1][zw] floats through
 // memory (107 MB at 20,000 coalitions of 21 rows of 64) and the transform of one coalition by one wave. 20,000
 // coalitions, 999 players, 820 entries: 259 -> 109 us here (130 with f / F as a division and a reciprocal per column),
-// and 293 -> 69 us in the kernel of the later layers.
+// and 293 -> 69 us in the kernel of the later layers (12 with masked_gat_last_layer_kernel).
 // v_mfma_f32_32x32x2f32: lane l supplies A[m = l%32][k = l/32] and B[k = l/32][n = l%32]; accumulator
 // register i of lane l is D[8*(i/4) + 4*(l/32) + i%4][l%32]. Per row a wave accumulates up to three
 // 32-column tiles of the numerator plus the denominator tile (one row per head).
@@ -445,7 +571,8 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
-template <bool FUSE, int TILES>   // TILES: numerator tiles per pass
+// FUSE: 0 layer 1's rows go out, 1 layer 2's transformed rows as [coalition][row][column], 2 as [block of 64][row][column][64]
+template <int FUSE, int TILES>   // TILES: numerator tiles per pass
 __global__ __launch_bounds__(kThreads, TILES <= 2 ? 3 : 2) void masked_gat_layer1_mfma_kernel(GatL1Args g) {
   if (*g.bad != 0) return;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_l1[];
@@ -487,7 +614,7 @@ __global__ __launch_bounds__(kThreads, TILES <= 2 ? 3 : 2) void masked_gat_layer
     for (int t = part; t < g.R1; t += g.parts) {
       const int e0 = __builtin_amdgcn_readfirstlane(g.row_ptr[t]), e1 = __builtin_amdgcn_readfirstlane(g.row_ptr[t + 1]);
       // (index e1 stands for the self term)
-      float16_t z2;   // FUSE: the row's transform, [coalition 8*(i/4) + 4*half + i%4][column l32]
+      float16_t z2;   // FUSE: the row's transform, [coalition 8*(i/4) + 4*half + i%4][column l32] (2: transposed)
 #pragma unroll
       for (int i = 0; i < 16; ++i) z2[i] = 0.f;
       for (int fg = 0; fg < FT; fg += TILES) {
@@ -570,8 +697,10 @@ __global__ __launch_bounds__(kThreads, TILES <= 2 ? 3 : 2) void masked_gat_layer
             wave_lds_fence();
             if (FUSE) {
 #pragma unroll
-              for (int u = 0; u < 16; ++u) 
-                z2 = __builtin_amdgcn_mfma_f32_32x32x2f32(T_w[l32 * 33 + 2 * u + half], w2L[(ft * 32 + 2 * u + half) * 32 + l32], z2, 0, 0, 0);
+              for (int u = 0; u < 16; ++u) {
+                const float tv = T_w[l32 * 33 + 2 * u + half], wv = w2L[(ft * 32 + 2 * u + half) * 32 + l32];
+                z2 = FUSE == 2 ? __builtin_amdgcn_mfma_f32_32x32x2f32(wv, tv, z2, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x2f32(tv, wv, z2, 0, 0, 0);
+              }
             } else if (ft_in_range(ft, l32, g.zw)) {
 #pragma unroll 4
               for (int cc = 0; cc < 16; ++cc) {
@@ -584,7 +713,16 @@ __global__ __launch_bounds__(kThreads, TILES <= 2 ? 3 : 2) void masked_gat_layer
           }
         }
       }
-      if (FUSE && l32 < g.zw2) {
+      if (FUSE == 2) {   // lane = coalition, registers = columns
+        const int64_t rw = row_base + l32;
+        float* out = g.z2 + (((size_t)(rw >> 6) * g.R1 + t) * g.zw2) * 64 + (rw & 63);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int c = 8 * (i / 4) + 4 * half + (i % 4);
+          if (c < g.zw2 && rw < g.k) out[c * 64] = z2[i];
+        }
+      }
+      if (FUSE == 1 && l32 < g.zw2) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int64_t rw = row_base + 8 * (i / 4) + 4 * half + (i % 4);
@@ -650,6 +788,7 @@ GatLayout gat_layout(const ds_ctx* ctx, const ds_cgraph* cg, int64_t k, int thre
 // the matrix-core path for layer 1 applies to models with at least two layers and enough coalitions
 struct GatL1Layout {
   bool use, transpose, fuse;
+  bool last;   // the second layer is the last one: masked_gat_last_layer_kernel follows
   int parts;
   int32_t R1, E1, zwr, zwp;
   int64_t KW;
@@ -682,7 +821,8 @@ GatL1Layout gat_l1_layout(const ds_ctx* ctx, const ds_cgraph* cg, int64_t k) {
   // layer 2's transform rides along where its columns fit one matrix-core tile and its weights LDS, and where what it
   // hands on is no larger than the first layer's output, by which the workspace was admitted above
   q.fuse = ctx->gat.zw[1] <= 32 && q.zwr <= 256 && ctx->gat.zw[1] <= ctx->gat.zw[0];
-  if (q.fuse) q.h1_bytes = (size_t)k * q.R1 * ctx->gat.zw[1] * 4;   // z2 in its place
+  q.last = q.fuse && L == 2;
+  if (q.fuse) q.h1_bytes = (size_t)(q.last ? q.KW * 64 : k) * q.R1 * ctx->gat.zw[1] * 4;   // z2 in its place
   q.lds_bytes = (((size_t)2 * (q.E1 + 2) * 8 + 15) & ~(size_t)15) + (q.fuse ? (size_t)q.zwr * 128 : 0) +
                 (size_t)kWaves * (ctx->gat.heads[0] * 33 + 32 * 33) * 4;
   // as many workgroups as fit (registers: three waves a SIMD up to 64 columns, else two; LDS), the rows of a block of coalitions shared accordingly
@@ -748,7 +888,7 @@ int gat_launch(ds_ctx* ctx, const GatArgs& a, const GatLayout& g, int grid) {
 
 size_t ds_gat_eval_arena_bytes(ds_ctx* ctx, const ds_cgraph* cg, int64_t k) {
   const GatL1Layout q = gat_l1_layout(ctx, cg, k);
-  const GatLayout g = gat_layout(ctx, cg, k > 1 ? k : 1, q.use ? 64 : kThreads);
+  const GatLayout g = gat_layout(ctx, cg, k > 1 ? k : 1, q.use && !q.last ? 64 : kThreads);
   const GatLayout g1 = gat_layout(ctx, cg, 1);
   const size_t W = (cg->info.num_players + 63) / 64;
   return (q.use ? ds_align(q.az_bytes) + ds_align(q.h1_bytes) + ds_align(q.zt_bytes + 8) + ds_align((size_t)q.R1 * 32 * 4) + 1024 : 0) +
@@ -798,7 +938,7 @@ int ds_gat_eval_impl(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, i
   DS_TRY(ds_gat_prepare_model(ctx, cg));
   if (k <= 0) return DS_OK;
   const GatL1Layout q = gat_l1_layout(ctx, cg, k);
-  const GatLayout g = gat_layout(ctx, cg, k, q.use ? 64 : kThreads);
+  const GatLayout g = gat_layout(ctx, cg, k, q.use && !q.last ? 64 : kThreads);
   float* gws = nullptr;
   if (g.gws_floats) {
     gws = (float*)ds_arena_alloc(ctx, (size_t)g.gws_floats * 4 * g.grid);
@@ -832,8 +972,11 @@ int ds_gat_eval_impl(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, i
     l1.W2 = a.Wl[1]; l1.z2 = h1; l1.zw2 = a.zw[1]; l1.parts = q.parts;   // (z2 or h1: one buffer)
     l1.rowmax = rowmax; l1.Zt = Zt; l1.KW = q.KW;
     Zt_w = Zt;
-    if (q.fuse) a.z2 = h1;
+    if (q.last) a.z2_lanes = h1;
+    else if (q.fuse) a.z2 = h1;
     else a.h1 = h1;
+    a.Zt = Zt;
+    a.KW = q.KW;
     a.h1_bad = bad;
   }
   DS_TRY(ds_kernel_mark(ctx, 0, 0));
@@ -843,14 +986,29 @@ int ds_gat_eval_impl(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, i
     hipLaunchKernelGGL(gat_entry_weights_kernel, dim3((q.E1 + q.R1 + kWaves - 1) / kWaves), dim3(kThreads), 0, ctx->stream, l1);
     DS_HIP(ctx, hipGetLastError());
     if (q.transpose) DS_TRY(ds_bit_transpose(ctx, Z, k, cg->info.num_players, a.W, 0, 1, Zt_w));
-    void (*const kern)(GatL1Args) = q.zwr <= 32   ? (q.fuse ? masked_gat_layer1_mfma_kernel<true, 1> : masked_gat_layer1_mfma_kernel<false, 1>)
-                                    : q.zwr <= 64 ? (q.fuse ? masked_gat_layer1_mfma_kernel<true, 2> : masked_gat_layer1_mfma_kernel<false, 2>)
-                                                  : (q.fuse ? masked_gat_layer1_mfma_kernel<true, 3> : masked_gat_layer1_mfma_kernel<false, 3>);
+    const int fuse = q.last ? 2 : q.fuse ? 1 : 0, tiles = q.zwr <= 32 ? 0 : q.zwr <= 64 ? 1 : 2;
+    void (*const kerns[3][3])(GatL1Args) = {
+        {masked_gat_layer1_mfma_kernel<0, 1>, masked_gat_layer1_mfma_kernel<0, 2>, masked_gat_layer1_mfma_kernel<0, 3>},
+        {masked_gat_layer1_mfma_kernel<1, 1>, masked_gat_layer1_mfma_kernel<1, 2>, masked_gat_layer1_mfma_kernel<1, 3>},
+        {masked_gat_layer1_mfma_kernel<2, 1>, masked_gat_layer1_mfma_kernel<2, 2>, masked_gat_layer1_mfma_kernel<2, 3>}};
+    void (*const kern)(GatL1Args) = kerns[fuse][tiles];
     if (q.lds_bytes > 48 * 1024)
       DS_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)q.lds_bytes));
     hipLaunchKernelGGL(kern, dim3(q.grid), dim3(kThreads), q.lds_bytes, ctx->stream, l1);
     DS_HIP(ctx, hipGetLastError());
   }
-  DS_TRY(gat_launch(ctx, a, g, g.grid));
+  if (q.last) {
+    const int F = a.fh[1];
+    void (*const kern)(GatArgs) = F <= 8    ? masked_gat_last_layer_kernel<8>
+                                  : F <= 16 ? masked_gat_last_layer_kernel<16>
+                                            : masked_gat_last_layer_kernel<32>;
+    if (g.lds_bytes > 40 * 1024)   // (the general body's buffers, beside the kernel's own)
+      DS_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_bytes));
+    // (the grid also bounds the general body's scratch)
+    hipLaunchKernelGGL(kern, dim3((unsigned)(q.KW < g.grid ? q.KW : g.grid)), dim3(kThreads), g.lds_bytes, ctx->stream, a);
+    DS_HIP(ctx, hipGetLastError());
+  } else {
+    DS_TRY(gat_launch(ctx, a, g, g.grid));
+  }
   return ds_kernel_mark(ctx, 0, 1);
 }

@@ -101,6 +101,21 @@ def test_masked_gat_second_transform_on_the_way_out(heads, widths):
     _eval_case(w, model, 2, False, 1, 257, rng, biases)   # two blocks of 128 coalitions and one row
 
 
+# the last layer with one coalition per lane: a head's columns at and one past the register sizes (8, 16, 32), several
+# heads, and coalitions that end at, one before and one past a block of 64
+@pytest.mark.parametrize("heads,widths,rows", [((4, 1), (8, 8), 256), ((4, 1), (8, 9), 319), ((4, 1), (8, 16), 320),
+                                               ((4, 1), (8, 17), 321), ((4, 1), (8, 32), 257), ((4, 4), (8, 8), 300),
+                                               ((2, 32), (16, 1), 300)])
+def test_masked_gat_last_layer_by_lanes(heads, widths, rows):
+    w = make_workload("gat_small")
+    say(f"gat last layer heads={heads} widths={widths} rows={rows}")
+    rng = np.random.default_rng(17)
+    model = _gat_model(rng, w.features.shape[1], heads, widths)
+    biases = [0.1 * rng.standard_normal(o).astype(np.float32) for o in (heads[0] * widths[0], widths[1])]
+    _eval_case(w, model, 2, False, 0, rows, rng, biases)
+    _eval_case(w, model, 2, False, 1, rows, rng)
+
+
 def test_masked_gat_workspace_follows_the_narrower_layer():
     """What the first layer's kernel hands on ([k][rows][columns]) is never larger than the first layer's own output,
     which the 2 GiB limit of that path is tested against: a narrow first layer in front of many classes keeps it small."""
