@@ -243,62 +243,87 @@ __global__ __launch_bounds__(kZThreads, 4) void zt_layer1_kernel(ZtArgs a, float
   }
 }
 
-// Aggregation of a later layer, one wave per (coalition, row t), lanes = features: q[t][f] = d_t^-1/2 ( sum over the
+// Aggregation of a later layer, one wave per (kAggCoal coalitions, row t), lanes = features: q[t][f] = d_t^-1/2 ( sum over the
 // ACTIVE entries of H'[src][f] + H'[t][f] ), H' being the previous layer's output times d^-1/2 of its own row (stored that
-// way). Only the coalition's own active entries are visited: the lanes test the bits of 64 entries together and the set
-// ones are walked eight at a time (eight 256-byte row loads in flight). The layer's input of one coalition (rows x d x 4
-// bytes: 2.5 MB on the hub workload) is read by all rows t of that coalition, about sixteen times over; with one row per
-// wave the whole GPU works on a few dozen coalitions at a time, so those re-reads come from the caches (HBM traffic of
-// the hub workload's second layer: 780 GB as [row][feature][64 coalitions] -> 53 GB). The launch also keeps the workgroups
-// of a coalition on one XCD (workgroups go to the XCDs round-robin by index); measured, that made no difference
-// against plain order.
-__global__ __launch_bounds__(kZThreads) void zt_aggregate_kernel(ZtArgs a, int l, const float* cur, float* q, int wg_per_coalition) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// way). Only a coalition's own active entries are visited: the lanes test the bits of 64 entries together and the set
+// ones are walked eight at a time for each coalition. A row is a chain of latencies (row bounds -> entries -> words ->
+// rows of H'), and its entries and words are the same for all coalitions of a block, so a wave goes through them once for
+// several coalitions and has the gathers of all of them in flight (50,021 players, 10,000 coalitions: 4.2 -> 3.5 ms). The layer's
+// input of one coalition (rows x d x 4 bytes: 2.5 MB on the hub workload) is read by all rows t of that coalition, about
+// sixteen times over; with a row per wave the whole GPU works on some hundred coalitions at a time, so those re-reads
+// come from the caches (HBM traffic of the hub workload's second layer: 780 GB as [row][feature][64 coalitions] -> 53 GB).
+// The launch also keeps the workgroups of a coalition on one XCD (workgroups go to the XCDs round-robin by index);
+// measured, that made no difference against plain order.
+constexpr int kAggCoal = 4;     // divides 64
+constexpr int kAggUnroll = 8;   // gathers in flight per coalition
+__global__ __launch_bounds__(kZThreads) void zt_aggregate_kernel(ZtArgs a, int l, const float* cur, float* q, int wg_per_group) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int din = a.dims[l - 1], rows = a.rows_out[l], rows_prev = a.rows_out[l - 1];
   const int xcd = blockIdx.x & 7;
   const int64_t slot = blockIdx.x >> 3;
-  const int64_t cl = (slot / wg_per_coalition) * 8 + xcd;   // coalition of the launch
-  const int t = (int)(slot % wg_per_coalition) * kZWaves + wave;
+  const int64_t cl = ((slot / wg_per_group) * 8 + xcd) * kAggCoal;   // first coalition of the group
+  const int t = (int)(slot % wg_per_group) * kZWaves + wave;
   if (cl >= (int64_t)a.nblk * 64 || t >= rows) return;
   const int64_t cbi = cl >> 6;
-  const int cb = (int)(cl & 63);   // the coalition's bit in its block's words
-  if (block_row(a, a.blk0 + cbi, cb) >= a.k) return;
+  const int cb = (int)(cl & 63);   // its bit in its block's words
+  if (block_row(a, a.blk0 + cbi, cb) >= a.k) return;   // (rows of a block ascend: the group's others are past the end too)
   uint64_t inv;
   const uint64_t* Tb = block_words(a, a.blk0 + cbi, &inv);
-  const float rst = a.rs[((size_t)cbi * a.V + t) * 64 + cb];
-  const float* hb = cur + (size_t)cl * rows_prev * din;
+  const char* hb[kAggCoal];
+#pragma unroll
+  for (int g = 0; g < kAggCoal; ++g) hb[g] = (const char*)(cur + (size_t)(cl + g) * rows_prev * din);
   const int e0 = a.row_ptr[t], e1 = a.row_ptr[t + 1];  // entry e1 stands for the self-loop
+  const uint32_t row_bytes = (uint32_t)din * 4u;       // (one coalition's rows are far below 4 GB)
   for (int f0 = 0; f0 < din; f0 += 64) {
     const bool fok = f0 + lane < din;
-    const float* hf = hb + (fok ? f0 + lane : 0);
-    float acc = 0.f;
+    const uint32_t col = (uint32_t)(fok ? f0 + lane : 0) * 4u;
+    float acc[kAggCoal];
+#pragma unroll
+    for (int g = 0; g < kAggCoal; ++g) acc[g] = 0.f;
     for (int eb = e0; eb <= e1; eb += 64) {
       const int e = eb + lane;
-      int sv = t;
-      bool on = e == e1;
+      uint32_t at = (uint32_t)t * row_bytes;
+      uint32_t bits = e == e1 ? (1u << kAggCoal) - 1u : 0u;
       if (e < e1) {
-        sv = a.col[e];
-        on = ((Tb[a.eid[e]] ^ inv) >> cb) & 1ull;
+        at = (uint32_t)a.col[e] * row_bytes;
+        bits = (uint32_t)((Tb[a.eid[e]] ^ inv) >> cb);
       }
-      unsigned long long act = __ballot(on);
-      while (act) {
-        float hv[8];
+      unsigned long long act[kAggCoal], any = 0ull;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const bool live = act != 0ull;
-          const int i = live ? __ffsll((long long)act) - 1 : 63;
-          act &= act - 1ull;
-          const int src = (int)rl((uint32_t)sv, i);
-          const float x = hf[(size_t)src * din];   // (issued unconditionally; a spent slot reads a valid row and adds zero)
-          hv[u] = live ? x : 0.f;
+      for (int g = 0; g < kAggCoal; ++g) {
+        act[g] = __ballot((bits >> g) & 1u);
+        any |= act[g];
+      }
+      while (any) {
+        float hv[kAggCoal][kAggUnroll];
+        any = 0ull;
+#pragma unroll
+        for (int g = 0; g < kAggCoal; ++g) {
+#pragma unroll
+          for (int u = 0; u < kAggUnroll; ++u) {
+            const bool live = act[g] != 0ull;
+            const int i = live ? __ffsll((long long)act[g]) - 1 : 63;
+            act[g] &= act[g] - 1ull;
+            const float x = *(const float*)(hb[g] + (rl(at, i) + col));   // (issued unconditionally; a spent slot reads a valid row and adds zero)
+            hv[g][u] = live ? x : 0.f;
+          }
+          any |= act[g];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += hv[u];
+        for (int g = 0; g < kAggCoal; ++g)
+#pragma unroll
+          for (int u = 0; u < kAggUnroll; ++u) acc[g] += hv[g][u];
       }
     }
+    const float4 rst = *(const float4*)(a.rs + ((size_t)cbi * a.V + t) * 64 + cb);
+    const float rt[4] = {rst.x, rst.y, rst.z, rst.w};
+    static_assert(kAggCoal == 4, "one 16-byte load of d_t^-1/2");
     if (fok) {
-      const float v = rst * acc;
-      q[((size_t)cl * rows + t) * din + f0 + lane] = a.bf16 ? zt_bf16_round(v) : v;
+#pragma unroll
+      for (int g = 0; g < kAggCoal; ++g) {
+        const float v = rt[g] * acc[g];
+        q[((size_t)(cl + g) * rows + t) * din + f0 + lane] = a.bf16 ? zt_bf16_round(v) : v;
+      }
     }
   }
 }
@@ -542,12 +567,12 @@ int ds_eval_zt(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, int sco
     float* cur = bufA;
     for (int l = 2; l <= ctx->L; ++l) {
       float* nxt = (l & 1) ? bufA : bufB;
-      const int wg_per_coalition = (a.rows_out[l] + kZWaves - 1) / kZWaves;
-      const int64_t agg_grid = (((int64_t)a.nblk * 64 + 7) / 8) * wg_per_coalition * 8;
+      const int wg_per_group = (a.rows_out[l] + kZWaves - 1) / kZWaves;
+      const int64_t agg_grid = (((int64_t)a.nblk * (64 / kAggCoal) + 7) / 8) * wg_per_group * 8;
       const int64_t tt = (a.rows_out[l] + 31) / 32, jt = (a.dims[l] + 31) / 32;
       if (agg_grid > 0x7fffffffLL) return ds_fail(ctx, DS_EINTERNAL, "eval: too many aggregation workgroups");
       hipLaunchKernelGGL(zt_aggregate_kernel, dim3((unsigned)agg_grid), dim3(kZThreads), 0, ctx->stream, a, l, (const float*)cur, q,
-                         wg_per_coalition);
+                         wg_per_group);
       const bool vec = (a.dims[l - 1] & 3) == 0;
       void (*const transform)(ZtArgs, int, const float*, float*) =
           a.bf16 ? (vec ? zt_transform_kernel<true, true> : zt_transform_kernel<true, false>)

@@ -288,6 +288,31 @@ def test_masked_inference_widths_and_row_lengths(dims, directed):
     _eval_case(w, len(dims) - 1, directed, 1, biases, 322, rng)
 
 
+# layer by layer a wave takes a row for four coalitions of a block of 64: row counts that end at every place in a group and
+# at a whole block, pairs included, over a row of more than 64 entries
+@pytest.mark.parametrize("rows,pairs", [(257, False), (258, True), (259, False), (260, True), (320, False), (384, True)])
+def test_layer_by_layer_inference_at_the_ends_of_groups(rows, pairs):
+    from paper_2506_22668_amd import Options, Tuning
+    w = make_workload("c4b_small")
+    rng = np.random.default_rng(rows)
+    ctx = make_context(w)
+    cg = ctx.extract(w.targets[0], Options(hops=3))
+    cgo = compgraph.extract(w.row_ptr, w.col, w.targets[0], 3)
+    bits = rng.random((rows, cgo["num_players"])) < rng.random((rows, 1))
+    if pairs:
+        bits[1::2] = ~bits[0::2]
+    Z = torch.from_numpy(sampling.pack_rows(bits).view(np.int64)).cuda()
+    say(f"layer by layer rows={rows} pairs={pairs}")
+    ctx.set_tuning(Tuning(eval_path=4))
+    y, pc = ctx.eval(cg, Z, 1, pairs=pairs)
+    f = gcn.ValueFunction(cgo, w.features, w.weights, None, "logit")
+    ref = f.batch(bits)
+    # float32 sums of at most a few hundred terms, three layers: some 1e-6 of the largest logit
+    assert pc == f.pred_class and np.abs(y.cpu().numpy() - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
+    ctx.cgraph_free(cg)
+    ctx.close()
+
+
 # graphs past the limits of the smaller ones above: degrees outside of LDS (more than 640 nodes), with the local CSR in LDS
 # and without, and more than 4,096 first-layer entries, where the waves of the paired external-input form add up a
 # shared row in a single tile; an odd width and one above 64 of each, two layers (as many shared rows as children above
