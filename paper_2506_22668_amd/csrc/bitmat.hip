@@ -45,22 +45,6 @@ __global__ __launch_bounds__(kThreads) void row_prep_kernel(const uint64_t* Z, i
 constexpr int kTrThreads = 512;
 constexpr int kTrPitch = 9;  // 64-bit words per LDS row of 8: lanes that read one word column of 64 rows spread over the banks
 
-__device__ __forceinline__ uint64_t transpose64_in_wave(uint64_t x, int lane) {
-  const uint64_t masks[6] = {0x00000000FFFFFFFFull, 0x0000FFFF0000FFFFull, 0x00FF00FF00FF00FFull,
-                             0x0F0F0F0F0F0F0F0Full, 0x3333333333333333ull, 0x5555555555555555ull};
-#pragma unroll
-  for (int s = 0; s < 6; ++s) {
-    const int j = 32 >> s;
-    const uint64_t m = masks[s];
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)x, j, 64), hi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), j, 64);
-    const uint64_t t = ((uint64_t)hi << 32) | lo;
-    // rows whose index has bit j clear keep their low bit blocks and take the partner's low blocks as their high
-    // ones; the others keep their high blocks and take the partner's high blocks as their low ones
-    x = (lane & j) ? (((t >> j) & m) | (x & ~m)) : ((x & m) | ((t & m) << j));
-  }
-  return x;
-}
-
 __global__ __launch_bounds__(kTrThreads) void bit_transpose_kernel(const uint64_t* in, int64_t rows, int64_t cols,
                                                                    int64_t in_stride, int64_t row_first, int64_t row_step,
                                                                    uint64_t* out, int64_t Wout, int64_t tiles_c, int block_major) {
@@ -82,7 +66,7 @@ __global__ __launch_bounds__(kTrThreads) void bit_transpose_kernel(const uint64_
   // wave `wave` transposes the blocks (row block rbi, word column wave) for the eight row blocks
 #pragma unroll
   for (int rbi = 0; rbi < 8; ++rbi) {
-    const uint64_t x = transpose64_in_wave(tin[(rbi * 64 + lane) * kTrPitch + wave], lane);
+    const uint64_t x = ds_transpose64_in_wave(tin[(rbi * 64 + lane) * kTrPitch + wave], lane);
     tout[(wave * 64 + lane) * kTrPitch + rbi] = x;   // lane = column within the word column, word = row block
   }
   __syncthreads();

@@ -149,6 +149,23 @@ __device__ __forceinline__ double ds_mm_sum(const int32_t* partial, int64_t rows
   ds_mm_sum_part(partial, rows, groups, r, 0, 1, S);
   return ds_mm_sum_finish(S);
 }
+// 64 x 64 bits, a row per lane, transposed: bit i of lane j = bit j of lane i. Six rounds of swapping bit blocks with the
+// lane 32, 16, ... 1 away.
+__device__ __forceinline__ uint64_t ds_transpose64_in_wave(uint64_t x, int lane) {
+  const uint64_t masks[6] = {0x00000000FFFFFFFFull, 0x0000FFFF0000FFFFull, 0x00FF00FF00FF00FFull,
+                             0x0F0F0F0F0F0F0F0Full, 0x3333333333333333ull, 0x5555555555555555ull};
+#pragma unroll
+  for (int s = 0; s < 6; ++s) {
+    const int j = 32 >> s;
+    const uint64_t m = masks[s];
+    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)x, j, 64), hi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), j, 64);
+    const uint64_t t = ((uint64_t)hi << 32) | lo;
+    // rows whose index has bit j clear keep their low bit blocks and take the partner's low blocks as their high
+    // ones; the others keep their high blocks and take the partner's high blocks as their low ones
+    x = (lane & j) ? (((t >> j) & m) | (x & ~m)) : ((x & m) | ((t & m) << j));
+  }
+  return x;
+}
 #endif
 
 // index lists of the set bits of rows (off = exclusive prefix sums of the row sizes)
