@@ -313,6 +313,36 @@ def test_layer_by_layer_inference_at_the_ends_of_groups(rows, pairs):
     ctx.close()
 
 
+# the later layers' transform with the weights in registers (widths that are multiples of four, at most 64, from 16 rows on):
+# whole and partial 32-feature tiles on either side, and the first widths outside
+@pytest.mark.parametrize("dims", [(32, 64, 64, 5), (32, 4, 64, 5), (32, 64, 4, 5), (32, 36, 28, 5), (32, 60, 32, 5), (32, 32, 36, 5),
+                                  (32, 68, 64, 5), (32, 64, 68, 5), (32, 62, 64, 5)])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_layer_by_layer_transform_widths(dims, dtype):
+    from paper_2506_22668_amd import Options, Tuning
+    from synth.workloads import glorot_uniform
+    w = make_workload("c4b_small")
+    rng = np.random.default_rng(sum(dims))
+    w = type(w)(**{**w.__dict__, "weights": [glorot_uniform(rng, dims[i], dims[i + 1]) for i in range(3)], "dims": dims})
+    biases = [0.1 * rng.standard_normal(d).astype(np.float32) for d in dims[1:]]
+    ctx = make_context(w, biases=biases, transform_dtype=dtype)
+    cg = ctx.extract(w.targets[0], Options(hops=3))
+    cgo = compgraph.extract(w.row_ptr, w.col, w.targets[0], 3)
+    assert cgo["ball"][1] >= 16
+    bits = rng.random((300, cgo["num_players"])) < rng.random((300, 1))
+    Z = torch.from_numpy(sampling.pack_rows(bits).view(np.int64)).cuda()
+    say(f"layer by layer dims={dims} dtype={dtype}")
+    ctx.set_tuning(Tuning(eval_path=4))
+    y, pc = ctx.eval(cg, Z, 1)
+    f = gcn.ValueFunction(cgo, w.features, w.weights, biases, "logit")
+    ref = f.batch(bits)
+    # float32: sums of at most a few hundred terms; bfloat16 operands: 2^-9 each, two transforms
+    tol = 1e-2 if dtype else 1e-5
+    assert (pc == f.pred_class or dtype) and (pc != f.pred_class or np.abs(y.cpu().numpy() - ref).max() <= tol * max(1.0, np.abs(ref).max()))
+    ctx.cgraph_free(cg)
+    ctx.close()
+
+
 # graphs past the limits of the smaller ones above: degrees outside of LDS (more than 640 nodes), with the local CSR in LDS
 # and without, and more than 4,096 first-layer entries, where the waves of the paired external-input form add up a
 # shared row in a single tile; an odd width and one above 64 of each, two layers (as many shared rows as children above
