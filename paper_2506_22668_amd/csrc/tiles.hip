@@ -11,7 +11,7 @@
 // the build left it, serves  d = S u  (accumulate by row, gather by column) and  s = S^T h  (accumulate by column,
 // gather by row), and no transposed copy is built.
 //
-// Row blocks hold at most 8192 rows and about 1/16 of the entries each (the rows are sorted by size, so the blocks of
+// Row blocks hold at most 8192 rows and about 1/12 to 1/64 of the entries each (the rows are sorted by size, so the blocks of
 // the largest rows are short; a tile of such a block holds several times more entries than the 8192 source values
 // staged for it); workgroups of the forward product own (row block, group of chunks),
 // those of the adjoint (chunk, group of row blocks of at most 32768 rows): both are balanced in entries. Tiles with few
@@ -237,13 +237,18 @@ int ceil_log2(int64_t v) {
 static void tile_shape(const ds_ctx* ctx, int64_t rows, int64_t cols, int64_t nnz, int64_t* budget, int64_t* gbudget,
                        int32_t* max_blocks, int32_t* ncb) {
   *ncb = (int32_t)((cols + kTileSpan - 1) / kTileSpan);
-  // entry-heavy row blocks: 16, or more where the matrix has few column chunks (the adjoint product runs one
-  // workgroup per chunk and group of row blocks, and wants two per compute unit)
-  int64_t parts = (2 * (int64_t)ctx->num_cus + *ncb - 1) / *ncb;
-  if (parts < 16) parts = 16;
-  if (parts > 64) parts = 64;
+  // A workgroup's two pieces fill a compute unit's LDS, and what bounds the products of all but the largest games is how
+  // often a unit has to start over (zero, stage, write out) and the partial vectors, one per group, that the loop adds up
+  // again: as many groups as let the adjoint product (one workgroup per chunk and group) run in a single round. (Two
+  // rounds' worth before: 99,981 players, 3.9 M entries, 41 groups, a third round nearly empty; an explanation with 120 CGLS
+  // iterations 21.92 ms, now 20.29. With 13 M entries 0.325 ms per iteration, now 0.311.) Fewer than six are too coarse a split of the rows: then four to six groups of blocks of a
+  // sixteenth of the entries.
+  int64_t groups = (int64_t)ctx->num_cus / *ncb - 2;   // (a block or two more come from the limit on rows)
+  if (groups > 64) groups = 64;
+  const int64_t per = groups >= 6 ? (11 + groups) / groups : 0;   // row blocks per group: at least twelve in all
+  const int64_t parts = per > 0 ? groups * per : 16;
   *budget = nnz / parts > 65536 ? nnz / parts : 65536;
-  *gbudget = parts > 16 ? *budget : (nnz / 6 > 4 * *budget ? nnz / 6 : 4 * *budget);
+  *gbudget = per > 0 ? per * *budget : (nnz / 6 > 4 * *budget ? nnz / 6 : 4 * *budget);
   *max_blocks = (int32_t)(rows / kTileSpan + 2 * (nnz / *budget) + 8);
 }
 
@@ -300,6 +305,18 @@ int ds_tile_build(ds_ctx* ctx, int64_t rows, int64_t cols, int64_t nnz, int64_t 
   if (gf < 1) gf = 1;
   plan->cpg = (ncb + gf - 1) / gf;
   plan->gf = (ncb + plan->cpg - 1) / plan->cpg;
+  // a second round that would be nearly empty is worth another chunk per workgroup, if that fills the first one (300,007 players,
+  // 10.7 M entries: 323 workgroups of two chunks -> 221 of three, 10.17 -> 9.95 ms for 30 iterations; 99,981 players, 13 M
+  // entries: 286 of one stay, 154 of two were 3 % slower)
+  const int64_t wgs = (int64_t)plan->nrb * plan->gf, cus = ctx->num_cus;
+  if (wgs > cus && 10 * wgs <= 13 * cus) {
+    const int32_t cpg = plan->cpg + 1, fewer = (ncb + cpg - 1) / cpg;
+    const int64_t then = (int64_t)plan->nrb * fewer;
+    if (then <= cus && 10 * then >= 8 * cus) {
+      plan->cpg = cpg;
+      plan->gf = fewer;
+    }
+  }
   const size_t pf = (size_t)plan->gf * rows * 8, pa = (size_t)plan->nga * cols * 8;
   plan->partial = (long long*)take(pf > pa ? pf : pa);
   // terms of one accumulator: forward at most max_row_size, adjoint at most the rows of a group; the integers are

@@ -515,6 +515,23 @@ def test_cgls_dense_row_threshold_leaves_the_solution_alone(ctx_tiny, dense_div)
     assert abs(rep.cgls_iterations - rep0.cgls_iterations) <= 2
 
 
+# how the sparse rows' tiles are grouped follows the number of column chunks: one chunk, two, enough for 64 groups, groups of
+# one row block (14 chunks), of two (22) and the coarse split of the widest games (37); more than 65,536 entries a block
+@pytest.mark.parametrize("n,ns", [(8192, 16000), (8193, 16000), (24_600, 16000), (110_000, 12000), (180_000, 8000), (300_007, 6000)])
+def test_cgls_tile_groups_by_width(ctx_tiny, n, ns):
+    from oracle import cfast
+    from paper_2506_22668_amd import Options, DS_SOLVER_CGLS
+    ctx, _ = ctx_tiny
+    say(f"cgls tile groups n={n} n_samples={ns}")
+    Z, w, sz = ctx.sample(n, ns, 11, 3)
+    y = torch.from_numpy(np.random.default_rng(n).random(Z.shape[0], dtype=np.float32)).cuda()
+    phi, rep, rc = ctx.solve(n, Z, w, y, Options(solver=DS_SOLVER_CGLS, paired=1, max_iter=4), allow_not_converged=True)
+    assert rep.cgls_iterations == 4
+    ref = cfast.cgls(n, to_u64(Z), w.cpu().numpy(), y.cpu().numpy(), tol=0.0, max_iter=4)[0]
+    # both in fp64 or exact integers of 2^-47 and better, four steps; the scores come as float32
+    assert np.abs(phi.cpu().numpy().astype(np.float64) - ref).max() <= 1e-6 * np.abs(ref).max()
+
+
 def test_cgls_one_iteration_under_enumeration(ctx_tiny):
     from paper_2506_22668_amd import Options, DS_SOLVER_CGLS
     ctx, _ = ctx_tiny
