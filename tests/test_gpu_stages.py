@@ -150,6 +150,38 @@ def test_extraction_isolated_and_pendant_targets():
     ctx.close()
 
 
+# The one-workgroup extraction takes graphs of at most 65,536 nodes (a thread to 64 of them) whose hops have at most 1,024 rows and
+# 16,384 entries; beyond that the general kernels follow. Sizes at both sides of each limit, single words, ragged last words,
+# more than one round of its prefix sums.
+@pytest.mark.parametrize("num_nodes,first,second,hops", [
+    (2, 1, 0, 1), (64, 20, 2, 2), (65, 21, 2, 2), (700, 40, 15, 7), (4097, 1023, 2, 3), (4097, 1024, 2, 3), (4097, 1025, 2, 3),
+    (40_000, 30, 540, 2), (40_000, 30, 550, 2), (65_536, 300, 50, 3), (65_537, 300, 50, 2),
+])
+@pytest.mark.parametrize("directed", [False, True])
+def test_extraction_in_one_workgroup_and_past_its_limits(num_nodes, first, second, hops, directed):
+    from synth.workloads import Workload
+    say(f"extract {num_nodes} {first} {second} hops={hops} directed={directed}")
+    rng = np.random.default_rng(num_nodes + first)
+    ids = rng.permutation(num_nodes)
+    kids = np.arange(1, 1 + first)
+    leaves = np.arange(1 + first, min(1 + first * (1 + second), num_nodes))
+    parent = np.concatenate([np.zeros(first, np.int64), 1 + (leaves - 1 - first) // max(second, 1)])
+    child = np.concatenate([kids, leaves])
+    more = rng.integers(0, num_nodes, (num_nodes // 8, 2))        # within the leaves and the rest of the graph
+    more = more[(more.min(axis=1) > first) & (more[:, 0] != more[:, 1])]
+    key = np.unique(np.minimum(np.r_[parent, more[:, 0]], np.r_[child, more[:, 1]]) * num_nodes +
+                    np.maximum(np.r_[parent, more[:, 0]], np.r_[child, more[:, 1]]))
+    rp, ci = csr_from_undirected_edges(num_nodes, ids[key // num_nodes], ids[key % num_nodes])
+    w = Workload("ball", num_nodes, rp, ci, rng.standard_normal((num_nodes, 4), dtype=np.float32), (4, 3, 2),
+                 [rng.standard_normal((4, 3)).astype(np.float32), rng.standard_normal((3, 2)).astype(np.float32)],
+                 [int(ids[0])], 16, 1, "gram_chol")
+    ctx = make_context(w)
+    for target in (int(ids[0]), int(ids[-1])):
+        cg, _ = _check_extraction(ctx, w, target, hops, directed)
+        ctx.cgraph_free(cg)
+    ctx.close()
+
+
 def test_malformed_graphs_are_rejected():
     from paper_2506_22668_amd import Context, DistShapError, DS_EINVAL, Options
     say("graph validation")
