@@ -62,13 +62,14 @@ __device__ __forceinline__ short bf16_bits(float x) {
   return (short)(u >> 16);
 }
 
+template <int WAVES>
 __device__ __forceinline__ int block_sum_int(int v, int* sh) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
   int t = 0;
 #pragma unroll
-  for (int i = 0; i < kWaves; ++i) t += sh[i];
+  for (int i = 0; i < WAVES; ++i) t += sh[i];
   __syncthreads();
   return t;
 }
@@ -81,6 +82,7 @@ __device__ __forceinline__ float readlane_f(float v, int l) {
 // dst[t, :] = rs[t] * ( sum_{active e in row t} rs[col e] * src[col e, :] + rs[t] * src[t, :] ) (+bias, ReLU)
 // One wave per row; lanes hold features; the 64 entries of a chunk test their mask
 // bits together and the set bits of the ballot are walked in order.
+template <int WAVES>
 __device__ __forceinline__ void aggregate_rows(const EvalArgs& a, const uint64_t* z, const float* rs,
                                                const float* src, int stride, int rows, int width,
                                                float* dst, const float* bias, bool relu, float* part) {
@@ -90,14 +92,14 @@ __device__ __forceinline__ void aggregate_rows(const EvalArgs& a, const uint64_t
     // a long row (a hub) is shared by all waves of the workgroup, 64 entries at a time each, and its
     // partial sums meet in LDS; short rows go to one wave each
     const bool coop = e1 - e0 > 2 * 64;
-    const int owner = t % kWaves;
+    const int owner = t % WAVES;
     if (!coop && owner != wave) continue;
     const float rst = rs[t];
     for (int f0 = 0; f0 < width; f0 += 256) {
       const int f = f0 + lane;
       float acc0 = 0.f, acc1 = 0.f, acc2 = 0.f, acc3 = 0.f;
       const bool h0 = f < width, h1 = f + 64 < width, h2 = f + 128 < width, h3 = f + 192 < width;
-      for (int base = e0 + (coop ? wave * 64 : 0); base < e1; base += (coop ? kWaves * 64 : 64)) {
+      for (int base = e0 + (coop ? wave * 64 : 0); base < e1; base += (coop ? WAVES * 64 : 64)) {
         const int e = base + lane;
         int srcn = 0;
         float coef = 0.f;
@@ -149,7 +151,7 @@ __device__ __forceinline__ void aggregate_rows(const EvalArgs& a, const uint64_t
         if (wave == owner) {
           acc0 = acc1 = acc2 = acc3 = 0.f;
 #pragma unroll
-          for (int w = 0; w < kWaves; ++w) {  // fixed order: the sum does not depend on timing
+          for (int w = 0; w < WAVES; ++w) {  // fixed order: the sum does not depend on timing
             const float* o = part + w * 256 + lane;
             acc0 += o[0];
             acc1 += o[64];
@@ -176,11 +178,12 @@ __device__ __forceinline__ void aggregate_rows(const EvalArgs& a, const uint64_t
 // Prediction": the |V_c| d^2 term), on the matrix cores: a wave takes a 32-row x 32-column tile of the result,
 // v_mfma_f32_32x32x2f32 with lane l supplying q[row l%32][i l/32] and W[i l/32][column l%32]; in the bf16 configuration
 // both operands are rounded to bfloat16 (nearest even) and v_mfma_f32_32x32x8bf16_1k accumulates in fp32.
+template <int WAVES>
 __device__ __forceinline__ void transform_rows(const float* q, int rows, int din, int dout, const float* Wm,
                                                const float* bias, bool relu, bool bf16, float* dst) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31, half = lane >> 5;
   const int tn = (dout + 31) / 32, tm = (rows + 31) / 32;
-  for (int tile = wave; tile < tm * tn; tile += kWaves) {
+  for (int tile = wave; tile < tm * tn; tile += WAVES) {
     const int m0 = (tile / tn) * 32, n0 = (tile - (tile / tn) * tn) * 32;
     const int am = m0 + r, bn = n0 + r;
     const bool aok = am < rows, bok = bn < dout;
@@ -226,8 +229,11 @@ __device__ __forceinline__ void transform_rows(const float* q, int rows, int din
   }
 }
 
-template <bool RS_LDS, bool BUF_LDS>
-__global__ __launch_bounds__(kThreads) void masked_gcn_eval_kernel(EvalArgs a) {
+// THREADS: 256, or 1,024 where there is at most one coalition per compute unit (the predicted class above all). A row is a chain of
+// latencies and the rows are dealt to the waves, so that what matters then is how many there are (1,010 players: 80 -> 53 us).
+template <bool RS_LDS, bool BUF_LDS, int THREADS>
+__global__ __launch_bounds__(THREADS) void masked_gcn_eval_kernel(EvalArgs a) {
+  constexpr int WAVES = THREADS / 64;
   extern __shared__ float smem[];
   int* red = (int*)smem;  // 16 ints of reduction scratch, then the per-wave partial sums of shared rows
   float* part = smem + 16;
@@ -235,7 +241,7 @@ __global__ __launch_bounds__(kThreads) void masked_gcn_eval_kernel(EvalArgs a) {
   float* bufA;
   float* bufB;
   {
-    float* lds = smem + 16 + kWaves * 256;
+    float* lds = smem + 16 + WAVES * 256;
     float* g = a.gws + (size_t)blockIdx.x * a.gws_stride;
     if (RS_LDS) { rs = lds; lds += a.V; } else { rs = g; g += a.V; }
     if (BUF_LDS) { bufA = lds; bufB = lds + a.bufA_floats; } else { bufA = g; bufB = g + a.bufA_floats; }
@@ -248,28 +254,28 @@ __global__ __launch_bounds__(kThreads) void masked_gcn_eval_kernel(EvalArgs a) {
     const uint64_t* z = a.Z + row * W;
     // coalition size decides which polarity is cheaper to walk
     int c = 0;
-    for (int64_t w0 = tid; w0 < W; w0 += 8 * kThreads) {  // eight independent loads per thread and step
+    for (int64_t w0 = tid; w0 < W; w0 += 8 * THREADS) {  // eight independent loads per thread and step
       uint64_t v[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        const int64_t w = w0 + (int64_t)q * kThreads;
+        const int64_t w = w0 + (int64_t)q * THREADS;
         v[q] = w < W ? (z[w] & (w == W - 1 ? tail_mask : ~0ull)) : 0ull;
       }
 #pragma unroll
       for (int q = 0; q < 8; ++q) c += __popcll(v[q]);
     }
-    const int total = block_sum_int(c, red);
+    const int total = block_sum_int<WAVES>(c, red);
     const bool dense = 2 * (int64_t)total > a.n;
     const int step = dense ? -1 : 1;
     int* deg = (int*)rs;
-    for (int i = tid; i < a.V; i += kThreads) deg[i] = dense ? (a.row_ptr[i + 1] - a.row_ptr[i] + 1) : 1;
+    for (int i = tid; i < a.V; i += THREADS) deg[i] = dense ? (a.row_ptr[i + 1] - a.row_ptr[i] + 1) : 1;
     __syncthreads();
     // every thread walks four words at a time, so that four end-point look-ups are in flight
-    for (int64_t w0 = tid; w0 < W; w0 += 4 * kThreads) {
+    for (int64_t w0 = tid; w0 < W; w0 += 4 * THREADS) {
       uint64_t bits[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int64_t w = w0 + (int64_t)q * kThreads;
+        const int64_t w = w0 + (int64_t)q * THREADS;
         uint64_t b = 0ull;
         if (w < W) {
           b = dense ? ~z[w] : z[w];
@@ -283,7 +289,7 @@ __global__ __launch_bounds__(kThreads) void masked_gcn_eval_kernel(EvalArgs a) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           live[q] = bits[q] != 0ull;
-          const int64_t p = (w0 + (int64_t)q * kThreads) * 64 + (live[q] ? __ffsll((long long)bits[q]) - 1 : 0);
+          const int64_t p = (w0 + (int64_t)q * THREADS) * 64 + (live[q] ? __ffsll((long long)bits[q]) - 1 : 0);
           e[q] = live[q] ? a.pl[p] : make_int2(0, 0);
           bits[q] &= bits[q] - 1;
         }
@@ -297,19 +303,19 @@ __global__ __launch_bounds__(kThreads) void masked_gcn_eval_kernel(EvalArgs a) {
       }
     }
     __syncthreads();
-    for (int i = tid; i < a.V; i += kThreads) {
+    for (int i = tid; i < a.V; i += THREADS) {
       const float d = (float)deg[i];
       rs[i] = 1.0f / sqrtf(d);
     }
     __syncthreads();
 
     // layer 1: aggregate the shared product P = X_c W_1
-    aggregate_rows(a, z, rs, a.P, a.dims[1], a.rows_out[1], a.dims[1], bufA, a.bias[0], a.L > 1, part);
+    aggregate_rows<WAVES>(a, z, rs, a.P, a.dims[1], a.rows_out[1], a.dims[1], bufA, a.bias[0], a.L > 1, part);
     __syncthreads();
     for (int l = 2; l <= a.L; ++l) {
-      aggregate_rows(a, z, rs, bufA, a.dims[l - 1], a.rows_out[l], a.dims[l - 1], bufB, nullptr, false, part);
+      aggregate_rows<WAVES>(a, z, rs, bufA, a.dims[l - 1], a.rows_out[l], a.dims[l - 1], bufB, nullptr, false, part);
       __syncthreads();
-      transform_rows(bufB, a.rows_out[l], a.dims[l - 1], a.dims[l], a.Wl[l - 1], a.bias[l - 1], l < a.L,
+      transform_rows<WAVES>(bufB, a.rows_out[l], a.dims[l - 1], a.dims[l], a.Wl[l - 1], a.bias[l - 1], l < a.L,
                      a.bf16 != 0, bufA);
       __syncthreads();
     }
@@ -1639,8 +1645,11 @@ __global__ __launch_bounds__(kSThreads) void stream_degrees_kernel(StreamArgs a)
 // MFMA 32x32x2 f32: lane l supplies A[row l%32][k l/32] and B[k l/32][col l%32]; the
 // accumulator register i of lane l is C[8*(i/4) + 4*(l/32) + i%4][l%32].
 // BF16: 32x32x8 bf16, lane l supplies k = 4*(l/32) .. +3.
+// Few tiles and a short loop: latency. Operands are requested 32 columns of A ahead, without branches (past the end from the last
+// row or column; what does not belong is multiplied as zero or not stored). 608 x 128 x 64: 28 -> 18 us.
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void first_transform_kernel(const float* A, const float* B, float* C, int M, int K, int Nn) {
+  constexpr int kStep = 32;
   const int lane = threadIdx.x & 63;
   const int wave_global = blockIdx.x * kWaves + (threadIdx.x >> 6);
   const int tiles_n = (Nn + 31) / 32;
@@ -1649,28 +1658,58 @@ __global__ __launch_bounds__(kThreads) void first_transform_kernel(const float* 
   const int m0 = (wave_global / tiles_n) * 32, n0 = (wave_global % tiles_n) * 32;
   const int r = lane & 31, half = lane >> 5;
   float16_t acc;
+#pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  const int am = m0 + r, bn = n0 + r;
-  if (BF16) {
-    for (int k0 = 0; k0 < K; k0 += 8) {
-      short4_t av, bv;
-      for (int j = 0; j < 4; ++j) {
-        const int kk = k0 + 4 * half + j;
-        const float x = (am < M && kk < K) ? A[(size_t)am * K + kk] : 0.f;
-        const float w = (bn < Nn && kk < K) ? B[(size_t)kk * Nn + bn] : 0.f;
-        av[j] = bf16_bits(x);
-        bv[j] = bf16_bits(w);
+  const int bn = n0 + r;
+  const float* const ap = A + (size_t)(m0 + r < M ? m0 + r : M - 1) * K;
+  const float* const bp = B + (bn < Nn ? bn : Nn - 1);
+  struct Ops {
+    float a[kStep / 2], b[kStep / 2];
+  };
+  // this lane's k of operand i of the step at k0
+  auto column = [&](int k0, int i) { return k0 + (BF16 ? 8 * (i >> 2) + 4 * half + (i & 3) : 2 * i + half); };
+  auto load = [&](Ops& o, int k0) {
+#pragma unroll
+    for (int i = 0; i < kStep / 2; ++i) {
+      const int kk = column(k0, i), kc = kk < K ? kk : K - 1;
+      o.a[i] = ap[kc];
+      o.b[i] = bp[(size_t)kc * Nn];
+    }
+  };
+  auto use = [&](const Ops& o, int k0) {
+#pragma unroll
+    for (int s = 0; s < kStep / 8; ++s) {
+      float x[4], w[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool ok = column(k0, 4 * s + u) < K;
+        x[u] = ok ? o.a[4 * s + u] : 0.f;
+        w[u] = ok ? o.b[4 * s + u] : 0.f;
       }
-      acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
+      if (BF16) {
+        short4_t av, bv;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          av[u] = bf16_bits(x[u]);
+          bv[u] = bf16_bits(w[u]);
+        }
+        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u], w[u], acc, 0, 0, 0);
+      }
     }
-  } else {
-    for (int k0 = 0; k0 < K; k0 += 2) {
-      const int kk = k0 + half;
-      const float x = (am < M && kk < K) ? A[(size_t)am * K + kk] : 0.f;
-      const float w = (bn < Nn && kk < K) ? B[(size_t)kk * Nn + bn] : 0.f;
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, w, acc, 0, 0, 0);
-    }
+  };
+  Ops o0, o1;
+  load(o0, 0);
+  for (int k0 = 0; k0 < K; k0 += 2 * kStep) {
+    load(o1, k0 + kStep);
+    use(o0, k0);
+    if (k0 + kStep >= K) break;
+    load(o0, k0 + 2 * kStep);
+    use(o1, k0 + kStep);
   }
+#pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int row = m0 + 8 * (i / 4) + 4 * half + (i % 4);
     if (row < M && bn < Nn) C[(size_t)row * Nn + bn] = acc[i];
@@ -1760,22 +1799,20 @@ int grid_for(const ds_ctx* ctx, const EvalLayout& lay, int64_t k) {
   return (int)g;
 }
 
+constexpr int kWideThreads = 1024;
+
 int launch_eval(ds_ctx* ctx, const EvalArgs& a, const EvalLayout& lay, int grid) {
-  const void* fn;
-  if (lay.rs_lds && lay.buf_lds) fn = (const void*)masked_gcn_eval_kernel<true, true>;
-  else if (lay.rs_lds) fn = (const void*)masked_gcn_eval_kernel<true, false>;
-  else if (lay.buf_lds) fn = (const void*)masked_gcn_eval_kernel<false, true>;
-  else fn = (const void*)masked_gcn_eval_kernel<false, false>;
-  if (lay.lds_bytes > 48 * 1024)
-    DS_HIP(ctx, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lay.lds_bytes));
-  if (lay.rs_lds && lay.buf_lds)
-    hipLaunchKernelGGL((masked_gcn_eval_kernel<true, true>), dim3(grid), dim3(kThreads), lay.lds_bytes, ctx->stream, a);
-  else if (lay.rs_lds)
-    hipLaunchKernelGGL((masked_gcn_eval_kernel<true, false>), dim3(grid), dim3(kThreads), lay.lds_bytes, ctx->stream, a);
-  else if (lay.buf_lds)
-    hipLaunchKernelGGL((masked_gcn_eval_kernel<false, true>), dim3(grid), dim3(kThreads), lay.lds_bytes, ctx->stream, a);
-  else
-    hipLaunchKernelGGL((masked_gcn_eval_kernel<false, false>), dim3(grid), dim3(kThreads), lay.lds_bytes, ctx->stream, a);
+  const size_t wide_lds = lay.lds_bytes + (size_t)(kWideThreads / 64 - kWaves) * 256 * 4;
+  const bool wide = grid <= ctx->num_cus && wide_lds <= kLdsLimit;
+  void (*const kerns[2][2][2])(EvalArgs) = {   // [rs in LDS][buffers in LDS][wide]
+      {{masked_gcn_eval_kernel<false, false, kThreads>, masked_gcn_eval_kernel<false, false, kWideThreads>},
+       {masked_gcn_eval_kernel<false, true, kThreads>, masked_gcn_eval_kernel<false, true, kWideThreads>}},
+      {{masked_gcn_eval_kernel<true, false, kThreads>, masked_gcn_eval_kernel<true, false, kWideThreads>},
+       {masked_gcn_eval_kernel<true, true, kThreads>, masked_gcn_eval_kernel<true, true, kWideThreads>}}};
+  void (*const kern)(EvalArgs) = kerns[lay.rs_lds][lay.buf_lds][wide];
+  const size_t lds = wide ? wide_lds : lay.lds_bytes;
+  if (lds > 48 * 1024) DS_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(wide ? kWideThreads : kThreads), lds, ctx->stream, a);
   DS_HIP(ctx, hipGetLastError());
   return DS_OK;
 }

@@ -229,6 +229,30 @@ def test_first_transform_matches_matmul(key, dtype, tol):
     ctx.close()
 
 
+# widths on both sides of the kernel's steps of 32 columns (two in flight) and of its tiles; rows that do not fill a tile. A sum of d0
+# products in fp32 is within d0 * 2^-24 of its terms' magnitudes
+@pytest.mark.parametrize("nodes,d0,d1", [(2, 1, 1), (31, 8, 33), (33, 31, 32), (64, 32, 31), (65, 33, 64), (90, 63, 65),
+                                         (40, 64, 5), (40, 65, 97), (33, 97, 3), (129, 128, 33), (70, 130, 40)])
+def test_first_transform_odd_widths(nodes, d0, d1):
+    from synth import csr_from_undirected_edges
+    from paper_2506_22668_amd import Context, Options
+    rng = np.random.default_rng(nodes + d0)
+    rp, ci = csr_from_undirected_edges(nodes, [0] * (nodes - 1), list(range(1, nodes)))
+    X = rng.standard_normal((nodes, d0), dtype=np.float32)
+    W1 = rng.standard_normal((d0, d1), dtype=np.float32)
+    say(f"first transform {nodes} x {d0} x {d1}")
+    ctx = Context("cuda:0")
+    ctx.set_graph(rp, ci)
+    ctx.set_features(X)
+    ctx.set_gcn([W1])
+    cg = ctx.extract(0, Options(hops=1))
+    P = ctx.cgraph_first_transform(cg).cpu().numpy().astype(np.float64)
+    bound = d0 * 2.0 ** -24 * (np.abs(X).astype(np.float64) @ np.abs(W1).astype(np.float64)) + 1e-30
+    assert (np.abs(P - X.astype(np.float64) @ W1.astype(np.float64)) <= bound).all()
+    ctx.cgraph_free(cg)
+    ctx.close()
+
+
 # ---------------------------------------------------------------- masked inference
 def _eval_case(w, hops, directed, score, biases, rows, rng, tol=1e-5, layers=None):
     from paper_2506_22668_amd import Options
