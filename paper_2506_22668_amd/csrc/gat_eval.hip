@@ -53,12 +53,26 @@ struct GatArgs {
   const uint64_t* Zt;   // with z2_lanes: the transposed masks, word blk of player p = its bits in the block's coalitions
   int64_t KW;
   const int32_t* h1_bad; // device flag: non-zero means h1 (z2) was not produced (attention range too wide)
+  int32_t waves_alone;  // masked_gat_last_layer_kernel without z2: waves of a workgroup that take a coalition each,
+  int32_t wave_lds;     // bytes of LDS of each,
+  int64_t units;        // and how many there are of them in all (their global scratch)
 };
 
 __device__ __forceinline__ int readlane_i(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
 
 __device__ __forceinline__ float lrelu(float x, float slope) { return x > 0.f ? x : slope * x; }
 __device__ __forceinline__ float elu(float x) { return x > 0.f ? x : expm1f(x); }
+
+// between lanes of the threads that share a coalition: a workgroup of WAVES waves, or a wave that shares a workgroup with others
+template <int WAVES>
+__device__ __forceinline__ void coalition_sync() {
+  if (WAVES > 1) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
 
 // Attention aggregation of rows [0, rows) for one layer.
 //   zsrc [.. x zw]: transformed rows; ssrc/sdst [.. x H]: attention scalars of the neighbour / receiver role.
@@ -71,7 +85,7 @@ __device__ __forceinline__ void gat_aggregate_nq(const GatArgs& a, const uint64_
                                               const float* ssrc, const float* sdst, int H, int F, int rows,
                                               float* dst, const float* bias, bool concat, float* part) {
   constexpr int UNROLL = WAVES == 1 ? 4 : kUnroll;  // the one-wave variant trades gather depth for occupancy
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = WAVES == 1 ? 0 : threadIdx.x >> 6;
   for (int t = 0; t < rows; ++t) {
     const int e0 = a.row_ptr[t], e1 = a.row_ptr[t + 1];
     const bool coop = e1 - e0 > 2 * 64;
@@ -152,7 +166,7 @@ __device__ __forceinline__ void gat_aggregate_nq(const GatArgs& a, const uint64_
           mine[kColsPerPass + 64 * q] = l[q];
           mine[2 * kColsPerPass + 64 * q] = acc[q];
         }
-        __syncthreads();
+        coalition_sync<WAVES>();
         if (wave == owner) {
 #pragma unroll
           for (int q = 0; q < NQ; ++q) {
@@ -183,7 +197,7 @@ __device__ __forceinline__ void gat_aggregate_nq(const GatArgs& a, const uint64_
           dst[(size_t)t * zw + f] = v;
         }
       }
-      if (coop) __syncthreads();
+      if (coop) coalition_sync<WAVES>();
     }
   }
 }
@@ -200,21 +214,20 @@ __device__ __forceinline__ void gat_aggregate(const GatArgs& a, const uint64_t* 
 }
 
 // THREADS = 256: a workgroup per coalition (every layer here); THREADS = 64: a wave per coalition, used when
-// layer 1 comes precomputed and only the small later layers are left.
+// layer 1 comes precomputed and only the small later layers are left. Unit `unit` of `units` takes the coalitions unit,
+// unit + units, ... in its own LDS at `part`.
 template <int THREADS>
-__device__ __forceinline__ void masked_gat_eval_body(const GatArgs& a) {
-  constexpr int WAVES = THREADS / 64;
-  extern __shared__ float smem[];
-  float* part = smem;  // [WAVES][3][kColsPerPass]
-  float* buf = a.buf_lds ? smem + WAVES * 3 * kColsPerPass : a.gws + (size_t)blockIdx.x * a.gws_stride;
+__device__ __forceinline__ void masked_gat_eval_body(const GatArgs& a, float* part, int64_t unit, int64_t units) {
+  constexpr int WAVES = THREADS / 64;   // part: [WAVES][3][kColsPerPass], then the buffers
+  float* buf = a.buf_lds ? part + WAVES * 3 * kColsPerPass : a.gws + (size_t)unit * a.gws_stride;
   float* bufH = buf;
   float* bufZ = bufH + a.bufH;
   float* bufS = bufZ + a.bufZ;
   float* bufT = bufS + a.bufS;
-  const int tid = threadIdx.x;
+  const int tid = THREADS == 64 ? threadIdx.x & 63 : threadIdx.x;
   const int L = a.L;
 
-  for (int64_t row = blockIdx.x; row < a.k; row += gridDim.x) {
+  for (int64_t row = unit; row < a.k; row += units) {
     const uint64_t* z = a.Z + row * a.W;
     // layer 1: already produced for all coalitions on the matrix cores, or aggregated here
     const bool have1 = a.h1_bad != nullptr && *a.h1_bad == 0;
@@ -224,13 +237,13 @@ __device__ __forceinline__ void masked_gat_eval_body(const GatArgs& a) {
       const int cnt = a.rows_out[1] * a.dims[1];
       const float* src = a.h1 + (size_t)row * cnt;
       for (int i = tid; i < cnt; i += THREADS) bufH[i] = src[i];
-      __syncthreads();
+      coalition_sync<WAVES>();
     } else {
       const int H = a.heads[0];
       const bool last = L == 1;
       gat_aggregate<WAVES>(a, z, a.P, a.zw[0], a.att1, a.att1 + (size_t)a.V * H, H, a.fh[0], a.rows_out[1],
                     last ? bufT : bufH, a.bias[0], !last, part);
-      __syncthreads();
+      coalition_sync<WAVES>();
     }
     for (int l = 2; l <= L; ++l) {
       const int rin = a.rows_out[l - 1], din = a.dims[l - 1], zw = a.zw[l - 1], H = a.heads[l - 1], F = a.fh[l - 1];
@@ -246,7 +259,7 @@ __device__ __forceinline__ void masked_gat_eval_body(const GatArgs& a) {
         for (int i = 0; i < din; ++i) s += hr[i] * Wm[(size_t)i * zw + j];
         bufZ[idx] = s;
       }
-      __syncthreads();
+      coalition_sync<WAVES>();
       for (int idx = tid; idx < rin * H; idx += THREADS) {
         const int r = idx / H, h = idx - r * H;
         const float* zr = bufZ + (size_t)r * zw + h * F;
@@ -259,11 +272,11 @@ __device__ __forceinline__ void masked_gat_eval_body(const GatArgs& a) {
         bufS[idx] = s0;
         bufS[rin * H + idx] = s1;
       }
-      __syncthreads();
+      coalition_sync<WAVES>();
       const bool last = l == L;
       gat_aggregate<WAVES>(a, z, bufZ, zw, bufS, bufS + rin * H, H, F, a.rows_out[l], last ? bufT : bufH, a.bias[l - 1],
                     !last, part);
-      __syncthreads();
+      coalition_sync<WAVES>();
     }
     // last layer: average the heads of the target's row, add the bias
     {
@@ -275,7 +288,7 @@ __device__ __forceinline__ void masked_gat_eval_body(const GatArgs& a) {
         if (a.bias[L - 1]) s += a.bias[L - 1][c];
         bufH[c] = s;
       }
-      __syncthreads();
+      coalition_sync<WAVES>();
     }
     if (tid < 64) {
       const int C = a.dims[L];
@@ -292,18 +305,20 @@ __device__ __forceinline__ void masked_gat_eval_body(const GatArgs& a) {
       if (a.logits_out)
         for (int c = tid; c < C; c += 64) a.logits_out[row * C + c] = bufH[c];
     }
-    __syncthreads();
+    coalition_sync<WAVES>();
   }
 }
 
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void masked_gat_eval_kernel(GatArgs a) {
-  masked_gat_eval_body<THREADS>(a);
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_gat[];
+  masked_gat_eval_body<THREADS>(a, (float*)smem_gat, blockIdx.x, gridDim.x);
 }
 
 // the wave-per-coalition variant lives on latency hiding: ask for at least six waves per SIMD
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 8))) void masked_gat_eval_wave_kernel(GatArgs a) {
-  masked_gat_eval_body<64>(a);
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_gat[];
+  masked_gat_eval_body<64>(a, (float*)smem_gat, blockIdx.x, gridDim.x);
 }
 
 // The last layer of a two-layer model on the rows that layer 1's kernel has already transformed (z2_lanes): only the
@@ -311,17 +326,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 8))) void
 // mask bits are one word of the transposed masks; the four waves of a workgroup take the entries of the target's row in
 // turn (a wave alone would be a chain of one L2 latency per entry) and wave 0 merges their running soft-maxima in wave
 // order. A wave per coalition with lanes over columns had ten of 64 lanes at work on ten classes: 20,000 coalitions, 999
-// players 69 us, now 12. F: columns of a head, at most NC. Raised flag: layer 1 was not produced, the general body does all.
+// players 69 us, now 12. F: columns of a head, at most NC. Raised flag: layer 1 was not produced, and waves with a coalition each do
+// both layers, no fewer of them than masked_gat_eval_wave_kernel would have (1,000 coalitions: 192 us either way).
 template <int NC>
-__global__ __launch_bounds__(kThreads) void masked_gat_last_layer_kernel(GatArgs a) {
+__global__ __launch_bounds__(kThreads, NC == 32 ? 3 : 4) void masked_gat_last_layer_kernel(GatArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_gat[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (*a.h1_bad != 0) {
-    masked_gat_eval_body<kThreads>(a);
+    const int64_t unit = (int64_t)blockIdx.x * a.waves_alone + wave;
+    if (wave < a.waves_alone && unit < a.units)
+      masked_gat_eval_body<64>(a, (float*)(smem_gat + (size_t)wave * a.wave_lds), unit, a.units);
     return;
   }
-  __shared__ float part[kWaves - 1][NC + 2][64];
-  __shared__ float att[2][32 * NC];   // attention vectors, NC to a head, zero from F on
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int H = a.heads[1], F = a.fh[1], zw = a.zw[1], R1 = a.rows_out[1];   // (H F <= 32)
+  float (*const part)[NC + 2][64] = (float (*)[NC + 2][64])smem_gat;   // [kWaves - 1], then
+  float (*const att)[32 * NC] = (float (*)[32 * NC])(part + (kWaves - 1));   // [2]: attention vectors, NC to a head, zero from F on
+  const int H = NC == 32 ? 1 : a.heads[1], F = a.fh[1], zw = a.zw[1], R1 = a.rows_out[1];   // (H F <= 32; 17 columns leave one head)
   for (int i = threadIdx.x; i < H * NC; i += kThreads) {
     const int h = i / NC, c = i - h * NC;
     att[0][i] = c < F ? a.asrc[1][h * F + c] : 0.f;
@@ -888,7 +907,7 @@ int gat_launch(ds_ctx* ctx, const GatArgs& a, const GatLayout& g, int grid) {
 
 size_t ds_gat_eval_arena_bytes(ds_ctx* ctx, const ds_cgraph* cg, int64_t k) {
   const GatL1Layout q = gat_l1_layout(ctx, cg, k);
-  const GatLayout g = gat_layout(ctx, cg, k > 1 ? k : 1, q.use && !q.last ? 64 : kThreads);
+  const GatLayout g = gat_layout(ctx, cg, k > 1 ? k : 1, q.use ? 64 : kThreads);
   const GatLayout g1 = gat_layout(ctx, cg, 1);
   const size_t W = (cg->info.num_players + 63) / 64;
   return (q.use ? ds_align(q.az_bytes) + ds_align(q.h1_bytes) + ds_align(q.zt_bytes + 8) + ds_align((size_t)q.R1 * 32 * 4) + 1024 : 0) +
@@ -938,7 +957,7 @@ int ds_gat_eval_impl(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, i
   DS_TRY(ds_gat_prepare_model(ctx, cg));
   if (k <= 0) return DS_OK;
   const GatL1Layout q = gat_l1_layout(ctx, cg, k);
-  const GatLayout g = gat_layout(ctx, cg, k, q.use && !q.last ? 64 : kThreads);
+  const GatLayout g = gat_layout(ctx, cg, k, q.use ? 64 : kThreads);
   float* gws = nullptr;
   if (g.gws_floats) {
     gws = (float*)ds_arena_alloc(ctx, (size_t)g.gws_floats * 4 * g.grid);
@@ -998,14 +1017,29 @@ int ds_gat_eval_impl(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, i
     DS_HIP(ctx, hipGetLastError());
   }
   if (q.last) {
-    const int F = a.fh[1];
-    void (*const kern)(GatArgs) = F <= 8    ? masked_gat_last_layer_kernel<8>
-                                  : F <= 16 ? masked_gat_last_layer_kernel<16>
-                                            : masked_gat_last_layer_kernel<32>;
-    if (g.lds_bytes > 40 * 1024)   // (the general body's buffers, beside the kernel's own)
-      DS_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_bytes));
-    // (the grid also bounds the general body's scratch)
-    hipLaunchKernelGGL(kern, dim3((unsigned)(q.KW < g.grid ? q.KW : g.grid)), dim3(kThreads), g.lds_bytes, ctx->stream, a);
+    const int F = a.fh[1], nc = F <= 8 ? 8 : F <= 16 ? 16 : 32;
+    void (*const kern)(GatArgs) = nc == 8    ? masked_gat_last_layer_kernel<8>
+                                  : nc == 16 ? masked_gat_last_layer_kernel<16>
+                                             : masked_gat_last_layer_kernel<32>;
+    // should layer 1 not have been produced, each of `waves_alone` waves of a workgroup takes whole coalitions: as many of them
+    // resident as in masked_gat_eval_wave_kernel, or what LDS holds
+    const size_t own = ((size_t)(kWaves - 1) * (nc + 2) * 64 + 2 * 32 * nc) * 4, each = (g.lds_bytes + 15) & ~(size_t)15;
+    size_t lds = 0;
+    int most = 0;
+    for (int w = kWaves; w >= 1; w /= 2) {
+      const size_t need = std::max(own, each * w);
+      const int resident = (int)std::min<size_t>((160 * 1024 - 512) / need, 2048 / kThreads) * w;
+      if (resident > most) {
+        most = resident;
+        lds = need;
+        a.waves_alone = w;
+      }
+    }
+    a.wave_lds = (int32_t)each;
+    a.units = g.grid;
+    const int64_t alone = (a.units + a.waves_alone - 1) / a.waves_alone;   // workgroups
+    if (lds > 48 * 1024) DS_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(kern, dim3((unsigned)std::max(std::min(q.KW, 8 * (int64_t)ctx->num_cus), alone)), dim3(kThreads), lds, ctx->stream, a);
     DS_HIP(ctx, hipGetLastError());
   } else {
     DS_TRY(gat_launch(ctx, a, g, g.grid));

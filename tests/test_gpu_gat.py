@@ -317,3 +317,73 @@ def test_gat_batch_equals_single_explanations_and_fidelity_matches_oracle():
     assert np.abs(np.array(plus) - rp).max() <= 2e-5 and np.abs(np.array(minus) - rm).max() <= 2e-5
     ctx.cgraph_free(cg)
     ctx.close()
+
+
+def _star_of_stars(degree, d0, rng):
+    """A target (node 0) with `degree` neighbours, three leaves on each, and a ring through the neighbours."""
+    from synth import csr_from_undirected_edges
+    from synth.workloads import Workload
+    kids = np.arange(1, degree + 1)
+    leaves = np.arange(degree + 1, 4 * degree + 1)
+    src = np.concatenate([np.zeros(degree, np.int64), np.repeat(kids, 3), kids[:-1]])
+    dst = np.concatenate([kids, leaves, kids[1:]])
+    N = 4 * degree + 1
+    rp, ci = csr_from_undirected_edges(N, src, dst)
+    return Workload("star of stars", N, rp, ci, rng.standard_normal((N, d0), dtype=np.float32), (d0, 0), [], [0], 16, 1, "gram_chol")
+
+
+def _ms(call, repeats=9):
+    call()
+    start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    times = []
+    for _ in range(repeats):
+        torch.cuda.synchronize()
+        start.record()
+        call()
+        torch.cuda.synchronize()
+        end.record()
+        end.synchronize()
+        times.append(start.elapsed_time(end))
+    return sorted(times)[repeats // 2]
+
+
+def _one_call_and_parts(degree, heads, widths, scale, rows, tol):
+    """Values of `rows` coalitions in one call and in calls of fewer than 256, which take the per-coalition kernel for every layer;
+    the first 40 against the oracle. Returns the times (ms) of the one call and of all parts."""
+    from paper_2506_22668_amd import Options
+    rng = np.random.default_rng(degree + rows)
+    w = _star_of_stars(degree, 16, rng)
+    model = _gat_model(rng, 16, heads, widths)
+    model["a_src"] = [a * scale for a in model["a_src"]]
+    model["a_dst"] = [a * scale for a in model["a_dst"]]
+    biases = [0.1 * rng.standard_normal(o).astype(np.float32) for o in (heads[0] * widths[0], widths[1])]
+    ctx = _context(w, model, biases)
+    cg = ctx.extract(0, Options(hops=2))
+    cgo = compgraph.extract(w.row_ptr, w.col, 0, 2)
+    bits = _random_rows(cgo["num_players"], rows, rng)
+    Z = torch.from_numpy(sampling.pack_rows(bits).view(np.int64)).cuda()
+    cuts = [Z[i:i + 250].contiguous() for i in range(0, rows, 250)]
+    y, pc = ctx.eval(cg, Z, 1)
+    parts = torch.cat([ctx.eval(cg, c, 1)[0] for c in cuts])
+    f = ogat.ValueFunction(cgo, w.features, dict(model, bias=biases), "logit")
+    ref = f.batch(bits[:40])
+    scale = max(1.0, np.abs(ref).max())
+    assert pc == f.pred_class and np.abs(y[:40].cpu().numpy() - ref).max() <= tol * scale
+    assert (y - parts).abs().max().item() <= tol * scale   # both within it of the same value, about
+    one, all_parts = _ms(lambda: ctx.eval(cg, Z, 1)), _ms(lambda: [ctx.eval(cg, c, 1) for c in cuts])
+    say(f"  one call {one * 1e3:.0f} us, in parts {all_parts * 1e3:.0f} us")
+    ctx.cgraph_free(cg)
+    ctx.close()
+    return one, all_parts
+
+
+# no layer-1 rows from the matrix cores (attention range too wide): the coalitions spread over the whole GPU all the same. Rows of the
+# target that a wave holds in LDS (four, two and one to a workgroup) and that it does not; more coalitions than waves; the
+# widest last layer. In parts of 250 a workgroup of four waves takes a coalition, in the one call a wave: four times as long for the same
+# number of coalitions at a time, and the parts come one after the other.
+@pytest.mark.parametrize("degree,heads,widths,rows", [(20, (4, 2), (8, 6), 1000), (60, (4, 1), (8, 17), 700), (250, (4, 2), (8, 6), 600),
+                                                      (500, (4, 1), (8, 12), 300), (3, (2, 1), (4, 3), 9001)])
+def test_masked_gat_wide_attention_range_uses_the_whole_gpu(degree, heads, widths, rows):
+    say(f"gat wide range degree={degree} heads={heads} widths={widths} rows={rows}")
+    one, parts = _one_call_and_parts(degree, heads, widths, 60.0, rows, 1e-4)
+    assert one <= 4.0 * parts
