@@ -382,23 +382,34 @@ __global__ __launch_bounds__(kThreads, NC == 32 ? 3 : 4) void masked_gat_last_la
 #pragma unroll
         for (int c = 0; c < NC; ++c) acc[c] = z[c];
       }
+      // entry -> node and player -> row and mask word: the entry's own pair is requested two steps ahead, what it names one
+      // (past the end the last entry again)
       int e = wave;
-      if (e < e1) load(a.col[e], z);
-      for (; e < e1; e += kWaves) {
-        const uint64_t word = a.Zt[(size_t)a.eid[e] * a.KW + blk];
-        if (e + kWaves < e1) load(a.col[e + kWaves], zn);
-        const float ee = lrelu(dot(as, z) + sd, a.slope);
-        if ((word >> lane) & 1ull) {
-          // of the two factors exp(m - max) and exp(e - max) one is always 1
-          const float d = ee - m, x = __expf(-fabsf(d));
-          const float sc = d > 0.f ? x : 1.f, pe = d > 0.f ? 1.f : x;
-          l = l * sc + pe;
+      if (e < e1) {
+        auto at = [&](int i) { return i < e1 ? i : e1 - 1; };
+        auto word_of = [&](int player) { return a.Zt[(size_t)player * a.KW + blk]; };
+        load(a.col[e], z);
+        uint64_t word = word_of(a.eid[e]);
+        int node = a.col[at(e + kWaves)], player = a.eid[at(e + kWaves)];
+        for (; e < e1; e += kWaves) {
+          load(node, zn);
+          const uint64_t word_n = word_of(player);
+          node = a.col[at(e + 2 * kWaves)];
+          player = a.eid[at(e + 2 * kWaves)];
+          const float ee = lrelu(dot(as, z) + sd, a.slope);
+          if ((word >> lane) & 1ull) {
+            // of the two factors exp(m - max) and exp(e - max) one is always 1
+            const float d = ee - m, x = __expf(-fabsf(d));
+            const float sc = d > 0.f ? x : 1.f, pe = d > 0.f ? 1.f : x;
+            l = l * sc + pe;
 #pragma unroll
-          for (int c = 0; c < NC; ++c) acc[c] = acc[c] * sc + pe * z[c];
-          m = fmaxf(m, ee);
+            for (int c = 0; c < NC; ++c) acc[c] = acc[c] * sc + pe * z[c];
+            m = fmaxf(m, ee);
+          }
+          word = word_n;
+#pragma unroll
+          for (int c = 0; c < NC; ++c) z[c] = zn[c];
         }
-#pragma unroll
-        for (int c = 0; c < NC; ++c) z[c] = zn[c];
       }
       if (wave > 0) {
         part[wave - 1][NC][lane] = m;
@@ -840,7 +851,16 @@ GatL1Layout gat_l1_layout(const ds_ctx* ctx, const ds_cgraph* cg, int64_t k) {
   // layer 2's transform rides along where its columns fit one matrix-core tile and its weights LDS, and where what it
   // hands on is no larger than the first layer's output, by which the workspace was admitted above
   q.fuse = ctx->gat.zw[1] <= 32 && q.zwr <= 256 && ctx->gat.zw[1] <= ctx->gat.zw[0];
-  q.last = q.fuse && L == 2;
+  // The last layer with a coalition per lane goes through the target's entries once per head, a latency each, however few blocks of
+  // 64 there are. A wave per coalition has all heads at once, but its time grows with the coalitions, the sooner the longer
+  // the target's row is (in LDS its rows leave fewer waves to a compute unit; past LDS they are as many as before). One head: the lanes
+  // are no slower anywhere. More: from the products of coalitions and entries below on. Whole calls, wave / lane: 2 heads, 60 entries, 1,200
+  // coalitions 95 / 93 us, 2,400 118 / 107; 8 heads, 21 entries, 9,600 136 / 133; 100 entries, 1,200 155 / 183, 2,400 211 / 201; 16 heads,
+  // 60 entries, 4,800 200 / 230, 9,600 300 / 257; past LDS: 8 heads, 250 entries, 2,400 283 / 364, 4,800 441 / 411; 32 heads, 500
+  // entries, 1,000 451 / 1,811, 20,000 3,670 / 3,550.
+  const int64_t lh = L == 2 ? ctx->gat.heads[1] : 0, target_entries = cg->ball_entries[0];
+  q.last = q.fuse && L == 2 &&
+           (lh == 1 || k * target_entries >= (gat_layout(ctx, cg, k, 64).buf_lds ? 25000 * (lh + 2) : 15000 * lh * lh));
   if (q.fuse) q.h1_bytes = (size_t)(q.last ? q.KW * 64 : k) * q.R1 * ctx->gat.zw[1] * 4;   // z2 in its place
   q.lds_bytes = (((size_t)2 * (q.E1 + 2) * 8 + 15) & ~(size_t)15) + (q.fuse ? (size_t)q.zwr * 128 : 0) +
                 (size_t)kWaves * (ctx->gat.heads[0] * 33 + 32 * 33) * 4;

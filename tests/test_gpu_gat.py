@@ -349,7 +349,7 @@ def _ms(call, repeats=9):
 
 def _one_call_and_parts(degree, heads, widths, scale, rows, tol):
     """Values of `rows` coalitions in one call and in calls of fewer than 256, which take the per-coalition kernel for every layer;
-    the first 40 against the oracle. Returns the times (ms) of the one call and of all parts."""
+    the first 12 against the oracle. Returns the times (ms) of the one call and of all parts."""
     from paper_2506_22668_amd import Options
     rng = np.random.default_rng(degree + rows)
     w = _star_of_stars(degree, 16, rng)
@@ -366,9 +366,9 @@ def _one_call_and_parts(degree, heads, widths, scale, rows, tol):
     y, pc = ctx.eval(cg, Z, 1)
     parts = torch.cat([ctx.eval(cg, c, 1)[0] for c in cuts])
     f = ogat.ValueFunction(cgo, w.features, dict(model, bias=biases), "logit")
-    ref = f.batch(bits[:40])
+    ref = f.batch(bits[:12])
     scale = max(1.0, np.abs(ref).max())
-    assert pc == f.pred_class and np.abs(y[:40].cpu().numpy() - ref).max() <= tol * scale
+    assert pc == f.pred_class and np.abs(y[:12].cpu().numpy() - ref).max() <= tol * scale
     assert (y - parts).abs().max().item() <= tol * scale   # both within it of the same value, about
     one, all_parts = _ms(lambda: ctx.eval(cg, Z, 1)), _ms(lambda: [ctx.eval(cg, c, 1) for c in cuts])
     say(f"  one call {one * 1e3:.0f} us, in parts {all_parts * 1e3:.0f} us")
@@ -387,3 +387,24 @@ def test_masked_gat_wide_attention_range_uses_the_whole_gpu(degree, heads, width
     say(f"gat wide range degree={degree} heads={heads} widths={widths} rows={rows}")
     one, parts = _one_call_and_parts(degree, heads, widths, 60.0, rows, 1e-4)
     assert one <= 4.0 * parts
+
+
+# the last layer of several heads: a wave per coalition below a number of coalitions times entries of the target, a lane each from it on
+# (25,000 (heads + 2), or 15,000 heads^2 where the waves' rows do not fit LDS): one below and at that number, heads of every register
+# size, a target whose entries are no multiple of the four waves that share them, fewer entries than waves
+@pytest.mark.parametrize("degree,heads,widths,rows", [(301, (4, 2), (4, 8), 332), (301, (4, 2), (4, 8), 333), (251, (4, 4), (4, 7), 597),
+                                                      (251, (4, 4), (4, 7), 598), (150, (4, 8), (4, 4), 1666), (150, (4, 8), (4, 4), 1667),
+                                                      (250, (3, 3), (8, 9), 500), (500, (4, 4), (8, 8), 479), (500, (4, 4), (8, 8), 480),
+                                                      (3, (2, 1), (4, 30), 257), (2, (2, 1), (4, 12), 321)])
+def test_masked_gat_last_layer_by_lanes_or_waves(degree, heads, widths, rows):
+    say(f"gat lanes or waves degree={degree} heads={heads} widths={widths} rows={rows}")
+    _one_call_and_parts(degree, heads, widths, 1.0, rows, 1e-5)
+
+
+# many heads on few coalitions: lanes took ten times the waves' time (256 coalitions of a 500-entry target, 32 heads) and longer
+# than the per-coalition kernel takes for both layers
+@pytest.mark.parametrize("heads,widths", [((2, 32), (16, 1)), ((8, 16), (8, 2))])
+def test_masked_gat_many_heads_on_few_coalitions(heads, widths):
+    say(f"gat many heads {heads}")
+    one, parts = _one_call_and_parts(500, heads, widths, 1.0, 256, 1e-5)
+    assert one <= parts
