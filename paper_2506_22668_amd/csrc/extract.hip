@@ -175,8 +175,8 @@ __global__ void fill_i32(int32_t* p, int64_t count, int32_t v) {
   if (i < count) p[i] = v;
 }
 
-// mail layout (int64 slots): [0..7] level counts, [8] nnz_c, [9] players, [10] error, [11] members, [12] ball_small_kernel gave
-// up, [40..47] CSR entries of the rows within h hops
+// mail layout (int64 slots): [0..7] level counts, [8] nnz_c, [9] players, [10] error, [11] members, [12] the hop before which
+// ball_small_kernel gave up, [13] the frontier it leaves, [40..47] CSR entries of the rows within h hops
 __global__ void bfs_seed(int32_t* dist, int32_t* frontier, int64_t* mail, int64_t target) {
   dist[target] = 0;
   frontier[0] = (int32_t)target;
@@ -348,12 +348,14 @@ __global__ void backfill_entries(GraphOut out, const int32_t* rank_scan, const i
 // claim is an atomic OR, and the rank of a node among those of its hop is a prefix sum of popcounts, so that nothing has to be
 // sorted; two more launches count the entries. ds_extract of 16 players in 10,000 nodes: 135 -> 52 us; 3,000 players in
 // 60,000 nodes, 1,000 rows visited: 155 -> 104 us. Bound by the latency of the visited rows, which one workgroup has to itself:
-// 15,000 entries cost as much as the launches saved (161 -> 142 us), and past the limits below it gives up (slot 12) and the
-// general kernels follow, 25 us late.
+// past the limits below it hands over the hops it has (slot 12), the whole GPU visits the others, and the nodes are numbered by a
+// workgroup to 1,024 of them, each of which counts all the others for itself.
+// ds_extract of 4,000 players, 1,200 rows in hop 2, 160 -> 102 us (the scans of the general kernels behind a workgroup that gave up: 190);
+// 62,000 players, 800 rows in hop 1, 375 -> 343 us (407).
 constexpr int kBallThreads = 1024;
 constexpr int64_t kBallNodes = 64 * kBallThreads;   // a thread to a word of the bitmaps
 constexpr int kBallRows = 1024;                     // rows visited per hop, a thread to each
-constexpr int kBallEntries = 16384;                 // entries of these
+constexpr int kBallEntries = 16384;                 // entries of all rows visited
 constexpr int kBallWaves = kBallThreads / 64;
 
 size_t ball_lds_bytes(int64_t N, int levels) {
@@ -374,7 +376,7 @@ __device__ __forceinline__ int wave_scan(int v) {
 __global__ __launch_bounds__(kBallThreads) void ball_small_kernel(const int64_t* row_ptr, const int32_t* col, int64_t N, int hops,
                                                                   int32_t target, int32_t* dist, int32_t* lid, int32_t* rank,
                                                                   int64_t* node_gid, int32_t* hop, int32_t* lid_of_rank,
-                                                                  int64_t* mail) {
+                                                                  int64_t* mail, unsigned long long* maps_out) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_ball[];
   __shared__ int wave_sums[DS_MAX_HOPS + 2][kBallWaves];
   __shared__ int totals[DS_MAX_HOPS + 2];
@@ -393,13 +395,12 @@ __global__ __launch_bounds__(kBallThreads) void ball_small_kernel(const int64_t*
   if (tid == 0) {
     maps[target >> 6] = all[target >> 6] = 1ull << (target & 63);
     cur[0] = target;
+    entries = 0;
   }
-  int count = 1;
-  bool give_up = false;
+  int count = 1, left = 0;   // left: the hop before which it gives up
   for (int h = 1; h <= hops; ++h) {
     __syncthreads();   // `cur` is complete, the counters have been read
-    if (tid == 0) claimed = entries = 0;
-    __syncthreads();
+    if (tid == 0) claimed = 0;
     if (tid < count) {
       const int g = cur[tid];
       const int64_t a = row_ptr[g], len = row_ptr[g + 1] - a;
@@ -409,7 +410,7 @@ __global__ __launch_bounds__(kBallThreads) void ball_small_kernel(const int64_t*
     }
     __syncthreads();
     if (entries > kBallEntries) {
-      give_up = true;
+      left = h;
       break;
     }
     for (int f = wave; f < count; f += kBallWaves) {
@@ -428,15 +429,16 @@ __global__ __launch_bounds__(kBallThreads) void ball_small_kernel(const int64_t*
     __syncthreads();
     if (h < hops) count = claimed;
     if (count > kBallRows) {
-      give_up = true;
+      left = h + 1;
       break;
     }
     int* const t = cur;
     cur = next;
     next = t;
   }
-  if (give_up) {   // (no members: the kernels queued behind this one have nothing to do)
-    if (tid < 16) mail[tid] = tid == 12 ? 1 : 0;
+  if (left) {   // (no members: the kernels queued behind this one have nothing to do)
+    for (int i = tid; i < words * left; i += kBallThreads) maps_out[i] = maps[i];
+    if (tid < 16) mail[tid] = tid == left - 1 ? count : tid == 12 ? left : 0;
     return;
   }
   for (int q = 0; q <= levels; ++q) {
@@ -477,6 +479,103 @@ __global__ __launch_bounds__(kBallThreads) void ball_small_kernel(const int64_t*
     hop[l] = d;
     lid_of_rank[rk] = l;
   }
+}
+
+// `levels` bitmaps of hops -> distances (-1: none), and the nodes of the last of them as the frontier of bfs_visit
+__global__ void ball_unpack_kernel(const unsigned long long* maps, int64_t N, int levels, int32_t* dist, int32_t* frontier, int64_t* mail) {
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, words = (N + 63) / 64;
+  if (g >= N) return;
+  int d = -1;
+  for (int q = 0; q < levels; ++q)
+    if ((maps[q * words + (g >> 6)] >> (g & 63)) & 1ull) d = q;
+  dist[g] = d;
+  if (d == levels - 1) frontier[atomicAdd((unsigned long long*)&mail[13], 1ull)] = (int32_t)g;
+}
+
+// ball_small_kernel's numbering from the distances, a workgroup to 1,024 nodes: each counts the nodes of every hop among all nodes and
+// among those before its own (a byte per hop and thread: 64 nodes at most)
+__global__ __launch_bounds__(kBallThreads) void ball_rank_kernel(const int32_t* dist, int64_t N, int levels, int32_t* lid, int32_t* rank,
+                                                                 int64_t* node_gid, int32_t* hop, int32_t* lid_of_rank, int64_t* mail) {
+  __shared__ unsigned long long sums[kBallWaves][4];
+  __shared__ int own[DS_MAX_HOPS + 2][kBallWaves];     // this workgroup's nodes of a hop (of any, last), by wave
+  __shared__ int total[DS_MAX_HOPS + 1], first[DS_MAX_HOPS + 2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = (int)N, base = (int)blockIdx.x * kBallThreads, g = base + tid;
+  unsigned long long before = 0ull, all = 0ull;
+  auto count = [&](int i, int d) {
+    if (d < 0) return;
+    all += 1ull << (8 * d);
+    if (i < base) before += 1ull << (8 * d);
+  };
+  for (int i = 4 * tid; i < n; i += 4 * kBallThreads) {
+    if (i + 3 < n) {
+      const int4 d = *(const int4*)(dist + i);
+      count(i, d.x);
+      count(i + 1, d.y);
+      count(i + 2, d.z);
+      count(i + 3, d.w);
+    } else {
+      for (int u = i; u < n; ++u) count(u, dist[u]);
+    }
+  }
+  // (64 lanes: 16 bits to a hop, the even and the odd ones apart)
+  const unsigned long long even = 0x00ff00ff00ff00ffull;
+  unsigned long long part[4] = {all & even, (all >> 8) & even, before & even, (before >> 8) & even};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    for (int o = 32; o > 0; o >>= 1) part[i] += __shfl_xor(part[i], o, 64);
+    if (lane == 0) sums[wave][i] = part[i];
+  }
+  const int d = g < n ? dist[g] : -1;
+  const unsigned long long lt = (1ull << lane) - 1ull, members = __ballot(d >= 0);
+  int in_hop = 0;   // nodes of the same hop in the wave before this lane
+  for (int q = 0; q < levels; ++q) {
+    const unsigned long long m = __ballot(d == q);
+    if (d == q) in_hop = __popcll(m & lt);
+    if (lane == 0) own[q][wave] = __popcll(m);
+  }
+  if (lane == 0) own[levels][wave] = __popcll(members);
+  __syncthreads();
+  if (tid < levels) {
+    int t = 0, f = 0;
+    for (int w = 0; w < kBallWaves; ++w) {
+      t += (int)(sums[w][tid & 1] >> (16 * (tid >> 1))) & 0xffff;
+      f += (int)(sums[w][2 + (tid & 1)] >> (16 * (tid >> 1))) & 0xffff;
+    }
+    total[tid] = t;
+    first[tid] = f;
+  }
+  __syncthreads();
+  if (tid <= levels) {   // exclusive sums over the waves, from the nodes before this workgroup's on
+    int run = 0;
+    if (tid < levels) {
+      run = first[tid];
+    } else {
+      for (int q = 0; q < levels; ++q) run += first[q];
+    }
+    for (int w = 0; w < kBallWaves; ++w) {
+      const int c = own[tid][w];
+      own[tid][w] = run;
+      run += c;
+    }
+  }
+  if (blockIdx.x == 0 && tid < 16) {
+    int v = 0;
+    if (tid < levels) v = total[tid];
+    else if (tid == 11)
+      for (int q = 0; q < levels; ++q) v += total[q];
+    mail[tid] = v;
+  }
+  __syncthreads();
+  if (d < 0) return;
+  int l = own[d][wave] + in_hop;   // local ids ascend by hop, then by global id
+  for (int q = 0; q < d; ++q) l += total[q];
+  const int rk = own[levels][wave] + __popcll(members & lt);
+  lid[g] = l;
+  rank[g] = rk;
+  node_gid[l] = g;
+  hop[l] = d;
+  lid_of_rank[rk] = l;
 }
 
 // the members' entry and player counts into row and player starts (V + 1 each, in place), their totals and the entries of every
@@ -524,6 +623,51 @@ __global__ __launch_bounds__(kBallThreads) void ball_rows_kernel(int32_t* row_st
   if (tid == 0) {
     mail[8] = at_row;
     mail[9] = at_player;
+  }
+}
+
+// the same for many members, a workgroup to 1,024 of them, each of which sums the counts before its own for itself; into other
+// arrays, the counts being read by all
+__global__ __launch_bounds__(kBallThreads) void ball_rows_wide_kernel(const int32_t* row_count, const int32_t* player_count, int32_t* row_start,
+                                                                      int32_t* player_start, int64_t* mail) {
+  __shared__ int sums[2][kBallWaves], own[2][kBallWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int V = (int)mail[11], base = (int)blockIdx.x * kBallThreads, i = base + tid;
+  if (base > V) return;
+  int sa = 0, sb = 0;
+  for (int j = 4 * tid; j < base; j += 4 * kBallThreads) {
+    const int4 a = *(const int4*)(row_count + j), b = *(const int4*)(player_count + j);
+    sa += a.x + a.y + a.z + a.w;
+    sb += b.x + b.y + b.z + b.w;
+  }
+  const int a = i < V ? row_count[i] : 0, b = i < V ? player_count[i] : 0;
+  sa = wave_scan(sa);
+  sb = wave_scan(sb);
+  const int ia = wave_scan(a), ib = wave_scan(b);
+  if (lane == 63) {
+    sums[0][wave] = sa;
+    sums[1][wave] = sb;
+    own[0][wave] = ia;
+    own[1][wave] = ib;
+  }
+  __syncthreads();
+  int ea = ia - a, eb = ib - b;
+#pragma unroll
+  for (int w = 0; w < kBallWaves; ++w) {
+    ea += sums[0][w] + (w < wave ? own[0][w] : 0);
+    eb += sums[1][w] + (w < wave ? own[1][w] : 0);
+  }
+  if (i > V) return;
+  row_start[i] = ea;
+  player_start[i] = eb;
+  int ball = 0;
+  for (int h = 0; h < 8; ++h) {
+    ball += (int)mail[h];
+    if (ball == i) mail[40 + h] = ea;
+  }
+  if (i == V) {
+    mail[8] = ea;
+    mail[9] = eb;
   }
 }
 
@@ -628,29 +772,48 @@ int ds_extract_impl(ds_ctx* ctx, int64_t target, int hops, int directed, ds_cgra
     cnt_up_rank = (int32_t*)ds_arena_alloc(ctx, (v + 1) * 4);
     return node_gid_tmp && hop_tmp && lid_of_rank && rowptr_tmp && cnt_all_rank && cnt_up_rank;
   };
-  bool small = N <= kBallNodes;
+  const bool small = N <= kBallNodes;
   if (small) {
     dist = (int32_t*)ds_arena_alloc(ctx, N * 4);
     rank_scan = (int32_t*)ds_arena_alloc(ctx, N * 4);
     lid_scan = (int32_t*)ds_arena_alloc(ctx, N * 4);
-    if (!dist || !rank_scan || !lid_scan || !member_arrays(N)) return ds_fail(ctx, DS_EINTERNAL, "extract: arena exhausted");
+    int32_t* cur = (int32_t*)ds_arena_alloc(ctx, N * 4);
+    int32_t* nxt = (int32_t*)ds_arena_alloc(ctx, N * 4);
+    unsigned long long* maps = (unsigned long long*)ds_arena_alloc(ctx, (size_t)(N + 63) / 64 * levels * 8);
+    if (!dist || !rank_scan || !lid_scan || !cur || !nxt || !maps || !member_arrays(N)) return ds_fail(ctx, DS_EINTERNAL, "extract: arena exhausted");
     const size_t lds = ball_lds_bytes(N, levels);
     if (lds > 48 * 1024)
       DS_HIP(ctx, hipFuncSetAttribute((const void*)ball_small_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(ball_small_kernel, dim3(1), dim3(kBallThreads), lds, st, ctx->row_ptr, ctx->col, N, hops, (int32_t)target, dist,
-                       lid_scan, rank_scan, node_gid_tmp, hop_tmp, lid_of_rank, mail);
+                       lid_scan, rank_scan, node_gid_tmp, hop_tmp, lid_of_rank, mail, maps);
     hipLaunchKernelGGL(count_entries, dim3(ctx->num_cus * 2), dim3(kThreads), 0, st, ctx->row_ptr, ctx->col, dist, node_gid_tmp, lid_of_rank,
                        mail + 11, rowptr_tmp, cnt_all_rank, cnt_up_rank);
     hipLaunchKernelGGL(ball_rows_kernel, dim3(1), dim3(kBallThreads), 0, st, rowptr_tmp, directed ? cnt_all_rank : cnt_up_rank, mail);
     DS_HIP(ctx, hipGetLastError());
     DS_TRY(ds_mail_fetch(ctx, 48));
-    small = ctx->h_mail[12] == 0;
-    if (small) {
-      DS_TRY(ball_sizes());
-      lid_stride = 0;
-    } else {
-      ds_arena_reset(ctx);
+    if (ctx->h_mail[12] != 0) {   // more than one workgroup's work
+      int h = (int)ctx->h_mail[12];
+      hipLaunchKernelGGL(ball_unpack_kernel, dim3(blocks_for(N)), dim3(kThreads), 0, st, maps, N, h, dist, cur, mail);
+      for (; h <= hops; ++h) {
+        hipLaunchKernelGGL(bfs_visit, dim3(ctx->num_cus * 4), dim3(kThreads), 0, st, ctx->row_ptr, ctx->col, dist, cur, nxt, mail, h);
+        int32_t* t = cur; cur = nxt; nxt = t;
+      }
+      hipLaunchKernelGGL(ball_rank_kernel, dim3(blocks_for(N, kBallThreads)), dim3(kBallThreads), 0, st, dist, N, levels, lid_scan, rank_scan,
+                         node_gid_tmp, hop_tmp, lid_of_rank, mail);
+      hipLaunchKernelGGL(count_entries, dim3(ctx->num_cus * 8), dim3(kThreads), 0, st, ctx->row_ptr, ctx->col, dist, node_gid_tmp, lid_of_rank,
+                         mail + 11, rowptr_tmp, cnt_all_rank, cnt_up_rank);
+      int32_t* const rows_out = (int32_t*)ds_arena_alloc(ctx, (N + 1) * 4);
+      int32_t* const players_out = (int32_t*)ds_arena_alloc(ctx, (N + 1) * 4);
+      if (!rows_out || !players_out) return ds_fail(ctx, DS_EINTERNAL, "extract: arena exhausted");
+      hipLaunchKernelGGL(ball_rows_wide_kernel, dim3(blocks_for(N + 1, kBallThreads)), dim3(kBallThreads), 0, st, rowptr_tmp,
+                         directed ? cnt_all_rank : cnt_up_rank, rows_out, players_out, mail);
+      rowptr_tmp = rows_out;
+      cnt_all_rank = cnt_up_rank = players_out;
+      DS_HIP(ctx, hipGetLastError());
+      DS_TRY(ds_mail_fetch(ctx, 48));
     }
+    DS_TRY(ball_sizes());
+    lid_stride = 0;
   }
   const auto wave_blocks = [&]() { return (unsigned)((V * 64 + kThreads - 1) / kThreads < (int64_t)ctx->num_cus * 8 ? (V * 64 + kThreads - 1) / kThreads : (int64_t)ctx->num_cus * 8); };
   if (!small) {

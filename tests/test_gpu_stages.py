@@ -182,6 +182,47 @@ def test_extraction_in_one_workgroup_and_past_its_limits(num_nodes, first, secon
     ctx.close()
 
 
+# ... and where it hands over: before hop 1 (the target's entries at and one past the limit), before a middle hop because of the rows
+# or of the entries so far, several hops to go, more members than a workgroup numbers, last words and blocks that are not whole
+@pytest.mark.parametrize("num_nodes,first,second,hops", [
+    (20_001, 16_384, 0, 1), (20_001, 16_385, 0, 1), (5000, 1500, 2, 5), (33_000, 40, 700, 4), (9000, 1024, 5, 2), (65_473, 1100, 40, 7),
+])
+@pytest.mark.parametrize("directed", [False, True])
+def test_extraction_handed_over_by_the_one_workgroup(num_nodes, first, second, hops, directed):
+    test_extraction_in_one_workgroup_and_past_its_limits(num_nodes, first, second, hops, directed)
+
+
+def test_extraction_handed_over_is_no_slower_than_the_general_kernels():
+    """1,200 rows in hop 2: past what one workgroup takes. The same graph with more than 65,536 nodes goes to the general
+    kernels at once, which took 25 us less than the workgroup that gave up and they after it."""
+    import time
+    from paper_2506_22668_amd import Context, Options
+    from synth import csr_from_undirected_edges
+    kids, leaves = np.arange(1, 31), np.arange(31, 1231)
+    more = np.arange(1231, 2431)
+    src, dst = np.r_[np.zeros(30, np.int64), 1 + (leaves - 31) % 30, leaves], np.r_[kids, leaves, more]
+    rng = np.random.default_rng(0)
+    times = {}
+    for N in (3000, 66_000):
+        ctx = Context("cuda:0")
+        rp, ci = csr_from_undirected_edges(N, src, dst)
+        ctx.set_graph(rp, ci)
+        ctx.set_features(rng.standard_normal((N, 4), dtype=np.float32))
+        ctx.set_gcn([rng.standard_normal((4, 4)).astype(np.float32) for _ in range(3)])
+        t = []
+        for i in range(60):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            cg = ctx.extract(0, Options(hops=3))
+            t.append(time.perf_counter() - t0)
+            assert ctx.cgraph_info(cg).num_players == 2430
+            ctx.cgraph_free(cg)
+        times[N] = 1e6 * sorted(t[10:])[25]
+        ctx.close()
+    say(f"extract past one workgroup {times[3000]:.0f} us, general {times[66_000]:.0f} us")
+    assert times[3000] <= 0.95 * times[66_000]
+
+
 def test_malformed_graphs_are_rejected():
     from paper_2506_22668_amd import Context, DistShapError, DS_EINVAL, Options
     say("graph validation")
