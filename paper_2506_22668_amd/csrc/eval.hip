@@ -1072,48 +1072,79 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
         float acc[16];
 #pragma unroll
         for (int f = 0; f < 16; ++f) acc[f] = 0.f;
-        // A step is look-ups in LDS (entry, mask bit, degree), then sixteen features of four rows from memory: the next step's look-ups run
-        // while this one's are on their way, and nothing is conditional (past the end the last entry again, multiplied by zero;
-        // entry 0 has room in every copy of the CSR). With the bias above and the readout below, 9,999 rows of 1,010 players: 175 -> 155 us.
-        struct Step {
-          float c[4];
-          const float* h[4];
-        };
-        auto step = [&](Step& o, int eb) {   // entry e1 stands for the self-loop
+        if constexpr (CSR_LDS || EXT) {
+          // A step is look-ups (entry, mask bit, degree), then sixteen features of four rows from memory: the next step's look-ups run while this
+          // one's are on their way, and nothing is conditional (past the end the last entry again, multiplied by zero; entry 0 has
+          // room in every copy of the CSR). With the bias above and the readout below, 9,999 rows of 1,010 players: 175 -> 155 us.
+          struct Step {
+            float c[4];
+            const float* h[4];
+          };
+          auto step = [&](Step& o, int eb) {   // entry e1 stands for the self-loop
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int e = eb + u;
-            const int ec = e < e1 ? e : e1 > e0 ? e1 - 1 : 0;
-            const int cv = col_[ec], kv = key_[ec];
-            const int src = __builtin_amdgcn_readfirstlane(e < e1 ? cv : t);
-            const bool on = entry_bit(e < e1 ? kv : 0);
-            const float rv = rs_of(src);
-            o.c[u] = e < e1 ? (on ? rv : 0.f) : e == e1 ? rst : 0.f;
-            o.h[u] = cur + ((size_t)src * din + f0) * 64;
-          }
-        };
-        Step now;
-        step(now, e0);
-        for (int eb = e0; eb <= e1; eb += 4) {
-          float hv[4][16];
-          if (f0 + 16 <= din) {
+            for (int u = 0; u < 4; ++u) {
+              const int e = eb + u;
+              const int ec = e < e1 ? e : e1 > e0 ? e1 - 1 : 0;
+              const int cv = col_[ec], kv = key_[ec];
+              const int src = __builtin_amdgcn_readfirstlane(e < e1 ? cv : t);
+              const bool on = entry_bit(e < e1 ? kv : 0);
+              const float rv = rs_of(src);
+              o.c[u] = e < e1 ? (on ? rv : 0.f) : e == e1 ? rst : 0.f;
+              o.h[u] = cur + ((size_t)src * din + f0) * 64;
+            }
+          };
+          Step now;
+          step(now, e0);
+          for (int eb = e0; eb <= e1; eb += 4) {
+            float hv[4][16];
+            if (f0 + 16 <= din) {
+#pragma unroll
+              for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int f = 0; f < 16; ++f) hv[u][f] = now.h[u][f * 64 + lane];
+            } else {
+#pragma unroll
+              for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int f = 0; f < 16; ++f) hv[u][f] = (f0 + f < din) ? now.h[u][f * 64 + lane] : 0.f;
+            }
+            Step next;   // its look-ups run while the rows are on their way
+            step(next, eb + 4);
 #pragma unroll
             for (int u = 0; u < 4; ++u)
 #pragma unroll
-              for (int f = 0; f < 16; ++f) hv[u][f] = now.h[u][f * 64 + lane];
-          } else {
+              for (int f = 0; f < 16; ++f) acc[f] += now.c[u] * hv[u][f];
+            now = next;
+          }
+        } else {
+          // (masks on chip, the CSR in memory: the look-ups are three loads in a row, and those behind a row's last step have nobody to wait for
+          // them: 2,000 rows of a hub target of 10,000 players 2.86 ms with the loop above, 2.72 so)
+          for (int eb = e0; eb <= e1; eb += 4) {  // entry e1 stands for the self-loop
+            float c[4];
+            const float* hp[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int e = eb + u;
+              int src = t;
+              c[u] = 0.f;
+              if (e < e1) {
+                src = col_[e];
+                c[u] = entry_bit(key_[e]) ? rs_of(src) : 0.f;
+              } else if (e == e1) {
+                c[u] = rst;
+              }
+              hp[u] = cur + ((size_t)src * din + f0) * 64 + lane;
+            }
+            float hv[4][16];
 #pragma unroll
             for (int u = 0; u < 4; ++u)
 #pragma unroll
-              for (int f = 0; f < 16; ++f) hv[u][f] = (f0 + f < din) ? now.h[u][f * 64 + lane] : 0.f;
+              for (int f = 0; f < 16; ++f) hv[u][f] = (f0 + f < din) ? hp[u][(size_t)f * 64] : 0.f;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+              for (int f = 0; f < 16; ++f) acc[f] += c[u] * hv[u][f];
           }
-          Step next;   // its look-ups run while the rows are on their way
-          step(next, eb + 4);
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int f = 0; f < 16; ++f) acc[f] += now.c[u] * hv[u][f];
-          now = next;
         }
 #pragma unroll
         for (int f = 0; f < 16; ++f)
@@ -1131,7 +1162,9 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
 
     // readout: logits of the target are cur[c][lane], c < d_L (row 0)
     if (wave == 0 && valid) {
-      const int C = a.dims[a.L];
+      int C = a.dims[a.L];
+      // (not known to be the same in every block: the sixteen offsets below would be formed before the first and kept through all)
+      if constexpr (!EXT) asm volatile("" : "+s"(C));
       float m = -INFINITY, sum = 0.f;
       if constexpr (EXT) {
         for (int c = 0; c < C; ++c) m = fmaxf(m, cur[(size_t)c * 64 + lane]);

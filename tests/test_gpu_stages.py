@@ -472,6 +472,25 @@ def test_masked_inference_beyond_the_on_chip_limits(kids, dims):
     _eval_case(w, len(dims) - 1, False, 1, biases, 322, rng)
 
 
+# masks on chip, degrees in LDS and the local CSR, of more entries than fit beside them, in memory: later layers whose rows end at every
+# place in a step of four entries, slices of whole and partial widths
+@pytest.mark.parametrize("nodes,edges,dims", [(600, 5000, (6, 33, 17, 3)), (640, 4500, (6, 64, 16, 12)), (630, 4700, (6, 5, 40, 30))])
+def test_masked_inference_csr_outside_of_lds(nodes, edges, dims):
+    from synth import csr_from_undirected_edges
+    from synth.workloads import Workload, glorot_uniform
+    rng = np.random.default_rng(edges)
+    kids = np.arange(1, 8)
+    u, v = rng.integers(1, nodes, edges), rng.integers(8, nodes, edges)
+    rp, ci = csr_from_undirected_edges(nodes, np.r_[np.zeros(7, np.int64), u[u != v]], np.r_[kids, v[u != v]])
+    n = len(ci) // 2
+    assert 4096 < n < 8192 and 512 * ((n + 63) // 64) + 128 * nodes + 8 * len(ci) + 16384 > 160 * 1024
+    w = Workload("csr in memory", nodes, rp, ci, rng.standard_normal((nodes, dims[0]), dtype=np.float32), dims,
+                 [glorot_uniform(rng, dims[i], dims[i + 1]) for i in range(3)], [0], 0, 0, "gram_chol")
+    biases = [0.1 * rng.standard_normal(d).astype(np.float32) for d in dims[1:]]
+    say(f"masked inference CSR in memory nodes={nodes} players={n} dims={dims}")
+    _eval_case(w, 3, False, 1, biases, 322, rng)
+
+
 # a row's own term stays what it is where the row's features are infinite: the slots that fill up the last step of a row
 # (steps of 2, 4 and 8 entries) must not multiply it by a zero. One layer, so that no other row reads the target's.
 @pytest.mark.parametrize("leaves", [1, 2, 3, 4, 5, 6, 7, 8, 9, 21, 260, 301])
