@@ -229,8 +229,9 @@ __device__ __forceinline__ void transform_rows(const float* q, int rows, int din
   }
 }
 
-// THREADS: 256, or 1,024 where there is at most one coalition per compute unit (the predicted class above all). A row is a chain of
-// latencies and the rows are dealt to the waves, so that what matters then is how many there are (1,010 players: 80 -> 53 us).
+// THREADS: 256, or 1,024 where a compute unit has at most one workgroup: few coalitions (the predicted class above all) or degrees and
+// buffers that fill its LDS. A row is a chain of latencies and the rows are dealt to the waves, so that what matters then is how
+// many there are (one coalition of 1,010 players 80 -> 53 us; 1,000 of a graph of 25,000 nodes 4.03 -> 1.54 ms).
 template <bool RS_LDS, bool BUF_LDS, int THREADS>
 __global__ __launch_bounds__(THREADS) void masked_gcn_eval_kernel(EvalArgs a) {
   constexpr int WAVES = THREADS / 64;
@@ -1887,7 +1888,8 @@ constexpr int kWideThreads = 1024;
 
 int launch_eval(ds_ctx* ctx, const EvalArgs& a, const EvalLayout& lay, int grid) {
   const size_t wide_lds = lay.lds_bytes + (size_t)(kWideThreads / 64 - kWaves) * 256 * 4;
-  const bool wide = grid <= ctx->num_cus && wide_lds <= kLdsLimit;
+  // (by what the GPU would hold, not by `grid`, which a bounded workspace makes smaller: the same sums in either entry point)
+  const bool wide = grid_for(ctx, lay, a.k) <= ctx->num_cus && wide_lds <= kLdsLimit;
   void (*const kerns[2][2][2])(EvalArgs) = {   // [rs in LDS][buffers in LDS][wide]
       {{masked_gcn_eval_kernel<false, false, kThreads>, masked_gcn_eval_kernel<false, false, kWideThreads>},
        {masked_gcn_eval_kernel<false, true, kThreads>, masked_gcn_eval_kernel<false, true, kWideThreads>}},

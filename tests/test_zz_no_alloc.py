@@ -55,3 +55,29 @@ def test_eval_noalloc_matches_eval_twice_second_call_smaller():
         ctx2.eval_noalloc(cg2, Z, y, score=9)
     ctx2.cgraph_free(cg2)
     ctx2.close()
+
+
+def test_eval_noalloc_sums_in_the_order_of_eval():
+    """One workgroup per coalition, whose buffers (180 KB) are in the workspace: the static array holds 186 of them, fewer
+    than there are compute units, and that must not choose another number of waves to share a long row's sum."""
+    from paper_2506_22668_amd import Context, Options, Tuning
+    from synth import csr_from_undirected_edges
+    kids = 700
+    rp, ci = csr_from_undirected_edges(2 * kids + 1, [0] * kids + list(range(1, kids + 1)),
+                                       list(range(1, kids + 1)) + list(range(kids + 1, 2 * kids + 1)))
+    rng = np.random.default_rng(5)
+    ctx = Context("cuda:0")
+    ctx.set_graph(rp, ci)
+    ctx.set_features(rng.standard_normal((2 * kids + 1, 8), dtype=np.float32))
+    ctx.set_gcn([rng.standard_normal((8, 64)).astype(np.float32), rng.standard_normal((64, 5)).astype(np.float32)])
+    cg = ctx.extract(0, Options(hops=2))
+    ctx.set_tuning(Tuning(eval_path=1))
+    say("eval_noalloc with fewer workgroups than compute units")
+    Z = _masks(2 * kids, 600, 4)
+    ref, _ = ctx.eval(cg, Z, 1)
+    y = torch.empty(600, dtype=torch.float32, device="cuda")
+    ctx.eval_noalloc(cg, Z, y, 1)
+    ctx.synchronize()
+    assert torch.equal(y, ref)
+    ctx.cgraph_free(cg)
+    ctx.close()
