@@ -181,7 +181,18 @@ __global__ __launch_bounds__(kTileThreads) void tile_spmv_kernel(TileArgs a) {
     if (!direct) {
       if (staged) __syncthreads();  // the piece staged before is no longer read
       const int len = (int)(s_end - s0);
-      for (int i = tid; i < len; i += kTileThreads) src[i] = drop_bits(qs[i], a.sh);
+      // (all of a thread's loads in flight: a group of short rows stages several pieces one behind the other)
+      long long piece[kTileSpan / kTileThreads];
+#pragma unroll
+      for (int u = 0; u < kTileSpan / kTileThreads; ++u) {
+        const int i = tid + u * kTileThreads;
+        piece[u] = qs[i < len ? i : len - 1];
+      }
+#pragma unroll
+      for (int u = 0; u < kTileSpan / kTileThreads; ++u) {
+        const int i = tid + u * kTileThreads;
+        if (i < len) src[i] = drop_bits(piece[u], a.sh);
+      }
       __syncthreads();
       staged = true;
     }
