@@ -71,52 +71,68 @@ __global__ void tile_blocks_kernel(const int32_t* off, int64_t rows, int64_t bud
   mail[1] = g;
 }
 
-__device__ __forceinline__ int block_of_row(const int32_t* rb_start, int nrb, int64_t r) {
-  int lo = 0, hi = nrb - 1;  // last block whose first row is <= r
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (rb_start[mid] <= r) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
-// One wave per row; the columns of a row ascend, so the lanes of a 64-entry step that fall into one chunk are a run:
-// the first lane of each run adds the run's length to its tile's counter (FILL: takes that many slots from the tile's
-// cursor and the lanes of the run write their entries there).
+// A workgroup takes a part of a row block's rows, a wave to a row; the columns of a row ascend, so the lanes of a 64-entry step that
+// fall into one chunk are a run, and the first lane of each run adds the run's length to its chunk's counter. The counters are the
+// workgroup's own, in LDS, and go to the tile's in one addition each (FILL: which reserves the workgroup's slots; a second walk has the
+// runs take theirs and the lanes write their entries there). With a counter in memory per tile, all runs of all waves met on
+// them, the more so the fewer tiles there are: 99,981 players, 13 M entries in 286 tiles: the two walks 640 and 940 us (in 572 tiles
+// 385 and 530), now 36 and 64; 30,000 players, 4.3 M entries: 420 and 510, now 41 and 69.
+constexpr int kChunkWindow = 4096;   // chunks counted per walk
 template <bool FILL>
-__global__ __launch_bounds__(kThreads) void tile_scatter_kernel(const int32_t* off, const int32_t* idx, int64_t rows, int32_t nrb,
-                                                                int32_t ncb, const int32_t* rb_start, int32_t* counter,
-                                                                const int32_t* tile_off, uint32_t* ent) {
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t r = wave; r < rows; r += nwaves) {
-    const int rb = block_of_row(rb_start, nrb, r);
-    const uint32_t rl = (uint32_t)(r - rb_start[rb]);
-    const int32_t a = off[r], b = off[r + 1];
-    for (int32_t e0 = a; e0 < b; e0 += 64) {
-      const int32_t e = e0 + lane;
-      const bool valid = e < b;
-      const int32_t col = valid ? idx[e] : -1;
-      const int32_t ch = valid ? (col >> kTileBits) : -1;
-      const int32_t prev = __shfl_up(ch, 1, 64);
-      const bool head = valid && (lane == 0 || ch != prev);
-      const uint64_t heads = __ballot(head);
-      const int nvalid = __popcll(__ballot(valid));
-      int32_t base = 0;
-      if (head) {
-        const uint64_t above = lane == 63 ? 0ull : heads >> (lane + 1);
-        const int len = above ? (__ffsll((long long)above)) : (nvalid - lane);
-        base = atomicAdd(&counter[(int64_t)rb * ncb + ch], len);
+__global__ __launch_bounds__(kThreads) void tile_scatter_kernel(const int32_t* off, const int32_t* idx, int32_t parts, int32_t ncb,
+                                                                const int32_t* rb_start, int32_t* counter, const int32_t* tile_off,
+                                                                uint32_t* ent) {
+  __shared__ int32_t cnt[kChunkWindow];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int rb = (int)blockIdx.x / parts, part = (int)blockIdx.x % parts;
+  const int first = rb_start[rb], len = rb_start[rb + 1] - first;
+  const int r_begin = first + (int)((int64_t)len * part / parts), r_end = first + (int)((int64_t)len * (part + 1) / parts);
+  if (r_begin == r_end) return;
+  for (int c0 = 0; c0 < ncb; c0 += kChunkWindow) {
+    const int window = ncb - c0 < kChunkWindow ? ncb - c0 : kChunkWindow;
+    for (int c = tid; c < window; c += kThreads) cnt[c] = 0;
+    __syncthreads();
+    auto walk = [&](bool write) {
+      for (int r = r_begin + wave; r < r_end; r += kThreads / 64) {
+        const uint32_t rl = (uint32_t)(r - first);
+        const int32_t a = off[r], b = off[r + 1];
+        for (int32_t e0 = a; e0 < b; e0 += 64) {
+          const int32_t e = e0 + lane;
+          const bool valid = e < b;
+          const int32_t col = valid ? idx[e] : -1;
+          const int32_t ch = valid ? (col >> kTileBits) : -1;
+          const int32_t prev = __shfl_up(ch, 1, 64);
+          const bool head = valid && (lane == 0 || ch != prev);
+          const bool in = ch >= c0 && ch < c0 + window;
+          const uint64_t heads = __ballot(head);
+          const int nvalid = __popcll(__ballot(valid));
+          int32_t base = 0;
+          if (head && in) {
+            const uint64_t above = lane == 63 ? 0ull : heads >> (lane + 1);
+            const int run = above ? (__ffsll((long long)above)) : (nvalid - lane);
+            base = atomicAdd(&cnt[ch - c0], run);
+          }
+          if (write) {
+            const uint64_t upto = heads & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));   // heads at or below this lane
+            const int headlane = valid ? 63 - __clzll((long long)upto) : 0;
+            const int32_t hb = __shfl(base, headlane, 64);
+            if (valid && in) ent[hb + (lane - headlane)] = (rl << kTileBits) | (uint32_t)(col & (kTileSpan - 1));
+          }
+        }
       }
-      if (FILL) {
-        const uint64_t upto = heads & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));   // heads at or below this lane
-        const int headlane = valid ? 63 - __clzll((long long)upto) : 0;
-        const int32_t hb = __shfl(base, headlane, 64);
-        if (valid) ent[(int64_t)tile_off[(int64_t)rb * ncb + ch] + hb + (lane - headlane)] = (rl << kTileBits) | (uint32_t)(col & (kTileSpan - 1));
+      __syncthreads();
+    };
+    walk(false);
+    for (int c = tid; c < window; c += kThreads) {
+      const int64_t t = (int64_t)rb * ncb + c0 + c;
+      const int32_t n = cnt[c];
+      if (n > 0) {
+        const int32_t at = atomicAdd(&counter[t], n);
+        if (FILL) cnt[c] = tile_off[t] + at;
       }
     }
+    __syncthreads();
+    if (FILL) walk(true);
   }
 }
 
@@ -252,8 +268,8 @@ static void tile_shape(const ds_ctx* ctx, int64_t rows, int64_t cols, int64_t nn
   // often a unit has to start over (zero, stage, write out) and the partial vectors, one per group, that the loop adds up
   // again: as many groups as let the adjoint product (one workgroup per chunk and group) run in a single round. (Two
   // rounds' worth before: 99,981 players, 3.9 M entries, 41 groups, a third round nearly empty; an explanation with 120 CGLS
-  // iterations 21.92 ms, now 20.29. With 13 M entries 0.325 ms per iteration, now 0.311.) Fewer than six are too coarse a split of the rows: then four to six groups of blocks of a
-  // sixteenth of the entries.
+  // iterations 21.92 ms, now 20.29. With 13 M entries 0.325 ms per iteration, now 0.311.) Fewer than six are too coarse a split of the rows:
+  // then four to six groups of blocks of a sixteenth of the entries.
   int64_t groups = (int64_t)ctx->num_cus / *ncb - 2;   // (a block or two more come from the limit on rows)
   if (groups > 64) groups = 64;
   const int64_t per = groups >= 6 ? (11 + groups) / groups : 0;   // row blocks per group: at least twelve in all
@@ -337,16 +353,18 @@ int ds_tile_build(ds_ctx* ctx, int64_t rows, int64_t cols, int64_t nnz, int64_t 
   plan->sh_a = ceil_log2(rows_per_group < rows ? rows_per_group : rows) - 8;
   if (plan->sh_f < 0) plan->sh_f = 0;
   if (plan->sh_a < 0) plan->sh_a = 0;
-  int64_t blocks = (rows * 64 + kThreads - 1) / kThreads;
-  if (blocks > (int64_t)ctx->num_cus * 16) blocks = (int64_t)ctx->num_cus * 16;
+  // workgroups of a row block: eight to a compute unit in all, four rows each at least
+  int64_t parts = ((int64_t)ctx->num_cus * 8 + plan->nrb - 1) / plan->nrb;
+  const int64_t per_block = (rows + plan->nrb - 1) / plan->nrb;
+  if (parts > (per_block + 3) / 4) parts = (per_block + 3) / 4;
   DS_HIP(ctx, hipMemsetAsync(counter, 0, (tiles + 1) * 4, st));
-  hipLaunchKernelGGL(tile_scatter_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, st, off, idx, rows, plan->nrb, ncb,
+  hipLaunchKernelGGL(tile_scatter_kernel<false>, dim3((unsigned)(parts * plan->nrb)), dim3(kThreads), 0, st, off, idx, (int32_t)parts, ncb,
                      plan->rb_start, counter, (const int32_t*)nullptr, (uint32_t*)nullptr);
   DS_HIP(ctx, hipGetLastError());
   // the scan's scratch comes from the context's arena, after everything the caller holds
   DS_TRY(ds_scan_exclusive_i32(ctx, counter, plan->tile_off, tiles + 1, nullptr));
   DS_HIP(ctx, hipMemsetAsync(counter, 0, (tiles + 1) * 4, st));
-  hipLaunchKernelGGL(tile_scatter_kernel<true>, dim3((unsigned)blocks), dim3(kThreads), 0, st, off, idx, rows, plan->nrb, ncb,
+  hipLaunchKernelGGL(tile_scatter_kernel<true>, dim3((unsigned)(parts * plan->nrb)), dim3(kThreads), 0, st, off, idx, (int32_t)parts, ncb,
                      plan->rb_start, counter, plan->tile_off, plan->ent);
   DS_HIP(ctx, hipGetLastError());
   // the index lists are not needed any more: their memory takes the entries in their final order

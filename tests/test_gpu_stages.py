@@ -631,8 +631,8 @@ def test_cgls_dense_row_threshold_leaves_the_solution_alone(ctx_tiny, dense_div)
     assert abs(rep.cgls_iterations - rep0.cgls_iterations) <= 2
 
 
-# how the sparse rows' tiles are grouped follows the number of column chunks: one chunk, two, enough for 64 groups, groups of
-# one row block (14 chunks), of two (22) and the coarse split of the widest games (37); more than 65,536 entries a block
+# the sparse rows' tiles by the number of column chunks: one, two, four, 14, 22 and 37. At these numbers of rows a block holds 65,536
+# entries (all but the last: 67,000 each in sixteen parts), so that blocks and groups are few
 @pytest.mark.parametrize("n,ns", [(8192, 16000), (8193, 16000), (24_600, 16000), (110_000, 12000), (180_000, 8000), (300_007, 6000)])
 def test_cgls_tile_groups_by_width(ctx_tiny, n, ns):
     from oracle import cfast
@@ -642,6 +642,30 @@ def test_cgls_tile_groups_by_width(ctx_tiny, n, ns):
     Z, w, sz = ctx.sample(n, ns, 11, 3)
     y = torch.from_numpy(np.random.default_rng(n).random(Z.shape[0], dtype=np.float32)).cuda()
     phi, rep, rc = ctx.solve(n, Z, w, y, Options(solver=DS_SOLVER_CGLS, paired=1, max_iter=4), allow_not_converged=True)
+    assert rep.cgls_iterations == 4
+    ref = cfast.cgls(n, to_u64(Z), w.cpu().numpy(), y.cpu().numpy(), tol=0.0, max_iter=4)[0]
+    # both in fp64 or exact integers of 2^-47 and better, four steps; the scores come as float32
+    assert np.abs(phi.cpu().numpy().astype(np.float64) - ref).max() <= 1e-6 * np.abs(ref).max()
+
+
+# ... and where the blocks' entries follow from the number of groups, more than 65,536 of them: 62 groups of a block each (four chunks),
+# 17 (14 chunks), ten of two blocks (22 chunks); the coarse split of 37 chunks, whose forward product takes a third chunk per
+# workgroup instead of a second round
+@pytest.mark.parametrize("n,ns,dense_div", [(24_600, 120_000, 32), (110_000, 12000, 32), (180_000, 8000, 32), (300_007, 8000, 64)])
+def test_cgls_tile_groups_by_entries(ctx_tiny, n, ns, dense_div):
+    from oracle import cfast
+    from paper_2506_22668_amd import Options, Tuning, DS_SOLVER_CGLS
+    ctx, _ = ctx_tiny
+    say(f"cgls tile groups n={n} n_samples={ns} dense_div={dense_div}")
+    Z, w, sz = ctx.sample(n, ns, 11, 3)
+    small = sz.view(-1, 2).min(dim=1).values
+    assert small[small <= n // dense_div].sum().item() > 65536 * (62 if n == 24_600 else 16)   # (in so many parts)
+    y = torch.from_numpy(np.random.default_rng(n).random(Z.shape[0], dtype=np.float32)).cuda()
+    try:
+        ctx.set_tuning(Tuning(cgls_dense_div=dense_div))
+        phi, rep, rc = ctx.solve(n, Z, w, y, Options(solver=DS_SOLVER_CGLS, paired=1, max_iter=4), allow_not_converged=True)
+    finally:
+        ctx.set_tuning(None)
     assert rep.cgls_iterations == 4
     ref = cfast.cgls(n, to_u64(Z), w.cpu().numpy(), y.cpu().numpy(), tol=0.0, max_iter=4)[0]
     # both in fp64 or exact integers of 2^-47 and better, four steps; the scores come as float32
