@@ -21,6 +21,7 @@
 // Layer 1 uses the coalition-independent product P = X_c W_1 (computed once per
 // target with MFMA) and aggregates it; layers >= 2 aggregate, then transform.
 #include "internal.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -528,7 +529,8 @@ constexpr int kSharedRow = 256;  // a row with more entries than this is shared 
 
 // PAIRED (external inputs only): the records are complementary pairs and the first layer's coefficients are formed by
 // the lanes that feed them to the matrix cores (see there)
-template <bool DEG_LDS, bool CSR_LDS, bool EXT, bool PAIRED = false>
+// LOOKAHEAD: the later layers' loop that has the next step's look-ups in flight.
+template <bool DEG_LDS, bool CSR_LDS, bool EXT, bool PAIRED = false, bool LOOKAHEAD = true>
 __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 2 : 1)) void masked_gcn_eval_batched_kernel(BatchedArgs b) {
   const EvalArgs& a = b.e;
   constexpr int kBThreads = batched_threads<EXT, PAIRED>(), kBWaves = kBThreads / 64;
@@ -1073,7 +1075,7 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
         float acc[16];
 #pragma unroll
         for (int f = 0; f < 16; ++f) acc[f] = 0.f;
-        if constexpr (CSR_LDS || EXT) {
+        if constexpr (LOOKAHEAD) {
           // A step is look-ups (entry, mask bit, degree), then sixteen features of four rows from memory: the next step's look-ups run while this
           // one's are on their way, and nothing is conditional (past the end the last entry again, multiplied by zero; entry 0 has
           // room in every copy of the CSR). With the bias above and the readout below, 9,999 rows of 1,010 players: 175 -> 155 us.
@@ -1118,8 +1120,7 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
             now = next;
           }
         } else {
-          // (masks on chip, the CSR in memory: the look-ups are three loads in a row, and those behind a row's last step have nobody to wait for
-          // them: 2,000 rows of a hub target of 10,000 players 2.86 ms with the loop above, 2.72 so)
+          // (launch_batched says where)
           for (int eb = e0; eb <= e1; eb += 4) {  // entry e1 stands for the self-loop
             float c[4];
             const float* hp[4];
@@ -1173,6 +1174,8 @@ __global__ __launch_bounds__((batched_threads<EXT, PAIRED>()), (EXT && PAIRED ? 
       } else {
         // sixteen classes' loads in flight: one at a time took 12 of a block's 150 us at ten classes. (With external inputs the
         // same lines cost the first layer more than they gave, eval of 100,000 rows 1.86 -> 2.05 ms: registers.)
+        // They are 30 of this kernel's 65 to 68 spilled registers. Models without a bias, 17 sizes of 300 to 12,000 players, take 0.95 to
+        // 1.00 of the time from before this and the look-ups ahead.
         auto classes = [&](int c0, float (&v)[16]) {
 #pragma unroll
           for (int i = 0; i < 16; ++i) v[i] = cur[(size_t)(c0 + i < C ? c0 + i : C - 1) * 64 + lane];
@@ -2052,10 +2055,19 @@ int launch_batched(ds_ctx* ctx, const BatchedLayout& bl, const BatchedArgs& b, i
   void (*kern)(BatchedArgs);
   if (EXT) {  // (external inputs: neither the degrees nor the local CSR are kept in LDS)
     kern = b.ext_paired ? masked_gcn_eval_batched_kernel<false, false, EXT, EXT> : masked_gcn_eval_batched_kernel<false, false, EXT, false>;
-  } else if (bl.deg_lds && bl.csr_lds) kern = masked_gcn_eval_batched_kernel<true, true, false>;
-  else if (bl.deg_lds) kern = masked_gcn_eval_batched_kernel<true, false, false>;
-  else if (bl.csr_lds) kern = masked_gcn_eval_batched_kernel<false, true, false>;
-  else kern = masked_gcn_eval_batched_kernel<false, false, false>;
+  } else if (bl.csr_lds) {
+    kern = bl.deg_lds ? masked_gcn_eval_batched_kernel<true, true, false> : masked_gcn_eval_batched_kernel<false, true, false>;
+  } else {
+    // Masks on chip, the CSR in memory: a step's look-ups are three loads in a row. Where the later layers are a few items a wave, nothing
+    // else hides them and the next step's are worth requesting ahead (10,000 players, 28 items on 16 waves: 5,000 rows 290 -> 278 us, 500 rows
+    // 260 -> 248; 56 items 379 -> 372); with more, waves hide them from each other and those behind every row's last step are
+    // work for nobody (112 items 604 -> 615; a hub target of 10,000 players, 2,000 rows 2.60 -> 2.74 ms). The order of the sums is one.
+    int items = 0;   // of the layer that has most
+    for (int l = 2; l <= b.e.L; ++l) items = std::max(items, b.e.rows_out[l] * ((b.e.dims[l - 1] + 15) / 16));
+    const bool ahead = b.e.n > 0 && items <= 4 * (batched_threads<false>() / 64);
+    if (bl.deg_lds) kern = ahead ? masked_gcn_eval_batched_kernel<true, false, false> : masked_gcn_eval_batched_kernel<true, false, false, false, false>;
+    else kern = ahead ? masked_gcn_eval_batched_kernel<false, false, false> : masked_gcn_eval_batched_kernel<false, false, false, false, false>;
+  }
   if (EXT && (bl.deg_lds || bl.csr_lds)) return ds_fail(ctx, DS_EINTERNAL, "eval: external inputs with on-chip degrees or CSR");
   if (bl.lds_bytes > 48 * 1024)
     DS_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bl.lds_bytes));

@@ -494,6 +494,26 @@ def test_masked_inference_csr_outside_of_lds(nodes, edges, dims):
     _eval_case(w, 3, False, 1, biases, 322, rng)
 
 
+# ... with as many (row, 16 features) items as one look-ahead loop takes (64: four to a wave) and more, degrees in LDS and in memory
+@pytest.mark.parametrize("nodes,edges", [(640, 5000), (900, 8200)])
+@pytest.mark.parametrize("kids,dims", [(15, (6, 64, 33, 3)), (16, (6, 64, 16, 12)), (15, (6, 49, 100, 5)), (21, (6, 33, 65, 40))])
+def test_masked_inference_csr_outside_of_lds_by_items(nodes, edges, kids, dims):
+    from synth import csr_from_undirected_edges
+    from synth.workloads import Workload, glorot_uniform
+    rng = np.random.default_rng(edges + kids)
+    near = np.arange(1, kids + 1)
+    u, v = rng.integers(1, nodes, edges), rng.integers(kids + 1, nodes, edges)
+    rp, ci = csr_from_undirected_edges(nodes, np.r_[np.zeros(kids, np.int64), u[u != v]], np.r_[near, v[u != v]])
+    n = len(ci) // 2
+    assert 4096 < n < 12_288 and 512 * ((n + 63) // 64) + (128 * nodes if nodes <= 640 else 0) + 8 * len(ci) + 16384 > 160 * 1024
+    assert ((kids + 1) * ((dims[1] + 15) // 16) <= 64) == (kids == 15)
+    w = Workload("csr in memory", nodes, rp, ci, rng.standard_normal((nodes, dims[0]), dtype=np.float32), dims,
+                 [glorot_uniform(rng, dims[i], dims[i + 1]) for i in range(3)], [0], 0, 0, "gram_chol")
+    biases = [0.1 * rng.standard_normal(d).astype(np.float32) for d in dims[1:]]
+    say(f"masked inference CSR in memory nodes={nodes} players={n} items={(kids + 1) * ((dims[1] + 15) // 16)}")
+    _eval_case(w, 3, False, 1, biases, 322, rng)
+
+
 # a row's own term stays what it is where the row's features are infinite: the slots that fill up the last step of a row
 # (steps of 2, 4 and 8 entries) must not multiply it by a zero. One layer, so that no other row reads the target's.
 @pytest.mark.parametrize("leaves", [1, 2, 3, 4, 5, 6, 7, 8, 9, 21, 260, 301])
