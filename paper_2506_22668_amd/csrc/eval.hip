@@ -1732,10 +1732,8 @@ __global__ __launch_bounds__(kSThreads) void stream_degrees_kernel(StreamArgs a)
 // One wave per 32x32 tile of C = A[M x K] * B[K x Nn] (row-major, fp32 in memory).
 // MFMA 32x32x2 f32: lane l supplies A[row l%32][k l/32] and B[k l/32][col l%32]; the
 // accumulator register i of lane l is C[8*(i/4) + 4*(l/32) + i%4][l%32].
-// BF16: 32x32x8 bf16, lane l supplies k = 4*(l/32) .. +3.
 // Few tiles and a short loop: latency. Operands are requested 32 columns of A ahead, without branches (past the end from the last
 // row or column; what does not belong is multiplied as zero or not stored). 608 x 128 x 64: 28 -> 18 us.
-template <bool BF16>
 __global__ __launch_bounds__(kThreads) void first_transform_kernel(const float* A, const float* B, float* C, int M, int K, int Nn) {
   constexpr int kStep = 32;
   const int lane = threadIdx.x & 63;
@@ -1755,7 +1753,7 @@ __global__ __launch_bounds__(kThreads) void first_transform_kernel(const float* 
     float a[kStep / 2], b[kStep / 2];
   };
   // this lane's k of operand i of the step at k0
-  auto column = [&](int k0, int i) { return k0 + (BF16 ? 8 * (i >> 2) + 4 * half + (i & 3) : 2 * i + half); };
+  auto column = [&](int k0, int i) { return k0 + 2 * i + half; };
   auto load = [&](Ops& o, int k0) {
 #pragma unroll
     for (int i = 0; i < kStep / 2; ++i) {
@@ -1766,26 +1764,9 @@ __global__ __launch_bounds__(kThreads) void first_transform_kernel(const float* 
   };
   auto use = [&](const Ops& o, int k0) {
 #pragma unroll
-    for (int s = 0; s < kStep / 8; ++s) {
-      float x[4], w[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const bool ok = column(k0, 4 * s + u) < K;
-        x[u] = ok ? o.a[4 * s + u] : 0.f;
-        w[u] = ok ? o.b[4 * s + u] : 0.f;
-      }
-      if (BF16) {
-        short4_t av, bv;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          av[u] = bf16_bits(x[u]);
-          bv[u] = bf16_bits(w[u]);
-        }
-        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, bv, acc, 0, 0, 0);
-      } else {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[u], w[u], acc, 0, 0, 0);
-      }
+    for (int i = 0; i < kStep / 2; ++i) {
+      const bool ok = column(k0, i) < K;
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ok ? o.a[i] : 0.f, ok ? o.b[i] : 0.f, acc, 0, 0, 0);
     }
   };
   Ops o0, o1;
@@ -2099,13 +2080,10 @@ int ds_static_scratch_init(int device) {
 
 void* ds_static_scratch(int device) { return device >= 0 && device < DS_MAX_DEVICES ? g_scratch_ptr[device] : nullptr; }
 
-int ds_launch_first_transform(ds_ctx* ctx, const float* A, const float* B, float* C, int M, int K, int Nn, int bf16) {
+int ds_launch_first_transform(ds_ctx* ctx, const float* A, const float* B, float* C, int M, int K, int Nn) {
   const int tiles = ((M + 31) / 32) * ((Nn + 31) / 32);
   const int blocks = (tiles + kWaves - 1) / kWaves;
-  if (bf16)
-    hipLaunchKernelGGL((first_transform_kernel<true>), dim3(blocks), dim3(kThreads), 0, ctx->stream, A, B, C, M, K, Nn);
-  else
-    hipLaunchKernelGGL((first_transform_kernel<false>), dim3(blocks), dim3(kThreads), 0, ctx->stream, A, B, C, M, K, Nn);
+  hipLaunchKernelGGL(first_transform_kernel, dim3(blocks), dim3(kThreads), 0, ctx->stream, A, B, C, M, K, Nn);
   DS_HIP(ctx, hipGetLastError());
   return DS_OK;
 }
@@ -2170,7 +2148,7 @@ int ds_prepare_model(ds_ctx* ctx, ds_cgraph* cg) {
   if (cg->d1 != ctx->dims[1]) return ds_fail(ctx, DS_EINVAL, "the computational graph was extracted for a model with first hidden width %d (now %d): extract again", cg->d1, ctx->dims[1]);
   // The shared product is formed once per target and feeds every coalition: it stays in fp32 also in the
   // reduced-precision configuration (only the per-coalition transforms round their operands to bfloat16).
-  DS_TRY(ds_launch_first_transform(ctx, cg->Xc, ctx->W[0], cg->P, (int)cg->info.num_nodes, ctx->dims[0], ctx->dims[1], 0));
+  DS_TRY(ds_launch_first_transform(ctx, cg->Xc, ctx->W[0], cg->P, (int)cg->info.num_nodes, ctx->dims[0], ctx->dims[1]));
   // predicted class: evaluate the full coalition once and take the first maximum
   const int64_t n = cg->info.num_players;
   const int64_t W = (n + 63) / 64;

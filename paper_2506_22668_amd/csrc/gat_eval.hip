@@ -942,7 +942,7 @@ int ds_gat_prepare_model(ds_ctx* ctx, ds_cgraph* cg) {
   if (cg->d1 != ctx->gat.zw[0] || cg->att_heads != H)
     return ds_fail(ctx, DS_EINVAL, "the computational graph was extracted for another model (first transform width %d, now %d): extract again", cg->d1, ctx->gat.zw[0]);
   const int V = (int)cg->info.num_nodes;
-  DS_TRY(ds_launch_first_transform(ctx, cg->Xc, ctx->W[0], cg->P, V, ctx->dims[0], ctx->gat.zw[0], 0));
+  DS_TRY(ds_launch_first_transform(ctx, cg->Xc, ctx->W[0], cg->P, V, ctx->dims[0], ctx->gat.zw[0]));
   hipLaunchKernelGGL(gat_att_scalars_kernel, dim3((V * H + 255) / 256), dim3(256), 0, ctx->stream, cg->P,
                      ctx->gat.att_src[0], ctx->gat.att_dst[0], V, H, F, cg->att);
   DS_HIP(ctx, hipGetLastError());

@@ -195,7 +195,7 @@ static inline int32_t ds_first_width(const ds_ctx* ctx) {
   return ctx->model_kind == DS_MODEL_GAT ? ctx->gat.zw[0] : ctx->dims[1];
 }
 // small launchers shared by the two model families (defined next to the GCN kernels)
-int ds_launch_first_transform(ds_ctx* ctx, const float* A, const float* B, float* C, int M, int K, int Nn, int bf16);
+int ds_launch_first_transform(ds_ctx* ctx, const float* A, const float* B, float* C, int M, int K, int Nn);
 int ds_launch_full_mask(ds_ctx* ctx, uint64_t* z, int64_t W, int64_t n);
 int ds_launch_argmax(ds_ctx* ctx, const float* logits, int C, int32_t* out);
 // GAT counterparts of the three functions above (same contracts)

@@ -274,7 +274,7 @@ def test_first_transform_matches_matmul(key, dtype, tol):
 # products in fp32 is within d0 * 2^-24 of its terms' magnitudes
 @pytest.mark.parametrize("nodes,d0,d1", [(2, 1, 1), (31, 8, 33), (33, 31, 32), (64, 32, 31), (65, 33, 64), (90, 63, 65),
                                          (40, 64, 5), (40, 65, 97), (33, 97, 3), (129, 128, 33), (70, 130, 40)])
-def test_first_transform_odd_widths(nodes, d0, d1):
+def test_first_transform_odd_widths(nodes, d0, d1, transform_dtype=0):
     from synth import csr_from_undirected_edges
     from paper_2506_22668_amd import Context, Options
     rng = np.random.default_rng(nodes + d0)
@@ -285,13 +285,19 @@ def test_first_transform_odd_widths(nodes, d0, d1):
     ctx = Context("cuda:0")
     ctx.set_graph(rp, ci)
     ctx.set_features(X)
-    ctx.set_gcn([W1])
+    ctx.set_gcn([W1], transform_dtype=transform_dtype)
     cg = ctx.extract(0, Options(hops=1))
     P = ctx.cgraph_first_transform(cg).cpu().numpy().astype(np.float64)
     bound = d0 * 2.0 ** -24 * (np.abs(X).astype(np.float64) @ np.abs(W1).astype(np.float64)) + 1e-30
     assert (np.abs(P - X.astype(np.float64) @ W1.astype(np.float64)) <= bound).all()
     ctx.cgraph_free(cg)
     ctx.close()
+
+
+# ... which the bfloat16 configuration does not round: the product is formed once per target and feeds every coalition
+@pytest.mark.parametrize("nodes,d0,d1", [(31, 8, 33), (65, 33, 64), (40, 65, 97), (70, 130, 40)])
+def test_first_transform_odd_widths_bf16(nodes, d0, d1):
+    test_first_transform_odd_widths(nodes, d0, d1, transform_dtype=1)
 
 
 # ---------------------------------------------------------------- masked inference
