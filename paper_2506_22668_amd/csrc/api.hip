@@ -668,35 +668,44 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   ctx->arena_used = mark;
   DS_HIP(ctx, hipEventRecord(ctx->ev[2], st));
 
-  // The Gram matrix and the system matrix of the direct solver need the masks and weights but not
-  // the model outputs: they are built on the side stream while the main stream runs the inference.
+  // The direct solver's matrix needs the masks and weights but not the model outputs: it is built on the side stream
+  // while the main stream runs the inference, and small ones (chains of launches of a few workgroups) are factorised
+  // there too; the right-hand side follows with a forward solve. The inference is queued first: its workgroups are the
+  // ones that the call waits for, and the host needs some 100 us for the launches of the other chain.
   const bool direct = n >= 2 && (o.solver == DS_SOLVER_GRAM_CHOL || (o.solver == DS_SOLVER_AUTO && n <= 16384));
+  const bool ahead = direct && ds_gram_ahead_applies(n);
   ds_gram_state gs;
   if (direct) {
+    DS_TRY(ds_gram_alloc(ctx, n, k, 1, &gs));   // (stays allocated below `mark2`)
     DS_HIP(ctx, hipEventRecord(ctx->fork2_ev, st));
     DS_HIP(ctx, hipStreamWaitEvent(ctx->side, ctx->fork2_ev, 0));
-    ctx->stream = ctx->side;
-    const int grc = ds_gram_begin(ctx, n, k, Z, w, 1, &gs);  // its buffers stay allocated below `mark2`
-    ctx->stream = st;
-    DS_TRY(grc);
-    DS_HIP(ctx, hipEventRecord(ctx->join2_ev, ctx->side));
   }
   const size_t mark2 = ctx->arena_used;
 
   DS_HIP(ctx, hipStreamWaitEvent(st, ctx->join_ev, 0));
   ctx->lists = lists;
-  const int erc = ds_eval_impl(ctx, cg, Z, k, o.score, y, DS_EVAL_PAIRED, n >= 2 ? sz : nullptr);  // the sampler's rows are complementary pairs
+  const int erc = ds_eval_impl(ctx, cg, Z, k, o.score, y, DS_EVAL_PAIRED | (ahead ? DS_EVAL_BESIDE : 0), n >= 2 ? sz : nullptr);  // the sampler's rows are complementary pairs
   ctx->lists = ds_pair_lists{};
   DS_TRY(erc);
   ctx->arena_used = mark2;
   DS_HIP(ctx, hipEventRecord(ctx->ev[3], st));
+  if (direct) {
+    ctx->stream = ctx->side;
+    int grc = ds_gram_begin(ctx, &gs, Z, w);
+    if (grc == DS_OK && hipEventRecord(ctx->join_ev, ctx->side) != hipSuccess) grc = ds_fail(ctx, DS_EDEVICE, "cannot record an event");
+    if (grc == DS_OK && ahead) grc = ds_gram_factor_ahead(ctx, &gs, ctx->fork2_ev);
+    ctx->stream = st;
+    DS_TRY(grc);
+    DS_HIP(ctx, hipEventRecord(ctx->join2_ev, ctx->side));
+  }
 
   int rc = DS_OK;
   if (n == 1) {
     hipLaunchKernelGGL(single_player_kernel, dim3(1), dim3(1), 0, st, y, phi);
   } else if (direct) {
-    DS_HIP(ctx, hipStreamWaitEvent(st, ctx->join2_ev, 0));
-    rc = ds_gram_finish(ctx, &gs, Z, w, y, phi, 1);  // the pivot flag comes back with the final read-back
+    DS_HIP(ctx, hipStreamWaitEvent(st, ctx->join_ev, 0));
+    // (the pivot flag comes back with the final read-back)
+    rc = ds_gram_finish(ctx, &gs, Z, w, y, phi, 1, ahead ? ctx->fork2_ev : nullptr, ahead ? ctx->join2_ev : nullptr);
     rep.solver_used = DS_SOLVER_GRAM_CHOL;
   } else {
     rc = solve_dispatch(ctx, n, k, Z, w, y, o, 1, phi, &rep);

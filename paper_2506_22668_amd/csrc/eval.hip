@@ -2303,6 +2303,12 @@ int ds_eval_impl(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, int s
     // a bounded workspace (the entry point that may not allocate) runs fewer workgroups at a time instead of failing
     const size_t avail = ctx->arena_bytes - ctx->arena_used > 512 ? ctx->arena_bytes - ctx->arena_used - 512 : 0;
     int bgrid = bl.grid;
+    if ((flags & DS_EVAL_BESIDE) && !bl.ext) {
+      // a block fills a compute unit: as many as the whole GPU would run one after the other on each, on fewer units
+      const int64_t blocks = (k + 63) / 64, rounds = (blocks + ctx->num_cus - 1) / ctx->num_cus;
+      const int even = (int)((blocks + rounds - 1) / rounds);
+      if (bgrid > even) bgrid = even;
+    }
     if (bounded) {
       const size_t fit = avail / ((size_t)bl.stride * 4);
       if (fit < 1) return ds_fail(ctx, DS_ECAPACITY, "eval: one workgroup needs %zu bytes of scratch, %zu are left", (size_t)bl.stride * 4, avail);

@@ -983,7 +983,7 @@ __global__ __launch_bounds__(kThreads) void chol_update_kernel(double* M, int64_
   __syncthreads();
   if (FUSE && ti == 0 && tj == 0) {  // Lj holds the rows of the next diagonal block in this panel (zero past column n)
     // a short last block shares its tile with the right-hand-side row, which still needs this update
-    if (n - base < NB && (int64_t)threadIdx.x < n - base) {
+    if (rows_total > n && n - base < NB && (int64_t)threadIdx.x < n - base) {
       const int rr = (int)(n - base), c = threadIdx.x;
       double sum = 0.0;
       for (int k = 0; k < NB; ++k) sum += Li[rr][k] * Lj[c][k];
@@ -1057,7 +1057,7 @@ __global__ __launch_bounds__(kThreads) void chol_step_kernel(double* M, int64_t 
   __syncthreads();
   if (ti == 0) {  // tj == 0 too: the next diagonal block
     // a short last block shares its tile with the right-hand-side row, which still needs this update
-    if (n - base < NB && (int64_t)threadIdx.x < n - base) {
+    if (rows_total > n && n - base < NB && (int64_t)threadIdx.x < n - base) {
       const int rr = (int)(n - base), c = threadIdx.x;
       double sum = 0.0;
       for (int k = 0; k < NB; ++k) sum += Li[rr][k] * Lj[c][k];
@@ -1329,97 +1329,161 @@ __global__ __launch_bounds__(kWideThreads, 2) void chol_update_wide_kernel(doubl
 }
 
 
-// L^T psi = y (y = row n of M after the factorisation, worked on in place), 256 unknowns per launch from the end, phi =
-// psi + (y1 - y0)/n. Every workgroup solves the launch's unknowns itself, 64 at a time from the stored inverses of the
-// diagonal blocks (psi_c = sum_{r >= c} Linv[r][c] y_r, then their contribution leaves the entries of the 64s below),
-// and removes the contribution of all 256 from its own 64 of the earlier entries. What bounds it is latency: a chain
-// of launches, and four dependent 64 x 64 products in each, whose operands are therefore requested one product ahead.
-// (One launch per 64 unknowns: 6,007 unknowns 787 us, now 323; a single workgroup for all of up to 2,048: 1,010 unknowns 111 us,
-// now 50.) Sums have a fixed order.
+// Triangular solves with the factor, kSolveBlocks * 64 unknowns per launch (BLOCKS blocks of 64 from column J on). Every workgroup
+// solves the launch's unknowns itself from the stored inverses of the diagonal blocks, then takes their contribution off
+// its own 64 entries of v that are still to be solved. What bounds them is latency: a chain of launches, in each eight dependent
+// products of a 64 x 64 tile with a vector. All of a thread's matrix entries (8 per tile, 14 tiles) are therefore requested before the
+// first product, and partial sums stay in registers until their block's turn. Sums have a fixed order.
 constexpr int64_t kFuseMaxRows = 2048;
-constexpr int kBackBlocks = 4;                    // diagonal blocks per launch
-constexpr int kBackPer = NB * NB / kThreads;      // entries of a 64 x 64 block per thread
-__global__ __launch_bounds__(kThreads) void chol_back_kernel(double* M, int64_t ld, int64_t n, int64_t J, int blocks,
-                                                             const double* linv, const float* y01, float* phi) {
-  constexpr int kParts = kThreads / NB;           // rows of a block go to the threads of a column in turn
-  __shared__ double ys[kBackBlocks * NB];         // right-hand side of the launch's blocks, then their unknowns
-  __shared__ double part[kParts][kBackBlocks * NB];
-  const int tid = threadIdx.x, c = tid & (NB - 1), g = tid / NB;
-  double* const y = M + n * ld;
-  const double shift = ((double)y01[1] - (double)y01[0]) / (double)n;
-  // a thread's entries of a block with rows r0 .. and columns c0 .. (rows past n are read from row n - 1 and meet zeros)
-  auto fetch = [&](double (&v)[kBackPer], int64_t r0, int64_t c0) {
+constexpr int kSolveBlocks = 4;                    // diagonal blocks per launch
+constexpr int kSolveThreads = 512;
+constexpr int kSolvePer = NB * NB / kSolveThreads; // entries of a 64 x 64 tile per thread: one output, eight terms
+
+// sum over the eight neighbouring lanes that share lane / 8, in all of them
+__device__ __forceinline__ double sum_of_8_lanes(double a) {
+#define DS_DPP_ADD(ctrl)                                                                          \
+  a += __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(a), ctrl, 0xf, 0xf, false), \
+                        __builtin_amdgcn_update_dpp(0, __double2loint(a), ctrl, 0xf, 0xf, false))
+  DS_DPP_ADD(0xb1);    // quad_perm [1,0,3,2]
+  DS_DPP_ADD(0x4e);    // quad_perm [2,3,0,1]
+  DS_DPP_ADD(0x141);   // row_half_mirror
+#undef DS_DPP_ADD
+  return a;
+}
+
+// L x = v from the front, out = x (for a factorisation that ran without the right-hand side as its row n). Eight neighbouring lanes
+// share a row of a tile, 16 bytes each at a time, and fold its sum by three DPP moves.
+template <int BLOCKS>
+__global__ __launch_bounds__(kSolveThreads) void chol_forward_kernel(const double* M, int64_t ld, int64_t n, int64_t J,
+                                                                     const double* linv, double* v, double* out) {
+  __shared__ __align__(16) double xs[NB];
+  __shared__ __align__(16) double ys[BLOCKS][NB];
+  typedef double pair_t __attribute__((ext_vector_type(2)));
+  const int tid = threadIdx.x, o = tid >> 3, q = tid & 7;   // row of a tile, share of its columns
+  struct Terms { pair_t a[kSolvePer / 2]; };
+  auto fetch = [&](Terms& t, const double* A, int64_t stride, int64_t row0, int64_t rows, int64_t col0) {
+    // (rows past n are read from row n - 1; their sums are not used)
+    const double* row = A + (row0 + o < rows ? row0 + o : rows - 1) * stride + col0 + 2 * q;
 #pragma unroll
-    for (int i = 0; i < kBackPer; ++i) {
-      const int64_t r = r0 + g + kParts * i;
-      v[i] = M[(r < n ? r : n - 1) * ld + c0 + c];
-    }
+    for (int i = 0; i < kSolvePer / 2; ++i) t.a[i] = *(const pair_t*)(row + 16 * i);
   };
-  auto fetch_inverse = [&](double (&v)[kBackPer], int b) {
-    const double* li = linv + (size_t)(J / NB + b) * NB * NB;
-#pragma unroll
-    for (int i = 0; i < kBackPer; ++i) v[i] = li[(g + kParts * i) * NB + c];   // (identity-padded, zero above the diagonal)
-  };
-  auto dot = [&](const double (&v)[kBackPer], const double* x) {
+  auto dot = [&](const Terms& t, const double* x) {
     double s = 0.0;
 #pragma unroll
-    for (int i = 0; i < kBackPer; ++i) s += v[i] * x[g + kParts * i];
+    for (int i = 0; i < kSolvePer / 2; ++i) {
+      const pair_t w = *(const pair_t*)(x + 16 * i + 2 * q);
+      s += t.a[i].x * w.x;
+      s += t.a[i].y * w.y;
+    }
     return s;
   };
-  // this workgroup's 64 of the earlier entries (workgroup 0 of a launch without any: none)
-  const int64_t j0 = (int64_t)blockIdx.x * NB;
-  const bool earlier = j0 < J;
-  double li[kBackPer], lo[kBackBlocks - 1][kBackPer];
-  fetch_inverse(li, blocks - 1);
-  if (tid < blocks * NB) ys[tid] = J + tid < n ? y[J + tid] : 0.0;
-  __syncthreads();
-  for (int b = blocks - 1; b >= 0; --b) {
+  Terms inv[BLOCKS], in[BLOCKS][BLOCKS], rest[BLOCKS];
+  double rhs[BLOCKS], acc[BLOCKS];
+  const int64_t j0 = J + BLOCKS * NB + (int64_t)blockIdx.x * NB;
+  const bool more = j0 < n;   // (the last launch: workgroup 0 only, no entries left)
 #pragma unroll
-    for (int k = 0; k < kBackBlocks - 1; ++k)
-      if (k < b) fetch(lo[k], J + b * NB, J + k * NB);
-    part[g][c] = dot(li, ys + b * NB);
-    if (b > 0) fetch_inverse(li, b - 1);
+  for (int b = 0; b < BLOCKS; ++b) {
+    fetch(inv[b], linv + (size_t)(J / NB + b) * NB * NB, NB, 0, NB, 0);
+    const int64_t at = J + b * NB + o;
+    rhs[b] = at < n ? v[at] : 0.0;
+    acc[b] = 0.0;
+#pragma unroll
+    for (int c = b + 1; c < BLOCKS; ++c) fetch(in[b][c], M, ld, J + c * NB, n, J + b * NB);
+  }
+#pragma unroll
+  for (int b = 0; b < BLOCKS; ++b) {
+    const int64_t at = J + b * NB + o;
+    const double x = at < n ? rhs[b] - (b > 0 ? sum_of_8_lanes(acc[b]) : 0.0) : 0.0;
+    if (q == 0) xs[o] = x;
     __syncthreads();
-    if (tid < NB) {
-      double s = 0.0;
+    const double y = sum_of_8_lanes(dot(inv[b], xs));
+    if (q == 0) ys[b][o] = y;
+    if (q == 0 && blockIdx.x == 0 && at < n) out[at] = y;
+    if (more) fetch(rest[b], M, ld, j0, n, J + b * NB);   // (the remaining steps hide it)
+    __syncthreads();
 #pragma unroll
-      for (int q = 0; q < kParts; ++q) s += part[q][tid];
-      ys[b * NB + tid] = s;
-      const int64_t at = J + b * NB + tid;
+    for (int c = b + 1; c < BLOCKS; ++c) acc[c] += dot(in[b][c], ys[b]);
+  }
+  if (!more) return;
+  double sum = 0.0;
+#pragma unroll
+  for (int b = 0; b < BLOCKS; ++b) sum += dot(rest[b], ys[b]);
+  sum = sum_of_8_lanes(sum);
+  if (q == 0 && j0 + o < n) v[j0 + o] -= sum;
+}
+
+// L^T psi = v from the end, phi = psi + (y1 - y0)/n. A wave reads whole rows of a tile (lane = column), and the eight waves'
+// partial sums meet in LDS: lanes that share a column, as in the forward solve, would read 64 bytes of a row each (a launch then
+// takes 20 us instead of 13).
+template <int BLOCKS>
+__global__ __launch_bounds__(kSolveThreads) void chol_back_kernel(const double* M, int64_t ld, int64_t n, int64_t J,
+                                                                  const double* linv, double* v, const float* y01, float* phi) {
+  constexpr int kWavesHere = kSolveThreads / NB;
+  __shared__ double xs[NB];
+  __shared__ double ys[BLOCKS][NB];
+  __shared__ double part[kWavesHere][NB];
+  const int tid = threadIdx.x, c = tid & (NB - 1), g = tid / NB;   // column of a tile, first of its rows
+  struct Terms { double a[kSolvePer]; };
+  auto fetch = [&](Terms& t, const double* A, int64_t stride, int64_t row0, int64_t rows, int64_t col0) {
+#pragma unroll
+    for (int i = 0; i < kSolvePer; ++i) {   // (rows past n are read from row n - 1 and meet zeros)
+      const int64_t r = row0 + g + kWavesHere * i;
+      t.a[i] = A[(r < rows ? r : rows - 1) * stride + col0 + c];
+    }
+  };
+  auto dot = [&](const Terms& t, const double* x) {
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < kSolvePer; ++i) s += t.a[i] * x[g + kWavesHere * i];
+    return s;
+  };
+  auto folded = [&]() {   // the first wave: the sum of the partial sums of its lane's column
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWavesHere; ++w) s += part[w][c];
+    return s;
+  };
+  Terms inv[BLOCKS], in[BLOCKS][BLOCKS], rest[BLOCKS];
+  double rhs[BLOCKS], acc[BLOCKS];
+  const int64_t j0 = (int64_t)blockIdx.x * NB;
+  const bool more = j0 < J;   // (the last launch: workgroup 0 only, no entries left)
+#pragma unroll
+  for (int b = BLOCKS - 1; b >= 0; --b) {
+    fetch(inv[b], linv + (size_t)(J / NB + b) * NB * NB, NB, 0, NB, 0);   // (identity-padded, zero above the diagonal)
+    rhs[b] = J + b * NB + c < n ? v[J + b * NB + c] : 0.0;
+    acc[b] = 0.0;
+#pragma unroll
+    for (int k = b - 1; k >= 0; --k) fetch(in[b][k], M, ld, J + b * NB, n, J + k * NB);
+  }
+  const double shift = ((double)y01[1] - (double)y01[0]) / (double)n;
+#pragma unroll
+  for (int b = BLOCKS - 1; b >= 0; --b) {
+    if (b < BLOCKS - 1) {
+      part[g][c] = acc[b];
+      __syncthreads();
+    }
+    if (g == 0) xs[c] = b < BLOCKS - 1 ? rhs[b] - folded() : rhs[b];
+    __syncthreads();
+    part[g][c] = dot(inv[b], xs);
+    if (more) fetch(rest[b], M, ld, J + b * NB, n, j0);   // (the remaining steps hide it)
+    __syncthreads();
+    if (g == 0) {
+      const double s = folded();
+      ys[b][c] = s;
+      const int64_t at = J + b * NB + c;
       if (blockIdx.x == 0 && at < n) phi[at] = (float)(s + shift);
     }
     __syncthreads();
-    if (b > 0) {
 #pragma unroll
-      for (int k = 0; k < kBackBlocks - 1; ++k)
-        if (k < b) part[g][k * NB + c] = dot(lo[k], ys + b * NB);
-      __syncthreads();
-      if (tid < b * NB) {
-        double s = 0.0;
+    for (int k = b - 1; k >= 0; --k) acc[k] += dot(in[b][k], ys[b]);
+  }
+  if (!more) return;
+  double sum = 0.0;
 #pragma unroll
-        for (int q = 0; q < kParts; ++q) s += part[q][tid];
-        ys[tid] -= s;
-      }
-      __syncthreads();
-    }
-  }
-  if (!earlier) return;
-  double s = 0.0;
-  for (int b = 0; b < blocks; b += 2) {   // two blocks' loads in flight
-    double v0[kBackPer], v1[kBackPer];
-    fetch(v0, J + b * NB, j0);
-    if (b + 1 < blocks) fetch(v1, J + (b + 1) * NB, j0);
-    s += dot(v0, ys + b * NB);
-    if (b + 1 < blocks) s += dot(v1, ys + (b + 1) * NB);
-  }
-  part[g][c] = s;
+  for (int b = BLOCKS - 1; b >= 0; --b) sum += dot(rest[b], ys[b]);
+  part[g][c] = sum;
   __syncthreads();
-  if (tid < NB) {
-    double t = 0.0;
-#pragma unroll
-    for (int q = 0; q < kParts; ++q) t += part[q][tid];
-    y[j0 + tid] -= t;
-  }
+  if (g == 0) v[j0 + c] -= folded();
 }
 
 inline float dense_fraction(const ds_ctx* ctx) {
@@ -1472,31 +1536,29 @@ size_t ds_gram_arena_bytes(int64_t n, int64_t k) {
          ds_align((size_t)((n + 63) / 64) * d.R * 8 + 8) + ds_align((size_t)d.RW * 8 + 8) + ds_align((size_t)d.R * 8 + 8) + 256;
 }
 
-// Part 1: everything that does not need the model outputs y (Gram matrix, projection, system matrix).
-// It may run on another stream than part 2, concurrently with the masked inference.
-int ds_gram_begin(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const float* w, int paired, ds_gram_state* gs) {
-  hipStream_t st = ctx->stream;
+// The buffers of all parts, from one contiguous region of the arena.
+int ds_gram_alloc(ds_ctx* ctx, int64_t n, int64_t k, int paired, ds_gram_state* gs) {
   if (paired && (k & 1)) return ds_fail(ctx, DS_EINVAL, "paired rows need an even row count");
   const int64_t W = (n + 63) / 64;
   const GramDims d = gram_dims(n, k, paired, ctx->num_cus);
   const int64_t R = d.R, RW = d.RW, ld = d.ld;
   gs->n = n; gs->k = k; gs->R = R; gs->RW = RW; gs->ld = ld; gs->nblk = d.nblk; gs->paired = paired;
   gs->Zt = (uint64_t*)ds_arena_alloc(ctx, (size_t)n * RW * 8);
-  double* Gp = (double*)ds_arena_alloc(ctx, (size_t)d.slices * n * n * 8);
+  gs->slices = d.slices; gs->words_per_slice = d.words_per_slice;
+  gs->Gp = (double*)ds_arena_alloc(ctx, (size_t)d.slices * n * n * 8);
   gs->M = (double*)ds_arena_alloc(ctx, (size_t)(n + 1) * ld * 8);
   gs->linv = (double*)ds_arena_alloc(ctx, (size_t)d.nblk * NB * NB * 8);
   gs->panel[0] = (double*)ds_arena_alloc(ctx, panel_bytes(n));
   gs->panel[1] = (double*)ds_arena_alloc(ctx, panel_bytes(n));
-  float* gw = (float*)ds_arena_alloc(ctx, R * 4);
-  float* wu = (float*)ds_arena_alloc(ctx, RW * 4);
-  int32_t* uni = (int32_t*)ds_arena_alloc(ctx, RW * 4);
-  double* m = (double*)ds_arena_alloc(ctx, n * 8);
-  double* stats = (double*)ds_arena_alloc(ctx, 64);
-  uint64_t* Zc = (uint64_t*)ds_arena_alloc(ctx, (size_t)W * R * 8 + 8);
-  uint64_t* keep = (uint64_t*)ds_arena_alloc(ctx, (size_t)RW * 8 + 8);
-  uint64_t* wq = (uint64_t*)ds_arena_alloc(ctx, (size_t)R * 8 + 8);
-  double* gscale = (double*)ds_arena_alloc(ctx, 64);
-  // buffers of part 2, reserved here so that both parts draw from one contiguous region
+  gs->gw = (float*)ds_arena_alloc(ctx, R * 4);
+  gs->wu = (float*)ds_arena_alloc(ctx, RW * 4);
+  gs->uni = (int32_t*)ds_arena_alloc(ctx, RW * 4);
+  gs->m = (double*)ds_arena_alloc(ctx, n * 8);
+  gs->stats = (double*)ds_arena_alloc(ctx, 64);
+  gs->Zc = (uint64_t*)ds_arena_alloc(ctx, (size_t)W * R * 8 + 8);
+  gs->keep = (uint64_t*)ds_arena_alloc(ctx, (size_t)RW * 8 + 8);
+  gs->wq = (uint64_t*)ds_arena_alloc(ctx, (size_t)R * 8 + 8);
+  gs->gscale = (double*)ds_arena_alloc(ctx, 64);
   gs->sz = (int32_t*)ds_arena_alloc(ctx, k * 4);
   gs->wc = (float*)ds_arena_alloc(ctx, k * 4);
   gs->t = (double*)ds_arena_alloc(ctx, k * 8);
@@ -1504,9 +1566,23 @@ int ds_gram_begin(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const fl
   gs->gc = (double*)ds_arena_alloc(ctx, R * 8);
   gs->c = (double*)ds_arena_alloc(ctx, n * 8);
   gs->flag = (int*)ds_arena_alloc(ctx, 64);
-  if (!gs->Zt || !Gp || !gs->M || !gs->linv || !gs->panel[0] || !gs->panel[1] || !gw || !wu || !uni || !m || !stats || !Zc || !keep || !wq || !gscale || !gs->sz || !gs->wc || !gs->t ||
-      !gs->sqw || !gs->gc || !gs->c || !gs->flag)
+  if (!gs->Zt || !gs->Gp || !gs->M || !gs->linv || !gs->panel[0] || !gs->panel[1] || !gs->gw || !gs->wu || !gs->uni || !gs->m ||
+      !gs->stats || !gs->Zc || !gs->keep || !gs->wq || !gs->gscale || !gs->sz || !gs->wc || !gs->t || !gs->sqw || !gs->gc || !gs->c ||
+      !gs->flag)
     return ds_fail(ctx, DS_EINTERNAL, "gram: arena exhausted");
+  return DS_OK;
+}
+
+// Part 1: everything that does not need the model outputs y (Gram matrix, projection, system matrix, first diagonal block).
+// It may run on another stream than part 3, concurrently with the masked inference.
+int ds_gram_begin(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, const float* w) {
+  hipStream_t st = ctx->stream;
+  const int64_t n = gs->n, R = gs->R, RW = gs->RW, ld = gs->ld, W = (n + 63) / 64;
+  const int paired = gs->paired;
+  float *gw = gs->gw, *wu = gs->wu;
+  int32_t* uni = gs->uni;
+  double *Gp = gs->Gp, *m = gs->m, *stats = gs->stats, *gscale = gs->gscale;
+  uint64_t *Zc = gs->Zc, *keep = gs->keep, *wq = gs->wq;
   hipLaunchKernelGGL(used_row_weights_kernel, dim3(nblocks(R, 256)), dim3(256), 0, st, w, R, paired, gw);
   DS_TRY(ds_bit_transpose(ctx, Z, R, n, W, 0, paired ? 2 : 1, gs->Zt));
   // sparse rows: row-wise outer products into slice 0; the rest (bits in `keep`) column-wise on top of it
@@ -1525,11 +1601,11 @@ int ds_gram_begin(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const fl
   DS_TRY(ds_kernel_mark(ctx, 1, 0));
   hipLaunchKernelGGL(gram_rows_kernel, dim3(tiles, tiles), dim3(kThreads), 0, st, Zc, (const unsigned long long*)wq, R, n,
                      gscale, Gp);
-  hipLaunchKernelGGL(gram_kernel, dim3(tiles, tiles, d.slices), dim3(kThreads), 0, st, gs->Zt, n, R, RW, gw, wu, uni, keep,
-                     Gp, d.words_per_slice);
+  hipLaunchKernelGGL(gram_kernel, dim3(tiles, tiles, gs->slices), dim3(kThreads), 0, st, gs->Zt, n, R, RW, gw, wu, uni, keep,
+                     Gp, gs->words_per_slice);
   DS_TRY(ds_kernel_mark(ctx, 1, 1));
   const unsigned wblocks = (unsigned)(n < (int64_t)ctx->num_cus * 16 ? n : (int64_t)ctx->num_cus * 16);
-  hipLaunchKernelGGL(sum_slices_row_mean_kernel, dim3(wblocks), dim3(kThreads), 0, st, Gp, n, d.slices, m);
+  hipLaunchKernelGGL(sum_slices_row_mean_kernel, dim3(wblocks), dim3(kThreads), 0, st, Gp, n, gs->slices, m);
   hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(kThreads), 0, st, Gp, m, n, stats);
   hipLaunchKernelGGL(build_matrix_kernel, dim3(nblocks(n * n, 256)), dim3(256), 0, st, Gp, m, stats, n, ld, gs->M,
                      (double*)(gs->flag + 2));
@@ -1542,20 +1618,16 @@ int ds_gram_begin(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const fl
   return DS_OK;
 }
 
-// Part 2: right-hand side from y, factorisation (the right-hand side rides along as row n), back substitution.
-int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, const float* w, const float* y, float* phi,
-                    int defer_check) {
+// Part 2: the factorisation on ctx->stream (and, where the trailing matrix is large, the side stream). rows_total = n + 1: row n of
+// the matrix carries the right-hand side along, which leaves L^-1 rhs in it. rows_total = n: the factor alone; mid, if
+// not null, is recorded behind the last full group of kSolveBlocks blocks that is not the last group at all.
+static int gram_factor(ds_ctx* ctx, const ds_gram_state* gs, int64_t rows_total, hipEvent_t mid) {
   hipStream_t st = ctx->stream;
-  const int64_t n = gs->n, k = gs->k, R = gs->R, RW = gs->RW, ld = gs->ld;
+  const int64_t n = gs->n, ld = gs->ld;
   double* M = gs->M;
   double* linv = gs->linv;
-  DS_TRY(ds_row_prep(ctx, Z, k, n, gs->paired, w, y, gs->sz, gs->t, gs->sqw, gs->wc));
-  hipLaunchKernelGGL(used_row_rhs_kernel, dim3(nblocks(R, 256)), dim3(256), 0, st, gs->wc, gs->t, R, gs->paired, gs->gc);
-  DS_TRY(ds_bit_spmv(ctx, gs->Zt, n, R, RW, 0, 1, gs->gc, gs->c));  // c_j = sum over the rows containing j of gc
-  hipLaunchKernelGGL(build_rhs_kernel, dim3(1), dim3(kThreads), 0, st, gs->c, n, ld, M);
-  DS_HIP(ctx, hipGetLastError());
+  const int64_t mid_at = (gs->nblk - 1) / kSolveBlocks * kSolveBlocks * NB;
   DS_TRY(ds_kernel_mark(ctx, 2, 0));
-  const int64_t rows_total = n + 1;  // row n carries the right-hand side
   // While the trailing matrix is large the blocks are taken four at a time (a super-panel of 256 columns):
   // inside it the updates reach only the super-panel's own columns, and the rest of the trailing matrix is
   // updated once with all 256 columns. Below kFuseMaxRows trailing rows: one block per step, the update
@@ -1571,6 +1643,7 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
   int pbuf = 0;
   int64_t j0 = 0;
   while (j0 < n) {
+    if (mid && j0 == mid_at) DS_HIP(ctx, hipEventRecord(mid, st));   // (the launch before has left block j0 factorised)
     const bool super = rows_total - j0 - kSuperCols > kFuseMaxRows && n - j0 >= kSuperCols + NB;
     if (super) {
       if (chain == st) {   // the first one
@@ -1633,7 +1706,7 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
       j0 += nb;
       continue;
     }
-    hipLaunchKernelGGL(chol_panel_kernel, dim3(nblocks(rest, kTile)), dim3(kThreads), 0, st, M, ld, rows_total, j0, nb, li);
+    if (rest > 0) hipLaunchKernelGGL(chol_panel_kernel, dim3(nblocks(rest, kTile)), dim3(kThreads), 0, st, M, ld, rows_total, j0, nb, li);
     if (n - j0 - nb > 0) {
       const unsigned tt = nblocks(rest, kTile);
       if (rest <= kFuseMaxRows) {
@@ -1647,12 +1720,60 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
     }
     j0 += nb;
   }
-  DS_TRY(ds_kernel_mark(ctx, 2, 1));
-  for (int64_t last = gs->nblk; last > 0;) {   // blocks J / NB .. last - 1 per launch
-    const int64_t first = (last - 1) / kBackBlocks * kBackBlocks;
-    const int64_t J = first * NB;
-    hipLaunchKernelGGL(chol_back_kernel, dim3((unsigned)(first > 0 ? first : 1)), dim3(kThreads), 0, st, M, ld, n, J,
-                       (int)(last - first), linv, y, phi);
+  DS_HIP(ctx, hipGetLastError());
+  return ds_kernel_mark(ctx, 2, 1);
+}
+
+// one launch of a triangular solve: `blocks` blocks from column J on, `pieces` blocks of 64 entries still to be solved
+static void launch_forward(hipStream_t st, int blocks, int64_t pieces, const ds_gram_state* gs, int64_t J, double* v, double* out) {
+  static_assert(kSolveBlocks == 4, "one instance per number of blocks");
+  void (*const kern)(const double*, int64_t, int64_t, int64_t, const double*, double*, double*) =
+      blocks == 4 ? chol_forward_kernel<4> : blocks == 3 ? chol_forward_kernel<3> : blocks == 2 ? chol_forward_kernel<2> : chol_forward_kernel<1>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(pieces > 0 ? pieces : 1)), dim3(kSolveThreads), 0, st, gs->M, gs->ld, gs->n, J, gs->linv, v, out);
+}
+static void launch_back(hipStream_t st, int blocks, int64_t pieces, const ds_gram_state* gs, int64_t J, double* v, const float* y01,
+                        float* phi) {
+  void (*const kern)(const double*, int64_t, int64_t, int64_t, const double*, double*, const float*, float*) =
+      blocks == 4 ? chol_back_kernel<4> : blocks == 3 ? chol_back_kernel<3> : blocks == 2 ? chol_back_kernel<2> : chol_back_kernel<1>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(pieces > 0 ? pieces : 1)), dim3(kSolveThreads), 0, st, gs->M, gs->ld, gs->n, J, gs->linv, v, y01,
+                     phi);
+}
+
+// Whether a factorisation may run beside the inference, ahead of the right-hand side: no super-panels, whose wide updates fill the
+// GPU and want the main stream.
+bool ds_gram_ahead_applies(int64_t n) { return n - kSuperCols <= kFuseMaxRows; }
+
+// Part 2 without the right-hand side (ds_gram_ahead_applies); `mid` as for gram_factor.
+int ds_gram_factor_ahead(ds_ctx* ctx, const ds_gram_state* gs, hipEvent_t mid) { return gram_factor(ctx, gs, gs->n, mid); }
+
+// Part 3: right-hand side from y, factorisation (unless it runs ahead on another stream: `mid` and `done` are its events), back
+// substitution.
+int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, const float* w, const float* y, float* phi,
+                   int defer_check, hipEvent_t mid, hipEvent_t done) {
+  hipStream_t st = ctx->stream;
+  const int64_t n = gs->n, k = gs->k, R = gs->R, RW = gs->RW, ld = gs->ld;
+  DS_TRY(ds_row_prep(ctx, Z, k, n, gs->paired, w, y, gs->sz, gs->t, gs->sqw, gs->wc));
+  hipLaunchKernelGGL(used_row_rhs_kernel, dim3(nblocks(R, 256)), dim3(256), 0, st, gs->wc, gs->t, R, gs->paired, gs->gc);
+  DS_TRY(ds_bit_spmv(ctx, gs->Zt, n, R, RW, 0, 1, gs->gc, gs->c));  // c_j = sum over the rows containing j of gc
+  hipLaunchKernelGGL(build_rhs_kernel, dim3(1), dim3(kThreads), 0, st, gs->c, n, ld, gs->M);
+  DS_HIP(ctx, hipGetLastError());
+  double* const rhs = gs->M + n * ld;
+  double* v = rhs;   // L^-1 rhs
+  if (done) {
+    v = gs->c;       // (the sums have gone into the right-hand side)
+    const int64_t groups = (gs->nblk + kSolveBlocks - 1) / kSolveBlocks;
+    for (int64_t g = 0; g < groups; ++g) {
+      if (g == 0 && groups > 1) DS_HIP(ctx, hipStreamWaitEvent(st, mid, 0));
+      if (g == groups - 1) DS_HIP(ctx, hipStreamWaitEvent(st, done, 0));
+      const int64_t first = g * kSolveBlocks, last = first + kSolveBlocks < gs->nblk ? first + kSolveBlocks : gs->nblk;
+      launch_forward(st, (int)(last - first), gs->nblk - last, gs, first * NB, rhs, v);
+    }
+  } else {
+    DS_TRY(gram_factor(ctx, gs, n + 1, nullptr));
+  }
+  for (int64_t last = gs->nblk; last > 0;) {   // blocks first .. last - 1 per launch
+    const int64_t first = (last - 1) / kSolveBlocks * kSolveBlocks;
+    launch_back(st, (int)(last - first), first, gs, first * NB, v, y, phi);
     last = first;
   }
   DS_HIP(ctx, hipGetLastError());
@@ -1667,6 +1788,7 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
 int ds_solve_gram_chol(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const float* w, const float* y, int paired,
                        float* phi) {
   ds_gram_state gs;
-  DS_TRY(ds_gram_begin(ctx, n, k, Z, w, paired, &gs));
-  return ds_gram_finish(ctx, &gs, Z, w, y, phi, 0);
+  DS_TRY(ds_gram_alloc(ctx, n, k, paired, &gs));
+  DS_TRY(ds_gram_begin(ctx, &gs, Z, w));
+  return ds_gram_finish(ctx, &gs, Z, w, y, phi, 0, nullptr, nullptr);
 }

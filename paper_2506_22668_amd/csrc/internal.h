@@ -173,6 +173,7 @@ int ds_validate_csr(ds_ctx* ctx);
 
 #define DS_EVAL_BOUNDED 1  // the workspace is not the context's own arena: fit the launch into what is there
 #define DS_EVAL_PAIRED 2   // rows 2r, 2r+1 are complementary pairs: only row 2r of each is read
+#define DS_EVAL_BESIDE 4   // the direct solver's matrix is built and factorised on another stream: leave it compute units
 // sz: coalition size of every row (the sampler's output) or nullptr
 int ds_eval_impl(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, int score, float* y, int flags,
                  const int32_t* sz = nullptr);
@@ -203,21 +204,27 @@ int ds_gat_prepare_model(ds_ctx* ctx, ds_cgraph* cg);
 int ds_gat_eval_impl(ds_ctx* ctx, ds_cgraph* cg, const uint64_t* Z, int64_t k, int score, float* y);
 size_t ds_gat_eval_arena_bytes(ds_ctx* ctx, const ds_cgraph* cg, int64_t k);
 
-// the direct solver in two parts: the first needs only the masks and weights
+// the direct solver in parts: the buffers, what needs only the masks and weights, the factorisation, what needs the model outputs
 struct ds_gram_state {
-  int64_t n, k, R, RW, ld, nblk;
-  int paired;
-  uint64_t* Zt;
-  double *M, *linv, *t, *sqw, *gc, *c;
+  int64_t n, k, R, RW, ld, nblk, words_per_slice;
+  int paired, slices;
+  uint64_t *Zt, *Zc, *keep, *wq;
+  double *Gp, *m, *stats, *gscale, *M, *linv, *t, *sqw, *gc, *c;
   double* panel[2];  // rows of the current and of the next 64-column panel (fused steps of the factorisation)
-  int32_t* sz;
-  float* wc;
+  int32_t *uni, *sz;
+  float *gw, *wu, *wc;
   int* flag;
 };
-int ds_gram_begin(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const float* w, int paired, ds_gram_state* gs);
-// defer_check != 0: the non-positive-pivot flag (gs->flag, device int) is left for the caller to read back
+int ds_gram_alloc(ds_ctx* ctx, int64_t n, int64_t k, int paired, ds_gram_state* gs);
+int ds_gram_begin(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, const float* w);
+// The factorisation ahead of the right-hand side, behind ds_gram_begin on the same stream: `mid` is recorded where all but
+// the last group of blocks is factorised (never, if there is one group), the caller records `done` behind the call.
+bool ds_gram_ahead_applies(int64_t n);
+int ds_gram_factor_ahead(ds_ctx* ctx, const ds_gram_state* gs, hipEvent_t mid);
+// defer_check != 0: the non-positive-pivot flag (gs->flag, device int) is left for the caller to read back;
+// done != nullptr: the factorisation runs ahead on another stream, these are its events
 int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, const float* w, const float* y, float* phi,
-                    int defer_check);
+                    int defer_check, hipEvent_t mid, hipEvent_t done);
 int ds_solve_gram_chol(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const float* w, const float* y,
                        int paired, float* phi);
 size_t ds_gram_arena_bytes(int64_t n, int64_t k);
