@@ -669,9 +669,9 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   DS_HIP(ctx, hipEventRecord(ctx->ev[2], st));
 
   // The direct solver's matrix needs the masks and weights but not the model outputs: it is built on the side stream
-  // while the main stream runs the inference, and small ones (chains of launches of a few workgroups) are factorised
-  // there too; the right-hand side follows with a forward solve. The inference is queued first: its workgroups are the
-  // ones that the call waits for, and the host needs some 100 us for the launches of the other chain.
+  // while the main stream runs the inference. A small one (its factorisation is a chain of launches of a few workgroups) is
+  // factorised there too, and the right-hand side follows with a forward solve; the inference then starts behind the Gram
+  // kernels, which would wait for its first round of workgroups, and takes no more compute units than its rounds need.
   const bool direct = n >= 2 && (o.solver == DS_SOLVER_GRAM_CHOL || (o.solver == DS_SOLVER_AUTO && n <= 16384));
   const bool ahead = direct && ds_gram_ahead_applies(n);
   ds_gram_state gs;
@@ -679,6 +679,12 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
     DS_TRY(ds_gram_alloc(ctx, n, k, 1, &gs));   // (stays allocated below `mark2`)
     DS_HIP(ctx, hipEventRecord(ctx->fork2_ev, st));
     DS_HIP(ctx, hipStreamWaitEvent(ctx->side, ctx->fork2_ev, 0));
+    ctx->stream = ctx->side;
+    const int grc = ds_gram_begin(ctx, &gs, Z, w);
+    ctx->stream = st;
+    DS_TRY(grc);
+    if (ahead) DS_HIP(ctx, hipStreamWaitEvent(st, gs.formed, 0));
+    else DS_HIP(ctx, hipEventRecord(ctx->join2_ev, ctx->side));
   }
   const size_t mark2 = ctx->arena_used;
 
@@ -689,13 +695,11 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   DS_TRY(erc);
   ctx->arena_used = mark2;
   DS_HIP(ctx, hipEventRecord(ctx->ev[3], st));
-  if (direct) {
+  if (ahead) {   // (queued behind the inference: the host takes a few us per launch)
     ctx->stream = ctx->side;
-    int grc = ds_gram_begin(ctx, &gs, Z, w);
-    if (grc == DS_OK && hipEventRecord(ctx->join_ev, ctx->side) != hipSuccess) grc = ds_fail(ctx, DS_EDEVICE, "cannot record an event");
-    if (grc == DS_OK && ahead) grc = ds_gram_factor_ahead(ctx, &gs, ctx->fork2_ev);
+    const int frc = ds_gram_factor_ahead(ctx, &gs, ctx->fork2_ev);
     ctx->stream = st;
-    DS_TRY(grc);
+    DS_TRY(frc);
     DS_HIP(ctx, hipEventRecord(ctx->join2_ev, ctx->side));
   }
 
@@ -703,7 +707,7 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   if (n == 1) {
     hipLaunchKernelGGL(single_player_kernel, dim3(1), dim3(1), 0, st, y, phi);
   } else if (direct) {
-    DS_HIP(ctx, hipStreamWaitEvent(st, ctx->join_ev, 0));
+    if (!ahead) DS_HIP(ctx, hipStreamWaitEvent(st, ctx->join2_ev, 0));
     // (the pivot flag comes back with the final read-back)
     rc = ds_gram_finish(ctx, &gs, Z, w, y, phi, 1, ahead ? ctx->fork2_ev : nullptr, ahead ? ctx->join2_ev : nullptr);
     rep.solver_used = DS_SOLVER_GRAM_CHOL;

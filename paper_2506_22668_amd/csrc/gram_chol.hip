@@ -26,12 +26,10 @@ constexpr int kChunk = 32;  // 64-row words per LDS chunk
 // Paired rows (2r, 2r+1 complementary, one weight w): z z^T + zc zc^T = 2 z z^T - z 1^T - 1 z^T + 11^T and
 // t z + tc zc = (t - tc) z + tc 1; the terms with 1 vanish under the projection P, so only the small
 // member is used, with weight 2w and coefficient w (t_2r - t_2r+1). Otherwise every row is used.
-__global__ void used_row_weights_kernel(const float* w, int64_t R, int paired, float* gw) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= R) return;
+__device__ __forceinline__ float used_row_weight(const float* w, int64_t r, int paired) {
   const int64_t i = paired ? 2 * r : r;
-  const float wi = i < 2 ? 0.f : w[i];  // the two constraint rows carry no weight
-  gw[r] = paired ? 2.0f * wi : wi;
+  const float wi = w[i];
+  return i < 2 ? 0.f : paired ? 2.0f * wi : wi;  // the two constraint rows carry no weight
 }
 
 __global__ void used_row_rhs_kernel(const float* wc, const double* t, int64_t R, int paired, double* gc) {
@@ -40,41 +38,12 @@ __global__ void used_row_rhs_kernel(const float* wc, const double* t, int64_t R,
   gc[r] = paired ? (double)wc[2 * r] * (t[2 * r] - t[2 * r + 1]) : (double)wc[r] * t[r];
 }
 
-// per word of 64 rows: the common weight and how the Gram kernel treats the word:
-// 1 = one weight (popcount), 0 = mixed weights and sparse rows (walk the set bits of the AND),
-// 2 = mixed weights and dense rows (matrix cores). The density is read off the first row of the word
-// (rows are ordered by size): with a fraction p of the columns set, a pair of columns shares about 64 p^2
-// rows of the word, and walking them costs more than the fixed-price contraction from p of about 0.08 on (measured).
+// How the column-wise Gram kernel treats a word of 64 rows (`uni`): 1 = one weight (popcount), 0 = mixed weights and sparse rows
+// (walk the set bits of the AND), 2 = mixed weights and dense rows (matrix cores), 3 = none of its rows is left to it. The density
+// is read off the first row of the word (rows are ordered by size): with a fraction p of the columns set, a pair of
+// columns shares about 64 p^2 rows of the word, and walking them costs more than the fixed-price contraction from p of
+// about 0.08 on (measured).
 constexpr float kDenseFraction = 0.08f;
-__global__ void word_weights_kernel(const float* w, int64_t k, int64_t KW, const uint64_t* Z, int64_t W, int64_t n,
-                                    int64_t row_step, float dense_fraction, const uint64_t* keep, float* wu,
-                                    int32_t* uni) {
-  const int64_t wd = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (wd >= KW) return;
-  const int64_t i0 = wd * 64;
-  const uint64_t km = keep[wd];  // rows of this word that are left to the column-wise kernel
-  if (km == 0ull) {
-    wu[wd] = 0.f;
-    uni[wd] = 3;  // nothing to do
-    return;
-  }
-  const int fb = __ffsll((long long)km) - 1;
-  const float first = w[i0 + fb];
-  int same = 1;
-  for (int b = fb + 1; b < 64; ++b) {
-    const int64_t i = i0 + b;
-    if (((km >> b) & 1ull) && i < k && w[i] != first) same = 0;
-  }
-  wu[wd] = first;
-  int mode = same;
-  if (!same) {
-    const uint64_t* zr = Z + (i0 + fb) * row_step * W;
-    int64_t c = 0;
-    for (int64_t x = 0; x < W; ++x) c += __popcll(zr[x]);
-    if ((float)c > dense_fraction * (float)n) mode = 2;
-  }
-  uni[wd] = mode;
-}
 
 // ---- sparse rows: row-wise outer products -------------------------------------------------------
 // A row with s of n columns set touches s^2 entries of G, while the column-wise kernel pays for all
@@ -88,27 +57,37 @@ __global__ void word_weights_kernel(const float* w, int64_t k, int64_t KW, const
 //               overflow, they are exact, and they do not depend on the order of the atomic additions.
 constexpr int kSparseDivisor = 12;  // rows with at most n / 12 columns set are sparse (measured optimum: flat from 8 to 16)
 
-// scale[0] = 2^e (0 if the weights are not all finite and non-negative: then every row is kept)
-__global__ __launch_bounds__(kThreads) void gram_scale_kernel(const float* gw, int64_t R, double* scale) {
-  __shared__ double sh[kThreads];
-  __shared__ int bad[kThreads];
+// The used rows' weights gw and scale[0] = 2^e (0 if they are not all finite and non-negative: then every row is kept). One
+// workgroup; what bounds it is the latency of its loads, so that each of its threads has eight under way.
+constexpr int kWeightThreads = 1024;
+__global__ __launch_bounds__(kWeightThreads) void gram_weights_kernel(const float* w, int64_t R, int paired, float* gw, double* scale) {
+  constexpr int kAhead = 8;
+  __shared__ double sh[kWeightThreads / 64];
+  const int tid = threadIdx.x;
   double a = 0.0;
   int b = 0;
-  for (int64_t i = threadIdx.x; i < R; i += kThreads) {
-    const float v = gw[i];
-    if (!(v >= 0.f) || v > 3.0e38f) b = 1;
-    a += (double)v;
-  }
-  sh[threadIdx.x] = a;
-  bad[threadIdx.x] = b;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double x = 0.0;
-    int anyb = 0;
-    for (int i = 0; i < kThreads; ++i) {
-      x += sh[i];
-      anyb |= bad[i];
+  for (int64_t i0 = tid; i0 < R; i0 += kAhead * kWeightThreads) {
+    float v[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int64_t i = i0 + u * kWeightThreads;
+      v[u] = used_row_weight(w, i < R ? i : R - 1, paired);
     }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int64_t i = i0 + u * kWeightThreads;
+      if (i >= R) break;
+      gw[i] = v[u];
+      if (!(v[u] >= 0.f) || v[u] > 3.0e38f) b = 1;
+      a += (double)v[u];
+    }
+  }
+  a = ds_wave_sum(a);
+  if ((tid & 63) == 0) sh[tid >> 6] = a;
+  const int anyb = __syncthreads_or(b);
+  if (tid == 0) {
+    double x = 0.0;
+    for (int i = 0; i < kWeightThreads / 64; ++i) x += sh[i];
     double sc = 0.0;
     if (!anyb && x > 0.0 && x < 1e300) {
       int e;
@@ -119,35 +98,71 @@ __global__ __launch_bounds__(kThreads) void gram_scale_kernel(const float* gw, i
   }
 }
 
-// one wave per used row
-__global__ __launch_bounds__(kThreads) void gram_row_class_kernel(const uint64_t* Z, int64_t R, int64_t W, int64_t n,
-                                                                  int64_t row_step, const float* gw, const double* scale,
-                                                                  int sparse_divisor, uint64_t* Zc,
-                                                                  unsigned long long* keep, unsigned long long* wq) {
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+// Sparse or kept, for every used row, and from that what the column-wise kernel does with the words of 64 rows: a workgroup takes the
+// rows of a word, each wave four of them with their loads in flight together. (As a kernel of a wave per row, one that
+// read the rows' weights back word by word, and two that cleared and summed for them, it took 42 us at 10,000 rows of 1,010 columns; the
+// two kernels here take 11.)
+constexpr int kClassWaves = 16;
+__global__ __launch_bounds__(64 * kClassWaves) void gram_row_class_kernel(const uint64_t* Z, int64_t R, int64_t W, int64_t n,
+                                                                          int64_t row_step, const float* gw, const double* scale,
+                                                                          int sparse_divisor, float dense_fraction, uint64_t* Zc,
+                                                                          unsigned long long* keep, unsigned long long* wq, float* wu,
+                                                                          int32_t* uni) {
+  constexpr int kRows = 64 / kClassWaves;
+  __shared__ int set[64];   // columns set in a row of the word
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t wd = blockIdx.x, r0 = wd * 64 + wave * kRows;
   const double sc = scale[0];
-  for (int64_t r = wave; r < R; r += nwaves) {
-    const uint64_t* zr = Z + r * row_step * W;
-    int c = 0;
-    for (int64_t x = lane; x < W; x += 64) c += __popcll(zr[x]);
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
-    const bool sparse = sc > 0.0 && (int64_t)c * sparse_divisor <= n;
-    for (int64_t x = lane; x < W; x += 64) Zc[x * R + r] = sparse ? zr[x] : 0ull;
-    if (lane == 0) {
-      wq[r] = sparse ? (unsigned long long)llrint((double)gw[r] * sc) : 0ull;
-      if (!sparse) atomicOr(&keep[r >> 6], 1ull << (r & 63));
+  const uint64_t* zr[kRows];
+  int c[kRows];
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {
+    zr[u] = Z + (r0 + u < R ? r0 + u : R - 1) * row_step * W;
+    c[u] = 0;
+  }
+  uint64_t z0[kRows];   // the first 64 words stay in registers for the copy
+  for (int64_t x0 = 0; x0 < W; x0 += 64) {
+    uint64_t z[kRows];
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) z[u] = zr[u][x0 + lane < W ? x0 + lane : W - 1];
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      if (x0 == 0) z0[u] = z[u];
+      c[u] += x0 + lane < W ? __popcll(z[u]) : 0;
     }
+  }
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) c[u] += __shfl_xor(c[u], o, 64);
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {
+    const int64_t r = r0 + u;
+    if (lane == 0) set[wave * kRows + u] = c[u];
+    if (r >= R) continue;
+    const bool sparse = sc > 0.0 && (int64_t)c[u] * sparse_divisor <= n;
+    if (lane < W) Zc[lane * R + r] = sparse ? z0[u] : 0ull;
+    for (int64_t x = 64 + lane; x < W; x += 64) Zc[x * R + r] = sparse ? zr[u][x] : 0ull;
+    if (lane == 0) wq[r] = sparse ? (unsigned long long)llrint((double)gw[r] * sc) : 0ull;
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  const int64_t r = wd * 64 + lane;
+  const int mine = set[lane];
+  const bool kept = r < R && !(sc > 0.0 && (int64_t)mine * sparse_divisor <= n);
+  const unsigned long long km = __ballot(kept);
+  const int fb = km ? __ffsll((long long)km) - 1 : 0;   // the first kept row stands for the word
+  const float wr = gw[r < R ? r : R - 1], first = __shfl(wr, fb, 64);
+  const int same = __ballot(kept && wr != first) == 0ull;
+  if (lane == 0) {
+    keep[wd] = km;
+    wu[wd] = km ? first : 0.f;
+    uni[wd] = !km ? 3 : same ? 1 : (float)set[fb] > dense_fraction * (float)n ? 2 : 0;
   }
 }
 
 // One 64x64 tile of G per workgroup (lower tiles); streams the two column-block words of every row.
-__global__ __launch_bounds__(kThreads) void gram_rows_kernel(const uint64_t* Zc, const unsigned long long* wq, int64_t R,
-                                                             int64_t n, const double* scale, double* G) {
-  const int ta = blockIdx.y, tb = blockIdx.x;
-  if (tb > ta) return;
-  __shared__ unsigned long long acc[kTile * kTile];
+__device__ __forceinline__ void gram_rows_tile(const uint64_t* Zc, const unsigned long long* wq, int64_t R, int64_t n,
+                                               const double* scale, double* G, int ta, int tb, unsigned long long* acc) {
   const int tid = threadIdx.x;
   for (int i = tid; i < kTile * kTile; i += kThreads) acc[i] = 0ull;
   __syncthreads();
@@ -194,6 +209,13 @@ __global__ __launch_bounds__(kThreads) void gram_rows_kernel(const uint64_t* Zc,
   }
 }
 
+__global__ __launch_bounds__(kThreads) void gram_rows_kernel(const uint64_t* Zc, const unsigned long long* wq, int64_t R,
+                                                             int64_t n, const double* scale, double* G) {
+  if (blockIdx.x > blockIdx.y) return;
+  __shared__ unsigned long long acc[kTile * kTile];
+  gram_rows_tile(Zc, wq, R, n, scale, G, blockIdx.y, blockIdx.x, acc);
+}
+
 // One 64x64 tile of G per workgroup and slice of the row words (split-K); each slice
 // writes its own full symmetric partial matrix, summed later in a fixed order.
 // A word of 64 rows that share one weight costs an AND and a popcount per pair of columns. A word that
@@ -208,6 +230,9 @@ __global__ __launch_bounds__(kThreads) void gram_rows_kernel(const uint64_t* Zc,
 // bfloat16 ones for B), which the packed weight pieces are ANDed with. Each wave owns a 32x32 quadrant of the
 // tile (accumulator register i of lane l is D[8*(i/4) + 4*(l/32) + i%4][l%32]). Both paths add up in fp32
 // within a chunk of 32 words and in fp64 across chunks.
+// The sparse rows' part is in slice 0 already (`rows_apart`: gram_rows_kernel, whose own launch holds more workgroups per compute unit), or
+// it is the launch's last slice: where the tiles of one triangle do not fill the GPU, both kinds run together
+// (1,010 columns, 10,000 rows: 48 + 51 us apart, 76 together).
 typedef float gram_f16_t __attribute__((ext_vector_type(16)));
 typedef short gram_s4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int gram_u2_t __attribute__((ext_vector_type(2)));
@@ -224,7 +249,8 @@ __device__ __forceinline__ uint32_t pair_mask(uint32_t two_bits) {
 
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 4))) void gram_kernel(const uint64_t* Zt, int64_t n, int64_t k, int64_t KW,
                                                         const float* w, const float* wu, const int32_t* uni,
-                                                        const uint64_t* keep, double* Gp, int64_t words_per_slice) {
+                                                        const uint64_t* keep, double* Gp, int64_t words_per_slice, int rows_apart,
+                                                        const uint64_t* Zc, const unsigned long long* wq, const double* scale) {
   const int ta = blockIdx.y, tb = blockIdx.x;
   if (tb > ta) return;
   // As | Bs during the accumulation; reused as one 64 x 65 fp64 tile when the two paths are merged
@@ -237,6 +263,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 4))
   __shared__ gram_u2_t tabA[16], tabB[16];   // four bits -> 16-bit masks / bfloat16 ones (two registers)
   __shared__ float wus[kChunk];
   __shared__ int unis[kChunk];
+  if (!rows_apart && blockIdx.z == gridDim.z - 1) {
+    static_assert(sizeof(uint64_t) * kTile * kTile <= sizeof(raw), "the accumulators of the sparse rows must fit");
+    gram_rows_tile(Zc, wq, k, n, scale, Gp + (size_t)blockIdx.z * n * n, ta, tb, (unsigned long long*)raw);
+    return;
+  }
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   const int lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
   if (tid < 16) {
@@ -410,7 +441,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 4))
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int64_t a = a0 + ty + 16 * i, b = b0 + tx + 16 * j;
-      prev[i][j] = blockIdx.z == 0 ? G[(a < n ? a : n - 1) * n + (b < n ? b : n - 1)] : 0.0;
+      prev[i][j] = rows_apart && blockIdx.z == 0 ? G[(a < n ? a : n - 1) * n + (b < n ? b : n - 1)] : 0.0;
     }
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -449,8 +480,8 @@ __global__ __launch_bounds__(kThreads) void sum_slices_row_mean_kernel(double* G
   }
 }
 
-// single block: stats[0] = mu (grand mean of G), stats[1] = trace(G)
-__global__ __launch_bounds__(kThreads) void stats_kernel(const double* G, const double* m, int64_t n, double* stats) {
+// single block: stats[0] = mu (grand mean of G), stats[1] = trace(G); clears the factorisation's flag
+__global__ __launch_bounds__(kThreads) void stats_kernel(const double* G, const double* m, int64_t n, double* stats, int* flag) {
   __shared__ double sh[2][kThreads];
   double a = 0, b = 0;
   for (int64_t i = threadIdx.x; i < n; i += kThreads) {
@@ -468,6 +499,7 @@ __global__ __launch_bounds__(kThreads) void stats_kernel(const double* G, const 
     }
     stats[0] = x / (double)n;
     stats[1] = yv;
+    *flag = 0;
   }
 }
 
@@ -1497,7 +1529,8 @@ inline unsigned nblocks(int64_t n, int per) { return (unsigned)((n + per - 1) / 
 
 struct GramDims {
   int64_t R, RW, ld, nblk;
-  int slices;
+  int slices;       // of the column-wise part, and one more of the sparse rows unless they have a launch of their own
+  int rows_apart;
   int64_t words_per_slice;
 };
 
@@ -1518,6 +1551,8 @@ GramDims gram_dims(int64_t n, int64_t k, int paired, int num_cus) {
   const int64_t cps = (chunks + s - 1) / s;  // chunks per slice
   d.words_per_slice = cps * kChunk;
   d.slices = (int)((chunks + cps - 1) / cps);
+  d.rows_apart = lower > num_cus;
+  if (!d.rows_apart) ++d.slices;
   return d;
 }
 
@@ -1544,7 +1579,7 @@ int ds_gram_alloc(ds_ctx* ctx, int64_t n, int64_t k, int paired, ds_gram_state* 
   const int64_t R = d.R, RW = d.RW, ld = d.ld;
   gs->n = n; gs->k = k; gs->R = R; gs->RW = RW; gs->ld = ld; gs->nblk = d.nblk; gs->paired = paired;
   gs->Zt = (uint64_t*)ds_arena_alloc(ctx, (size_t)n * RW * 8);
-  gs->slices = d.slices; gs->words_per_slice = d.words_per_slice;
+  gs->slices = d.slices; gs->rows_apart = d.rows_apart; gs->words_per_slice = d.words_per_slice;
   gs->Gp = (double*)ds_arena_alloc(ctx, (size_t)d.slices * n * n * 8);
   gs->M = (double*)ds_arena_alloc(ctx, (size_t)(n + 1) * ld * 8);
   gs->linv = (double*)ds_arena_alloc(ctx, (size_t)d.nblk * NB * NB * 8);
@@ -1575,7 +1610,7 @@ int ds_gram_alloc(ds_ctx* ctx, int64_t n, int64_t k, int paired, ds_gram_state* 
 
 // Part 1: everything that does not need the model outputs y (Gram matrix, projection, system matrix, first diagonal block).
 // It may run on another stream than part 3, concurrently with the masked inference.
-int ds_gram_begin(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, const float* w) {
+int ds_gram_begin(ds_ctx* ctx, ds_gram_state* gs, const uint64_t* Z, const float* w) {
   hipStream_t st = ctx->stream;
   const int64_t n = gs->n, R = gs->R, RW = gs->RW, ld = gs->ld, W = (n + 63) / 64;
   const int paired = gs->paired;
@@ -1583,35 +1618,28 @@ int ds_gram_begin(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, const
   int32_t* uni = gs->uni;
   double *Gp = gs->Gp, *m = gs->m, *stats = gs->stats, *gscale = gs->gscale;
   uint64_t *Zc = gs->Zc, *keep = gs->keep, *wq = gs->wq;
-  hipLaunchKernelGGL(used_row_weights_kernel, dim3(nblocks(R, 256)), dim3(256), 0, st, w, R, paired, gw);
   DS_TRY(ds_bit_transpose(ctx, Z, R, n, W, 0, paired ? 2 : 1, gs->Zt));
-  // sparse rows: row-wise outer products into slice 0; the rest (bits in `keep`) column-wise on top of it
+  // sparse rows: row-wise outer products; the rest (bits in `keep`) column-wise
   const int64_t row_step = paired ? 2 : 1;
-  DS_HIP(ctx, hipMemsetAsync(keep, 0, (size_t)RW * 8, st));
-  hipLaunchKernelGGL(gram_scale_kernel, dim3(1), dim3(kThreads), 0, st, gw, R, gscale);
-  {
-    int64_t blocks = (R * 64 + kThreads - 1) / kThreads;
-    if (blocks > (int64_t)ctx->num_cus * 16) blocks = (int64_t)ctx->num_cus * 16;
-    hipLaunchKernelGGL(gram_row_class_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, Z, R, W, n, row_step, gw,
-                       gscale, sparse_divisor(ctx), Zc, (unsigned long long*)keep, (unsigned long long*)wq);
-  }
-  hipLaunchKernelGGL(word_weights_kernel, dim3(nblocks(RW, 256)), dim3(256), 0, st, gw, R, RW, Z, W, n, row_step,
-                     dense_fraction(ctx), keep, wu, uni);
+  hipLaunchKernelGGL(gram_weights_kernel, dim3(1), dim3(kWeightThreads), 0, st, w, R, paired, gw, gscale);
+  hipLaunchKernelGGL(gram_row_class_kernel, dim3((unsigned)RW), dim3(64 * kClassWaves), 0, st, Z, R, W, n, row_step, gw, gscale,
+                     sparse_divisor(ctx), dense_fraction(ctx), Zc, (unsigned long long*)keep, (unsigned long long*)wq, wu, uni);
   const unsigned tiles = nblocks(n, kTile);
   DS_TRY(ds_kernel_mark(ctx, 1, 0));
-  hipLaunchKernelGGL(gram_rows_kernel, dim3(tiles, tiles), dim3(kThreads), 0, st, Zc, (const unsigned long long*)wq, R, n,
-                     gscale, Gp);
+  if (gs->rows_apart)
+    hipLaunchKernelGGL(gram_rows_kernel, dim3(tiles, tiles), dim3(kThreads), 0, st, Zc, (const unsigned long long*)wq, R, n,
+                       gscale, Gp);
   hipLaunchKernelGGL(gram_kernel, dim3(tiles, tiles, gs->slices), dim3(kThreads), 0, st, gs->Zt, n, R, RW, gw, wu, uni, keep,
-                     Gp, gs->words_per_slice);
+                     Gp, gs->words_per_slice, gs->rows_apart, Zc, (const unsigned long long*)wq, gscale);
   DS_TRY(ds_kernel_mark(ctx, 1, 1));
+  gs->formed = ctx->kev[3];   // (the mark's event)
   const unsigned wblocks = (unsigned)(n < (int64_t)ctx->num_cus * 16 ? n : (int64_t)ctx->num_cus * 16);
   hipLaunchKernelGGL(sum_slices_row_mean_kernel, dim3(wblocks), dim3(kThreads), 0, st, Gp, n, gs->slices, m);
-  hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(kThreads), 0, st, Gp, m, n, stats);
+  hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(kThreads), 0, st, Gp, m, n, stats, gs->flag);
   hipLaunchKernelGGL(build_matrix_kernel, dim3(nblocks(n * n, 256)), dim3(256), 0, st, Gp, m, stats, n, ld, gs->M,
                      (double*)(gs->flag + 2));
   // the first diagonal block does not involve the right-hand side either: factorised here, off the path that waits
   // for the model outputs
-  DS_HIP(ctx, hipMemsetAsync(gs->flag, 0, sizeof(int), st));
   hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(kThreads), 0, st, gs->M, ld, (int64_t)0, (int)(n < NB ? n : NB), gs->linv,
                      gs->flag);
   DS_HIP(ctx, hipGetLastError());

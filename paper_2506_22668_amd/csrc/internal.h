@@ -207,16 +207,17 @@ size_t ds_gat_eval_arena_bytes(ds_ctx* ctx, const ds_cgraph* cg, int64_t k);
 // the direct solver in parts: the buffers, what needs only the masks and weights, the factorisation, what needs the model outputs
 struct ds_gram_state {
   int64_t n, k, R, RW, ld, nblk, words_per_slice;
-  int paired, slices;
+  int paired, slices, rows_apart;
   uint64_t *Zt, *Zc, *keep, *wq;
   double *Gp, *m, *stats, *gscale, *M, *linv, *t, *sqw, *gc, *c;
   double* panel[2];  // rows of the current and of the next 64-column panel (fused steps of the factorisation)
   int32_t *uni, *sz;
   float *gw, *wu, *wc;
   int* flag;
+  hipEvent_t formed; // recorded by ds_gram_begin behind the Gram kernels: Zt is there, the short launches are left
 };
 int ds_gram_alloc(ds_ctx* ctx, int64_t n, int64_t k, int paired, ds_gram_state* gs);
-int ds_gram_begin(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, const float* w);
+int ds_gram_begin(ds_ctx* ctx, ds_gram_state* gs, const uint64_t* Z, const float* w);
 // The factorisation ahead of the right-hand side, behind ds_gram_begin on the same stream: `mid` is recorded where all but
 // the last group of blocks is factorised (never, if there is one group), the caller records `done` behind the call.
 bool ds_gram_ahead_applies(int64_t n);

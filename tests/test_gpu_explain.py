@@ -286,6 +286,37 @@ def test_degenerate_graphs_and_error_paths():
     ctx2.close()
 
 
+# The factorisation beside the inference and its forward solve, 256 unknowns per launch: one block, one column more, one
+# launch exactly, one column more, two launches and a short block, the largest such game and one player more (whose
+# right-hand side is a row of the matrix again).
+@pytest.mark.parametrize("players", [2, 64, 65, 256, 257, 600, 2304, 2305])
+def test_factorising_ahead_of_the_scores_equals_solving_with_them(players):
+    from paper_2506_22668_amd import Options, DS_SOLVER_GRAM_CHOL
+    from synth.workloads import Workload
+    say(f"explain ahead players={players}")
+    rng = np.random.default_rng(players)
+    leaves = max(2, int(2 * np.sqrt(players)))                   # a star and edges between its leaves
+    i, j = np.triu_indices(leaves, 1)
+    pick = rng.permutation(len(i))[:players - leaves] if players > leaves else []
+    V = leaves + 1
+    rp, ci = csr_from_undirected_edges(V, np.concatenate([np.zeros(leaves, int), 1 + i[pick]]),
+                                       np.concatenate([1 + np.arange(leaves), 1 + j[pick]]))
+    W = [rng.standard_normal((8, 16)).astype(np.float32), rng.standard_normal((16, 3)).astype(np.float32)]
+    ns = 4 * max(players, 200)
+    w = Workload("star", V, rp, ci, rng.standard_normal((V, 8), dtype=np.float32), (8, 16, 3), W, [0], ns, 5, "gram_chol")
+    ctx = make_context(w)
+    phi, _, _, rep, _ = ctx.explain(0, ns, 5, Options(solver=DS_SOLVER_GRAM_CHOL))
+    assert rep.num_players == players
+    cg = ctx.extract(0)
+    Z, wt, _ = ctx.sample(players, ns, 5, 0)
+    y = ctx.eval(cg, Z, pairs=True)[0]
+    ref = ctx.solve(players, Z, wt, y, Options(solver=DS_SOLVER_GRAM_CHOL, paired=1))[0]
+    # the same float32 scores, two orders of fp64 sums: what is left is one rounding to float32 either side
+    assert (phi - ref).abs().max() <= 1.2e-7 * ref.abs().max()
+    ctx.cgraph_free(cg)
+    ctx.close()
+
+
 def test_directed_players_and_wider_extraction():
     """Directed players (one CSR entry each) and a computational graph wider than the receptive
     field: edges joining two nodes beyond L hops are exact null players."""

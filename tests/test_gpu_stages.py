@@ -742,6 +742,28 @@ def test_gram_cholesky_mid_size_crosses_every_factorisation_regime(ctx_tiny):
     assert err <= 1e-4 * np.abs(ref).max()
 
 
+# Which rows are sparse is decided 64 rows at a time: rows of more than 64 words (copied in two rounds), a last word of a
+# few rows, a single word; and the sizes up to which the sparse rows' tiles ride in the column-wise kernel's launch.
+@pytest.mark.parametrize("n,ns", [(4161, 17030), (33, 256), (1408, 6000), (1409, 6000)])
+def test_gram_row_classes(ctx_tiny, n, ns):
+    from paper_2506_22668_amd import Options, DS_SOLVER_GRAM_CHOL
+    ctx, _ = ctx_tiny
+    say(f"gram classes n={n}")
+    Z, w, bits, y = _solve_inputs(n, ns, 40 + n)
+    y, B, wt = y.astype(np.float64), bits[2:].astype(np.float64), w[2:].astype(np.float64)
+    delta = y[1] - y[0]
+    G, c = (B * wt[:, None]).T @ B, B.T @ (wt * (y[2:] - y[0] - delta / n * B.sum(1)))
+    P = lambda a: a - a.mean(0)
+    A = P(P(G).T)
+    psi = np.linalg.solve(A + np.trace(A) / n / n, P(c))
+    ref = psi - psi.mean() + delta / n
+    for paired in (0, 1):
+        got = ctx.solve(n, torch.from_numpy(Z.view(np.int64)).cuda(), torch.from_numpy(w).cuda(), torch.from_numpy(y.astype(np.float32)).cuda(),
+                        Options(solver=DS_SOLVER_GRAM_CHOL, paired=paired))[0].cpu().numpy().astype(np.float64)
+        # the column-wise sums are fp32 over 2,048 rows, 2^-24 of an entry, times the condition of the system (1e3 here)
+        assert np.abs(got - ref).max() <= 1e-4 * np.abs(ref).max()
+
+
 # The 128 x 128 tiles of the wide update start at row 512: 2,304 leaves a last row of tiles that holds nothing but the
 # right-hand side, 2,305 one of a single column, 2,431 a whole last tile less the right-hand side; 2,561 runs two
 # super-panels, the second one's columns updated ahead of the rest.
