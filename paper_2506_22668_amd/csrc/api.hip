@@ -670,8 +670,9 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
 
   // The direct solver's matrix needs the masks and weights but not the model outputs: it is built on the side stream
   // while the main stream runs the inference. A small one (its factorisation is a chain of launches of a few workgroups) is
-  // factorised there too, and the right-hand side follows with a forward solve; the inference then starts behind the Gram
-  // kernels, which would wait for its first round of workgroups, and takes no more compute units than its rounds need.
+  // factorised there too, and the right-hand side follows with a forward solve. The inference then takes no more compute
+  // units than its rounds of workgroups need, and where that is more than half of them it starts behind the Gram kernels
+  // (1,010 players, 157 units: the Gram kernels take 76 us in front of it, 164 beside it, and the factorisation waits for them).
   const bool direct = n >= 2 && (o.solver == DS_SOLVER_GRAM_CHOL || (o.solver == DS_SOLVER_AUTO && n <= 16384));
   const bool ahead = direct && ds_gram_ahead_applies(n);
   ds_gram_state gs;
@@ -683,8 +684,8 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
     const int grc = ds_gram_begin(ctx, &gs, Z, w);
     ctx->stream = st;
     DS_TRY(grc);
-    if (ahead) DS_HIP(ctx, hipStreamWaitEvent(st, gs.formed, 0));
-    else DS_HIP(ctx, hipEventRecord(ctx->join2_ev, ctx->side));
+    if (ahead && gs.formed && k > (int64_t)ctx->num_cus * 32) DS_HIP(ctx, hipStreamWaitEvent(st, gs.formed, 0));
+    if (!ahead) DS_HIP(ctx, hipEventRecord(ctx->join2_ev, ctx->side));
   }
   const size_t mark2 = ctx->arena_used;
 
@@ -708,6 +709,7 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
     hipLaunchKernelGGL(single_player_kernel, dim3(1), dim3(1), 0, st, y, phi);
   } else if (direct) {
     if (!ahead) DS_HIP(ctx, hipStreamWaitEvent(st, ctx->join2_ev, 0));
+    else if (gs.formed) DS_HIP(ctx, hipStreamWaitEvent(st, gs.formed, 0));   // (its transposed rows)
     // (the pivot flag comes back with the final read-back)
     rc = ds_gram_finish(ctx, &gs, Z, w, y, phi, 1, ahead ? ctx->fork2_ev : nullptr, ahead ? ctx->join2_ev : nullptr);
     rep.solver_used = DS_SOLVER_GRAM_CHOL;

@@ -1525,7 +1525,218 @@ inline int sparse_divisor(const ds_ctx* ctx) {
   return ctx->tuning.gram_sparse_div >= 1 ? ctx->tuning.gram_sparse_div : kSparseDivisor;
 }
 
+// ---------------- games of at most 64 players ----------------
+// One mask word per row and one diagonal block: four launches in place of fourteen, each of which costs its start and a
+// trip through memory for a few kilobytes of matrix (an explanation of 12 players, 4,096 coalitions: 324 us; now 232). Sums of the weights themselves
+// in fp64, in a fixed order; a pair of players costs six instructions per row.
+constexpr int kSmallMax = 64;
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallPairs = kSmallMax * (kSmallMax + 1) / 2;
+constexpr int kSmallPerThread = (kSmallPairs + kSmallThreads - 1) / kSmallThreads;
+constexpr int kSmallChunk = 512;    // rows per step
+constexpr int kSmallParts = 64;     // workgroups at most, each with a part of the rows
+
+// a >= b of the p-th pair
+__device__ __forceinline__ void small_pair(int p, int& a, int& b) {
+  a = (int)((sqrtf(8.f * (float)p + 1.f) - 1.f) * 0.5f);
+  while (a * (a + 1) / 2 > p) --a;
+  while ((a + 1) * (a + 2) / 2 <= p) ++a;
+  b = p - a * (a + 1) / 2;
+}
+
+// part[blockIdx.x][p] = sum of the weights of this workgroup's rows that hold both players of pair p. The threads form
+// groups of (at least) one per pair, which take the rows in turn.
+__global__ __launch_bounds__(kSmallThreads) void small_gram_kernel(const uint64_t* Z, const float* w, int64_t R, int paired, int n,
+                                                                   double* part) {
+  __shared__ uint64_t zs[kSmallChunk];
+  __shared__ double ws[kSmallChunk];
+  __shared__ double red[kSmallThreads];
+  const int tid = threadIdx.x, pairs = n * (n + 1) / 2;
+  const int width = pairs < kSmallThreads ? (pairs + 63) & ~63 : kSmallThreads;   // threads of a group
+  const int groups = kSmallThreads / width, g = tid / width, t = tid - g * width;
+  uint64_t mask[kSmallPerThread];
+  double acc[kSmallPerThread];
+#pragma unroll
+  for (int u = 0; u < kSmallPerThread; ++u) {
+    const int p = t + u * width;
+    int a = 0, b = 0;
+    small_pair(p < pairs ? p : 0, a, b);
+    mask[u] = (1ull << a) | (1ull << b);
+    acc[u] = 0.0;
+  }
+  const int64_t per = (R + gridDim.x - 1) / gridDim.x;
+  const int64_t first = per * blockIdx.x, last = first + per < R ? first + per : R;
+  for (int64_t r0 = first; r0 < last; r0 += kSmallChunk) {
+    const int count = (int)(last - r0 < kSmallChunk ? last - r0 : kSmallChunk);
+    __syncthreads();
+    if (tid < count) {
+      zs[tid] = Z[(r0 + tid) * (paired ? 2 : 1)];
+      ws[tid] = (double)used_row_weight(w, r0 + tid, paired);
+    }
+    __syncthreads();
+    if (g < groups)
+      for (int i = g; i < count; i += groups) {
+        const uint64_t z = zs[i];
+        const double wi = ws[i];
+#pragma unroll
+        for (int u = 0; u < kSmallPerThread; ++u)
+          if (u * width < pairs) acc[u] += (z & mask[u]) == mask[u] ? wi : 0.0;
+      }
+  }
+  if (groups > 1) {
+    red[tid] = acc[0];
+    __syncthreads();
+    if (g > 0) return;
+    for (int i = 1; i < groups; ++i) acc[0] += red[i * width + t];
+  }
+#pragma unroll
+  for (int u = 0; u < kSmallPerThread; ++u)
+    if (t + u * width < pairs) part[(size_t)blockIdx.x * pairs + t + u * width] = acc[u];
+}
+
+// The system matrix from the parts (as sum_slices_row_mean, stats and build_matrix form it) and its factor: one workgroup.
+__global__ __launch_bounds__(kThreads) void small_system_kernel(const double* part, int parts, int n, int64_t ld, double* M,
+                                                                double* linv, int* flag) {
+  __shared__ double S[kTile][NB + 1];
+  __shared__ double Y[kTile][NB + 1];
+  __shared__ double mean[NB];
+  constexpr int kAhead = 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, pairs = n * (n + 1) / 2;
+  for (int p = tid; p < pairs; p += kThreads) {
+    double sum = 0.0;
+    for (int i0 = 0; i0 < parts; i0 += kAhead) {   // (all of a step's loads in flight; past the end the last part is read again)
+      double v[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) v[u] = part[(size_t)(i0 + u < parts ? i0 + u : parts - 1) * pairs + p];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) sum += i0 + u < parts ? v[u] : 0.0;
+    }
+    int a, b;
+    small_pair(p, a, b);
+    S[a][b] = sum;
+    S[b][a] = sum;
+  }
+  __syncthreads();
+  if (tid < n) {
+    double sum = 0.0;
+    for (int b = 0; b < n; ++b) sum += S[tid][b];
+    mean[tid] = sum / (double)n;
+  }
+  __syncthreads();
+  double mu = 0.0, tr = 0.0;
+  for (int i = 0; i < n; ++i) {
+    mu += mean[i];
+    tr += S[i][i];
+  }
+  mu /= (double)n;
+  tr -= (double)n * mu;
+  double gamma = tr / (double)(n > 1 ? n - 1 : 1);
+  if (!(gamma > 0.0)) gamma = 1.0;
+  if (tid == 0) {
+    *flag = 0;
+    *(double*)(flag + 2) = 256.0 * (double)n * 0x1p-52 * ((tr > 0.0 ? tr : 0.0) + gamma) / (double)n;   // see build_matrix_kernel
+    __threadfence_block();
+  }
+  DiagRegs mt;
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    const int t = wave + 4 * u;
+    if (t >= kDiagTiles) break;
+    int r0, c0;
+    diag_subtile(t, r0, c0);
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const int r = r0 + 4 * r4 + (lane >> 4), c = c0 + (lane & 15);
+      mt.v[u][r4] = r < n && c < n ? S[r][c] - mean[r] - mean[c] + mu + gamma / (double)n : (r == c ? 1.0 : 0.0);
+    }
+  }
+  __syncthreads();   // every wave has read the sums before the block's tile is written
+  chol_diag_body(M, ld, 0, n, linv, flag, nullptr, S, Y, mt);
+}
+
+// cpart[blockIdx.x][a] = sum over this workgroup's rows that hold player a of the right-hand side's coefficients
+// (used_row_rhs_kernel on row_prep's values)
+__global__ __launch_bounds__(kSmallThreads) void small_rhs_kernel(const uint64_t* Z, const float* w, const float* y, int64_t R,
+                                                                  int paired, int n, double* cpart) {
+  __shared__ uint64_t zs[kSmallChunk];
+  __shared__ double gs[kSmallChunk];
+  __shared__ double red[kSmallThreads / 64][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const double f0 = (double)y[0], slope = ((double)y[1] - (double)y[0]) / (double)n;
+  const uint64_t all = n < 64 ? (1ull << n) - 1ull : ~0ull;
+  const int64_t per = (R + gridDim.x - 1) / gridDim.x;
+  const int64_t first = per * blockIdx.x, last = first + per < R ? first + per : R;
+  double acc = 0.0;
+  for (int64_t r0 = first; r0 < last; r0 += kSmallChunk) {
+    const int count = (int)(last - r0 < kSmallChunk ? last - r0 : kSmallChunk);
+    __syncthreads();
+    if (tid < count) {
+      const int64_t i = (r0 + tid) * (paired ? 2 : 1);
+      const uint64_t z = Z[i];
+      const int size = __popcll(z & all);
+      auto t = [&](int64_t row, int members) { return row < 2 ? 0.0 : (double)y[row] - f0 - slope * (double)members; };
+      const double wi = i < 2 ? 0.0 : (double)w[i];
+      zs[tid] = z;
+      gs[tid] = paired ? wi * (t(i, size) - t(i + 1, n - size)) : wi * t(i, size);
+    }
+    __syncthreads();
+    for (int i = wave; i < count; i += kSmallThreads / 64) acc += (zs[i] >> lane) & 1ull ? gs[i] : 0.0;
+  }
+  red[wave][lane] = acc;
+  __syncthreads();
+  if (wave > 0) return;
+  for (int i = 1; i < kSmallThreads / 64; ++i) acc += red[i][lane];
+  cpart[(size_t)blockIdx.x * 64 + lane] = acc;
+}
+
+// right-hand side from its parts, forward and back substitution by the inverse of the one block, phi: one workgroup
+__global__ __launch_bounds__(kThreads) void small_solve_kernel(const double* cpart, int parts, int n, const double* linv,
+                                                               const float* y01, float* phi) {
+  constexpr int kPer = NB * NB / kThreads;
+  __shared__ double xs[2][NB];
+  __shared__ double part[kThreads / NB][NB];
+  const int tid = threadIdx.x, c = tid & (NB - 1), g = tid / NB;
+  double li[kPer];   // rows g, g + 4, .. of column c
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) li[i] = linv[(g + (kThreads / NB) * i) * NB + c];
+  double sum = 0.0;
+  for (int i = g; i < parts; i += kThreads / NB) sum += cpart[(size_t)i * 64 + c];
+  part[g][c] = sum;
+  __syncthreads();
+  if (g == 0) {   // the first wave: c - mean(c)
+    double x = 0.0;
+    for (int i = 0; i < kThreads / NB; ++i) x += part[i][c];
+    x = c < n ? x : 0.0;
+    const double mean = ds_wave_sum(x) / (double)n;
+    xs[0][c] = c < n ? x - mean : 0.0;
+  }
+  __syncthreads();
+  // y = Linv x: a wave's rows one after the other, folded over its lanes
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const double v = ds_wave_sum(li[i] * xs[0][c]);
+    if (c == 0) xs[1][g + (kThreads / NB) * i] = v;
+  }
+  __syncthreads();
+  double s = 0.0;   // psi = Linv^T y
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) s += li[i] * xs[1][g + (kThreads / NB) * i];
+  part[g][c] = s;
+  __syncthreads();
+  if (g == 0 && c < n) {
+    double v = 0.0;
+    for (int i = 0; i < kThreads / NB; ++i) v += part[i][c];
+    phi[c] = (float)(v + ((double)y01[1] - (double)y01[0]) / (double)n);
+  }
+}
+
 inline unsigned nblocks(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
+
+// workgroups of the small games' two passes over the rows
+inline unsigned small_parts(int64_t R) {
+  const int64_t parts = (R + 63) / 64;
+  return (unsigned)(parts < 1 ? 1 : parts > kSmallParts ? kSmallParts : parts);
+}
 
 struct GramDims {
   int64_t R, RW, ld, nblk;
@@ -1558,6 +1769,9 @@ GramDims gram_dims(int64_t n, int64_t k, int paired, int num_cus) {
 
 }  // namespace
 
+// the parts of the sums of a game of at most 64 players: per pair of players, and per player
+static constexpr size_t small_bytes = (size_t)kSmallParts * kSmallPairs * 8;
+
 // rows of a 64-column panel, one buffer (the fused steps of the factorisation keep two)
 static size_t panel_bytes(int64_t n) { return (size_t)(n + 1) * NB * 8; }
 
@@ -1565,7 +1779,7 @@ size_t ds_gram_arena_bytes(int64_t n, int64_t k) {
   const GramDims d = gram_dims(n, k, 0, 256);  // the unpaired layout is the larger one
   const GramDims dp = gram_dims(n, k, 1, 256);
   const size_t slices = (size_t)(d.slices > dp.slices ? d.slices : dp.slices) + 1;  // +1: CU counts differ a little
-  return ds_align((size_t)n * d.RW * 8) + ds_align(slices * (size_t)n * n * 8) + ds_align((size_t)(n + 1) * d.ld * 8) +
+  return (n <= kSmallMax ? 2 * ds_align(small_bytes) : 0) + ds_align((size_t)n * d.RW * 8) + ds_align(slices * (size_t)n * n * 8) + ds_align((size_t)(n + 1) * d.ld * 8) +
          ds_align((size_t)d.nblk * NB * NB * 8) + 2 * ds_align(panel_bytes(n)) + 2 * ds_align(k * 4) + 2 * ds_align(k * 8) + ds_align(k * 4) +
          ds_align(k * 8) + ds_align(d.RW * 4) * 2 + 4 * ds_align(n * 8) + 8192 +
          ds_align((size_t)((n + 63) / 64) * d.R * 8 + 8) + ds_align((size_t)d.RW * 8 + 8) + ds_align((size_t)d.R * 8 + 8) + 256;
@@ -1580,7 +1794,7 @@ int ds_gram_alloc(ds_ctx* ctx, int64_t n, int64_t k, int paired, ds_gram_state* 
   gs->n = n; gs->k = k; gs->R = R; gs->RW = RW; gs->ld = ld; gs->nblk = d.nblk; gs->paired = paired;
   gs->Zt = (uint64_t*)ds_arena_alloc(ctx, (size_t)n * RW * 8);
   gs->slices = d.slices; gs->rows_apart = d.rows_apart; gs->words_per_slice = d.words_per_slice;
-  gs->Gp = (double*)ds_arena_alloc(ctx, (size_t)d.slices * n * n * 8);
+  gs->Gp = (double*)ds_arena_alloc(ctx, n <= kSmallMax ? small_bytes : (size_t)d.slices * n * n * 8);
   gs->M = (double*)ds_arena_alloc(ctx, (size_t)(n + 1) * ld * 8);
   gs->linv = (double*)ds_arena_alloc(ctx, (size_t)d.nblk * NB * NB * 8);
   gs->panel[0] = (double*)ds_arena_alloc(ctx, panel_bytes(n));
@@ -1596,7 +1810,7 @@ int ds_gram_alloc(ds_ctx* ctx, int64_t n, int64_t k, int paired, ds_gram_state* 
   gs->gscale = (double*)ds_arena_alloc(ctx, 64);
   gs->sz = (int32_t*)ds_arena_alloc(ctx, k * 4);
   gs->wc = (float*)ds_arena_alloc(ctx, k * 4);
-  gs->t = (double*)ds_arena_alloc(ctx, k * 8);
+  gs->t = (double*)ds_arena_alloc(ctx, n <= kSmallMax ? small_bytes : k * 8);
   gs->sqw = (double*)ds_arena_alloc(ctx, k * 8);
   gs->gc = (double*)ds_arena_alloc(ctx, R * 8);
   gs->c = (double*)ds_arena_alloc(ctx, n * 8);
@@ -1614,6 +1828,17 @@ int ds_gram_begin(ds_ctx* ctx, ds_gram_state* gs, const uint64_t* Z, const float
   hipStream_t st = ctx->stream;
   const int64_t n = gs->n, R = gs->R, RW = gs->RW, ld = gs->ld, W = (n + 63) / 64;
   const int paired = gs->paired;
+  gs->formed = n > kSmallMax ? ctx->kev[3] : nullptr;   // (the event of the mark below)
+  if (n <= kSmallMax) {
+    const unsigned parts = small_parts(R);
+    DS_TRY(ds_kernel_mark(ctx, 1, 0));
+    hipLaunchKernelGGL(small_gram_kernel, dim3(parts), dim3(kSmallThreads), 0, st, Z, w, R, paired, (int)n, gs->Gp);
+    DS_TRY(ds_kernel_mark(ctx, 1, 1));
+    DS_TRY(ds_kernel_mark(ctx, 2, 0));
+    hipLaunchKernelGGL(small_system_kernel, dim3(1), dim3(kThreads), 0, st, gs->Gp, (int)parts, (int)n, ld, gs->M, gs->linv, gs->flag);
+    DS_HIP(ctx, hipGetLastError());
+    return ds_kernel_mark(ctx, 2, 1);
+  }
   float *gw = gs->gw, *wu = gs->wu;
   int32_t* uni = gs->uni;
   double *Gp = gs->Gp, *m = gs->m, *stats = gs->stats, *gscale = gs->gscale;
@@ -1632,7 +1857,6 @@ int ds_gram_begin(ds_ctx* ctx, ds_gram_state* gs, const uint64_t* Z, const float
   hipLaunchKernelGGL(gram_kernel, dim3(tiles, tiles, gs->slices), dim3(kThreads), 0, st, gs->Zt, n, R, RW, gw, wu, uni, keep,
                      Gp, gs->words_per_slice, gs->rows_apart, Zc, (const unsigned long long*)wq, gscale);
   DS_TRY(ds_kernel_mark(ctx, 1, 1));
-  gs->formed = ctx->kev[3];   // (the mark's event)
   const unsigned wblocks = (unsigned)(n < (int64_t)ctx->num_cus * 16 ? n : (int64_t)ctx->num_cus * 16);
   hipLaunchKernelGGL(sum_slices_row_mean_kernel, dim3(wblocks), dim3(kThreads), 0, st, Gp, n, gs->slices, m);
   hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(kThreads), 0, st, Gp, m, n, stats, gs->flag);
@@ -1772,7 +1996,17 @@ static void launch_back(hipStream_t st, int blocks, int64_t pieces, const ds_gra
 bool ds_gram_ahead_applies(int64_t n) { return n - kSuperCols <= kFuseMaxRows; }
 
 // Part 2 without the right-hand side (ds_gram_ahead_applies); `mid` as for gram_factor.
-int ds_gram_factor_ahead(ds_ctx* ctx, const ds_gram_state* gs, hipEvent_t mid) { return gram_factor(ctx, gs, gs->n, mid); }
+int ds_gram_factor_ahead(ds_ctx* ctx, const ds_gram_state* gs, hipEvent_t mid) {
+  return gs->n <= kSmallMax ? DS_OK : gram_factor(ctx, gs, gs->n, mid);   // (ds_gram_begin has factorised a single block)
+}
+
+static int gram_check(ds_ctx* ctx, const ds_gram_state* gs) {
+  DS_HIP(ctx, hipMemcpyAsync(ctx->h_mail, gs->flag, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+  DS_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  if (*(int*)ctx->h_mail != 0)
+    return ds_fail(ctx, DS_ESINGULAR, "Cholesky met a non-positive pivot: the sampled rows do not determine all %lld players", (long long)gs->n);
+  return DS_OK;
+}
 
 // Part 3: right-hand side from y, factorisation (unless it runs ahead on another stream: `mid` and `done` are its events), back
 // substitution.
@@ -1780,6 +2014,14 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
                    int defer_check, hipEvent_t mid, hipEvent_t done) {
   hipStream_t st = ctx->stream;
   const int64_t n = gs->n, k = gs->k, R = gs->R, RW = gs->RW, ld = gs->ld;
+  if (n <= kSmallMax) {
+    const unsigned parts = small_parts(R);
+    hipLaunchKernelGGL(small_rhs_kernel, dim3(parts), dim3(kSmallThreads), 0, st, Z, w, y, R, gs->paired, (int)n, gs->t);
+    if (done) DS_HIP(ctx, hipStreamWaitEvent(st, done, 0));
+    hipLaunchKernelGGL(small_solve_kernel, dim3(1), dim3(kThreads), 0, st, gs->t, (int)parts, (int)n, gs->linv, y, phi);
+    DS_HIP(ctx, hipGetLastError());
+    return defer_check ? DS_OK : gram_check(ctx, gs);
+  }
   DS_TRY(ds_row_prep(ctx, Z, k, n, gs->paired, w, y, gs->sz, gs->t, gs->sqw, gs->wc));
   hipLaunchKernelGGL(used_row_rhs_kernel, dim3(nblocks(R, 256)), dim3(256), 0, st, gs->wc, gs->t, R, gs->paired, gs->gc);
   DS_TRY(ds_bit_spmv(ctx, gs->Zt, n, R, RW, 0, 1, gs->gc, gs->c));  // c_j = sum over the rows containing j of gc
@@ -1805,12 +2047,7 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
     last = first;
   }
   DS_HIP(ctx, hipGetLastError());
-  if (defer_check) return DS_OK;  // the caller reads gs->flag back with its own results
-  DS_HIP(ctx, hipMemcpyAsync(ctx->h_mail, gs->flag, sizeof(int), hipMemcpyDeviceToHost, st));
-  DS_HIP(ctx, hipStreamSynchronize(st));
-  if (*(int*)ctx->h_mail != 0)
-    return ds_fail(ctx, DS_ESINGULAR, "Cholesky met a non-positive pivot: the sampled rows do not determine all %lld players", (long long)n);
-  return DS_OK;
+  return defer_check ? DS_OK : gram_check(ctx, gs);   // (deferred: the caller reads gs->flag back with its own results)
 }
 
 int ds_solve_gram_chol(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, const float* w, const float* y, int paired,

@@ -214,7 +214,7 @@ struct ds_gram_state {
   int32_t *uni, *sz;
   float *gw, *wu, *wc;
   int* flag;
-  hipEvent_t formed; // recorded by ds_gram_begin behind the Gram kernels: Zt is there, the short launches are left
+  hipEvent_t formed; // recorded by ds_gram_begin behind the Gram kernels: Zt is there, the short launches are left (nullptr: neither)
 };
 int ds_gram_alloc(ds_ctx* ctx, int64_t n, int64_t k, int paired, ds_gram_state* gs);
 int ds_gram_begin(ds_ctx* ctx, ds_gram_state* gs, const uint64_t* Z, const float* w);
