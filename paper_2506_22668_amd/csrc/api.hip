@@ -522,17 +522,14 @@ int ds_copy_probe(ds_ctx* ctx, void* dst, const void* src, int64_t bytes) {
 static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t n_samples, uint64_t seed, const ds_options& o,
                              float* phi, int64_t* M_inout, int64_t* edge_src, int64_t* edge_dst, ds_report* report);
 
-// what ds_explain reads back at its end, in mailbox slots out[0..4]: (y[0], y[1]) as two floats | unused | predicted
-// class | sampler overflow flag | pivot flag of the factorisation (0 without one)
-__global__ void final_mail_kernel(const float* y, const int32_t* pred, const int64_t* sampler_flag, const int* pivot_flag,
-                                  int64_t* out) {
+// what ds_explain reads back at its end, straight into the host's mailbox slots out[0..2]: (y[0], y[1]) as two floats | predicted
+// class | pivot flag of the factorisation (0 without one)
+__global__ void final_mail_kernel(const float* y, const int32_t* pred, const int* pivot_flag, int64_t* out) {
   float* f = (float*)out;
   f[0] = y[0];
   f[1] = y[1];
-  out[1] = 0;
-  out[2] = (int64_t)*pred;
-  out[3] = *sampler_flag;
-  out[4] = pivot_flag ? (int64_t)*pivot_flag : 0;
+  out[1] = (int64_t)*pred;
+  out[2] = pivot_flag ? (int64_t)*pivot_flag : 0;
 }
 
 int ds_explain(ds_ctx* ctx, int64_t target, int64_t n_samples, uint64_t seed, const ds_options* opts, float* phi,
@@ -718,18 +715,15 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   }
   if (rc != DS_OK && rc != DS_ENOTCONV) return rc;
   DS_HIP(ctx, hipEventRecord(ctx->ev[4], st));
-  // one round trip for everything the host still needs: f(empty), f(full), predicted class, sampler flag, pivot
-  // flag, gathered into consecutive mailbox slots by one small kernel and copied once
+  // one round trip for everything the host still needs: f(empty), f(full), predicted class, pivot flag (the sampler's flag is the host's)
   float* f01 = (float*)(ctx->h_mail + 32);
-  hipLaunchKernelGGL(final_mail_kernel, dim3(1), dim3(1), 0, st, y, cg->d_pred, ctx->d_mail + DS_MAIL_SAMPLER,
-                     direct ? gs.flag : (const int*)nullptr, ctx->d_mail + 32);
+  hipLaunchKernelGGL(final_mail_kernel, dim3(1), dim3(1), 0, st, y, cg->d_pred, direct ? gs.flag : (const int*)nullptr, ctx->h_mail + 32);
   DS_HIP(ctx, hipGetLastError());
-  DS_HIP(ctx, hipMemcpyAsync(ctx->h_mail + 32, ctx->d_mail + 32, 5 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
   DS_HIP(ctx, hipStreamSynchronize(st));
   guard.queued = false;
-  if (n >= 2 && ctx->h_mail[35] != 0)
+  if (n >= 2 && ctx->h_mail[DS_MAIL_SAMPLER] != 0)
     return ds_fail(ctx, DS_EINTERNAL, "sampler: candidate list overflow (too many keys share a 24-bit prefix)");
-  if (direct && *(int*)(ctx->h_mail + 36) != 0) {
+  if (direct && ctx->h_mail[34] != 0) {
     if (o.solver != DS_SOLVER_AUTO)
       return ds_fail(ctx, DS_ESINGULAR, "Cholesky met a non-positive pivot: the sampled rows do not determine all %lld players", (long long)n);
     // rank-deficient: the minimum-norm solve instead
@@ -747,7 +741,7 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   }
   rep.f_empty = f01[0];
   rep.f_full = f01[1];
-  rep.pred_class = *(int32_t*)(ctx->h_mail + 34);
+  rep.pred_class = (int32_t)ctx->h_mail[33];
   cg->pred_class = rep.pred_class;
   const bool apart = cg->ms_extract > 0.f;   // (the clock then starts with ev[1])
   if (apart) rep.ms_extract = cg->ms_extract;

@@ -43,9 +43,10 @@ struct EvalArgs {
   const float* P;
   const float* Wl[DS_MAX_LAYERS];
   const float* bias[DS_MAX_LAYERS];
-  const uint64_t* Z;
+  const uint64_t* Z;  // nullptr: every player is present in every row
   float* y;
   float* logits_out;  // optional: [k x d_L]
+  int32_t* class_out; // optional: the first maximum of the (last) row's logits, and no score
   float* gws;         // per-workgroup global scratch when LDS is too small
   int64_t gws_stride; // floats per workgroup
   int32_t bufA_floats, bufB_floats;
@@ -108,7 +109,7 @@ __device__ __forceinline__ void aggregate_rows(const EvalArgs& a, const uint64_t
         if (e < e1) {
           const int p = a.eid[e];
           srcn = a.col[e];
-          bit = (z[p >> 6] >> (p & 63)) & 1ull;
+          bit = !z || ((z[p >> 6] >> (p & 63)) & 1ull);
           coef = rs[srcn];
         }
         unsigned long long mask = __ballot(bit);
@@ -230,6 +231,22 @@ __device__ __forceinline__ void transform_rows(const float* q, int rows, int din
   }
 }
 
+// first maximum of logits[0..C) (ties -> lowest index), one wave; the value in every lane
+__device__ __forceinline__ int first_maximum(const float* logits, int C) {
+  float best = -INFINITY;
+  int arg = 0x7fffffff;
+  for (int c = threadIdx.x & 63; c < C; c += 64) {
+    const float v = logits[c];
+    if (v > best) { best = v; arg = c; }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const float ob = __shfl_xor(best, o, 64);
+    const int oa = __shfl_xor(arg, o, 64);
+    if (ob > best || (ob == best && oa < arg)) { best = ob; arg = oa; }
+  }
+  return arg == 0x7fffffff ? 0 : arg;
+}
+
 // THREADS: 256, or 1,024 where a compute unit has at most one workgroup: few coalitions (the predicted class above all) or degrees and
 // buffers that fill its LDS. A row is a chain of latencies and the rows are dealt to the waves, so that what matters then is how
 // many there are (one coalition of 1,010 players 80 -> 53 us; 1,000 of a graph of 25,000 nodes 4.03 -> 1.54 ms).
@@ -253,10 +270,10 @@ __global__ __launch_bounds__(THREADS) void masked_gcn_eval_kernel(EvalArgs a) {
   const uint64_t tail_mask = (a.n & 63) ? ((1ull << (a.n & 63)) - 1ull) : ~0ull;
 
   for (int64_t row = blockIdx.x; row < a.k; row += gridDim.x) {
-    const uint64_t* z = a.Z + row * W;
+    const uint64_t* z = a.Z ? a.Z + row * W : nullptr;
     // coalition size decides which polarity is cheaper to walk
     int c = 0;
-    for (int64_t w0 = tid; w0 < W; w0 += 8 * THREADS) {  // eight independent loads per thread and step
+    for (int64_t w0 = tid; z && w0 < W; w0 += 8 * THREADS) {  // eight independent loads per thread and step
       uint64_t v[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
@@ -267,13 +284,13 @@ __global__ __launch_bounds__(THREADS) void masked_gcn_eval_kernel(EvalArgs a) {
       for (int q = 0; q < 8; ++q) c += __popcll(v[q]);
     }
     const int total = block_sum_int<WAVES>(c, red);
-    const bool dense = 2 * (int64_t)total > a.n;
+    const bool dense = !z || 2 * (int64_t)total > a.n;
     const int step = dense ? -1 : 1;
     int* deg = (int*)rs;
     for (int i = tid; i < a.V; i += THREADS) deg[i] = dense ? (a.row_ptr[i + 1] - a.row_ptr[i] + 1) : 1;
     __syncthreads();
     // every thread walks four words at a time, so that four end-point look-ups are in flight
-    for (int64_t w0 = tid; w0 < W; w0 += 4 * THREADS) {
+    for (int64_t w0 = tid; z && w0 < W; w0 += 4 * THREADS) {   // (nobody is missing otherwise)
       uint64_t bits[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -330,7 +347,10 @@ __global__ __launch_bounds__(THREADS) void masked_gcn_eval_kernel(EvalArgs a) {
       float s = 0.f;
       for (int cidx = tid; cidx < C; cidx += 64) s += expf(bufA[cidx] - m);
       for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-      if (tid == 0) {
+      if (a.class_out) {
+        const int arg = first_maximum(bufA, C);
+        if (tid == 0) *a.class_out = arg;
+      } else if (tid == 0) {
         const float zc = bufA[*a.pred_ptr];
         a.y[row] = a.score == DS_SCORE_LOGIT ? zc : expf(zc - m) / s;
       }
@@ -1785,21 +1805,10 @@ __global__ __launch_bounds__(kThreads) void first_transform_kernel(const float* 
   }
 }
 
-// first maximum of logits[0..C) (ties -> lowest index), one wave
+// one wave
 __global__ void argmax_kernel(const float* logits, int C, int32_t* out) {
-  const int lane = threadIdx.x;
-  float best = -INFINITY;
-  int arg = 0x7fffffff;
-  for (int c = lane; c < C; c += 64) {
-    const float v = logits[c];
-    if (v > best) { best = v; arg = c; }
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ob = __shfl_xor(best, o, 64);
-    const int oa = __shfl_xor(arg, o, 64);
-    if (ob > best || (ob == best && oa < arg)) { best = ob; arg = oa; }
-  }
-  if (lane == 0) *out = arg == 0x7fffffff ? 0 : arg;
+  const int arg = first_maximum(logits, C);
+  if (threadIdx.x == 0) *out = arg;
 }
 
 __global__ void store_i32_kernel(int32_t* p, int32_t v) { *p = v; }
@@ -2158,26 +2167,23 @@ int ds_prepare_model(ds_ctx* ctx, ds_cgraph* cg) {
   float* logits = (float*)ds_arena_alloc(ctx, C * 4 + 8);
   float* gws = lay.gws_floats ? (float*)ds_arena_alloc(ctx, (size_t)lay.gws_floats * 4) : nullptr;
   if (!zfull || !logits || (lay.gws_floats && !gws)) return ds_fail(ctx, DS_EINTERNAL, "prepare: arena exhausted");
-  if (W > 0) hipLaunchKernelGGL(fill_full_mask, dim3((unsigned)((W + 255) / 256)), dim3(256), 0, ctx->stream, zfull, W, (int)n);
-  EvalArgs a;
-  fill_args(ctx, cg, lay, &a);
-  a.Z = zfull;
-  a.k = 1;
-  a.y = logits + C;  // one float of scratch after the logits
-  a.logits_out = logits;
-  a.gws = gws;
-  a.score = DS_SCORE_LOGIT;
-  hipLaunchKernelGGL(store_i32_kernel, dim3(1), dim3(1), 0, ctx->stream, cg->d_pred, 0);  // a kernel, not a memset node
-  a.pred_ptr = cg->d_pred;
   // a large graph: one workgroup would walk every entry alone (21 ms for 200k entries); the layer-by-layer kernels
   // spread the rows of the one coalition over the whole GPU
   // (where the workspace has the room: the entry point that may not allocate keeps the one-workgroup form)
-  if (prepare_uses_blocks(ctx, cg) && ctx->arena_bytes - ctx->arena_used >= ds_eval_zt_arena_bytes(ctx, cg, 1, 1))
-    DS_TRY(ds_eval_zt(ctx, cg, zfull, 1, DS_SCORE_LOGIT, logits + C, logits, cg->d_pred));
-  else
+  if (prepare_uses_blocks(ctx, cg) && ctx->arena_bytes - ctx->arena_used >= ds_eval_zt_arena_bytes(ctx, cg, 1, 1)) {
+    DS_TRY(ds_launch_full_mask(ctx, zfull, W, n));
+    hipLaunchKernelGGL(store_i32_kernel, dim3(1), dim3(1), 0, ctx->stream, cg->d_pred, 0);  // a kernel, not a memset node
+    DS_TRY(ds_eval_zt(ctx, cg, zfull, 1, DS_SCORE_LOGIT, logits + C, logits, cg->d_pred));   // (one float of scratch after the logits)
+    DS_TRY(ds_launch_argmax(ctx, logits, C, cg->d_pred));
+  } else {   // one launch: no mask row to be filled, the class where the logits are
+    EvalArgs a;
+    fill_args(ctx, cg, lay, &a);
+    a.Z = nullptr;
+    a.k = 1;
+    a.class_out = cg->d_pred;
+    a.gws = gws;
     DS_TRY(launch_eval(ctx, a, lay, 1));
-  hipLaunchKernelGGL(argmax_kernel, dim3(1), dim3(64), 0, ctx->stream, logits, C, cg->d_pred);
-  DS_HIP(ctx, hipGetLastError());
+  }
   cg->pred_class = -1;
   cg->model_version = ctx->model_version;
   return DS_OK;

@@ -220,6 +220,7 @@ struct GraphOut {
   int2* pl;
   int64_t* node_gid;
   int32_t* hop;
+  float* Xc;
 };
 
 __global__ void assign_nodes(const int32_t* dist, const int32_t* lid_scan, const int32_t* rank_scan, int64_t N,
@@ -268,20 +269,28 @@ __global__ __launch_bounds__(kThreads) void count_entries(const int64_t* row_ptr
 
 // one wave per member: ordered compaction of its row into the local CSR, player ids
 // for the entries this row owns (undirected: neighbours with larger global id;
-// directed: every entry). The local id of node j at hop d is lid[d * lid_stride + j].
+// directed: every entry), and the member's own entries of the per-node arrays and its feature row. The local id of node j at
+// hop d is lid[d * lid_stride + j].
 __global__ __launch_bounds__(kThreads) void fill_entries(const int64_t* row_ptr, const int32_t* col, const int32_t* dist,
                                                          const int32_t* lid_scan, int64_t lid_stride, const int32_t* lid_of_rank,
-                                                         const int32_t* player_start_rank, int64_t V, int directed,
-                                                         GraphOut out) {
+                                                         const int32_t* player_start_rank, const int32_t* row_start,
+                                                         const int64_t* node_gid, const int32_t* hop, const float* X, int d0,
+                                                         int64_t V, int directed, GraphOut out) {
   const int lane = threadIdx.x & 63;
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
   const unsigned long long lt = (1ull << lane) - 1ull;
   for (int64_t rk = wave; rk < V; rk += nwaves) {
     const int32_t lid = lid_of_rank[rk];
-    const int64_t g = out.node_gid[lid];
+    const int64_t g = node_gid[lid];
     const int64_t a = row_ptr[g], b = row_ptr[g + 1];
-    int32_t pos = out.row_ptr[lid];
+    int32_t pos = row_start[lid];
+    if (lane == 0) {
+      out.row_ptr[lid] = pos;
+      out.node_gid[lid] = g;
+      out.hop[lid] = hop[lid];
+      if (rk == 0) out.row_ptr[V] = row_start[V];
+    }
     int32_t ppos = player_start_rank[rk];
     for (int64_t e0 = a; e0 < b; e0 += 64) {
       const int64_t e = e0 + lane;
@@ -307,13 +316,22 @@ __global__ __launch_bounds__(kThreads) void fill_entries(const int64_t* row_ptr,
       pos += __popcll(m_in);
       ppos += __popcll(m_own);
     }
+    constexpr int kAhead = 4;
+    for (int f0 = lane; f0 < d0; f0 += 64 * kAhead) {   // (its loads in flight together; past the end the last feature is read again)
+      float x[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) x[u] = X[g * d0 + (f0 + 64 * u < d0 ? f0 + 64 * u : d0 - 1)];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (f0 + 64 * u < d0) out.Xc[(int64_t)lid * d0 + f0 + 64 * u] = x[u];
+    }
   }
 }
 
 // undirected: entries (row b, neighbour a) with gid(a) < gid(b) look their player
-// up in a's owned range (ascending in the global id of the far end).
+// up in a's owned range (ascending in the global id of the far end). unmatched: host memory, set if one has none.
 __global__ void backfill_entries(GraphOut out, const int32_t* rank_scan, const int32_t* player_start_rank, int64_t V,
-                                 int64_t* mail) {
+                                 volatile int64_t* unmatched) {
   const int lane = threadIdx.x & 63;
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -335,7 +353,7 @@ __global__ void backfill_entries(GraphOut out, const int32_t* rank_scan, const i
         }
         if (bg < g) lo = mid + 1; else hi = mid;
       }
-      if (found < 0) atomicExch((unsigned long long*)&mail[10], 1ull);
+      if (found < 0) *unmatched = 1;
       out.eid[e] = found < 0 ? 0 : found;
     }
   }
@@ -579,8 +597,8 @@ __global__ __launch_bounds__(kBallThreads) void ball_rank_kernel(const int32_t* 
 }
 
 // the members' entry and player counts into row and player starts (V + 1 each, in place), their totals and the entries of every
-// ball: one workgroup
-__global__ __launch_bounds__(kBallThreads) void ball_rows_kernel(int32_t* row_start, int32_t* player_start, int64_t* mail) {
+// ball: one workgroup, which leaves the mailbox with the host too (a copy behind it would be one more launch to wait for)
+__global__ __launch_bounds__(kBallThreads) void ball_rows_kernel(int32_t* row_start, int32_t* player_start, int64_t* mail, int64_t* host_mail) {
   __shared__ int sums[2][kBallWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int V = (int)mail[11];
@@ -624,6 +642,8 @@ __global__ __launch_bounds__(kBallThreads) void ball_rows_kernel(int32_t* row_st
     mail[8] = at_row;
     mail[9] = at_player;
   }
+  __syncthreads();
+  if (tid < 48) host_mail[tid] = mail[tid];
 }
 
 // the same for many members, a workgroup to 1,024 of them, each of which sums the counts before its own for itself; into other
@@ -671,14 +691,6 @@ __global__ __launch_bounds__(kBallThreads) void ball_rows_wide_kernel(const int3
   }
 }
 
-__global__ void gather_rows(const float* X, const int64_t* node_gid, int64_t V, int d0, float* Xc) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= V * d0) return;
-  const int64_t t = idx / d0;
-  const int f = (int)(idx - t * d0);
-  Xc[idx] = X[node_gid[t] * d0 + f];
-}
-
 inline unsigned blocks_for(int64_t n, int per = kThreads) { return (unsigned)((n + per - 1) / per); }
 
 }  // namespace
@@ -714,16 +726,6 @@ __global__ void zero_three_kernel(int32_t* a, int32_t* b, int32_t* c) {
     *a = 0;
     *b = 0;
     *c = 0;
-  }
-}
-// the three per-node arrays of the computational graph in one launch (row_ptr has V + 1 entries)
-__global__ void copy_node_arrays_kernel(const int32_t* rp, const int64_t* gid, const int32_t* hop, int64_t V, int32_t* rp_out,
-                                        int64_t* gid_out, int32_t* hop_out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i <= V) rp_out[i] = rp[i];
-  if (i < V) {
-    gid_out[i] = gid[i];
-    hop_out[i] = hop[i];
   }
 }
 struct BallSizes { int32_t v[8]; };
@@ -788,9 +790,10 @@ int ds_extract_impl(ds_ctx* ctx, int64_t target, int hops, int directed, ds_cgra
                        lid_scan, rank_scan, node_gid_tmp, hop_tmp, lid_of_rank, mail, maps);
     hipLaunchKernelGGL(count_entries, dim3(ctx->num_cus * 2), dim3(kThreads), 0, st, ctx->row_ptr, ctx->col, dist, node_gid_tmp, lid_of_rank,
                        mail + 11, rowptr_tmp, cnt_all_rank, cnt_up_rank);
-    hipLaunchKernelGGL(ball_rows_kernel, dim3(1), dim3(kBallThreads), 0, st, rowptr_tmp, directed ? cnt_all_rank : cnt_up_rank, mail);
+    hipLaunchKernelGGL(ball_rows_kernel, dim3(1), dim3(kBallThreads), 0, st, rowptr_tmp, directed ? cnt_all_rank : cnt_up_rank, mail,
+                       ctx->h_mail);
     DS_HIP(ctx, hipGetLastError());
-    DS_TRY(ds_mail_fetch(ctx, 48));
+    DS_HIP(ctx, hipStreamSynchronize(st));
     if (ctx->h_mail[12] != 0) {   // more than one workgroup's work
       int h = (int)ctx->h_mail[12];
       hipLaunchKernelGGL(ball_unpack_kernel, dim3(blocks_for(N)), dim3(kThreads), 0, st, maps, N, h, dist, cur, mail);
@@ -914,16 +917,14 @@ int ds_extract_impl(ds_ctx* ctx, int64_t target, int hops, int directed, ds_cgra
   ctx->graphs.push_back(cg);
   *out_cg = cg;
 
-  hipLaunchKernelGGL(copy_node_arrays_kernel, dim3((unsigned)((V + 1 + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
-                     rowptr_tmp, node_gid_tmp, hop_tmp, V, cg->row_ptr, cg->node_gid, cg->hop);
-  GraphOut go{cg->row_ptr, cg->col, cg->eid, cg->pl, cg->node_gid, cg->hop};
-  hipLaunchKernelGGL(fill_entries, dim3(wave_blocks()), dim3(kThreads), 0, st, ctx->row_ptr, ctx->col, dist, lid_scan, lid_stride, lid_of_rank, player_start, V, directed, go);
+  ctx->h_mail[10] = 0;   // (nothing is under way: the sizes have been read)
+  GraphOut go{cg->row_ptr, cg->col, cg->eid, cg->pl, cg->node_gid, cg->hop, cg->Xc};
+  hipLaunchKernelGGL(fill_entries, dim3(wave_blocks()), dim3(kThreads), 0, st, ctx->row_ptr, ctx->col, dist, lid_scan, lid_stride, lid_of_rank,
+                     player_start, rowptr_tmp, node_gid_tmp, hop_tmp, ctx->X, d0, V, directed, go);
   if (!directed && nnz_c > 0)
-    hipLaunchKernelGGL(backfill_entries, dim3(wave_blocks()), dim3(kThreads), 0, st, go, rank_scan, player_start, V, mail);
-  if (V * d0 > 0)
-    hipLaunchKernelGGL(gather_rows, dim3(blocks_for(V * d0)), dim3(kThreads), 0, st, ctx->X, cg->node_gid, V, d0, cg->Xc);
+    hipLaunchKernelGGL(backfill_entries, dim3(wave_blocks()), dim3(kThreads), 0, st, go, rank_scan, player_start, V, ctx->h_mail + 10);
   DS_HIP(ctx, hipGetLastError());
-  DS_TRY(ds_mail_fetch(ctx, 16));
+  DS_HIP(ctx, hipStreamSynchronize(st));
   ds_arena_reset(ctx);
   if (ctx->h_mail[10] != 0) {
     ds_cgraph_free(ctx, cg);

@@ -150,7 +150,7 @@ struct ds_plan {
 };
 int ds_make_plan(ds_ctx* ctx, int64_t n, int64_t n_samples, ds_plan* plan, int weighting = DS_WEIGHT_CLASS_MASS,
                  int saturate = 0);
-// launches the sampler; the overflow flag is left in device mailbox slot DS_MAIL_SAMPLER (checked by the caller)
+// launches the sampler; the overflow flag is left in host mailbox slot DS_MAIL_SAMPLER (checked by the caller behind the kernels)
 // lists (optional, only with pair_begin == 0): filled as described at ds_pair_lists; entries and offset are the
 // caller's allocations (ds_pair_list_entries(plan, max_size) entries, plan.k / 2 offsets)
 int ds_sample_launch(ds_ctx* ctx, const ds_plan& plan, uint64_t seed, uint32_t tag, int64_t pair_begin,
@@ -161,7 +161,7 @@ bool ds_sampler_lists_possible(const ds_ctx* ctx, const ds_plan& plan);
 // whether ds_eval_impl would run the mask-streaming kernel on k paired rows of this graph (the consumer of the lists)
 bool ds_eval_streams_pairs(ds_ctx* ctx, const ds_cgraph* cg, int64_t k);
 int ds_sample_check(ds_ctx* ctx);  // synchronises and turns the flag into a status
-#define DS_MAIL_SAMPLER 20
+#define DS_MAIL_SAMPLER 50   // (beyond what the extraction and the CGLS loop leave in the mailbox)
 int ds_fetch_pred_class(ds_ctx* ctx, ds_cgraph* cg);  // device -> host copy of the predicted class (synchronises)
 size_t ds_sample_arena_bytes(const ds_plan& plan);
 

@@ -137,7 +137,7 @@ struct SampleArgs {
   uint64_t* Z;
   float* w;
   int32_t* sz;
-  int* error_flag;
+  volatile int64_t* error_flag;   // host memory
   uint32_t window_cap;  // entries of the dynamic-LDS window list
   int32_t* retry;          // pairs the one-pass kernel hands to the multi-pass kernel (offsets from pair_begin), or null
   uint32_t* retry_count;
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(THREADS) void sample_pairs_kernel(SampleArgs a) {
     }
     uint32_t nc = cand_count;
     if (nc > kCandMax) {  // never in practice (needs > 2048 of n keys in one 2^-24 slice)
-      if (t == 0) atomicExch(a.error_flag, 1);
+      if (t == 0) *a.error_flag = 1;
       nc = kCandMax;
     }
     for (uint32_t i = t; i < nc; i += THREADS) {
@@ -619,13 +619,15 @@ int ds_sample_launch(ds_ctx* ctx, const ds_plan& plan, uint64_t seed, uint32_t t
   if (plan.enum_upto > 0 && (double)plan.K * (double)plan.n >= 4.0e18)
     return ds_fail(ctx, DS_EINVAL, "saturated size classes: the plan is too large for exact 64-bit unranking");
   const int64_t H = plan.H;
-  int64_t* d_b = (int64_t*)ds_arena_alloc(ctx, (H + 1) * sizeof(int64_t));
-  float* d_wtab = (float*)ds_arena_alloc(ctx, (H + 1) * sizeof(float));
   const int64_t lmax = lists ? (lists->max_size < H ? lists->max_size : H) : 0;
-  int64_t* d_cum = lists ? (int64_t*)ds_arena_alloc(ctx, (lmax + 2) * sizeof(int64_t)) : nullptr;
-  if (!d_b || !d_wtab || (lists && !d_cum)) return ds_fail(ctx, DS_EINTERNAL, "sampler: arena exhausted");
-  // the plan tables go through pinned staging so that the upload is asynchronous
-  const size_t need = ds_align((H + 1) * sizeof(int64_t)) + ds_align((H + 1) * sizeof(float)) + ds_align((lmax + 2) * sizeof(int64_t));
+  // the plan's tables and the retry counter's zero go through pinned staging in one asynchronous upload
+  const size_t at_w = ds_align((H + 1) * sizeof(int64_t)), at_cum = at_w + ds_align((H + 1) * sizeof(float));
+  const size_t at_retry = at_cum + (lists ? ds_align((lmax + 2) * sizeof(int64_t)) : 0), need = at_retry + 256;
+  char* const tables = (char*)ds_arena_alloc(ctx, need);
+  if (!tables) return ds_fail(ctx, DS_EINTERNAL, "sampler: arena exhausted");
+  int64_t* const d_b = (int64_t*)tables;
+  float* const d_wtab = (float*)(tables + at_w);
+  int64_t* const d_cum = lists ? (int64_t*)(tables + at_cum) : nullptr;
   if (ctx->stage_busy) {
     DS_HIP(ctx, hipEventSynchronize(ctx->stage_ev));
     ctx->stage_busy = false;
@@ -639,24 +641,21 @@ int ds_sample_launch(ds_ctx* ctx, const ds_plan& plan, uint64_t seed, uint32_t t
     ctx->h_stage_bytes = need;
   }
   char* hb = ctx->h_stage;
-  char* hw = ctx->h_stage + ds_align((H + 1) * sizeof(int64_t));
   memcpy(hb, plan.b.data(), (H + 1) * sizeof(int64_t));
-  memcpy(hw, plan.wtab.data(), (H + 1) * sizeof(float));
-  DS_HIP(ctx, hipMemcpyAsync(d_b, hb, (H + 1) * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream));
-  DS_HIP(ctx, hipMemcpyAsync(d_wtab, hw, (H + 1) * sizeof(float), hipMemcpyHostToDevice, ctx->stream));
+  memcpy(hb + at_w, plan.wtab.data(), (H + 1) * sizeof(float));
+  memset(hb + at_retry, 0, 256);
   if (lists) {   // entries before each listed class; every pair starts without a list
-    int64_t* hc = (int64_t*)(hw + ds_align((H + 1) * sizeof(float)));
+    int64_t* hc = (int64_t*)(hb + at_cum);
     hc[0] = 0;
     hc[1] = 0;
     for (int64_t s = 1; s <= lmax; ++s) hc[s + 1] = hc[s] + (plan.b[s] - plan.b[s - 1]) * s;
     if (hc[lmax + 1] > lists->total) return ds_fail(ctx, DS_EINTERNAL, "sampler: the player lists need %lld entries, %lld are reserved", (long long)hc[lmax + 1], (long long)lists->total);
-    DS_HIP(ctx, hipMemcpyAsync(d_cum, hc, (lmax + 2) * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream));
     DS_HIP(ctx, hipMemsetAsync(lists->offset, 0xFF, (size_t)(pair_end - pair_begin) * sizeof(int64_t), ctx->stream));
   }
+  DS_HIP(ctx, hipMemcpyAsync(tables, hb, need, hipMemcpyHostToDevice, ctx->stream));
   DS_HIP(ctx, hipEventRecord(ctx->stage_ev, ctx->stream));
   ctx->stage_busy = true;
-  int* d_err = (int*)(ctx->d_mail + DS_MAIL_SAMPLER);
-  DS_HIP(ctx, hipMemsetAsync(d_err, 0, sizeof(int64_t), ctx->stream));
+  ctx->h_mail[DS_MAIL_SAMPLER] = 0;   // (every sampling call has waited for its kernels)
   SampleArgs a;
   a.n = plan.n;
   a.W = (plan.n + 63) / 64;
@@ -673,7 +672,7 @@ int ds_sample_launch(ds_ctx* ctx, const ds_plan& plan, uint64_t seed, uint32_t t
   a.Z = Z;
   a.w = w;
   a.sz = sz;
-  a.error_flag = d_err;
+  a.error_flag = ctx->h_mail + DS_MAIL_SAMPLER;
   a.list = lists ? lists->entries : nullptr;
   a.list_cum = d_cum;
   a.list_offset = lists ? lists->offset : nullptr;
@@ -703,9 +702,8 @@ int ds_sample_launch(ds_ctx* ctx, const ds_plan& plan, uint64_t seed, uint32_t t
     if (a.window_cap > 0 && pairs < 0x7fffffffLL && plan.n >= 4096) {   // (a lane makes 32 columns: short rows leave the one-pass kernel idle)
       // one pass for the pairs whose threshold falls where it is expected, the multi-pass kernel for the rest
       a.retry = (int32_t*)ds_arena_alloc(ctx, (size_t)(pairs + 1) * 4);
-      a.retry_count = (uint32_t*)ds_arena_alloc(ctx, 256);
-      if (!a.retry || !a.retry_count) return ds_fail(ctx, DS_EINTERNAL, "sampler: arena exhausted");
-      DS_HIP(ctx, hipMemsetAsync(a.retry_count, 0, 4, ctx->stream));
+      a.retry_count = (uint32_t*)(tables + at_retry);
+      if (!a.retry) return ds_fail(ctx, DS_EINTERNAL, "sampler: arena exhausted");
       const int64_t fblocks = pairs < (int64_t)ctx->num_cus * 32 ? pairs : (int64_t)ctx->num_cus * 32;
       hipLaunchKernelGGL(sample_pairs_fast_kernel, dim3((unsigned)fblocks), dim3(kFastThreads), 0, ctx->stream, a);
       const int64_t rblocks = blocks < (int64_t)ctx->num_cus * 4 ? blocks : (int64_t)ctx->num_cus * 4;
@@ -721,8 +719,6 @@ int ds_sample_launch(ds_ctx* ctx, const ds_plan& plan, uint64_t seed, uint32_t t
 }
 
 int ds_sample_check(ds_ctx* ctx) {
-  DS_HIP(ctx, hipMemcpyAsync(ctx->h_mail + DS_MAIL_SAMPLER, ctx->d_mail + DS_MAIL_SAMPLER, sizeof(int64_t),
-                             hipMemcpyDeviceToHost, ctx->stream));
   DS_HIP(ctx, hipStreamSynchronize(ctx->stream));
   if (ctx->h_mail[DS_MAIL_SAMPLER] != 0)
     return ds_fail(ctx, DS_EINTERNAL, "sampler: candidate list overflow (more than %d keys share a 24-bit prefix)", kCandMax);
