@@ -210,39 +210,54 @@ __global__ __launch_bounds__(kThreads) void bit_spmv_rows_kernel(const uint64_t*
   }
 }
 
-// ---- dense rows: product on the int8 matrix cores ------------------------------------------
+// ---- dense rows: product on the fp4 x fp6 matrix cores --------------------------------------
 // out[i] = sum over set bits j of row i of x[j], for rows dense enough that one look-up or one
 // gather per set bit (or per byte of mask) costs more than streaming the bits. The product is a
-// (rows x cols 0/1 matrix) . (cols x 7 matrix of base-256 digits of x): exact integer arithmetic.
-//  * x is scaled by a power of two so that max|x| < 2^54 and rounded to integers (the same 2^-54
-//    relative step for every entry); each integer is written in seven balanced base-256 digits
-//    (-128..127), one int8 plane per digit (`quantize_kernel`).
-//  * A operand of v_mfma_i32_16x16x64_i8 = 16 rows x 64 columns of mask bits as bytes. A lane holds
-//    16 bytes of one row; the bytes come from the lane's four 32-bit mask words by ONE AND each:
-//    word & (0x01010101 << j) puts bit j of every mask byte into a byte of its own (value 2^j), so
-//    operand j multiplies the columns {8i + j} and its accumulator carries the factor 2^(j & 3)
-//    (bits 4..7 after a shift of the word by 4), divided out exactly at the end. The digit planes
-//    are stored permuted to match: within every 128 columns, position j<<4 | v<<2 | i holds column
-//    v<<5 | i<<3 | j, so the B operand of (word group, j) is 16 contiguous bytes.
-//  * B operand = digits (7 of the 16 columns used; the eighth plane is zero and serves the idle
-//    columns). The planes of a 1024-column chunk are staged in LDS once per workgroup and read by
-//    all of its waves, one (half, nibble) group of four operands ahead of their use.
+// (rows x cols 0/1 matrix) . (cols x 14 matrix of base-16 digits of x): exact integer arithmetic, carried by
+// floating-point formats that hold these integers exactly.
+//  * x is scaled by a power of two so that max|x| < 2^54 and rounded to integers (the same 2^-54 relative step for
+//    every entry); 2^54 is added, so that the 14 digits are 0..15 and a digit is its own code in fp6 (e2m3: the magnitude
+//    codes 0..15 are the multiples of 1/8). A fifteenth plane of ones counts the columns, to take the 2^54s off again.
+//  * A operand of v_mfma_scale_f32_16x16x128_f8f6f4 = 16 rows x 128 columns of mask bits as fp4. A lane holds 32 nibbles
+//    of one row, which come from the lane's four 32-bit mask words by ONE AND each: word & (0x11111111 << j) leaves
+//    bit j of every nibble in place, the fp4 (e2m1) codes 1, 2, 4 are 1/2, 1, 2, and bit 3, the sign, is shifted down to
+//    code 4. The instruction's block scales (2, 1, 1/2, 1/2 and 8 for the digits) make every product digit x bit, so that
+//    operand j multiplies the columns {4i + j} and all four share one accumulator. Lane l supplies row (column of B)
+//    l % 16 and the k from 32 (l / 16) on; digits are stored in the order that matches: within 128 columns, operand j's
+//    element 8 w + i is column 32 w + 4 i + j, six bits each, 24 bytes.
+//  * Sums of up to 2^20 digits stay below 2^24 and are exact in the fp32 accumulators.
+//  * The planes of a 1024-column chunk are staged in LDS once per workgroup and read by all of its waves.
 //  * A wave owns 64 rows (four 16-row tiles); per chunk every row is visited with 128 contiguous
-//    bytes (two 16-byte loads per lane and tile), requested one chunk ahead.
-// The per-column-group partial sums are int32 (exact) and are added up, recombined
-// (sum_d 256^d S_d, as two exact integer halves) and rescaled by a second kernel, so the result does not
-// depend on the grouping.
+//    bytes (two 16-byte loads per lane and tile), requested two chunks ahead.
+// (On the int8 instruction, seven base-256 digits against bytes of one bit: half as many columns per instruction of the
+// same 16 cycles, twice the ANDs, four accumulators for the four places of a bit, which left no registers for a second
+// chunk on its way. The products of 99,981 players, 117 MB each: 37.5 us on average, now 32.5 in the loop and 29 alone, of which the
+// loads take 21; 300,007 players, 318 MB: 86.5 on average, now 81.)
+// The digit sums of a row are put together as two exact integers (2^24 hi + lo); those of its column groups are added up and rescaled by
+// whoever reads them, so the result does not depend on the grouping.
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int kMmTiles = 4;                          // 16-row tiles per wave
 constexpr int kMmWaves = 4;                          // waves per workgroup
+constexpr int kMmThreads = 64 * kMmWaves;
 constexpr int kMmWaveRows = 16 * kMmTiles;
 constexpr int kMmRows = kMmWaveRows * kMmWaves;      // rows per workgroup
 constexpr int kMmChunk = 1024;                       // columns per step
 constexpr int kMmHalves = kMmChunk / 512;            // 64-byte pieces of a row per chunk
-constexpr int kMmDigits = 7;
-constexpr int kMmPlanes = 8;
-constexpr int kMmPlanePitch = kMmChunk + 16;         // LDS pitch of a plane: the eight planes start 16 bytes (4 banks) apart
-constexpr int64_t kMmMaxGroupCols = 1 << 20;         // 2^20 columns * 128 * 2^3 = 2^30: the int32 accumulators cannot overflow
+constexpr int kMmDigits = 14;                        // base 16
+constexpr int kMmPlanes = kMmDigits + 1;             // and the plane of ones
+constexpr int kMmSums = 8;                           // sums of a row in LDS: seven base-256 digits, the count
+constexpr int kMmSumBytes = 16;                      // and in memory: hi, lo
+constexpr int kMmSumPitch = kMmSums + 1;
+constexpr int kMmOperand = 24;                       // bytes of a lane's B operand: 32 elements of six bits
+constexpr int kMmPlaneBytes = kMmChunk * 6 / 8;      // of a chunk: [512 columns][lane group of 128][j] operands
+constexpr int kMmChunkBytes = kMmPlanes * kMmPlaneBytes;
+// LDS image of a chunk: the four operands of a lane group in 128 bytes, planes 8 bytes further, so that the 32 lanes of half a
+// wave read 8 bytes each from all 64 banks
+constexpr int kMmGroupPitch = 128;
+constexpr int kMmPlanePitch = kMmHalves * 4 * kMmGroupPitch + 8;
+constexpr int64_t kMmMaxGroupCols = 1 << 20;         // 2^20 columns * 15 < 2^24: exact in fp32
 
 // max_parts[block] = bit pattern of the block's max |x| (non-negative doubles order like their bit patterns)
 __global__ __launch_bounds__(256) void absmax_kernel(const double* x, int64_t n, unsigned long long* max_parts) {
@@ -260,12 +275,25 @@ __global__ __launch_bounds__(256) void absmax_kernel(const double* x, int64_t n,
 // (NaN if the vector holds a non-finite value: the products are then NaN everywhere). max |x| is the largest of the
 // `parts` partial maxima, which every workgroup goes through itself: with one atomic per workgroup on a single slot
 // instead, the kernel that wrote the vector spent 8 us on a thousand atomics. Two roles per thread:
-//  * digit planes of xp[0..n) (npad > 0): one thread per 4 plane positions (i = 0..3: columns 8 apart);
+//  * digit planes of xp[0..n) (chunks > 0): one thread per half operand, 16 columns: 96 bits of every plane;
 //  * q64[i] = round(xq[i] * 2^f) for i < qlen (the index-tile products read these): four entries per thread.
-__global__ __launch_bounds__(256) void quantize_kernel(const double* xp, int64_t n, int64_t npad, const unsigned long long* max_parts,
+__global__ __launch_bounds__(256) void quantize_kernel(const double* xp, int64_t n, int64_t chunks, const unsigned long long* max_parts,
                                                        int parts, int8_t* D, double* scal, const double* xq, int64_t qlen,
                                                        long long* q64) {
   __shared__ unsigned long long wm[4];
+  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  // the columns of half operand id: (chunk, 128 columns, j, half); what does not wait for the maximum is requested first
+  constexpr int kHalf = 16;
+  const bool planes = id < chunks * (kMmChunk / kHalf);
+  const int64_t col0 = (id >> 3) * 128 + ((id & 1) << 6) + ((id >> 1) & 3);
+  double xv[kHalf];
+  if (planes) {
+#pragma unroll
+    for (int i = 0; i < kHalf; ++i) {
+      const int64_t col = col0 + 4 * i;
+      xv[i] = xp[col < n ? col : n - 1];
+    }
+  }
   unsigned long long m = 0;
   for (int i = threadIdx.x; i < parts; i += 256) m = max_parts[i] > m ? max_parts[i] : m;
   ds_block_max_256(m, wm);
@@ -274,172 +302,231 @@ __global__ __launch_bounds__(256) void quantize_kernel(const double* xp, int64_t
   int e = 0;
   if (finite && mx > 0.0) frexp(mx, &e);   // mx < 2^e
   const int f = 54 - e;
-  const int64_t q4 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q4 == 0) scal[0] = finite ? ldexp(1.0, -f) : __longlong_as_double(0x7ff8000000000000ll);
-  const int64_t pos0 = q4 * 4;
+  if (id == 0) scal[0] = finite ? ldexp(1.0, -f) : __longlong_as_double(0x7ff8000000000000ll);
+  const int64_t pos0 = id * 4;
   if (pos0 < qlen) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (pos0 + i < qlen) q64[pos0 + i] = finite ? __double2ll_rn(ldexp(xq[pos0 + i], f)) : 0ll;
   }
-  if (pos0 >= npad) return;
-  const int p = (int)(pos0 & 127);
-  const int j = p >> 4, v = (p >> 2) & 3;
-  const int64_t colbase = (pos0 & ~(int64_t)127) + (v << 5 | j);
-  int32_t packed[kMmDigits] = {0, 0, 0, 0, 0, 0, 0};
+  if (!planes) return;
+  unsigned long long q[kHalf];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t col = colbase + (i << 3);
-    long long q = (finite && col < n) ? __double2ll_rn(ldexp(xp[col], f)) : 0ll;
+  for (int i = 0; i < kHalf; ++i)
+    q[i] = col0 + 4 * i < n ? (unsigned long long)((finite ? __double2ll_rn(ldexp(xv[i], f)) : 0ll) + (1ll << 54)) : 0ull;
+  // (columns 4 i, i < 8, are word 0 (or 2) of the operand's four, the others word 1 (or 3): both 32 columns wide)
+  uint32_t* const out = (uint32_t*)(D + (id >> 6) * kMmChunkBytes + ((id >> 3) & 7) * (4 * kMmOperand) + ((id >> 1) & 3) * kMmOperand +
+                                    (id & 1) * (kMmOperand / 2));
 #pragma unroll
-    for (int d = 0; d < kMmDigits; ++d) {
-      const int di = (int)(int8_t)(q & 0xFF);
-      q = (q - di) >> 8;
-      packed[d] |= (di & 0xFF) << (8 * i);
+  for (int d = 0; d < kMmPlanes; ++d) {
+    uint32_t w[3] = {0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < kHalf; ++i) {
+      const uint32_t digit = d < kMmDigits ? (uint32_t)(q[i] >> (4 * d)) & 15u : (col0 + 4 * i < n ? 1u : 0u);
+      const int at = 6 * i, sh = at & 31;
+      w[at >> 5] |= digit << sh;
+      if (sh > 28) w[(at >> 5) + 1] |= digit >> (32 - sh);
     }
-  }
 #pragma unroll
-  for (int d = 0; d < kMmDigits; ++d) *(int32_t*)(D + d * npad + pos0) = packed[d];
+    for (int u = 0; u < 3; ++u) out[d * (kMmPlaneBytes / 4) + u] = w[u];
+  }
 }
 
-__global__ __launch_bounds__(kMmWaves * 64) void bit_spmv_mm_kernel(const uint64_t* B, int64_t rows, int64_t cols, int64_t stride,
+// A workgroup's units (a chunk of a row group each) are consecutive, row group by row group: cut evenly (even_units = their
+// total: workgroup b of G takes [b u / G, (b + 1) u / G) and leaves the sums of a row group in the slot that counts the workgroups from the
+// group's first one on; a plan clears the slots that nobody writes), or `groups` to a row group (even_units = 0). The mask words of
+// the two units ahead are on their way while one is used, across row groups too. Every load is issued unconditionally (behind the last
+// unit, of one cache line): a conditional one would make the wait for the current words a wait for all of them.
+__global__ __launch_bounds__(kMmThreads, 2) void bit_spmv_mm_kernel(const uint64_t* B, int64_t rows, int64_t cols, int64_t stride,
                                                                     int64_t row_first, int64_t row_step, const int8_t* D,
-                                                                    int64_t dstride, int32_t* partial, int64_t chunks_per_group,
-                                                                    int64_t n_chunks) {
+                                                                    longlong2* partial, int64_t even_units, int64_t groups,
+                                                                    int64_t chunks_per_group, int64_t n_chunks) {
   __shared__ __align__(16) int8_t Bs[2][kMmPlanes * kMmPlanePitch];
+  __shared__ int sums[kMmWaves][kMmWaveRows * kMmSumPitch];
+  typedef int v2i __attribute__((ext_vector_type(2)));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, g = lane >> 4;
   const int64_t Wc = (cols + 63) / 64;
-  const int64_t wave_row0 = ((int64_t)blockIdx.x * kMmWaves + wave) * kMmWaveRows;
-  const int64_t c_begin = (int64_t)blockIdx.y * chunks_per_group;
-  const int64_t c_end = c_begin + chunks_per_group < n_chunks ? c_begin + chunks_per_group : n_chunks;
+  const int64_t G = gridDim.x, bid = blockIdx.x;
+  int64_t rg, c;       // row group and chunk of the current unit
+  int64_t left;        // units from it on
+  int64_t slot = 0;    // where this workgroup's sums of the row group go
+  if (even_units > 0) {
+    const int64_t u0 = bid * even_units / G;
+    left = (bid + 1) * even_units / G - u0;
+    rg = u0 / n_chunks;
+    c = u0 - rg * n_chunks;
+    slot = bid - ((rg * n_chunks + 1) * G - 1) / even_units;   // (a later row group's first workgroup is this one)
+  } else {
+    const int64_t row_groups = G / groups;   // (consecutive workgroups: consecutive row groups of one column group)
+    slot = bid / row_groups;
+    rg = bid - slot * row_groups;
+    c = slot * chunks_per_group;
+    left = c + chunks_per_group < n_chunks ? chunks_per_group : n_chunks - c;
+  }
   const int64_t row_bytes = row_step * stride * 8;
   const char* Bb = (const char*)(B + row_first * stride);
   const uint32_t lane_off = (uint32_t)r16 * (uint32_t)row_bytes;   // the host keeps 16 * row_bytes below 2^32
-  v4i acc[kMmTiles][4];
+  v4f acc[kMmTiles];
+  auto clear = [&]() {
 #pragma unroll
-  for (int t = 0; t < kMmTiles; ++t)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc[t][q] = v4i{0, 0, 0, 0};
-  uint32_t a_cur[kMmTiles][4 * kMmHalves], a_next[kMmTiles][4 * kMmHalves];
-  // Rows past the end are read from a live row and never stored; in the last chunk, words past the row's end are
-  // read from its last word and meet zero digits (the planes are zero from column `cols` on).
-  // (one 16-byte load per lane, tile and half: as two 8-byte loads the same bytes took twice the requests and the
-  // kernel ran 17 % slower)
+    for (int t = 0; t < kMmTiles; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
+  };
+  // Rows past the end are read from a live row and never stored. Words past the row's end meet zero digits; the 16 bytes that
+  // would cross it are read 8 bytes earlier and moved into place where they are used (`fix`). (One 16-byte load per lane, tile and
+  // half: as two 8-byte loads the same bytes took twice the requests and the kernel ran 17 % slower.)
   typedef uint32_t u4a8 __attribute__((ext_vector_type(4), aligned(8)));   // rows are 8-byte aligned
-  auto load_a = [&](uint32_t (&a)[kMmTiles][4 * kMmHalves], int64_t c) {
-    if (c != n_chunks - 1) {
+  struct Words { u4a8 a[kMmTiles][kMmHalves]; };
+  const int64_t last_pair = Wc > 1 ? Wc - 2 : 0;   // (a single word: the caller's rows have 8 bytes more behind the last)
+  auto load_a = [&](Words& w, int64_t group, int64_t chunk, bool live) {
+    const int64_t wave_row0 = (group * kMmWaves + wave) * kMmWaveRows;
 #pragma unroll
-      for (int t = 0; t < kMmTiles; ++t) {
-        const int64_t r_t = wave_row0 + 16 * t;
-        const char* base = Bb + (r_t < rows ? r_t : rows - 1) * row_bytes;   // uniform over the wave
-        const uint32_t lo = (r_t + r16 < rows ? lane_off : 0u) + (uint32_t)(c * (kMmChunk / 8) + g * 16);
+    for (int t = 0; t < kMmTiles; ++t) {
+      const int64_t r_t = wave_row0 + 16 * t;
+      const char* base = live ? Bb + (r_t < rows ? r_t : rows - 1) * row_bytes : Bb;   // uniform over the wave
+      const uint32_t lo = live && r_t + r16 < rows ? lane_off : 0u;
 #pragma unroll
-        for (int h = 0; h < kMmHalves; ++h) {
-          const u4a8 v = *(const u4a8*)(base + (lo + h * 64));
-          a[t][4 * h + 0] = v.x;
-          a[t][4 * h + 1] = v.y;
-          a[t][4 * h + 2] = v.z;
-          a[t][4 * h + 3] = v.w;
-        }
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < kMmTiles; ++t) {
-        const int64_t r_t = wave_row0 + 16 * t;
-        const char* base = Bb + (r_t < rows ? r_t : rows - 1) * row_bytes;
-        const uint32_t lo = r_t + r16 < rows ? lane_off : 0u;
-#pragma unroll
-        for (int h = 0; h < kMmHalves; ++h) {
-          const int64_t w0 = c * (kMmChunk / 64) + h * 8 + g * 2, w1 = w0 + 1;
-          const uint32_t cb0 = (uint32_t)(w0 < Wc ? w0 : Wc - 1) * 8u, cb1 = (uint32_t)(w1 < Wc ? w1 : Wc - 1) * 8u;
-          const uint64_t v0 = *(const uint64_t*)(base + (lo + cb0)), v1 = *(const uint64_t*)(base + (lo + cb1));
-          a[t][4 * h + 0] = (uint32_t)v0;
-          a[t][4 * h + 1] = (uint32_t)(v0 >> 32);
-          a[t][4 * h + 2] = (uint32_t)v1;
-          a[t][4 * h + 3] = (uint32_t)(v1 >> 32);
-        }
+      for (int h = 0; h < kMmHalves; ++h) {
+        const int64_t w0 = chunk * (kMmChunk / 64) + h * 8 + g * 2;
+        w.a[t][h] = *(const u4a8*)(base + (lo + (live ? (uint32_t)(w0 < last_pair ? w0 : last_pair) * 8u : 0u)));
       }
     }
   };
-  // staging of a chunk's digit planes: thread -> (plane, 32-byte segment)
-  static_assert(kMmWaves * 64 * 32 == kMmPlanes * kMmChunk, "one 32-byte segment per thread");
-  const int st_plane = tid / (kMmChunk / 32), st_seg = tid % (kMmChunk / 32);
-  const int8_t* st_src = D + (int64_t)st_plane * dstride + st_seg * 32;
-  const int st_dst = st_plane * kMmPlanePitch + st_seg * 32;
-  v4i s0, s1;
-  auto stage_load = [&](int64_t c) {
-    s0 = *(const v4i*)(st_src + c * kMmChunk);
-    s1 = *(const v4i*)(st_src + c * kMmChunk + 16);
+  auto fix = [&](Words& w, int64_t chunk) {
+#pragma unroll
+    for (int h = 0; h < kMmHalves; ++h) {
+      const bool odd = chunk * (kMmChunk / 64) + h * 8 + g * 2 == Wc - 1 && Wc > 1;   // this lane's first word is the row's last
+#pragma unroll
+      for (int t = 0; t < kMmTiles; ++t) {
+        w.a[t][h].x = odd ? w.a[t][h].z : w.a[t][h].x;
+        w.a[t][h].y = odd ? w.a[t][h].w : w.a[t][h].y;
+      }
+    }
+  };
+  // staging of a chunk's digit planes, 16 bytes at a time: piece p of a plane is a sixth of a lane group's operands
+  constexpr int kPieces = kMmChunkBytes / 16, kStage = (kPieces + kMmThreads - 1) / kMmThreads, kPlanePieces = kMmPlaneBytes / 16;
+  int st_src[kStage], st_dst[kStage];
+#pragma unroll
+  for (int u = 0; u < kStage; ++u) {
+    const int p = tid + u * kMmThreads < kPieces ? tid + u * kMmThreads : tid;   // (past the end: the thread's first piece again)
+    const int plane = p / kPlanePieces, in = p - plane * kPlanePieces, group = in / (4 * kMmOperand / 16);
+    st_src[u] = p * 16;
+    st_dst[u] = plane * kMmPlanePitch + group * kMmGroupPitch + (in - group * (4 * kMmOperand / 16)) * 16;
+  }
+  v4i st[kStage];
+  auto stage_load = [&](int64_t chunk) {
+    const int8_t* const src = D + chunk * kMmChunkBytes;
+#pragma unroll
+    for (int u = 0; u < kStage; ++u) st[u] = *(const v4i*)(src + st_src[u]);
   };
   auto stage_store = [&](int buf) {
-    *(v4i*)(&Bs[buf][st_dst]) = s0;
-    *(v4i*)(&Bs[buf][st_dst + 16]) = s1;
+#pragma unroll
+    for (int u = 0; u < kStage; ++u) {   // (planes start at multiples of 8 bytes)
+      *(v2i*)&Bs[buf][st_dst[u]] = v2i{st[u].x, st[u].y};
+      *(v2i*)&Bs[buf][st_dst[u] + 8] = v2i{st[u].z, st[u].w};
+    }
   };
-  const int b_off = (r16 < kMmDigits ? r16 : kMmDigits) * kMmPlanePitch + g * 128;   // plane 7 is all zero
-  stage_load(c_begin);
-  load_a(a_cur, c_begin);
-  stage_store(0);
-  __syncthreads();
-  int buf = 0;
-  for (int64_t c = c_begin; c < c_end; ++c) {
-    const int64_t cn = c + 1 < c_end ? c + 1 : c;   // (the last chunk is requested again and not used)
-    stage_load(cn);
-    load_a(a_next, cn);
+  const int b_off = (r16 < kMmPlanes ? r16 : kMmPlanes - 1) * kMmPlanePitch + g * kMmGroupPitch;   // (column 15 is not looked at)
+  constexpr int kOne = 0x7f;   // block scale 2^0
+  const int scale_a[4] = {kOne + 1, kOne, kOne - 1, kOne - 1}, scale_b = kOne + 3;
+  auto multiply = [&](const Words& w, int buf) {
     const int8_t* bs = &Bs[buf][b_off];
-    v4i bq[2][4];
+    v2i bq[2][4][3];
+    auto operands = [&](int h) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) bq[0][q] = *(const v4i*)(bs + q * 16);
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int gi = 0; gi < 2 * kMmHalves; ++gi) {
-      const int h = gi >> 1, hi = gi & 1;
-      if (gi + 1 < 2 * kMmHalves) {
+        for (int u = 0; u < 3; ++u) bq[h & 1][j][u] = *(const v2i*)(bs + h * 4 * kMmGroupPitch + j * kMmOperand + u * 8);
+    };
+    operands(0);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          bq[(gi + 1) & 1][q] = *(const v4i*)(bs + ((gi + 1) >> 1) * 512 + (4 * ((gi + 1) & 1) + q) * 16);
-      }
+    for (int h = 0; h < kMmHalves; ++h) {
+      if (h + 1 < kMmHalves) operands(h + 1);
 #pragma unroll
       for (int t = 0; t < kMmTiles; ++t) {
-        uint32_t x0 = a_cur[t][4 * h + 0], x1 = a_cur[t][4 * h + 1], x2 = a_cur[t][4 * h + 2], x3 = a_cur[t][4 * h + 3];
-        if (hi) {
-          x0 >>= 4;
-          x1 >>= 4;
-          x2 >>= 4;
-          x3 >>= 4;
-        }
+        const u4a8 x = w.a[t][h];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const uint32_t m = 0x01010101u << q;
-          const v4i av = {(int)(x0 & m), (int)(x1 & m), (int)(x2 & m), (int)(x3 & m)};
-          acc[t][q] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, bq[gi & 1][q], acc[t][q], 0, 0, 0);
+        for (int j = 0; j < 4; ++j) {
+          const uint32_t m = j < 3 ? 0x11111111u << j : 0x44444444u;
+          const u4a8 y = j < 3 ? x : x >> 1;
+          const v8i av = {(int)(y.x & m), (int)(y.y & m), (int)(y.z & m), (int)(y.w & m), 0, 0, 0, 0};
+          const v2i* const q = bq[h & 1][j];
+          const v8i bv = {q[0].x, q[0].y, q[1].x, q[1].y, q[2].x, q[2].y, 0, 0};
+          acc[t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av, bv, acc[t], 4, 2, 0, scale_a[j], 0, scale_b);   // fp4, fp6 e2m3
         }
       }
     }
-    stage_store(buf ^ 1);
-    __syncthreads();   // every wave is done with Bs[buf]; Bs[buf ^ 1] is complete
-    buf ^= 1;
-#pragma unroll
-    for (int t = 0; t < kMmTiles; ++t)
-#pragma unroll
-      for (int k = 0; k < 4 * kMmHalves; ++k) a_cur[t][k] = a_next[t][k];
-  }
-  // lane (digit r16, lane group g) holds rows 4g + v of every tile
-  if (r16 < kMmPlanes) {
+  };
+  // Lane (plane r16, lane group g) holds rows 4g + v of every tile. Two neighbouring digits make a base-256 one, and through LDS a
+  // lane gets all those of a row: 16 contiguous bytes a lane go to memory. (Stored as eight 32-bit sums a row from the lanes
+  // that have them, 32 bytes at a time, the sums of 300,007 rows cost 13 us of 78.)
+  auto store_sums = [&]() {
+    int* const mine = sums[wave];
 #pragma unroll
     for (int t = 0; t < kMmTiles; ++t)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int64_t row = wave_row0 + 16 * t + 4 * g + v;
-        if (row < rows)
-          partial[((int64_t)blockIdx.y * rows + row) * kMmPlanes + r16] =
-              acc[t][0][v] + (acc[t][1][v] >> 1) + (acc[t][2][v] >> 2) + (acc[t][3][v] >> 3);
+        const int digit = (int)acc[t][v];
+        const int high = __builtin_amdgcn_update_dpp(0, digit, 0xf5, 0xf, 0xf, false);   // quad_perm [1,1,3,3]: the next plane's
+        if ((r16 & 1) == 0) mine[(16 * t + 4 * g + v) * kMmSumPitch + (r16 >> 1)] = r16 < kMmDigits ? digit + 16 * high : digit;
       }
+    const int64_t row = (rg * kMmWaves + wave) * kMmWaveRows + lane;
+    const int* const q = mine + lane * kMmSumPitch;
+    longlong2 out;   // sum_d 256^d S[d] - 2^54 count = 2^24 x + y
+    out.x = (((long long)q[6] * 256 + q[5]) * 256 + q[4]) * 256 + q[3] - ((long long)q[7] << 30);
+    out.y = ((long long)q[2] * 256 + q[1]) * 256 + q[0];
+    if (row < rows) partial[slot * rows + row] = out;
+  };
+  Words w0, w1, w2;
+  int64_t rg1 = rg, c1 = c;   // the next unit, then the one behind it; both stay on a live one behind the last
+  auto advance = [&](int64_t& group, int64_t& chunk) {
+    const bool wrap = chunk + 1 == n_chunks;
+    group = wrap ? group + 1 : group;
+    chunk = wrap ? 0 : chunk + 1;
+  };
+  // one unit from `cur`; `next` takes the words of the one behind the next. False behind the last.
+  auto unit = [&](Words& cur, Words& next, int buf) {
+    int64_t rg2 = rg1, c2 = c1;
+    advance(rg2, c2);
+    stage_load(left > 1 ? c1 : c);
+    load_a(next, rg2, c2, left > 2);
+    if (c == n_chunks - 1 && (Wc & 1)) fix(cur, c);
+    multiply(cur, buf);
+    if (c == n_chunks - 1 || left == 1) {
+      store_sums();
+      clear();
+      slot = 0;
+    }
+    if (left == 1) return false;
+    stage_store(buf ^ 1);
+    __syncthreads();   // every wave is done with Bs[buf]; Bs[buf ^ 1] is complete
+    rg = rg1;
+    c = c1;
+    rg1 = rg2;
+    c1 = c2;
+    --left;
+    return true;
+  };
+  advance(rg1, c1);
+  stage_load(c);
+  load_a(w0, rg, c, true);
+  load_a(w1, rg1, c1, left > 1);
+  clear();
+  stage_store(0);
+  __syncthreads();
+  for (;;) {   // (the words' three buffers and LDS's two in turn)
+    if (!unit(w0, w2, 0)) break;
+    if (!unit(w1, w0, 1)) break;
+    if (!unit(w2, w1, 0)) break;
+    if (!unit(w0, w2, 1)) break;
+    if (!unit(w1, w0, 0)) break;
+    if (!unit(w2, w1, 1)) break;
   }
 }
 
 // out[r] = (addend[r] or 0) + scal[0] * sum_d 256^d * (sum over the column groups of digit sum d)
-__global__ __launch_bounds__(256) void mm_reduce_kernel(const int32_t* partial, int64_t rows, int groups, const double* scal,
+__global__ __launch_bounds__(256) void mm_reduce_kernel(const longlong2* partial, int64_t rows, int groups, const double* scal,
                                                         const double* addend, double* out) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= rows) return;
@@ -510,8 +597,8 @@ int ds_row_prep(ds_ctx* ctx, const uint64_t* Z, int64_t k, int64_t n, int paired
 }
 
 int ds_bit_transpose(ds_ctx* ctx, const uint64_t* in, int64_t rows, int64_t cols, int64_t in_stride, int64_t row_first,
-                     int64_t row_step, uint64_t* out) {
-  const int64_t Wout = (rows + 63) / 64, Win = (cols + 63) / 64;
+                     int64_t row_step, uint64_t* out, int64_t out_stride) {
+  const int64_t Wout = out_stride > 0 ? out_stride : (rows + 63) / 64, Win = (cols + 63) / 64;
   const int64_t tiles_r = (rows + 511) / 512, tiles_c = (Win + 7) / 8;
   if (tiles_r < 1 || tiles_c < 1) return DS_OK;
   if (tiles_r * tiles_c > 0x7fffffffLL) return ds_fail(ctx, DS_EINVAL, "bit matrix too large to transpose");
@@ -538,24 +625,26 @@ static void mm_shape(const ds_ctx* ctx, int64_t rows, int64_t cols, ds_mm_plan* 
   p->cols = cols;
   p->row_groups = (rows + kMmRows - 1) / kMmRows;
   p->n_chunks = (cols + kMmChunk - 1) / kMmChunk;
-  p->npad = p->n_chunks * kMmChunk;
-  const ds_mm_split c = ds_mm_choose_split(ctx->num_cus, rows, p->row_groups, p->n_chunks, kMmMaxGroupCols / kMmChunk, kMmPlanes * 4);
+  const ds_mm_split c = ds_mm_choose_split(ctx->num_cus, rows, p->row_groups, p->n_chunks, kMmMaxGroupCols / kMmChunk, 2 * kMmSumBytes);
+  const ds_mm_even e = ds_mm_choose_even(ctx->num_cus, rows, p->row_groups, p->n_chunks, kMmMaxGroupCols / kMmChunk, kMmSumBytes, c);
   p->cpg = c.cpg;
-  p->groups = c.groups;
+  p->groups = e.wgs > 0 ? e.slots : c.groups;
+  p->even_wgs = e.wgs;
 }
 
 size_t ds_bit_spmv_mm_ws_bytes(const ds_ctx* ctx, int64_t rows, int64_t cols) {
   ds_mm_plan p;
   mm_shape(ctx, rows, cols, &p);
-  return ds_align((size_t)kMmPlanes * p.npad) + ds_align((size_t)p.groups * rows * kMmPlanes * 4);
+  return ds_align((size_t)p.n_chunks * kMmChunkBytes) + ds_align((size_t)p.groups * rows * kMmSumBytes);
 }
 
 int ds_bit_spmv_mm_prepare(ds_ctx* ctx, int64_t rows, int64_t cols, void* ws, ds_mm_plan* plan) {
   mm_shape(ctx, rows, cols, plan);
   char* p = (char*)ws;
   plan->D = (int8_t*)p;
-  plan->partial = (int32_t*)(p + ds_align((size_t)kMmPlanes * plan->npad));
-  DS_HIP(ctx, hipMemsetAsync(plan->D + (size_t)kMmDigits * plan->npad, 0, plan->npad, ctx->stream));  // the zero plane
+  plan->partial = (longlong2*)(p + ds_align((size_t)plan->n_chunks * kMmChunkBytes));
+  if (plan->even_wgs > 0)   // (slots of a row group that no workgroup reaches)
+    DS_HIP(ctx, hipMemsetAsync(plan->partial, 0, (size_t)plan->groups * rows * kMmSumBytes, ctx->stream));
   return DS_OK;
 }
 
@@ -568,10 +657,10 @@ int ds_vec_absmax(ds_ctx* ctx, const double* x, int64_t len, unsigned long long*
 int ds_vec_quantize(ds_ctx* ctx, const unsigned long long* max_parts, int parts, const ds_mm_plan* planes, const double* x_planes,
                     const double* x_q, int64_t qlen, long long* q64, double* scal) {
   const bool with_planes = planes && planes->rows > 0;
-  const int64_t npad = with_planes ? planes->npad : 0;
-  const int64_t span = npad > qlen ? npad : qlen;
-  hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)((span / 4 + 256) / 256)), dim3(256), 0, ctx->stream, x_planes,
-                     with_planes ? planes->cols : 0, npad, max_parts, parts, with_planes ? planes->D : nullptr, scal, x_q, qlen, q64);
+  const int64_t chunks = with_planes ? planes->n_chunks : 0;
+  const int64_t halves = chunks * (kMmChunk / 16), quads = (qlen + 3) / 4, threads = halves > quads ? halves : quads;
+  hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)(threads > 0 ? (threads + 255) / 256 : 1)), dim3(256), 0, ctx->stream, x_planes,
+                     with_planes ? planes->cols : 0, chunks, max_parts, parts, with_planes ? planes->D : nullptr, scal, x_q, qlen, q64);
   DS_HIP(ctx, hipGetLastError());
   return DS_OK;
 }
@@ -581,8 +670,10 @@ int ds_bit_spmv_mm_product(ds_ctx* ctx, const ds_mm_plan* p, const uint64_t* B, 
   if (p->rows <= 0) return DS_OK;
   if (row_step * stride * 8 * 16 >= ((int64_t)1 << 32))
     return ds_fail(ctx, DS_EINTERNAL, "matrix-core product: rows of %lld bytes are too far apart", (long long)(row_step * stride * 8));
-  hipLaunchKernelGGL(bit_spmv_mm_kernel, dim3((unsigned)p->row_groups, (unsigned)p->groups), dim3(kMmWaves * 64), 0, ctx->stream,
-                     B, p->rows, p->cols, stride, row_first, row_step, p->D, p->npad, p->partial, p->cpg, p->n_chunks);
+  const int64_t wgs = p->even_wgs > 0 ? p->even_wgs : p->row_groups * p->groups;
+  hipLaunchKernelGGL(bit_spmv_mm_kernel, dim3((unsigned)wgs), dim3(kMmThreads), 0, ctx->stream, B, p->rows, p->cols, stride,
+                     row_first, row_step, p->D, p->partial, p->even_wgs > 0 ? p->row_groups * p->n_chunks : (int64_t)0, p->groups,
+                     p->cpg, p->n_chunks);
   if (out)
     hipLaunchKernelGGL(mm_reduce_kernel, dim3((unsigned)((p->rows + 255) / 256)), dim3(256), 0, ctx->stream, p->partial, p->rows,
                        (int)p->groups, scal, addend, out);

@@ -17,6 +17,12 @@ struct ds_mm_split {
 //   34,267 x 99,981  335.0 -> 322.9 (428 MB; 3 and 1 groups instead of 7 and 5 left a fifth of the places empty)
 //   32,409 x 200,003 558.4 -> 537.7    15,121 x 500,009 618.7 -> 613.4    7,906 x 20,011 76.1 -> 72.7
 //   3,425 x 100,428 86.5 -> 86.9; 57,572 x 1,000,175, 9,424 x 300,007, 18,176 x 50,021 and 10,280 x 99,981: same splits
+inline double ds_mm_price(int64_t num_cus, int64_t wgs, int64_t chunks, int64_t sums) {
+  const int64_t cap = 2 * num_cus, rest = wgs % cap;
+  const double per_chunk = 2.6 * (double)(wgs / cap) + (rest == 0 ? 0.0 : rest <= num_cus ? 1.6 : 2.6);
+  return (double)chunks * per_chunk + (double)sums * 1.0e-6;
+}
+
 inline ds_mm_split ds_mm_choose_split(int64_t num_cus, int64_t rows, int64_t row_groups, int64_t n_chunks, int64_t max_cpg,
                                       int64_t sum_bytes) {
   const int64_t cap = 2 * num_cus, rg = row_groups > 0 ? row_groups : 1;
@@ -29,14 +35,45 @@ inline ds_mm_split ds_mm_choose_split(int64_t num_cus, int64_t rows, int64_t row
     if (cpg > max_cpg) cpg = max_cpg;
     if (cpg < 1) cpg = 1;
     const int64_t groups = (n_chunks + cpg - 1) / cpg;
-    const int64_t wgs = rg * groups, rest = wgs % cap;
-    const double per_chunk = 2.6 * (double)(wgs / cap) + (rest == 0 ? 0.0 : rest <= num_cus ? 1.6 : 2.6);
-    const double us = (double)cpg * per_chunk + (double)groups * (double)rows * (double)sum_bytes * 1.0e-6;
+    const double us = ds_mm_price(num_cus, rg * groups, cpg, groups * rows * sum_bytes);
     if (best_us < 0.0 || us < best_us) {
       best_us = us;
       best.cpg = cpg;
       best.groups = groups;
     }
+  }
+  return best;
+}
+
+// The same work cut evenly: the chunks of all row groups in one line, row group by row group, workgroup b of `wgs` takes
+// units [b u / wgs, (b + 1) u / wgs) of u. A row group's sums then come from up to `slots` workgroups.
+struct ds_mm_even {
+  int64_t wgs, slots;    // wgs == 0: the column groups are cheaper
+};
+
+// the workgroup that holds unit x
+inline int64_t ds_mm_even_owner(int64_t x, int64_t wgs, int64_t units) { return ((x + 1) * wgs - 1) / units; }
+
+// A workgroup to a compute unit, 1.6 to 1.8 us a unit (with two: 3.2 to 4.1). A workgroup that holds a row group whole meets no more than two others' ends, so that what
+// a cut within row groups costs is the second slot's sums (1 us per MB, as above). Taken where its price is below that of the column groups
+// at the same cost of a unit; no more of one row group than the accumulators hold.
+inline ds_mm_even ds_mm_choose_even(int64_t num_cus, int64_t rows, int64_t row_groups, int64_t n_chunks, int64_t max_cpg,
+                                    int64_t sum_bytes, const ds_mm_split& split) {
+  const double unit_us = 1.8;
+  ds_mm_even best = {0, 0};
+  const int64_t units = row_groups * n_chunks, wgs = units < num_cus ? units : num_cus;
+  if (units < 1) return best;
+  const int64_t per = (units + wgs - 1) / wgs, rounds = (row_groups * split.groups + num_cus - 1) / num_cus;
+  if ((per < n_chunks ? per : n_chunks) > max_cpg) return best;
+  int64_t slots = 1;
+  for (int64_t g = 0; g < row_groups; ++g) {
+    const int64_t s = ds_mm_even_owner((g + 1) * n_chunks - 1, wgs, units) - ds_mm_even_owner(g * n_chunks, wgs, units) + 1;
+    if (s > slots) slots = s;
+  }
+  const double sums = (double)(rows * sum_bytes) * 1.0e-6;
+  if (unit_us * (double)per + sums * (double)slots < unit_us * (double)(rounds * split.cpg) + sums * (double)split.groups) {
+    best.wgs = wgs;
+    best.slots = slots;
   }
   return best;
 }

@@ -7,9 +7,10 @@
 // and is not read
 int ds_row_prep(ds_ctx* ctx, const uint64_t* Z, int64_t k, int64_t n, int paired, const float* w, const float* y, int32_t* sz,
                 double* t, double* sqw, float* wc);
-// out[cols x ceil(rows/64)] = transpose of the rows row_first + i*row_step (i < rows) of `in`
+// out[cols x ceil(rows/64)] = transpose of the rows row_first + i*row_step (i < rows) of `in`; out_stride: words from one row of
+// `out` to the next, ceil(rows/64) unless given
 int ds_bit_transpose(ds_ctx* ctx, const uint64_t* in, int64_t rows, int64_t cols, int64_t in_stride, int64_t row_first,
-                     int64_t row_step, uint64_t* out);
+                     int64_t row_step, uint64_t* out, int64_t out_stride = 0);
 // the same transpose of the rows i * row_step (i < rows), laid out by blocks of 64 of them: out[b * 64*ceil(cols/64) + j] =
 // bits of column j in the rows 64b .. 64b+63 of that selection (rows past the last and columns past `cols` read as zero)
 int ds_bit_transpose_blocks(ds_ctx* ctx, const uint64_t* in, int64_t rows, int64_t cols, int64_t in_stride, int64_t row_step,
@@ -23,13 +24,14 @@ int ds_bit_spmv(ds_ctx* ctx, const uint64_t* B, int64_t rows, int64_t cols, int6
 // the vector is written as digit planes for the matrix-core product (x_planes[0..planes->cols), if `planes` has rows)
 // and/or as 64-bit integers q64[i] = round(x_q[i] * 2^f), i < qlen (if qlen > 0).
 //
-// Dense rows on the int8 matrix cores (x split into base-256 digits); out = (addend or 0) + result. A plan fixes
+// Dense rows on the matrix cores (x split into digits); out = (addend or 0) + result. A plan fixes
 // the launch shape and the scratch of one (rows, cols) shape: ds_bit_spmv_mm_ws_bytes bytes at `ws`, which
 // ds_bit_spmv_mm_prepare initialises (on ctx->stream).
 struct ds_mm_plan {
-  int64_t rows, cols, row_groups, n_chunks, groups, cpg, npad;
-  int8_t* D;         // eight digit planes of npad bytes (the last one stays zero)
-  int32_t* partial;  // [groups][rows][8] digit sums
+  int64_t rows, cols, row_groups, n_chunks, groups, cpg;
+  int64_t even_wgs;  // workgroups of an even cut (groups: the slots of a row group's sums); 0: a workgroup per row group and column group
+  int8_t* D;         // the vector's digits, chunk by chunk
+  longlong2* partial;  // [groups][rows]: a row's sum in units of the vector's fixed point is 2^24 x + y
 };
 size_t ds_bit_spmv_mm_ws_bytes(const ds_ctx* ctx, int64_t rows, int64_t cols);
 int ds_bit_spmv_mm_prepare(ds_ctx* ctx, int64_t rows, int64_t cols, void* ws, ds_mm_plan* plan);
@@ -66,7 +68,7 @@ struct ds_fixed_view {
   const long long* tile_partial;  // [tile_groups][tile_len]
   int64_t tile_len;
   int tile_groups, tile_sh;
-  const int32_t* mm_partial;      // [mm_groups][mm_rows][8]
+  const longlong2* mm_partial;    // [mm_groups][mm_rows]
   int64_t mm_rows;
   int mm_groups;
 };
@@ -111,43 +113,28 @@ __device__ __forceinline__ double ds_tile_sum(const long long* partial, int64_t 
   ds_tile_sum_part(partial, len, groups, i, 0, 1, hi, lo);
   return ds_tile_sum_finish(hi, lo, sh);
 }
-// matrix-core product, row r: S[d] = sum over the groups of digit sum d; the result is sum_d 256^d S[d]
-__device__ __forceinline__ void ds_mm_sum_part(const int32_t* partial, int64_t rows, int groups, int64_t r, int sub, int T,
-                                               long long S[7]) {
+// matrix-core product, row r: 2^24 hi + lo
+__device__ __forceinline__ void ds_mm_sum_part(const longlong2* partial, int64_t rows, int groups, int64_t r, int sub, int T,
+                                               long long& hi, long long& lo) {
   int g = sub;
-  for (; g + T < groups; g += 2 * T) {
-    const int4* p = (const int4*)(partial + ((int64_t)g * rows + r) * 8);
-    const int4* q = (const int4*)(partial + ((int64_t)(g + T) * rows + r) * 8);
-    const int4 u = p[0], w = p[1], u2 = q[0], w2 = q[1];
-    S[0] += (long long)u.x + u2.x;
-    S[1] += (long long)u.y + u2.y;
-    S[2] += (long long)u.z + u2.z;
-    S[3] += (long long)u.w + u2.w;
-    S[4] += (long long)w.x + w2.x;
-    S[5] += (long long)w.y + w2.y;
-    S[6] += (long long)w.z + w2.z;
+  for (; g + 3 * T < groups; g += 4 * T) {
+    const longlong2* p = partial + (int64_t)g * rows + r;
+    const int64_t st = (int64_t)T * rows;
+    const longlong2 a = p[0], b = p[st], c = p[2 * st], d = p[3 * st];
+    hi += a.x + b.x + c.x + d.x;
+    lo += a.y + b.y + c.y + d.y;
   }
   for (; g < groups; g += T) {
-    const int4* p = (const int4*)(partial + ((int64_t)g * rows + r) * 8);
-    const int4 u = p[0], w = p[1];
-    S[0] += u.x;
-    S[1] += u.y;
-    S[2] += u.z;
-    S[3] += u.w;
-    S[4] += w.x;
-    S[5] += w.y;
-    S[6] += w.z;
+    const longlong2 a = partial[(int64_t)g * rows + r];
+    hi += a.x;
+    lo += a.y;
   }
 }
-__device__ __forceinline__ double ds_mm_sum_finish(const long long S[7]) {
-  const long long hi = ((S[6] * 256 + S[5]) * 256 + S[4]) * 256 + S[3];
-  const long long lo = (S[2] * 256 + S[1]) * 256 + S[0];
-  return (double)hi * 16777216.0 + (double)lo;
-}
-__device__ __forceinline__ double ds_mm_sum(const int32_t* partial, int64_t rows, int groups, int64_t r) {
-  long long S[7] = {0, 0, 0, 0, 0, 0, 0};
-  ds_mm_sum_part(partial, rows, groups, r, 0, 1, S);
-  return ds_mm_sum_finish(S);
+__device__ __forceinline__ double ds_mm_sum_finish(long long hi, long long lo) { return (double)hi * 16777216.0 + (double)lo; }
+__device__ __forceinline__ double ds_mm_sum(const longlong2* partial, int64_t rows, int groups, int64_t r) {
+  long long hi = 0, lo = 0;
+  ds_mm_sum_part(partial, rows, groups, r, 0, 1, hi, lo);
+  return ds_mm_sum_finish(hi, lo);
 }
 // 64 x 64 bits, a row per lane, transposed: bit i of lane j = bit j of lane i. Six rounds of swapping bit blocks with the
 // lane 32, 16, ... 1 away.

@@ -633,6 +633,27 @@ def test_cgls_small_games_step_by_step(ctx_tiny, n, ns, paired):
         assert np.abs(phi.cpu().numpy() - ref).max() <= 3e-7 * np.abs(ref).max()
 
 
+# The matrix-core product of the dense rows (all of them here, but the empty coalition): transposed rows of one word, of an odd and of
+# an even number, padded to whole cache lines and not; fewer units of work than compute units, one more than a round, row
+# groups that two or more workgroups share; a last chunk of one column.
+@pytest.mark.parametrize("n,ns", [(4096, 40), (4097, 130), (5121, 2200), (4160, 15000), (9000, 20000), (30000, 3000)])
+def test_cgls_dense_products_step_by_step(ctx_tiny, n, ns):
+    from paper_2506_22668_amd import Options, Tuning, DS_SOLVER_CGLS
+    ctx, _ = ctx_tiny
+    Z, w, bits, y = _solve_inputs(n, ns, 700 + n)
+    args = (n, torch.from_numpy(Z.view(np.int64)).cuda(), torch.from_numpy(w).cuda(), torch.from_numpy(y).cuda())
+    ctx.set_tuning(Tuning(cgls_dense_div=65536))
+    for steps in (1, 3):
+        say(f"cgls dense n={n} n_samples={ns} steps={steps}")
+        ref, it_ref, rel_ref = solve.solve_cgls(bits, w, y, tol=1e-9, max_iter=steps)
+        phi, rep, _ = ctx.solve(*args, Options(solver=DS_SOLVER_CGLS, tol=1e-9, max_iter=steps, paired=1), allow_not_converged=True)
+        assert rep.cgls_iterations == it_ref
+        assert abs(rep.cgls_rel_residual - rel_ref) <= 1e-6 * rel_ref + 1e-12
+        # fp32 scores: half an ulp; vectors in fixed point at 2^-54 of their largest entry are far below it
+        assert np.abs(phi.cpu().numpy() - ref).max() <= 3e-7 * np.abs(ref).max()
+    ctx.set_tuning(Tuning())
+
+
 @pytest.mark.parametrize("dense_div", [32, 1024, 65536])
 def test_cgls_dense_row_threshold_leaves_the_solution_alone(ctx_tiny, dense_div):
     """Which pair rows are multiplied as bitmaps on the matrix cores and which as index lists is a tuning choice:
