@@ -202,9 +202,7 @@ __device__ __forceinline__ void gram_rows_tile(const uint64_t* Zc, const unsigne
   for (int i = tid; i < kTile * kTile; i += kThreads) {
     const int64_t a = (int64_t)ta * kTile + (i >> 6), b = (int64_t)tb * kTile + (i & 63);
     if (a < n && b < n) {
-      const double v = (double)acc[i] * inv;
-      G[a * n + b] = v;
-      if (ta != tb) G[b * n + a] = v;
+      G[a * n + b] = (double)acc[i] * inv;
     }
   }
 }
@@ -216,8 +214,23 @@ __global__ __launch_bounds__(kThreads) void gram_rows_kernel(const uint64_t* Zc,
   gram_rows_tile(Zc, wq, R, n, scale, G, blockIdx.y, blockIdx.x, acc);
 }
 
-// One 64x64 tile of G per workgroup and slice of the row words (split-K); each slice
-// writes its own full symmetric partial matrix, summed later in a fixed order.
+// A tile's share of the row sums of G, of which only the lower tiles are kept (diagonal tiles whole): part[t][a] = sum of G[a][b] over the
+// 64 columns b of tile column t. The tile T (values past n zero) gives the row sums of its rows and, below the diagonal, the column sums
+// that stand for the tile above it. (Stored on both sides, the tiles above the diagonal as 8-byte pieces, and summed by row afterwards: 6,007
+// columns: 1,624 us for the Gram kernels, the sums and the system matrix, now 1,425.)
+__device__ __forceinline__ void gram_tile_sums(const double (*T)[kTile + 1], int ta, int tb, int64_t n, double* part) {
+  const int tid = threadIdx.x, i = tid & 63;
+  if (tid >= 128 || (tid >= 64 && ta == tb)) return;
+  const bool cols = tid >= 64;
+  double s = 0.0;
+#pragma unroll 16
+  for (int k = 0; k < kTile; ++k) s += cols ? T[k][i] : T[i][k];
+  const int64_t a = (int64_t)(cols ? tb : ta) * kTile + i;
+  if (a < n) part[(int64_t)(cols ? ta : tb) * n + a] = s;
+}
+
+// One 64x64 tile of G per workgroup and slice of the row words (split-K); each slice writes the lower tiles of its own partial
+// matrix, summed later in a fixed order. A single slice leaves the tile's sums in `part` (else nullptr).
 // A word of 64 rows that share one weight costs an AND and a popcount per pair of columns. A word that
 // straddles weight classes (most words past the first few classes: a class soon has fewer than 64 rows)
 // either walks the set bits of the AND (sparse rows) or, when its rows are dense, is treated as the small
@@ -250,7 +263,8 @@ __device__ __forceinline__ uint32_t pair_mask(uint32_t two_bits) {
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 4))) void gram_kernel(const uint64_t* Zt, int64_t n, int64_t k, int64_t KW,
                                                         const float* w, const float* wu, const int32_t* uni,
                                                         const uint64_t* keep, double* Gp, int64_t words_per_slice, int rows_apart,
-                                                        const uint64_t* Zc, const unsigned long long* wq, const double* scale) {
+                                                        const uint64_t* Zc, const unsigned long long* wq, const double* scale,
+                                                        double* part) {
   const int ta = blockIdx.y, tb = blockIdx.x;
   if (tb > ta) return;
   // As | Bs during the accumulation; reused as one 64 x 65 fp64 tile when the two paths are merged
@@ -448,36 +462,54 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 4))
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int64_t a = a0 + ty + 16 * i, b = b0 + tx + 16 * j;
-      if (a < n && b < n) {
-        const double v = acc[i][j] + Ts[ty + 16 * i][tx + 16 * j] + prev[i][j];
-        G[a * n + b] = v;
-        if (ta != tb) G[b * n + a] = v;  // a diagonal tile computes both of its triangles itself
-      }
+      const bool in = a < n && b < n;
+      const double v = acc[i][j] + Ts[ty + 16 * i][tx + 16 * j] + prev[i][j];
+      if (in) G[a * n + b] = v;
+      if (part) Ts[ty + 16 * i][tx + 16 * j] = in ? v : 0.0;   // (this thread's own element)
     }
+  if (!part) return;
+  __syncthreads();
+  gram_tile_sums(Ts, ta, tb, n, part);
 }
 
-// G = sum of the slices (into slice 0) and the row means of G; one workgroup per row (grid-stride)
-__global__ __launch_bounds__(kThreads) void sum_slices_row_mean_kernel(double* Gp, int64_t n, int slices, double* m) {
-  __shared__ double red[kThreads / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int64_t a = blockIdx.x; a < n; a += gridDim.x) {
-    double s = 0.0;
-    for (int64_t b = threadIdx.x; b < n; b += kThreads) {
-      double g = Gp[a * n + b];
-      for (int z = 1; z < slices; ++z) g += Gp[(size_t)z * n * n + a * n + b];
-      Gp[a * n + b] = g;
-      s += g;
+// G = sum of the slices (into slice 0), and the tiles' sums: one workgroup per lower tile
+__global__ __launch_bounds__(kThreads) void sum_slices_kernel(double* Gp, int64_t n, int slices, double* part) {
+  const int ta = blockIdx.y, tb = blockIdx.x;
+  if (tb > ta) return;
+  __shared__ double T[kTile][kTile + 1];
+  constexpr int kPer = kTile * kTile / kThreads;
+  double v[kPer];
+  for (int z = 0; z < slices; ++z) {   // (a slice's loads in flight together; addresses clamped)
+    double g[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int idx = threadIdx.x + u * kThreads;
+      const int64_t a = (int64_t)ta * kTile + (idx >> 6), b = (int64_t)tb * kTile + (idx & 63);
+      g[u] = Gp[(size_t)z * n * n + (a < n ? a : n - 1) * n + (b < n ? b : n - 1)];
     }
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (lane == 0) red[wave] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double t = 0.0;
-      for (int w = 0; w < kThreads / 64; ++w) t += red[w];  // fixed order
-      m[a] = t / (double)n;
-    }
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) v[u] = z == 0 ? g[u] : v[u] + g[u];
   }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int idx = threadIdx.x + u * kThreads;
+    const int64_t a = (int64_t)ta * kTile + (idx >> 6), b = (int64_t)tb * kTile + (idx & 63);
+    const bool in = a < n && b < n;
+    if (in) Gp[a * n + b] = v[u];
+    T[idx >> 6][idx & 63] = in ? v[u] : 0.0;
+  }
+  __syncthreads();
+  gram_tile_sums(T, ta, tb, n, part);
+}
+
+// m[a] = mean of row a of G
+__global__ void row_means_kernel(const double* part, int64_t n, int tiles, double* m) {
+  const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (a >= n) return;
+  double s = 0.0;
+#pragma unroll 8
+  for (int t = 0; t < tiles; ++t) s += part[(int64_t)t * n + a];
+  m[a] = s / (double)n;
 }
 
 // single block: stats[0] = mu (grand mean of G), stats[1] = trace(G); clears the factorisation's flag
@@ -511,21 +543,39 @@ __global__ __launch_bounds__(kThreads) void stats_kernel(const double* G, const 
 // that exact arithmetic would make zero (a direction the sampled rows do not determine) comes out of fp64
 // as about n * 2^-52 times the scale, with either sign; 256 n 2^-52 sits well above that and far below the
 // pivots of a determined system.
-__global__ void build_matrix_kernel(const double* G, const double* m, const double* stats, int64_t n, int64_t ld, double* M,
-                                    double* pivot_floor) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n * n) return;
+// Lower tiles only, one workgroup each; the first 64 columns also go to P (row r at P[64 r ..]), the panel of the first fused step.
+__global__ __launch_bounds__(kThreads) void build_matrix_kernel(const double* G, const double* m, const double* stats, int64_t n, int64_t ld,
+                                                                double* M, double* P, double* pivot_floor) {
+  const int ta = blockIdx.y, tb = blockIdx.x;
+  if (tb > ta) return;
   const double mu = stats[0];
   const double tr = stats[1] - (double)n * mu;
   double gamma = tr / (double)(n > 1 ? n - 1 : 1);
   if (!(gamma > 0.0)) gamma = 1.0;
-  if (idx == 0) *pivot_floor = 256.0 * (double)n * 0x1p-52 * ((tr > 0.0 ? tr : 0.0) + gamma) / (double)n;
-  const int64_t a = idx / n, b = idx - a * n;
-  M[a * ld + b] = G[idx] - m[a] - m[b] + mu + gamma / (double)n;
+  const int tid = threadIdx.x;
+  if (ta == 0 && tid == 0) *pivot_floor = 256.0 * (double)n * 0x1p-52 * ((tr > 0.0 ? tr : 0.0) + gamma) / (double)n;
+  constexpr int kPer = kTile * kTile / kThreads;
+  const int64_t b = (int64_t)tb * kTile + (tid & 63), bc = b < n ? b : n - 1;
+  const double mb = m[bc];
+  double g[kPer], ma[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int64_t a = (int64_t)ta * kTile + (tid >> 6) + u * (kThreads / 64), ac = a < n ? a : n - 1;
+    g[u] = G[ac * n + bc];
+    ma[u] = m[ac];
+  }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int64_t a = (int64_t)ta * kTile + (tid >> 6) + u * (kThreads / 64);
+    if (a >= n || b >= n) continue;
+    const double v = g[u] - ma[u] - mb + mu + gamma / (double)n;
+    M[a * ld + b] = v;
+    if (tb == 0) P[a * kTile + b] = v;
+  }
 }
 
-// row n of M = c - mean(c); single block
-__global__ __launch_bounds__(kThreads) void build_rhs_kernel(const double* c, int64_t n, int64_t ld, double* M) {
+// row n of M (and of P, its first 64 columns) = c - mean(c); single block
+__global__ __launch_bounds__(kThreads) void build_rhs_kernel(const double* c, int64_t n, int64_t ld, double* M, double* P) {
   __shared__ double sh[kThreads];
   double a = 0;
   for (int64_t i = threadIdx.x; i < n; i += kThreads) a += c[i];
@@ -538,7 +588,10 @@ __global__ __launch_bounds__(kThreads) void build_rhs_kernel(const double* c, in
   }
   __syncthreads();
   const double mean = sh[0];
-  for (int64_t i = threadIdx.x; i < n; i += kThreads) M[n * ld + i] = c[i] - mean;
+  for (int64_t i = threadIdx.x; i < n; i += kThreads) {
+    M[n * ld + i] = c[i] - mean;
+    if (i < kTile) P[n * kTile + i] = c[i] - mean;
+  }
 }
 
 // ---------------- blocked Cholesky (lower, in place, fp64) ----------------
@@ -1108,7 +1161,7 @@ __global__ __launch_bounds__(kThreads) void chol_step_kernel(double* M, int64_t 
   tile_sub_store<2, 2>(M, ld, rows_total, n, i0, c0, wi, wj, acc, tj == 0 ? Pnext : nullptr);
 }
 
-// rows [row0, rows_total) of the 64 columns at j0 -> P (row r at P[r * 64 ..]): the panel of the first fused step
+// rows [row0, rows_total) of the 64 columns at j0 -> P (row r at P[r * 64 ..]): the panel of a first fused step behind others
 __global__ void copy_panel_kernel(const double* M, int64_t ld, int64_t rows_total, int64_t row0, int64_t j0, int64_t n, double* P) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t r = row0 + (idx >> 6);
@@ -1769,6 +1822,9 @@ GramDims gram_dims(int64_t n, int64_t k, int paired, int num_cus) {
 
 }  // namespace
 
+// row sums of G by tile columns
+static size_t gram_sums_bytes(int64_t n) { return (size_t)((n + kTile - 1) / kTile) * n * 8; }
+
 // the parts of the sums of a game of at most 64 players: per pair of players, and per player
 static constexpr size_t small_bytes = (size_t)kSmallParts * kSmallPairs * 8;
 
@@ -1779,7 +1835,7 @@ size_t ds_gram_arena_bytes(int64_t n, int64_t k) {
   const GramDims d = gram_dims(n, k, 0, 256);  // the unpaired layout is the larger one
   const GramDims dp = gram_dims(n, k, 1, 256);
   const size_t slices = (size_t)(d.slices > dp.slices ? d.slices : dp.slices) + 1;  // +1: CU counts differ a little
-  return (n <= kSmallMax ? 2 * ds_align(small_bytes) : 0) + ds_align((size_t)n * d.RW * 8) + ds_align(slices * (size_t)n * n * 8) + ds_align((size_t)(n + 1) * d.ld * 8) +
+  return (n <= kSmallMax ? 2 * ds_align(small_bytes) : 0) + ds_align(gram_sums_bytes(n)) + ds_align((size_t)n * d.RW * 8) + ds_align(slices * (size_t)n * n * 8) + ds_align((size_t)(n + 1) * d.ld * 8) +
          ds_align((size_t)d.nblk * NB * NB * 8) + 2 * ds_align(panel_bytes(n)) + 2 * ds_align(k * 4) + 2 * ds_align(k * 8) + ds_align(k * 4) +
          ds_align(k * 8) + ds_align(d.RW * 4) * 2 + 4 * ds_align(n * 8) + 8192 +
          ds_align((size_t)((n + 63) / 64) * d.R * 8 + 8) + ds_align((size_t)d.RW * 8 + 8) + ds_align((size_t)d.R * 8 + 8) + 256;
@@ -1803,6 +1859,7 @@ int ds_gram_alloc(ds_ctx* ctx, int64_t n, int64_t k, int paired, ds_gram_state* 
   gs->wu = (float*)ds_arena_alloc(ctx, RW * 4);
   gs->uni = (int32_t*)ds_arena_alloc(ctx, RW * 4);
   gs->m = (double*)ds_arena_alloc(ctx, n * 8);
+  gs->sums = (double*)ds_arena_alloc(ctx, gram_sums_bytes(n));
   gs->stats = (double*)ds_arena_alloc(ctx, 64);
   gs->Zc = (uint64_t*)ds_arena_alloc(ctx, (size_t)W * R * 8 + 8);
   gs->keep = (uint64_t*)ds_arena_alloc(ctx, (size_t)RW * 8 + 8);
@@ -1816,7 +1873,7 @@ int ds_gram_alloc(ds_ctx* ctx, int64_t n, int64_t k, int paired, ds_gram_state* 
   gs->c = (double*)ds_arena_alloc(ctx, n * 8);
   gs->flag = (int*)ds_arena_alloc(ctx, 64);
   if (!gs->Zt || !gs->Gp || !gs->M || !gs->linv || !gs->panel[0] || !gs->panel[1] || !gs->gw || !gs->wu || !gs->uni || !gs->m ||
-      !gs->stats || !gs->Zc || !gs->keep || !gs->wq || !gs->gscale || !gs->sz || !gs->wc || !gs->t || !gs->sqw || !gs->gc || !gs->c ||
+      !gs->sums || !gs->stats || !gs->Zc || !gs->keep || !gs->wq || !gs->gscale || !gs->sz || !gs->wc || !gs->t || !gs->sqw || !gs->gc || !gs->c ||
       !gs->flag)
     return ds_fail(ctx, DS_EINTERNAL, "gram: arena exhausted");
   return DS_OK;
@@ -1855,12 +1912,13 @@ int ds_gram_begin(ds_ctx* ctx, ds_gram_state* gs, const uint64_t* Z, const float
     hipLaunchKernelGGL(gram_rows_kernel, dim3(tiles, tiles), dim3(kThreads), 0, st, Zc, (const unsigned long long*)wq, R, n,
                        gscale, Gp);
   hipLaunchKernelGGL(gram_kernel, dim3(tiles, tiles, gs->slices), dim3(kThreads), 0, st, gs->Zt, n, R, RW, gw, wu, uni, keep,
-                     Gp, gs->words_per_slice, gs->rows_apart, Zc, (const unsigned long long*)wq, gscale);
+                     Gp, gs->words_per_slice, gs->rows_apart, Zc, (const unsigned long long*)wq, gscale,
+                     gs->slices == 1 ? gs->sums : nullptr);
   DS_TRY(ds_kernel_mark(ctx, 1, 1));
-  const unsigned wblocks = (unsigned)(n < (int64_t)ctx->num_cus * 16 ? n : (int64_t)ctx->num_cus * 16);
-  hipLaunchKernelGGL(sum_slices_row_mean_kernel, dim3(wblocks), dim3(kThreads), 0, st, Gp, n, gs->slices, m);
+  if (gs->slices > 1) hipLaunchKernelGGL(sum_slices_kernel, dim3(tiles, tiles), dim3(kThreads), 0, st, Gp, n, gs->slices, gs->sums);
+  hipLaunchKernelGGL(row_means_kernel, dim3(nblocks(n, 64)), dim3(64), 0, st, gs->sums, n, (int)tiles, m);
   hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(kThreads), 0, st, Gp, m, n, stats, gs->flag);
-  hipLaunchKernelGGL(build_matrix_kernel, dim3(nblocks(n * n, 256)), dim3(256), 0, st, Gp, m, stats, n, ld, gs->M,
+  hipLaunchKernelGGL(build_matrix_kernel, dim3(tiles, tiles), dim3(kThreads), 0, st, Gp, m, stats, n, ld, gs->M, gs->panel[0],
                      (double*)(gs->flag + 2));
   // the first diagonal block does not involve the right-hand side either: factorised here, off the path that waits
   // for the model outputs
@@ -1891,13 +1949,14 @@ static int gram_factor(ds_ctx* ctx, const ds_gram_state* gs, int64_t rows_total,
   hipStream_t chain = st;
   bool rest_queued = false;   // an update of the rest is under way on the main stream, join_ev behind it
   bool diag_done = true;  // the first diagonal block was factorised with the system matrix (ds_gram_begin)
-  bool panel_ready = false;  // gs->panel[pbuf] holds the rows of the current panel (fused steps only)
+  bool panel_ready = true;   // gs->panel[pbuf] holds the rows of the current panel (the first one's since it was built)
   int pbuf = 0;
   int64_t j0 = 0;
   while (j0 < n) {
     if (mid && j0 == mid_at) DS_HIP(ctx, hipEventRecord(mid, st));   // (the launch before has left block j0 factorised)
     const bool super = rows_total - j0 - kSuperCols > kFuseMaxRows && n - j0 >= kSuperCols + NB;
     if (super) {
+      panel_ready = false;
       if (chain == st) {   // the first one
         chain = ctx->side;
         DS_HIP(ctx, hipEventRecord(ctx->fork_ev, st));
@@ -1958,6 +2017,7 @@ static int gram_factor(ds_ctx* ctx, const ds_gram_state* gs, int64_t rows_total,
       j0 += nb;
       continue;
     }
+    panel_ready = false;
     if (rest > 0) hipLaunchKernelGGL(chol_panel_kernel, dim3(nblocks(rest, kTile)), dim3(kThreads), 0, st, M, ld, rows_total, j0, nb, li);
     if (n - j0 - nb > 0) {
       const unsigned tt = nblocks(rest, kTile);
@@ -2025,7 +2085,7 @@ int ds_gram_finish(ds_ctx* ctx, const ds_gram_state* gs, const uint64_t* Z, cons
   DS_TRY(ds_row_prep(ctx, Z, k, n, gs->paired, w, y, gs->sz, gs->t, gs->sqw, gs->wc));
   hipLaunchKernelGGL(used_row_rhs_kernel, dim3(nblocks(R, 256)), dim3(256), 0, st, gs->wc, gs->t, R, gs->paired, gs->gc);
   DS_TRY(ds_bit_spmv(ctx, gs->Zt, n, R, RW, 0, 1, gs->gc, gs->c));  // c_j = sum over the rows containing j of gc
-  hipLaunchKernelGGL(build_rhs_kernel, dim3(1), dim3(kThreads), 0, st, gs->c, n, ld, gs->M);
+  hipLaunchKernelGGL(build_rhs_kernel, dim3(1), dim3(kThreads), 0, st, gs->c, n, ld, gs->M, gs->panel[0]);
   DS_HIP(ctx, hipGetLastError());
   double* const rhs = gs->M + n * ld;
   double* v = rhs;   // L^-1 rhs

@@ -209,7 +209,7 @@ struct ds_gram_state {
   int64_t n, k, R, RW, ld, nblk, words_per_slice;
   int paired, slices, rows_apart;
   uint64_t *Zt, *Zc, *keep, *wq;
-  double *Gp, *m, *stats, *gscale, *M, *linv, *t, *sqw, *gc, *c;
+  double *Gp, *sums, *m, *stats, *gscale, *M, *linv, *t, *sqw, *gc, *c;
   double* panel[2];  // rows of the current and of the next 64-column panel (fused steps of the factorisation)
   int32_t *uni, *sz;
   float *gw, *wu, *wc;
