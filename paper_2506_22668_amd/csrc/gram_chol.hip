@@ -236,18 +236,20 @@ __device__ __forceinline__ void gram_tile_sums(const double (*T)[kTile + 1], int
 // either walks the set bits of the AND (sparse rows) or, when its rows are dense, is treated as the small
 // dense contraction it is, sum_r (w_r z_ra) z_rb, on the matrix cores. The fp32 weight is split into three
 // bfloat16 pieces (w = w1 + w2 + w3 to 24 bits; a bit is exactly 0 or 1 in bfloat16), so the contraction runs
-// as three v_mfma_f32_32x32x8bf16_1k per 8 rows with fp32 accumulation, several times the rate of the fp32
-// instruction: lane l supplies A[m = l%32][k = 4*(l/32) + j] = piece of row r * bit r of column m's word and
-// B[k][n = l%32] = bit r of column n's word, r = 8 kb + k, j < 4 (two values per register). Operands are
-// made with look-ups: a 16-entry LDS table turns four bits into the two registers of 16-bit masks (or of
-// bfloat16 ones for B), which the packed weight pieces are ANDed with. Each wave owns a 32x32 quadrant of the
+// as three v_mfma_f32_32x32x16_bf16 per 16 rows with fp32 accumulation, many times the rate of the fp32
+// instruction: lane l supplies A[m = l%32][k = 8*(l/32) + j] = piece of row r * bit r of column m's word and
+// B[k][n = l%32] = bit r of column n's word, r = 16 kb + k, j < 8 (two values per register). Operands are
+// made with look-ups: a 16-entry LDS table (whose entries lie in banks of their own, which those of a byte's would not) turns
+// four bits into the two registers of 16-bit masks (or of bfloat16 ones for B), which the packed weight pieces are ANDed with.
+// (Eight rows at a time with v_mfma_f32_32x32x8bf16_1k, the same 32 cycles each: 6,007 columns, 20,000 rows 1,050 us, now 877.) Each wave owns a 32x32 quadrant of the
 // tile (accumulator register i of lane l is D[8*(i/4) + 4*(l/32) + i%4][l%32]). Both paths add up in fp32
 // within a chunk of 32 words and in fp64 across chunks.
 // The sparse rows' part is in slice 0 already (`rows_apart`: gram_rows_kernel, whose own launch holds more workgroups per compute unit), or
 // it is the launch's last slice: where the tiles of one triangle do not fill the GPU, both kinds run together
 // (1,010 columns, 10,000 rows: 48 + 51 us apart, 76 together).
 typedef float gram_f16_t __attribute__((ext_vector_type(16)));
-typedef short gram_s4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 gram_b8_t __attribute__((ext_vector_type(8)));
+typedef unsigned int gram_u4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int gram_u2_t __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t bf16_bits_rn(float x) {  // nearest-even bfloat16 of a finite float, as 16 bits
@@ -273,7 +275,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 4))
   uint64_t (*As)[kChunk + 1] = (uint64_t (*)[kChunk + 1])raw;
   uint64_t (*Bs)[kChunk + 1] = (uint64_t (*)[kChunk + 1])(raw + kTile * (kChunk + 1));
   __shared__ float wrow[kChunk * 64];
-  __shared__ gram_u2_t wpk[3][kChunk * 16];  // weight pieces as bfloat16, rows 4j..4j+3 of a word per entry
+  __shared__ __align__(16) gram_u2_t wpk[3][kChunk * 16];  // weight pieces as bfloat16, rows 4j..4j+3 of a word per entry
   __shared__ gram_u2_t tabA[16], tabB[16];   // four bits -> 16-bit masks / bfloat16 ones (two registers)
   __shared__ float wus[kChunk];
   __shared__ int unis[kChunk];
@@ -397,22 +399,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 4))
       } else if (unis[c] == 3) {
         // no kept row in this word
       } else if (unis[c] == 2) {
-        // rows 8 kb + 4 half + j, j < 4: a nibble of each column word per step (pre-shifted by 4 half)
-        const uint64_t aw = As[wi + l32][c] >> (4 * half), bw = Bs[wj + l32][c] >> (4 * half);
-        const gram_u2_t* w1 = wpk[0] + c * 16 + half;
-        const gram_u2_t* w2 = wpk[1] + c * 16 + half;
-        const gram_u2_t* w3 = wpk[2] + c * 16 + half;
+        // rows 16 kb + 8 half + j, j < 8: a byte of each column word per step (pre-shifted by 8 half)
+        const uint64_t aw = As[wi + l32][c] >> (8 * half), bw = Bs[wj + l32][c] >> (8 * half);
+        const gram_u4_t* w1 = (const gram_u4_t*)(wpk[0] + c * 16) + half;
+        const gram_u4_t* w2 = (const gram_u4_t*)(wpk[1] + c * 16) + half;
+        const gram_u4_t* w3 = (const gram_u4_t*)(wpk[2] + c * 16) + half;
 #pragma unroll
-        for (int kb = 0; kb < 8; ++kb) {
-          const gram_u2_t am = tabA[(uint32_t)(aw >> (8 * kb)) & 15u];
-          const gram_s4_t bo = __builtin_bit_cast(gram_s4_t, tabB[(uint32_t)(bw >> (8 * kb)) & 15u]);
-          const gram_u2_t p1 = w1[2 * kb], p2 = w2[2 * kb], p3 = w3[2 * kb];
-          const gram_s4_t a1 = __builtin_bit_cast(gram_s4_t, gram_u2_t{p1.x & am.x, p1.y & am.y});
-          const gram_s4_t a2 = __builtin_bit_cast(gram_s4_t, gram_u2_t{p2.x & am.x, p2.y & am.y});
-          const gram_s4_t a3 = __builtin_bit_cast(gram_s4_t, gram_u2_t{p3.x & am.x, p3.y & am.y});
-          fm0 = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a1, bo, fm0, 0, 0, 0);
-          fm1 = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a2, bo, fm1, 0, 0, 0);
-          fm1 = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a3, bo, fm1, 0, 0, 0);
+        for (int kb = 0; kb < 4; ++kb) {
+          const uint32_t x = (uint32_t)(aw >> (16 * kb)), y = (uint32_t)(bw >> (16 * kb));
+          const gram_u2_t a0 = tabA[x & 15u], a1 = tabA[(x >> 4) & 15u], b0 = tabB[y & 15u], b1 = tabB[(y >> 4) & 15u];
+          const gram_u4_t am = {a0.x, a0.y, a1.x, a1.y};
+          const gram_b8_t bo = __builtin_bit_cast(gram_b8_t, gram_u4_t{b0.x, b0.y, b1.x, b1.y});
+          const gram_b8_t p1 = __builtin_bit_cast(gram_b8_t, w1[2 * kb] & am);
+          const gram_b8_t p2 = __builtin_bit_cast(gram_b8_t, w2[2 * kb] & am);
+          const gram_b8_t p3 = __builtin_bit_cast(gram_b8_t, w3[2 * kb] & am);
+          fm0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p1, bo, fm0, 0, 0, 0);
+          fm1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p2, bo, fm1, 0, 0, 0);
+          fm1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p3, bo, fm1, 0, 0, 0);
         }
       } else {
         uint64_t av[4], bv[4];
