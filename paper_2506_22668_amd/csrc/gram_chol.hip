@@ -1093,8 +1093,8 @@ __global__ __launch_bounds__(kThreads) void chol_update_kernel(double* M, int64_
   }
 }
 
-// One launch per 64-column step while the trailing matrix is small (at most kFuseMaxRows rows): panel solve,
-// trailing update and factorisation of the next diagonal block together. Every workgroup (ti, tj), tj <= ti, first
+// One launch per 64-column step: panel solve, update of the block columns ahead (all of them while the trailing matrix is small, those of
+// the super-panel, gridDim.x of them, before) and factorisation of the next diagonal block together. Every workgroup (ti, tj), tj <= ti, first
 // solves its own two 64-row pieces of the panel, X = A Linv^T, instead of waiting for a launch that does so
 // (twice the arithmetic of the update itself, on workgroups that would otherwise be idle), then updates its tile;
 // the workgroup of the first diagonal tile factorises that tile instead, as in chol_update_kernel<true>.
@@ -1177,12 +1177,13 @@ __global__ void copy_panel_kernel(const double* M, int64_t ld, int64_t rows_tota
 // is read and written once per super-panel instead of once per 64 columns. Two kernels share it.
 //
 // The next super-panel's own columns: 64x64 tiles (block columns 0 .. gridDim.x - 1), which fill the GPU, and the
-// workgroup of the first one goes on to factorise it, as in chol_update_kernel<true>. The next chunk of the two operands is
+// workgroup of the first one goes on to factorise it, as in chol_update_kernel<true>; the first block column also goes to P, the
+// panel of the fused step that follows. The next chunk of the two operands is
 // fetched into registers while the matrix cores work on the current one.
 template <int KW>  // known at compile time, so that the chunk loop unrolls (column offsets become immediates and the
                    // accumulators stay where the matrix cores want them)
 __global__ __launch_bounds__(kThreads) void chol_update_next_kernel(double* M, int64_t ld, int64_t rows_total, int64_t n, int64_t J,
-                                                                    int64_t base, double* linv_next, int* flag) {
+                                                                    int64_t base, double* linv_next, int* flag, double* P) {
   const int ti = blockIdx.y, tj = blockIdx.x;
   if (tj > ti) return;
   __shared__ double Li[kTile][NB + 1];
@@ -1251,7 +1252,7 @@ __global__ __launch_bounds__(kThreads) void chol_update_next_kernel(double* M, i
     return;
   }
   const int wave = tid >> 6;
-  tile_sub_store<2, 2>(M, ld, rows_total, n, i0, c0, (wave >> 1) * 32, (wave & 1) * 32, acc, nullptr);
+  tile_sub_store<2, 2>(M, ld, rows_total, n, i0, c0, (wave >> 1) * 32, (wave & 1) * 32, acc, tj == 0 ? P : nullptr);
 }
 
 // The rest of the matrix, 128x128 tiles from row/column `base` on (T rows of tiles), a 32x64 piece of one to each of
@@ -1946,7 +1947,7 @@ static int gram_factor(ds_ctx* ctx, const ds_gram_state* gs, int64_t rows_total,
   // updated once with all 256 columns. Below kFuseMaxRows trailing rows: one block per step, the update
   // factorising the next diagonal block on the way.
   // The super-panels run one ahead on the side stream: the columns of the next super-panel are updated first and its
-  // chain of small launches (panels, narrow updates with the diagonal blocks: a few workgroups each) goes on behind
+  // chain of small launches (fused steps on its own columns; panels and updates apart: six games of 1,175 to 6,007 10.3 ms, now 10.1) goes on behind
   // them, while the main stream updates the rest of the matrix. Every tile still meets the super-panels in their order:
   // the next super-panel's columns wait for the rest of the update before (join_ev), the rest for them (fork_ev).
   hipStream_t chain = st;
@@ -1959,7 +1960,6 @@ static int gram_factor(ds_ctx* ctx, const ds_gram_state* gs, int64_t rows_total,
     if (mid && j0 == mid_at) DS_HIP(ctx, hipEventRecord(mid, st));   // (the launch before has left block j0 factorised)
     const bool super = rows_total - j0 - kSuperCols > kFuseMaxRows && n - j0 >= kSuperCols + NB;
     if (super) {
-      panel_ready = false;
       if (chain == st) {   // the first one
         chain = ctx->side;
         DS_HIP(ctx, hipEventRecord(ctx->fork_ev, st));
@@ -1968,19 +1968,21 @@ static int gram_factor(ds_ctx* ctx, const ds_gram_state* gs, int64_t rows_total,
       for (int b = 0; b < kSuperCols / NB; ++b) {
         const int64_t jb = j0 + (int64_t)b * NB;
         double* li = linv + (size_t)(jb / NB) * NB * NB;
-        // the update before has factorised the diagonal block on the way
-        const int64_t rest = rows_total - jb - NB;
-        const unsigned tt = nblocks(rest, kTile);
-        hipLaunchKernelGGL(chol_panel_kernel, dim3(tt), dim3(kThreads), 0, chain, M, ld, rows_total, jb, NB, li);
+        // the launch before has factorised the diagonal block on the way
+        const unsigned tt = nblocks(rows_total - jb - NB, kTile);
         const unsigned inside = (unsigned)(kSuperCols / NB - 1 - b);  // block columns of the super-panel still ahead
-        if (inside > 0)
-          hipLaunchKernelGGL(chol_update_kernel<true>, dim3(inside, tt), dim3(kThreads), 0, chain, M, ld, rows_total, n, jb,
-                             NB, li + (size_t)NB * NB, gs->flag);
+        if (inside > 0) {
+          hipLaunchKernelGGL(chol_step_kernel, dim3(inside, tt), dim3(kThreads), 0, chain, M, ld, rows_total, n, jb, li, li + (size_t)NB * NB,
+                             gs->flag, gs->panel[pbuf], gs->panel[pbuf ^ 1]);
+          pbuf ^= 1;
+        } else {
+          hipLaunchKernelGGL(chol_panel_kernel, dim3(tt), dim3(kThreads), 0, chain, M, ld, rows_total, jb, NB, li);
+        }
       }
       const int64_t base = j0 + kSuperCols;
       if (rest_queued) DS_HIP(ctx, hipStreamWaitEvent(chain, ctx->join_ev, 0));
       hipLaunchKernelGGL(chol_update_next_kernel<(int)kSuperCols>, dim3((unsigned)(kSuperCols / NB), nblocks(rows_total - base, kTile)),
-                         dim3(kThreads), 0, chain, M, ld, rows_total, n, j0, base, linv + (size_t)(base / NB) * NB * NB, gs->flag);
+                         dim3(kThreads), 0, chain, M, ld, rows_total, n, j0, base, linv + (size_t)(base / NB) * NB * NB, gs->flag, gs->panel[pbuf]);
       DS_HIP(ctx, hipEventRecord(ctx->fork_ev, chain));
       DS_HIP(ctx, hipStreamWaitEvent(st, ctx->fork_ev, 0));
       const int64_t tw = (rows_total - base - kSuperCols + kWideTile - 1) / kWideTile;   // (kFuseMaxRows rows are left at least)
