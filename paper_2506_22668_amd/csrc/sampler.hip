@@ -149,7 +149,140 @@ struct SampleArgs {
   int64_t list_max;
 };
 
-// THREADS: 256 where every pair comes here (short rows), 1024 for the pairs that the one-pass kernel hands on: those are a
+// Short rows (n < kWaveMax): a wave makes a pair, the row's keys in its registers (CALLS generator calls per lane, n <= 256 CALLS). The
+// threshold is searched among them: a guess is tried by counting the keys below it (one compare per register, the
+// population counts on the scalar unit), and the miss moves it by as many mean distances; a handful of guesses meets the s-th
+// smallest key, with nothing shared between waves and no barrier. As a workgroup per pair with a histogram in LDS, a row of
+// 1,010 columns was a chain of barriers around four generator calls a lane: 10,000 pairs 70 us, now 16.
+constexpr int64_t kWaveMax = 4096;   // (from there on the one-pass kernel)
+constexpr int kWavePairs = 4;        // waves, pairs, of a workgroup
+template <int CALLS>
+__global__ __launch_bounds__(64 * kWavePairs) void sample_pairs_wave_kernel(SampleArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int n = (int)a.n, words32 = 2 * (int)a.W;
+  const int64_t r = a.pair_begin + (int64_t)blockIdx.x * kWavePairs + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (r >= a.pair_end) return;
+  const int64_t o = 2 * (r - a.pair_begin);
+  uint32_t* const row_small = (uint32_t*)(a.Z + o * a.W);
+  uint32_t* const row_big = row_small + words32;
+  auto columns = [&](int word) -> uint32_t {   // the columns that 32 bits of a row stand for
+    const int left = n - 32 * word;
+    return left >= 32 ? ~0u : left > 0 ? (1u << left) - 1u : 0u;
+  };
+  if (r == 0) {  // (empty, full): the two constraint rows
+    for (int x = lane; x < words32; x += 64) {
+      row_small[x] = 0u;
+      row_big[x] = columns(x);
+    }
+    if (lane == 0) {
+      a.w[0] = 0.f;
+      a.w[1] = 0.f;
+      a.sz[0] = 0;
+      a.sz[1] = n;
+    }
+    return;
+  }
+  // size of the small member: s = min{s : b_s >= r}, 64 candidates at a time
+  int s = 1;
+  for (int64_t range = a.H; range > 1;) {
+    const int step = (int)((range + 63) / 64);
+    const int64_t at = s + (int64_t)(lane + 1) * step - 1;   // last of this lane's part
+    const unsigned long long below = __ballot(at < s + range - 1 && a.b[at < a.H ? at : a.H] < r);
+    const int parts = __popcll(below);                        // (b ascends)
+    s += parts * step;
+    range = range - (int64_t)parts * step < step ? range - (int64_t)parts * step : step;
+  }
+  const PhiloxRow prow = philox_row((uint32_t)r, (uint32_t)((uint64_t)r >> 32), a.tag, a.seed_lo, a.seed_hi);
+  uint32_t key[CALLS][4];
+#pragma unroll
+  for (int i = 0; i < CALLS; ++i) {
+    const int q = lane + 64 * i;
+    philox_along_row(prow, philox_first_product((uint32_t)q), key[i]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (4 * q + u >= n) key[i][u] = ~0u;   // (not below any threshold)
+  }
+  auto below = [&](uint32_t t) {
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < CALLS; ++i)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) c += __popcll(__ballot(key[i][u] < t));
+    return c;
+  };
+  // lo: fewer than s keys below it; hi: more. Every guess is strictly between them, so that the search ends: with s keys
+  // below the guess, or with nothing between lo and hi (several keys are equal to lo).
+  const float gap = 4294967296.f / (float)n;
+  uint32_t lo = 0u, hi = ~0u, t = (uint32_t)((float)s * gap);
+  int at_lo = 0, count = 0;
+  for (int guess = 0;; ++guess) {
+    if (t <= lo || guess > 16) t = lo + (hi - lo) / 2u;   // (a run of misses: halves)
+    if (t >= hi) t = hi - 1u;
+    if (t == lo) break;
+    count = below(t);
+    if (count == s) break;
+    if (count < s) {
+      lo = t;
+      at_lo = count;
+    } else {
+      hi = t;
+    }
+    // as many mean distances as ranks are missing, saturating
+    const float want = (float)t + (float)(s - count) * gap;
+    t = want <= 0.f ? 0u : want >= 4294967040.f ? ~0u : (uint32_t)want;
+  }
+  const bool ties = t == lo;   // some of the keys equal to lo, in column order
+  int need = ties ? s - at_lo : 0;
+  uint32_t out = 0u;
+  constexpr int kRound = CALLS < 8 ? CALLS : 8;   // spans of 256 columns per store
+#pragma unroll
+  for (int i = 0; i < CALLS; ++i) {
+    uint32_t nib = 0u;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) nib |= (key[i][u] < t ? 1u : 0u) << u;
+    if (ties) {
+      uint32_t eq = 0u;
+      int before = 0, total = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool e = key[i][u] == t && 4 * (lane + 64 * i) + u < n;
+        const unsigned long long m = __ballot(e);
+        eq |= (e ? 1u : 0u) << u;
+        before += __popcll(m & ((1ull << lane) - 1ull));
+        total += __popcll(m);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if ((eq >> u) & 1u) {
+          if (before < need) nib |= 1u << u;
+          ++before;
+        }
+      need = need > total ? need - total : 0;
+    }
+    // eight lanes make 32 bits, which all of them then hold; lane j of the eight keeps those of span j
+    uint32_t v = nib << (4 * (lane & 7));
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, false);    // quad_perm [1,0,3,2]
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, false);    // quad_perm [2,3,0,1]
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false);   // row_half_mirror
+    if ((lane & 7) == (i & 7)) out = v;
+    if ((i + 1) % kRound == 0) {
+      const int x = 8 * ((lane & 7) + i + 1 - kRound) + (lane >> 3);
+      if ((lane & 7) < kRound && x < words32) {
+        row_small[x] = out;
+        row_big[x] = ~out & columns(x);
+      }
+    }
+  }
+  if (lane == 0) {
+    const float wt = a.wtab[s];
+    a.w[o] = wt;
+    a.w[o + 1] = wt;
+    a.sz[o] = s;
+    a.sz[o + 1] = n - s;
+  }
+}
+
+// THREADS: 256 where every pair comes here (short rows with enumerated classes), 1024 for the pairs that the one-pass kernel hands on: those are a
 // few per compute unit or fewer, so that the time is that of one row (400,013 players, 20,000 pairs, 60 of them handed
 // on: 368 -> 171 us)
 template <int THREADS>
@@ -709,6 +842,14 @@ int ds_sample_launch(ds_ctx* ctx, const ds_plan& plan, uint64_t seed, uint32_t t
       const int64_t rblocks = blocks < (int64_t)ctx->num_cus * 4 ? blocks : (int64_t)ctx->num_cus * 4;
       if (a.window_cap > 4096) a.window_cap = 4096;   // (the multi-pass kernel holds more static LDS)
       hipLaunchKernelGGL(sample_pairs_kernel<1024>, dim3((unsigned)rblocks), dim3(1024), (size_t)a.window_cap * 8, ctx->stream, a);
+    } else if (plan.n < kWaveMax && plan.enum_upto == 0 && ctx->tuning.sampler_window == 0) {
+      static_assert(kWaveMax <= 256 * 16, "one instance per number of calls");
+      void (*const kern)(SampleArgs) = plan.n <= 256    ? sample_pairs_wave_kernel<1>
+                                       : plan.n <= 512  ? sample_pairs_wave_kernel<2>
+                                       : plan.n <= 1024 ? sample_pairs_wave_kernel<4>
+                                       : plan.n <= 2048 ? sample_pairs_wave_kernel<8>
+                                                        : sample_pairs_wave_kernel<16>;
+      hipLaunchKernelGGL(kern, dim3((unsigned)((pairs + kWavePairs - 1) / kWavePairs)), dim3(64 * kWavePairs), 0, ctx->stream, a);
     } else {
       if (a.window_cap > 4096) a.window_cap = 4096;
       hipLaunchKernelGGL(sample_pairs_kernel<256>, dim3((unsigned)blocks), dim3(256), (size_t)a.window_cap * 8, ctx->stream, a);

@@ -27,6 +27,9 @@ def ctx_tiny():
     (255, 777, 1, 1), (256, 778, 1, 1), (257, 4, 1, 1),
     (1000, 20000, 22668002, 7965), (5000, 3000, 9, 10), (40000, 600, 13, 77),
     (4096, 500, 21, 3), (4099, 700, 23, 4), (6241, 9000, 25, 5),   # the one-pass kernel (4,096 players and more)
+    # a wave per pair below that: the most columns of each instance and one more, a workgroup that is not full
+    (511, 600, 2, 1), (512, 602, 3, 1), (513, 604, 4, 1), (1024, 700, 5, 1), (1025, 702, 6, 1), (2048, 900, 7, 1), (2049, 902, 8, 1),
+    (4095, 2002, 9, 1), (26, 6, 10, 1),
 ])
 def test_sampler_bit_exact(ctx_tiny, n, ns, seed, tag):
     ctx, _ = ctx_tiny
