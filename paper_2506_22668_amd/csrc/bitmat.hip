@@ -243,16 +243,10 @@ constexpr int kMmWaves = 4;                          // waves per workgroup
 constexpr int kMmThreads = 64 * kMmWaves;
 constexpr int kMmWaveRows = 16 * kMmTiles;
 constexpr int kMmRows = kMmWaveRows * kMmWaves;      // rows per workgroup
-constexpr int kMmChunk = 1024;                       // columns per step
 constexpr int kMmHalves = kMmChunk / 512;            // 64-byte pieces of a row per chunk
-constexpr int kMmDigits = 14;                        // base 16
-constexpr int kMmPlanes = kMmDigits + 1;             // and the plane of ones
 constexpr int kMmSums = 8;                           // sums of a row in LDS: seven base-256 digits, the count
 constexpr int kMmSumBytes = 16;                      // and in memory: hi, lo
 constexpr int kMmSumPitch = kMmSums + 1;
-constexpr int kMmOperand = 24;                       // bytes of a lane's B operand: 32 elements of six bits
-constexpr int kMmPlaneBytes = kMmChunk * 6 / 8;      // of a chunk: [512 columns][lane group of 128][j] operands
-constexpr int kMmChunkBytes = kMmPlanes * kMmPlaneBytes;
 // LDS image of a chunk: the four operands of a lane group in 128 bytes, planes 8 bytes further, so that the 32 lanes of half a
 // wave read 8 bytes each from all 64 banks
 constexpr int kMmGroupPitch = 128;
@@ -267,69 +261,19 @@ __global__ __launch_bounds__(256) void absmax_kernel(const double* x, int64_t n,
     const unsigned long long b = (unsigned long long)__double_as_longlong(x[i]) & 0x7fffffffffffffffull;
     m = b > m ? b : m;
   }
-  ds_block_max_256(m, wm);
+  ds_block_max<256>(m, wm);
   if (threadIdx.x == 0) max_parts[blockIdx.x] = m;
 }
 
-// The fixed-point form of a vector: scal[0] = the power of two that turns integer results back into the scale of x
-// (NaN if the vector holds a non-finite value: the products are then NaN everywhere). max |x| is the largest of the
-// `parts` partial maxima, which every workgroup goes through itself: with one atomic per workgroup on a single slot
-// instead, the kernel that wrote the vector spent 8 us on a thousand atomics. Two roles per thread:
-//  * digit planes of xp[0..n) (chunks > 0): one thread per half operand, 16 columns: 96 bits of every plane;
-//  * q64[i] = round(xq[i] * 2^f) for i < qlen (the index-tile products read these): four entries per thread.
-__global__ __launch_bounds__(256) void quantize_kernel(const double* xp, int64_t n, int64_t chunks, const unsigned long long* max_parts,
-                                                       int parts, int8_t* D, double* scal, const double* xq, int64_t qlen,
-                                                       long long* q64) {
-  __shared__ unsigned long long wm[4];
+// The digits of a vector whose game has no sparse rows (else tile_spmv_kernel makes them on the side): one thread per half operand.
+__global__ __launch_bounds__(256) void quantize_kernel(const double* x, int64_t n, int64_t chunks, const unsigned long long* max_parts,
+                                                       int parts, int8_t* D, double* scal) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  // the columns of half operand id: (chunk, 128 columns, j, half); what does not wait for the maximum is requested first
-  constexpr int kHalf = 16;
-  const bool planes = id < chunks * (kMmChunk / kHalf);
-  const int64_t col0 = (id >> 3) * 128 + ((id & 1) << 6) + ((id >> 1) & 3);
-  double xv[kHalf];
-  if (planes) {
-#pragma unroll
-    for (int i = 0; i < kHalf; ++i) {
-      const int64_t col = col0 + 4 * i;
-      xv[i] = xp[col < n ? col : n - 1];
-    }
-  }
-  unsigned long long m = 0;
-  for (int i = threadIdx.x; i < parts; i += 256) m = max_parts[i] > m ? max_parts[i] : m;
-  ds_block_max_256(m, wm);
-  const double mx = __longlong_as_double((long long)m);
-  const bool finite = mx < __longlong_as_double(0x7ff0000000000000ll);
-  int e = 0;
-  if (finite && mx > 0.0) frexp(mx, &e);   // mx < 2^e
-  const int f = 54 - e;
-  if (id == 0) scal[0] = finite ? ldexp(1.0, -f) : __longlong_as_double(0x7ff8000000000000ll);
-  const int64_t pos0 = id * 4;
-  if (pos0 < qlen) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (pos0 + i < qlen) q64[pos0 + i] = finite ? __double2ll_rn(ldexp(xq[pos0 + i], f)) : 0ll;
-  }
-  if (!planes) return;
-  unsigned long long q[kHalf];
-#pragma unroll
-  for (int i = 0; i < kHalf; ++i)
-    q[i] = col0 + 4 * i < n ? (unsigned long long)((finite ? __double2ll_rn(ldexp(xv[i], f)) : 0ll) + (1ll << 54)) : 0ull;
-  // (columns 4 i, i < 8, are word 0 (or 2) of the operand's four, the others word 1 (or 3): both 32 columns wide)
-  uint32_t* const out = (uint32_t*)(D + (id >> 6) * kMmChunkBytes + ((id >> 3) & 7) * (4 * kMmOperand) + ((id >> 1) & 3) * kMmOperand +
-                                    (id & 1) * (kMmOperand / 2));
-#pragma unroll
-  for (int d = 0; d < kMmPlanes; ++d) {
-    uint32_t w[3] = {0u, 0u, 0u};
-#pragma unroll
-    for (int i = 0; i < kHalf; ++i) {
-      const uint32_t digit = d < kMmDigits ? (uint32_t)(q[i] >> (4 * d)) & 15u : (col0 + 4 * i < n ? 1u : 0u);
-      const int at = 6 * i, sh = at & 31;
-      w[at >> 5] |= digit << sh;
-      if (sh > 28) w[(at >> 5) + 1] |= digit >> (32 - sh);
-    }
-#pragma unroll
-    for (int u = 0; u < 3; ++u) out[d * (kMmPlaneBytes / 4) + u] = w[u];
-  }
+  double xv[kMmHalf];
+  if (id < chunks * kMmHalves1024) ds_mm_half_operand(x, n, id, xv);   // (does not wait for the maximum)
+  const ds_fixed_point fp = ds_fixed_point_of<256>(max_parts, parts);
+  if (id == 0) scal[0] = fp.back();
+  if (id < chunks * kMmHalves1024) ds_mm_store_digits(xv, n, id, fp, D);
 }
 
 // A workgroup's units (a chunk of a row group each) are consecutive, row group by row group: cut evenly (even_units = their
@@ -654,13 +598,10 @@ int ds_vec_absmax(ds_ctx* ctx, const double* x, int64_t len, unsigned long long*
   return DS_OK;
 }
 
-int ds_vec_quantize(ds_ctx* ctx, const unsigned long long* max_parts, int parts, const ds_mm_plan* planes, const double* x_planes,
-                    const double* x_q, int64_t qlen, long long* q64, double* scal) {
-  const bool with_planes = planes && planes->rows > 0;
-  const int64_t chunks = with_planes ? planes->n_chunks : 0;
-  const int64_t halves = chunks * (kMmChunk / 16), quads = (qlen + 3) / 4, threads = halves > quads ? halves : quads;
-  hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)(threads > 0 ? (threads + 255) / 256 : 1)), dim3(256), 0, ctx->stream, x_planes,
-                     with_planes ? planes->cols : 0, chunks, max_parts, parts, with_planes ? planes->D : nullptr, scal, x_q, qlen, q64);
+int ds_mm_quantize(ds_ctx* ctx, const ds_mm_plan* p, const double* x, const unsigned long long* max_parts, int parts, double* scal) {
+  const int64_t threads = p->n_chunks * kMmHalves1024;
+  hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, ctx->stream, x, p->cols, p->n_chunks, max_parts,
+                     parts, p->D, scal);
   DS_HIP(ctx, hipGetLastError());
   return DS_OK;
 }

@@ -109,8 +109,7 @@ __device__ __forceinline__ double adjoint_result(const Vecs& a, double sc, int64
 // the workgroup's part of max |x| into max_parts[blockIdx.x] (every thread of the workgroup must call this)
 __device__ __forceinline__ void publish_absmax(unsigned long long m, unsigned long long* max_parts) {
   __shared__ unsigned long long wm[kThreads / 64];
-  static_assert(kThreads == 256, "ds_block_max_256");
-  ds_block_max_256(m, wm);
+  ds_block_max<kThreads>(m, wm);
   if (threadIdx.x == 0) max_parts[blockIdx.x] = m;
   __syncthreads();
 }
@@ -703,9 +702,9 @@ size_t ds_cgls_arena_bytes(int64_t n, int64_t k) {
   // is at most half of it, and the index lists of the sparse rows (needed while their tiles are built) and the tile
   // entries take 4 bytes per set bit of rows with at most n/32 of them each. Plus offsets, the scratch of the two
   // matrix-core products (digit planes, per-group digit sums) and of the tile products (per-group partial vectors,
-  // tile counters, the vectors as 64-bit integers).
+  // tile counters).
   const size_t tile_scratch = ds_align((size_t)(2 * (k / 32768) + 160) * n * 8) + ds_align((size_t)32 * k * 8) +
-                              ds_align((size_t)(k / 8192 + 160) * (n / 8192 + 2) * 8) + ds_align((size_t)(n + k) * 8);
+                              ds_align((size_t)(k / 8192 + 160) * (n / 8192 + 2) * 8);
   const size_t hybrid = 3 * ds_align((size_t)n * KW * 8) + 4 * ds_align((n + 2) * 4) + 2 * ds_align((k + 2) * 4) +
                         ds_align(112 * (size_t)(n > k ? n : k)) + ((size_t)80 << 20) + tile_scratch +
                         4 * ds_scan_arena_bytes(n > k ? n + 1 : k + 1);
@@ -789,7 +788,6 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
   uint64_t *Zt = nullptr, *Ztd = nullptr;
   ds_mm_plan mm_f = {}, mm_a = {};   // dense rows: forward (Rd x n) and adjoint (n x Rd) products
   ds_tile_plan tiles = {};           // sparse rows: one entry list for both products
-  long long *q64u = nullptr, *q64h = nullptr;   // the vectors of the two products as integers (for the sparse rows)
   double *scal_f = nullptr, *scal_a = nullptr;  // [0] scale of the forward / adjoint product's integers
   if (paired && n >= kHybridMinPlayers && n < ((int64_t)1 << 28)) {   // (the matrix-core product addresses rows with 32 bits)
     int32_t* cnt = (int32_t*)ds_arena_alloc(ctx, (R + 1) * 4);
@@ -819,11 +817,9 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
       void* ws_f = ds_arena_alloc(ctx, ds_bit_spmv_mm_ws_bytes(ctx, Rd, n));
       void* ws_a = ds_arena_alloc(ctx, ds_bit_spmv_mm_ws_bytes(ctx, n, Rd));
       void* ws_t = ds_arena_alloc(ctx, ds_tile_ws_bytes(ctx, Rs, n, nnz_s));
-      q64u = (long long*)ds_arena_alloc(ctx, n * 8);
-      q64h = (long long*)ds_arena_alloc(ctx, (Rs + 1) * 8);
       scal_f = (double*)ds_arena_alloc(ctx, 256 + 2 * kRed * 8);   // scalars, then max_u and max_h
       int32_t* csr_idx = (int32_t*)ds_arena_alloc(ctx, (nnz_s + 1) * 4);   // (index lists; the tile build keeps the memory)
-      if (!Ztd || !ws_f || !ws_a || !ws_t || !q64u || !q64h || !scal_f || !csr_idx) return ds_fail(ctx, DS_EINTERNAL, "cgls: arena exhausted");
+      if (!Ztd || !ws_f || !ws_a || !ws_t || !scal_f || !csr_idx) return ds_fail(ctx, DS_EINTERNAL, "cgls: arena exhausted");
       scal_a = scal_f + 16;
       DS_HIP(ctx, hipMemsetAsync(scal_f, 0, 256, st));
       if (Rd > 0) {
@@ -843,7 +839,7 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
     if (!Zt) return ds_fail(ctx, DS_EINTERNAL, "cgls: arena exhausted");
     DS_TRY(ds_bit_transpose(ctx, Z, R, n, W, 0, paired ? 2 : 1, Zt));
   }
-  // Hybrid layout: the vector is brought into fixed point once per product; the sparse rows' tiles and the dense
+  // Hybrid layout: the vector is brought into fixed point by the tile product; the sparse rows' tiles and the dense
   // rows' bitmap are multiplied one after the other (side by side on two streams they only competed for memory
   // bandwidth and the iteration took 8 % longer), the dense product adding the sparse result in the adjoint.
   const unsigned red_n = nblocks(n, kThreads) < (unsigned)kRed ? nblocks(n, kThreads) : (unsigned)kRed;
@@ -855,16 +851,14 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
   auto forward = [&](const double* u, double* d, int with_absmax) -> int {  // d = (rows) . u
     if (!hybrid) return ds_bit_spmv(ctx, Z, R, n, W, 0, paired ? 2 : 1, u, d);
     if (with_absmax) DS_TRY(ds_vec_absmax(ctx, u, n, a.max_u, (int)red_n));
-    DS_TRY(ds_vec_quantize(ctx, a.max_u, (int)red_n, &mm_f, u, u, Rs > 0 ? n : 0, q64u, scal_f));
-    if (Rs > 0) DS_TRY(ds_tile_spmv(ctx, &tiles, 0, q64u, scal_f, d));
+    DS_TRY(ds_tile_spmv(ctx, &tiles, 0, u, a.max_u, (int)red_n, &mm_f, u, scal_f, d));
     if (Rd > 0) DS_TRY(ds_bit_spmv_mm_product(ctx, &mm_f, Z, W, 2 * Rs, 2, scal_f, nullptr, d ? d + Rs : nullptr));
     return DS_OK;
   };
   auto adjoint = [&](const double* h, double* sv, int with_absmax) -> int {  // s = (rows)^T . h
     if (!hybrid) return ds_bit_spmv(ctx, Zt, n, R, RW, 0, 1, h, sv);
     if (with_absmax) DS_TRY(ds_vec_absmax(ctx, h, R, a.max_h, (int)red_r));
-    DS_TRY(ds_vec_quantize(ctx, a.max_h, (int)red_r, &mm_a, h + Rs, h, Rs, q64h, scal_a));
-    if (Rs > 0) DS_TRY(ds_tile_spmv(ctx, &tiles, 1, q64h, scal_a, sv));
+    DS_TRY(ds_tile_spmv(ctx, &tiles, 1, h, a.max_h, (int)red_r, &mm_a, h + Rs, scal_a, sv));
     if (Rd > 0) DS_TRY(ds_bit_spmv_mm_product(ctx, &mm_a, Ztd, RdS, 0, 1, scal_a, sv && Rs > 0 ? sv : nullptr, sv));
     return DS_OK;
   };

@@ -19,10 +19,10 @@ int ds_bit_transpose_blocks(ds_ctx* ctx, const uint64_t* in, int64_t rows, int64
 int ds_bit_spmv(ds_ctx* ctx, const uint64_t* B, int64_t rows, int64_t cols, int64_t stride, int64_t row_first,
                 int64_t row_step, const double* x, double* out);
 // ---- products of the CGLS matrix of a large game in fixed point (exact integer sums) ----
-// Every product starts with ds_vec_quantize: from the partial maxima of |x| (bit patterns, max_parts[0..parts); left by
-// the kernel that wrote x, or by ds_vec_absmax) scal[0] becomes the power of two that scales integer results back, and
-// the vector is written as digit planes for the matrix-core product (x_planes[0..planes->cols), if `planes` has rows)
-// and/or as 64-bit integers q64[i] = round(x_q[i] * 2^f), i < qlen (if qlen > 0).
+// The fixed point of a vector is 2^-54 of its largest entry, from the partial maxima of |x| (bit patterns, max_parts[0..parts), at most
+// 1,024; left by the kernel that wrote x, or by ds_vec_absmax); scal[0] becomes the power of two that scales integer
+// results back. The sparse rows' product comes first and leaves the digits for the dense rows' product on the way; without sparse
+// rows ds_mm_quantize does.
 //
 // Dense rows on the matrix cores (x split into digits); out = (addend or 0) + result. A plan fixes
 // the launch shape and the scratch of one (rows, cols) shape: ds_bit_spmv_mm_ws_bytes bytes at `ws`, which
@@ -36,8 +36,7 @@ struct ds_mm_plan {
 size_t ds_bit_spmv_mm_ws_bytes(const ds_ctx* ctx, int64_t rows, int64_t cols);
 int ds_bit_spmv_mm_prepare(ds_ctx* ctx, int64_t rows, int64_t cols, void* ws, ds_mm_plan* plan);
 int ds_vec_absmax(ds_ctx* ctx, const double* x, int64_t len, unsigned long long* max_parts, int parts);
-int ds_vec_quantize(ds_ctx* ctx, const unsigned long long* max_parts, int parts, const ds_mm_plan* planes, const double* x_planes,
-                    const double* x_q, int64_t qlen, long long* q64, double* scal);
+int ds_mm_quantize(ds_ctx* ctx, const ds_mm_plan* plan, const double* x, const unsigned long long* max_parts, int parts, double* scal);
 // out == nullptr: the per-group digit sums are left for the caller's own kernel to add up (ds_mm_sum below)
 int ds_bit_spmv_mm_product(ds_ctx* ctx, const ds_mm_plan* plan, const uint64_t* B, int64_t stride, int64_t row_first,
                            int64_t row_step, const double* scal, const double* addend, double* out);
@@ -57,10 +56,12 @@ struct ds_tile_plan {
 size_t ds_tile_ws_bytes(const ds_ctx* ctx, int64_t rows, int64_t cols, int64_t nnz);
 int ds_tile_build(ds_ctx* ctx, int64_t rows, int64_t cols, int64_t nnz, int64_t max_row_size, const int32_t* off,
                   int32_t* idx, void* ws, ds_tile_plan* plan);
-// forward: out[r] = sum of x[c] over the entries of row r (q64 = the 64-bit form of x, cols entries);
-// adjoint: out[c] = sum of x[r] over the entries of column c (q64 of rows entries)
+// forward: out[r] = sum of x[c] over the entries of row r (x: cols entries);
+// adjoint: out[c] = sum of x[r] over the entries of column c (x: rows entries)
+// planes (or nullptr): the dense rows' plan, whose digits of x_planes are made on the way
 // out == nullptr: the per-group partial vectors are left for the caller's own kernel to add up (ds_tile_sum below)
-int ds_tile_spmv(ds_ctx* ctx, const ds_tile_plan* plan, int adjoint, const long long* q64, const double* scal, double* out);
+int ds_tile_spmv(ds_ctx* ctx, const ds_tile_plan* plan, int adjoint, const double* x, const unsigned long long* max_parts, int parts,
+                 const ds_mm_plan* planes, const double* x_planes, double* scal, double* out);
 
 // Where the integer results of one product lie before they are added up, for kernels that consume them directly
 // (groups == 0: that part of the matrix is empty).
@@ -85,6 +86,82 @@ static inline ds_fixed_view ds_fixed_view_of(const ds_tile_plan* t, const ds_mm_
   return v;
 }
 #ifdef __HIPCC__
+// ---- the vectors of the products in fixed point ----
+// the largest m of a workgroup, in every thread; wm: a word of LDS per wave, of the call's own
+template <int THREADS>
+__device__ __forceinline__ void ds_block_max(unsigned long long& m, unsigned long long* wm) {
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long t = __shfl_xor(m, o, 64);
+    m = t > m ? t : m;
+  }
+  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < THREADS / 64; ++i) m = wm[i] > m ? wm[i] : m;
+}
+struct ds_fixed_point {
+  int f;         // x 2^f is below 2^54 in magnitude
+  bool finite;   // a vector with a non-finite entry: zeros, and NaN for the way back (the products are NaN everywhere)
+  __device__ __forceinline__ long long of(double x) const { return finite ? __double2ll_rn(ldexp(x, f)) : 0ll; }
+  __device__ __forceinline__ double back() const { return finite ? ldexp(1.0, -f) : __longlong_as_double(0x7ff8000000000000ll); }
+};
+// Every workgroup goes through the partial maxima itself: with one atomic per workgroup on a single slot instead, the
+// kernel that wrote the vector spent 8 us on a thousand atomics.
+template <int THREADS>
+__device__ __forceinline__ ds_fixed_point ds_fixed_point_of(const unsigned long long* max_parts, int parts) {
+  __shared__ unsigned long long wm[THREADS / 64];
+  unsigned long long m = 0;
+  for (int i = threadIdx.x; i < parts; i += THREADS) m = max_parts[i] > m ? max_parts[i] : m;
+  ds_block_max<THREADS>(m, wm);
+  const double mx = __longlong_as_double((long long)m);
+  ds_fixed_point fp;
+  fp.finite = mx < __longlong_as_double(0x7ff0000000000000ll);
+  int e = 0;
+  if (fp.finite && mx > 0.0) frexp(mx, &e);   // mx < 2^e
+  fp.f = 54 - e;
+  return fp;
+}
+// The digits that the dense rows' product reads (described there). A half operand, 16 columns, is a thread's share: 96 bits of every
+// plane. Half operand id: (chunk, 128 columns, j, half); its columns are 4 apart.
+constexpr int kMmChunk = 1024;                       // columns per step of the product
+constexpr int kMmDigits = 14;                        // base 16
+constexpr int kMmPlanes = kMmDigits + 1;             // and the plane of ones
+constexpr int kMmOperand = 24;                       // bytes of a lane's B operand: 32 elements of six bits
+constexpr int kMmPlaneBytes = kMmChunk * 6 / 8;      // of a chunk: [512 columns][lane group of 128][j] operands
+constexpr int kMmChunkBytes = kMmPlanes * kMmPlaneBytes;
+constexpr int kMmHalf = 16;
+constexpr int kMmHalves1024 = kMmChunk / kMmHalf;    // of a chunk
+__device__ __forceinline__ int64_t ds_mm_half_column(int64_t id) { return (id >> 3) * 128 + ((id & 1) << 6) + ((id >> 1) & 3); }
+__device__ __forceinline__ void ds_mm_half_operand(const double* x, int64_t n, int64_t id, double (&xv)[kMmHalf]) {
+  const int64_t col0 = ds_mm_half_column(id);
+#pragma unroll
+  for (int i = 0; i < kMmHalf; ++i) {
+    const int64_t col = col0 + 4 * i;
+    xv[i] = x[col < n ? col : n - 1];
+  }
+}
+__device__ __forceinline__ void ds_mm_store_digits(const double (&xv)[kMmHalf], int64_t n, int64_t id, const ds_fixed_point& fp, int8_t* D) {
+  const int64_t col0 = ds_mm_half_column(id);
+  unsigned long long q[kMmHalf];
+#pragma unroll
+  for (int i = 0; i < kMmHalf; ++i) q[i] = col0 + 4 * i < n ? (unsigned long long)(fp.of(xv[i]) + (1ll << 54)) : 0ull;
+  uint32_t* const out = (uint32_t*)(D + (id >> 6) * kMmChunkBytes + ((id >> 3) & 7) * (4 * kMmOperand) + ((id >> 1) & 3) * kMmOperand +
+                                    (id & 1) * (kMmOperand / 2));
+#pragma unroll
+  for (int d = 0; d < kMmPlanes; ++d) {
+    uint32_t w[3] = {0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < kMmHalf; ++i) {
+      const uint32_t digit = d < kMmDigits ? (uint32_t)(q[i] >> (4 * d)) & 15u : (col0 + 4 * i < n ? 1u : 0u);
+      const int at = 6 * i, sh = at & 31;
+      w[at >> 5] |= digit << sh;
+      if (sh > 28) w[(at >> 5) + 1] |= digit >> (32 - sh);
+    }
+#pragma unroll
+    for (int u = 0; u < 3; ++u) out[d * (kMmPlaneBytes / 4) + u] = w[u];
+  }
+}
+
 // The sums over the groups are exact integers, so they may be split over T lanes in any way: lane `sub` (0 <= sub < T)
 // adds the groups sub, sub + T, ... (four loads in flight), the lanes' integers are added, and one rounding ends it.
 // tile product, entry i: the groups as two 32-bit halves, so that the total may exceed 63 bits
@@ -186,16 +263,4 @@ __device__ __forceinline__ double ds_wave_sum(double a) {
   DS_DPP_ADD(0xb1);    // quad_perm [1,0,3,2]
 #undef DS_DPP_ADD
   return a;
-}
-
-// the largest m of a workgroup of 256 threads, in every thread; wm: four words of LDS of the call's own
-__device__ __forceinline__ void ds_block_max_256(unsigned long long& m, unsigned long long* wm) {
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long t = __shfl_xor(m, o, 64);
-    m = t > m ? t : m;
-  }
-  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 4; ++i) m = wm[i] > m ? wm[i] : m;
 }

@@ -163,8 +163,15 @@ struct TileArgs {
   int32_t nrb, ncb, cpg;
   const int32_t *rb_start, *ga_start, *tile_off;
   const uint32_t* ent;
-  const long long* q;  // the source vector as integers (forward: cols entries, adjoint: rows entries)
-  int sh;              // low bits dropped from them (rounded)
+  const double* x;     // the source vector (forward: cols entries, adjoint: rows entries)
+  int sh;              // low bits dropped from its integers (rounded)
+  const unsigned long long* max_parts;   // partial maxima of the whole vector, of which x is a part or all
+  int parts;
+  double* scal;
+  int nx, plane_wgs;   // tiles in x direction; workgroups in front of the tiles' that make the dense rows' digits
+  const double* x_planes;
+  int64_t cols_planes, chunks;
+  int8_t* D;
   long long* partial;  // forward: [chunk groups][rows]; adjoint: [row-block groups][cols]
 };
 
@@ -176,12 +183,24 @@ __global__ __launch_bounds__(kTileThreads) void tile_spmv_kernel(TileArgs a) {
   long long* acc = tile_smem;            // [kTileSpan] target piece
   long long* src = tile_smem + kTileSpan;  // [kTileSpan] source piece
   const int tid = threadIdx.x;
-  for (int i = tid; i < kTileSpan; i += kTileThreads) acc[i] = 0;
+  // The vector becomes integers where it is staged (the conversion hides behind the loads and the LDS atomics: 12 us either way at
+  // 99,981 players), and the first workgroups make the digits of the dense rows' product. A kernel in front of each product that
+  // wrote both forms down cost 6.5 us twice of an iteration's 126, now 113; it and its two vectors are gone.
+  const int64_t half = (int64_t)blockIdx.x * kTileThreads + tid;
+  const bool planes = (int)blockIdx.x < a.plane_wgs && half < a.chunks * kMmHalves1024;
+  double xv[kMmHalf];
+  if (planes) ds_mm_half_operand(a.x_planes, a.cols_planes, half, xv);
+  else if ((int)blockIdx.x >= a.plane_wgs)
+    for (int i = tid; i < kTileSpan; i += kTileThreads) acc[i] = 0;
+  const ds_fixed_point fp = ds_fixed_point_of<kTileThreads>(a.max_parts, a.parts);
+  if (half == 0) a.scal[0] = fp.back();
+  if (planes) ds_mm_store_digits(xv, a.cols_planes, half, fp, a.D);
+  if ((int)blockIdx.x < a.plane_wgs) return;
   __syncthreads();
   // forward: x = row block, y = chunk group, walks chunks; adjoint: x = chunk, y = row-block group, walks row blocks
-  const int fixed = blockIdx.x;
-  const int w_begin = ADJ ? a.ga_start[blockIdx.y] : (int)blockIdx.y * a.cpg;
-  int w_end = ADJ ? a.ga_start[blockIdx.y + 1] : w_begin + a.cpg;
+  const int tile = (int)blockIdx.x - a.plane_wgs, group = tile / a.nx, fixed = tile - group * a.nx;
+  const int w_begin = ADJ ? a.ga_start[group] : group * a.cpg;
+  int w_end = ADJ ? a.ga_start[group + 1] : w_begin + a.cpg;
   if (!ADJ && w_end > a.ncb) w_end = a.ncb;
   bool staged = false;
   for (int w = w_begin; w < w_end; ++w) {
@@ -192,22 +211,22 @@ __global__ __launch_bounds__(kTileThreads) void tile_spmv_kernel(TileArgs a) {
     // source piece: forward = columns of the chunk, adjoint = rows of the block
     const int64_t s0 = ADJ ? (int64_t)a.rb_start[rb] : (int64_t)cb * kTileSpan;
     const int64_t s_end = ADJ ? (int64_t)a.rb_start[rb + 1] : (s0 + kTileSpan < a.cols ? s0 + kTileSpan : a.cols);
-    const long long* qs = a.q + s0;
+    const double* xs = a.x + s0;
     const bool direct = e1 - e0 < kTileDirect;
     if (!direct) {
       if (staged) __syncthreads();  // the piece staged before is no longer read
       const int len = (int)(s_end - s0);
       // (all of a thread's loads in flight: a group of short rows stages several pieces one behind the other)
-      long long piece[kTileSpan / kTileThreads];
+      double piece[kTileSpan / kTileThreads];
 #pragma unroll
       for (int u = 0; u < kTileSpan / kTileThreads; ++u) {
         const int i = tid + u * kTileThreads;
-        piece[u] = qs[i < len ? i : len - 1];
+        piece[u] = xs[i < len ? i : len - 1];
       }
 #pragma unroll
       for (int u = 0; u < kTileSpan / kTileThreads; ++u) {
         const int i = tid + u * kTileThreads;
-        if (i < len) src[i] = drop_bits(piece[u], a.sh);
+        if (i < len) src[i] = drop_bits(fp.of(piece[u]), a.sh);
       }
       __syncthreads();
       staged = true;
@@ -221,7 +240,7 @@ __global__ __launch_bounds__(kTileThreads) void tile_spmv_kernel(TileArgs a) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const uint32_t si = ADJ ? (v[u] >> kTileBits) : (v[u] & (kTileSpan - 1));
-        val[u] = direct ? drop_bits(qs[si], a.sh) : src[si];
+        val[u] = direct ? drop_bits(fp.of(xs[si]), a.sh) : src[si];
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -233,7 +252,7 @@ __global__ __launch_bounds__(kTileThreads) void tile_spmv_kernel(TileArgs a) {
       const uint32_t v = a.ent[e];
       const uint32_t si = ADJ ? (v >> kTileBits) : (v & (kTileSpan - 1));
       const uint32_t ti = ADJ ? (v & (kTileSpan - 1)) : (v >> kTileBits);
-      const long long val = direct ? drop_bits(qs[si], a.sh) : src[si];
+      const long long val = direct ? drop_bits(fp.of(xs[si]), a.sh) : src[si];
       atomicAdd((unsigned long long*)&acc[ti], (unsigned long long)val);
     }
   }
@@ -241,7 +260,7 @@ __global__ __launch_bounds__(kTileThreads) void tile_spmv_kernel(TileArgs a) {
   const int64_t t0 = ADJ ? (int64_t)fixed * kTileSpan : (int64_t)a.rb_start[fixed];
   const int64_t t_end = ADJ ? (t0 + kTileSpan < a.cols ? t0 + kTileSpan : a.cols) : (int64_t)a.rb_start[fixed + 1];
   const int64_t span = ADJ ? a.cols : a.rows;
-  long long* out = a.partial + (int64_t)blockIdx.y * span + t0;
+  long long* out = a.partial + (int64_t)group * span + t0;
   for (int i = tid; i < (int)(t_end - t0); i += kTileThreads) out[i] = acc[i];
 }
 
@@ -378,11 +397,12 @@ int ds_tile_build(ds_ctx* ctx, int64_t rows, int64_t cols, int64_t nnz, int64_t 
   return DS_OK;
 }
 
-int ds_tile_spmv(ds_ctx* ctx, const ds_tile_plan* p, int adjoint, const long long* q64, const double* scal, double* out) {
-  if (p->rows <= 0) return DS_OK;
-  if (p->nnz <= 0) {  // rows without a single entry (the empty coalition of pair 0): a zero result
-    if (out) DS_HIP(ctx, hipMemsetAsync(out, 0, (size_t)(adjoint ? p->cols : p->rows) * 8, ctx->stream));
-    return DS_OK;
+int ds_tile_spmv(ds_ctx* ctx, const ds_tile_plan* p, int adjoint, const double* x, const unsigned long long* max_parts, int parts,
+                 const ds_mm_plan* planes, const double* x_planes, double* scal, double* out) {
+  const bool dense = planes && planes->rows > 0;
+  if (p->rows <= 0 || p->nnz <= 0) {  // no sparse rows, or none with an entry (the empty coalition of pair 0): a zero result
+    if (p->rows > 0 && out) DS_HIP(ctx, hipMemsetAsync(out, 0, (size_t)(adjoint ? p->cols : p->rows) * 8, ctx->stream));
+    return dense ? ds_mm_quantize(ctx, planes, x_planes, max_parts, parts, scal) : DS_OK;
   }
   TileArgs a;
   a.rows = p->rows;
@@ -394,18 +414,28 @@ int ds_tile_spmv(ds_ctx* ctx, const ds_tile_plan* p, int adjoint, const long lon
   a.ga_start = p->ga_start;
   a.tile_off = p->tile_off;
   a.ent = p->ent;
-  a.q = q64;
+  a.x = x;
+  a.max_parts = max_parts;
+  a.parts = parts;
+  a.scal = scal;
+  a.x_planes = x_planes;
+  a.cols_planes = dense ? planes->cols : 0;
+  a.chunks = dense ? planes->n_chunks : 0;
+  a.D = dense ? planes->D : nullptr;
+  a.plane_wgs = (int)((a.chunks * kMmHalves1024 + kTileThreads - 1) / kTileThreads);
   a.partial = p->partial;
   const int lds = 2 * kTileSpan * 8;
   if (!adjoint) {
     a.sh = p->sh_f;
-    hipLaunchKernelGGL(tile_spmv_kernel<false>, dim3((unsigned)p->nrb, (unsigned)p->gf), dim3(kTileThreads), lds, ctx->stream, a);
+    a.nx = p->nrb;
+    hipLaunchKernelGGL(tile_spmv_kernel<false>, dim3((unsigned)(a.plane_wgs + p->nrb * p->gf)), dim3(kTileThreads), lds, ctx->stream, a);
     if (out)
       hipLaunchKernelGGL(tile_reduce_kernel, dim3((unsigned)((p->rows + 255) / 256)), dim3(256), 0, ctx->stream, p->partial,
                          p->rows, (int)p->gf, scal, p->sh_f, out);
   } else {
     a.sh = p->sh_a;
-    hipLaunchKernelGGL(tile_spmv_kernel<true>, dim3((unsigned)p->ncb, (unsigned)p->nga), dim3(kTileThreads), lds, ctx->stream, a);
+    a.nx = p->ncb;
+    hipLaunchKernelGGL(tile_spmv_kernel<true>, dim3((unsigned)(a.plane_wgs + p->ncb * p->nga)), dim3(kTileThreads), lds, ctx->stream, a);
     if (out)
       hipLaunchKernelGGL(tile_reduce_kernel, dim3((unsigned)((p->cols + 255) / 256)), dim3(256), 0, ctx->stream, p->partial,
                          p->cols, (int)p->nga, scal, p->sh_a, out);
