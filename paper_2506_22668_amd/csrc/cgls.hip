@@ -205,13 +205,9 @@ __global__ void fin_u_kernel(Vecs a, int nparts) {
 // the state that the result is made of (x, u, theta) is left alone by everything that still runs. ----
 constexpr int kPartV = 0, kPartS = 1, kPartG = 2, kPartU = 3;
 
-// all threads of the workgroup get the sum of the nparts partials of array `which`
-// (every workgroup adds them in the same order: thread t takes the partials t, t + kThreads, ..., then lanes, then waves)
-__device__ __forceinline__ double block_sum_partials(const Vecs& a, int which, int nparts) {
+// all threads of the workgroup get the sum of their values (lanes first, then waves)
+__device__ __forceinline__ double block_sum(double s) {
   __shared__ double bs[kThreads / 64];
-  const double* part = a.part + which * kRed;
-  double s = 0.0;
-  for (int i = threadIdx.x; i < nparts; i += kThreads) s += part[i];
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) bs[threadIdx.x >> 6] = s;
@@ -219,6 +215,14 @@ __device__ __forceinline__ double block_sum_partials(const Vecs& a, int which, i
   double t = bs[0];
   for (int i = 1; i < kThreads / 64; ++i) t += bs[i];
   return t;
+}
+// all threads of the workgroup get the sum of the nparts partials of array `which`
+// (every workgroup adds them in the same order: thread t takes the partials t, t + kThreads, ..., then lanes, then waves)
+__device__ __forceinline__ double block_sum_partials(const Vecs& a, int which, int nparts) {
+  const double* part = a.part + which * kRed;
+  double s = 0.0;
+  for (int i = threadIdx.x; i < nparts; i += kThreads) s += part[i];
+  return block_sum(s);
 }
 
 // v from d (after finishing sum(u) and moving gamma_new to gamma); partial |v|^2. T lanes per row (1 unless fused).
@@ -289,43 +293,75 @@ __global__ __launch_bounds__(kThreads) void loop_update_r_kernel(Vecs a, int par
   if (a.max_h) publish_absmax(hm, a.max_h);
 }
 
+// how many of n entries workgroup b of a grid of `grid` takes that stride over them, `per` to a workgroup at a time
+__device__ __forceinline__ uint32_t block_entries(uint32_t n, uint32_t per, uint32_t grid, uint32_t b) {
+  const uint32_t turn = per * grid, left = n % turn, first = per * b;
+  return n / turn * per + (left > first ? (left - first < per ? left - first : per) : 0);
+}
+
+// s; per workgroup the sum S of its entries and the sum M of their squared distances from their own mean. Together,
+// |P s|^2 = sum of M + count (S / count - mean)^2: nothing cancels, as sum(s^2) - n mean^2 would (see s_center_kernel), and there is
+// no second launch behind the mean of all. (A kernel that waited for it and wrote P s: an iteration of 113 us at 99,981 players, now 109.)
 template <int T>
 __global__ __launch_bounds__(kThreads) void loop_s_sum_kernel(Vecs a) {
-  double s1 = 0;
+  const int64_t first = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / T, step = (int64_t)gridDim.x * (kThreads / T);
+  const int sub = threadIdx.x & (T - 1);
+  double s1 = 0, v0 = 0;   // v0: the first entry, the only one of all but the largest games
   if (a.fused) {
     const double sc = a.scal_a[0];
-    const int sub = threadIdx.x & (T - 1);
-    for (int64_t j = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / T; j < a.n; j += (int64_t)gridDim.x * (kThreads / T)) {
+    for (int64_t j = first; j < a.n; j += step) {
       const double v = adjoint_result<T>(a, sc, j, sub);
       if (sub == 0) {
         a.s[j] = v;
         s1 += v;
+        if (j == first) v0 = v;
       }
     }
   } else {
-    for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < a.n; j += (int64_t)gridDim.x * kThreads) s1 += a.s[j];
+    for (int64_t j = first; j < a.n; j += step) {
+      const double v = a.s[j];
+      s1 += v;
+      if (j == first) v0 = v;
+    }
   }
-  double dummy;
-  block_reduce2(s1, 0.0, &a.part[kPartS * kRed + blockIdx.x], &dummy);
-}
-
-// s <- P s and partial |P s|^2 (two passes on purpose, see s_center_kernel)
-__global__ __launch_bounds__(kThreads) void loop_s_center_kernel(Vecs a, int parts_s) {
-  const double mean = block_sum_partials(a, kPartS, parts_s) / (double)a.n;
+  const double sum = block_sum(s1);
+  const double mean = sum / block_entries((uint32_t)a.n, kThreads / T, gridDim.x, blockIdx.x);
   double s2 = 0;
-  for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < a.n; j += (int64_t)gridDim.x * kThreads) {
-    const double v = a.s[j] - mean;
-    a.s[j] = v;
-    s2 += v * v;
+  if (sub == 0)
+    for (int64_t j = first; j < a.n; j += step) {
+      const double v = (j == first ? v0 : a.s[j]) - mean;
+      s2 += v * v;
+    }
+  s2 = block_sum(s2);
+  if (threadIdx.x == 0) {
+    a.part[kPartS * kRed + blockIdx.x] = sum;
+    a.part[kPartG * kRed + blockIdx.x] = s2;
   }
-  double dummy;
-  block_reduce2(s2, 0.0, &a.part[kPartG * kRed + blockIdx.x], &dummy);
 }
 
 // end of an iteration: gamma_new = |P s|^2, the stopping rule, and (if the iteration goes on and do_update)
-// x += theta u, u = s + beta u with the partial sums of the new u
-__global__ __launch_bounds__(kThreads) void loop_update_xu_kernel(Vecs a, int parts_g, double tol, int do_update) {
-  const double g = block_sum_partials(a, kPartG, parts_g);
+// x += theta u, u = P s + beta u with the partial sums of the new u. The partials are those of loop_s_sum_kernel, `per` entries
+// to a workgroup at a time.
+__global__ __launch_bounds__(kThreads) void loop_update_xu_kernel(Vecs a, int parts, int per, double tol, int do_update) {
+  constexpr int kMine = kRed / kThreads;
+  double ps[kMine], pm[kMine], s1 = 0;
+#pragma unroll
+  for (int i = 0; i < kMine; ++i) {
+    const int b = threadIdx.x + i * kThreads;
+    ps[i] = b < parts ? a.part[kPartS * kRed + b] : 0.0;
+    pm[i] = b < parts ? a.part[kPartG * kRed + b] : 0.0;
+    s1 += ps[i];
+  }
+  const double mean = block_sum(s1) / (double)a.n;
+  double g = 0;
+#pragma unroll
+  for (int i = 0; i < kMine; ++i) {
+    const int b = threadIdx.x + i * kThreads;
+    if (b >= parts) continue;
+    const double count = block_entries((uint32_t)a.n, per, parts, b), away = ps[i] / count - mean;
+    g += pm[i] + count * (away * away);
+  }
+  g = block_sum(g);
   if (a.scal[8] != 0.0) return;
   const double gamma = a.scal[0], gamma0 = a.scal[7];
   const double rel = sqrt(g) / sqrt(gamma0);
@@ -348,7 +384,7 @@ __global__ __launch_bounds__(kThreads) void loop_update_xu_kernel(Vecs a, int pa
   for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < a.n; j += (int64_t)gridDim.x * kThreads) {
     const double uo = a.u[j];
     a.x[j] += th * uo;
-    const double un = a.s[j] + beta * uo;
+    const double un = (a.s[j] - mean) + beta * uo;
     a.u[j] = un;
     acc += un;
     const unsigned long long b = abs_bits(un);
@@ -926,9 +962,8 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
       hipLaunchKernelGGL(loop_update_r_kernel, dim3(red_r), dim3(kThreads), 0, st, a, (int)grid_v);
       DS_TRY(adjoint(a.h, hybrid ? nullptr : a.s, 0));
       launch_s_sum();
-      hipLaunchKernelGGL(loop_s_center_kernel, dim3(red_n), dim3(kThreads), 0, st, a, (int)grid_s);
       // the last iteration allowed takes no further step: it only evaluates the stopping rule
-      hipLaunchKernelGGL(loop_update_xu_kernel, dim3(red_n), dim3(kThreads), 0, st, a, (int)red_n, tol,
+      hipLaunchKernelGGL(loop_update_xu_kernel, dim3(red_n), dim3(kThreads), 0, st, a, (int)grid_s, kThreads / lanes_s, tol,
                          launched + b + 1 < max_iter ? 1 : 0);
     }
     launched += burst;
