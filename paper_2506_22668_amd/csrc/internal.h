@@ -65,6 +65,13 @@ struct ds_pair_lists {
   int64_t total;       // entries reserved
 };
 
+constexpr int64_t kPlanKept = 1 << 20;   // size classes of the largest plan whose memory a context keeps (20 MB)
+struct ds_plan_memory {
+  std::vector<int64_t> b;
+  std::vector<float> wtab;
+  std::vector<double> c;
+};
+
 struct ds_ctx {
   int device;
   hipStream_t stream;
@@ -99,6 +106,7 @@ struct ds_ctx {
   void* cg_spare;
   size_t cg_spare_bytes;
   // pinned staging for the sampling plan tables, and the event that says the last upload from it is done
+  ds_plan_memory plan_memory;   // of the largest sampling plan so far, while no plan has it
   char* h_stage;
   size_t h_stage_bytes;
   hipEvent_t stage_ev;
@@ -142,11 +150,16 @@ int ds_mail_fetch(ds_ctx* ctx, int count);
 
 // ---- stages (host drivers; each launches its kernels on ctx->stream) ----
 struct ds_plan {
+  ds_ctx* owner = nullptr;   // gets the tables' memory back
   int64_t n, k, K, H;
   int enumerate;
   int64_t enum_upto;        // size classes 1..enum_upto are enumerated (every subset once), the rest sampled
   std::vector<int64_t> b;   // class boundaries b[0..H]
   std::vector<float> wtab;  // weight per pair class, wtab[0..H]
+  ds_plan() = default;
+  ds_plan(const ds_plan&) = delete;
+  ds_plan& operator=(const ds_plan&) = delete;
+  ~ds_plan();
 };
 int ds_make_plan(ds_ctx* ctx, int64_t n, int64_t n_samples, ds_plan* plan, int weighting = DS_WEIGHT_CLASS_MASS,
                  int saturate = 0);

@@ -67,6 +67,20 @@ def test_host_plan_tables_equal_the_oracle_bit_for_bit():
         binding.plan_tables(100, 3)
 
 
+# blocks of 32 masses: none, one to a class short or over, with and without the class of n / 2; counts of pairs on both sides of 2^31
+@pytest.mark.parametrize("n", [3, 62, 64, 65, 66, 67, 128, 131, 2049])
+@pytest.mark.parametrize("ns", [100, 2 ** 32 - 4, 2 ** 32 + 2, 2 ** 33])
+def test_host_plan_tables_at_the_edges_of_their_blocks(n, ns):
+    import numpy as np
+    from oracle import sampling
+    from paper_2506_22668_amd import binding
+    b, wtab = binding.plan_tables(n, ns)
+    plan = sampling.allocation(n, ns)
+    assert np.array_equal(wtab.view(np.uint32), plan["wtab"].view(np.uint32))
+    if not plan["enumerate"]:
+        assert np.array_equal(b, plan["b"])
+
+
 def test_host_plan_tables_with_saturated_classes_equal_the_oracle():
     import numpy as np
     from oracle import sampling
