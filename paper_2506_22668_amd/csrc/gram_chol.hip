@@ -1004,12 +1004,79 @@ __device__ __forceinline__ void chol_diag_body(double* M, int64_t ld, int64_t j0
   }
 }
 
+// a >= b of the p-th pair
+__device__ __forceinline__ void small_pair(int p, int& a, int& b) {
+  a = (int)((sqrtf(8.f * (float)p + 1.f) - 1.f) * 0.5f);
+  while (a * (a + 1) / 2 > p) --a;
+  while ((a + 1) * (a + 2) / 2 <= p) ++a;
+  b = p - a * (a + 1) / 2;
+}
+
+// The system matrix of a game of at most 64 players from the parts of its counts (as sum_slices_row_mean, stats and build_matrix form
+// it), one workgroup; S, mean: its LDS. The elimination follows in the same kernel, a launch fewer.
+__device__ __forceinline__ void small_system(const double* part, int parts, int n, int* flag, double (&S)[kTile][NB + 1],
+                                             double (&mean)[NB], DiagRegs& mt) {
+  constexpr int kAhead = 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, pairs = n * (n + 1) / 2;
+  for (int p = tid; p < pairs; p += kThreads) {
+    double sum = 0.0;
+    for (int i0 = 0; i0 < parts; i0 += kAhead) {   // (all of a step's loads in flight; past the end the last part is read again)
+      double v[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) v[u] = part[(size_t)(i0 + u < parts ? i0 + u : parts - 1) * pairs + p];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) sum += i0 + u < parts ? v[u] : 0.0;
+    }
+    int a, b;
+    small_pair(p, a, b);
+    S[a][b] = sum;
+    S[b][a] = sum;
+  }
+  __syncthreads();
+  if (tid < n) {
+    double sum = 0.0;
+    for (int b = 0; b < n; ++b) sum += S[tid][b];
+    mean[tid] = sum / (double)n;
+  }
+  __syncthreads();
+  double mu = 0.0, tr = 0.0;
+  for (int i = 0; i < n; ++i) {
+    mu += mean[i];
+    tr += S[i][i];
+  }
+  mu /= (double)n;
+  tr -= (double)n * mu;
+  double gamma = tr / (double)(n > 1 ? n - 1 : 1);
+  if (!(gamma > 0.0)) gamma = 1.0;
+  if (tid == 0) {
+    *flag = 0;
+    *(double*)(flag + 2) = 256.0 * (double)n * 0x1p-52 * ((tr > 0.0 ? tr : 0.0) + gamma) / (double)n;   // see build_matrix_kernel
+    __threadfence_block();
+  }
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    const int t = wave + 4 * u;
+    if (t >= kDiagTiles) break;
+    int r0, c0;
+    diag_subtile(t, r0, c0);
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const int r = r0 + 4 * r4 + (lane >> 4), c = c0 + (lane & 15);
+      mt.v[u][r4] = r < n && c < n ? S[r][c] - mean[r] - mean[c] + mu + gamma / (double)n : (r == c ? 1.0 : 0.0);
+    }
+  }
+  __syncthreads();   // every wave has read the sums before the block's tile is written
+}
+
+// part (or nullptr: the block lies in M): the counts of a small game
 __global__ __launch_bounds__(kThreads) void chol_diag_kernel(double* M, int64_t ld, int64_t j0, int nb, double* linv_out,
-                                                             int* flag) {
+                                                             int* flag, const double* part, int parts) {
   __shared__ double S[kTile][NB + 1];
   __shared__ double Y[kTile][NB + 1];
+  __shared__ double mean[NB];
   DiagRegs mt;
-  load_diag_block(M, ld, j0, nb, mt);
+  if (part) small_system(part, parts, nb, flag, S, mean, mt);
+  else load_diag_block(M, ld, j0, nb, mt);
   chol_diag_body(M, ld, j0, nb, linv_out, flag, nullptr, S, Y, mt);
 }
 
@@ -1593,14 +1660,6 @@ constexpr int kSmallPerThread = (kSmallPairs + kSmallThreads - 1) / kSmallThread
 constexpr int kSmallChunk = 512;    // rows per step
 constexpr int kSmallParts = 64;     // workgroups at most, each with a part of the rows
 
-// a >= b of the p-th pair
-__device__ __forceinline__ void small_pair(int p, int& a, int& b) {
-  a = (int)((sqrtf(8.f * (float)p + 1.f) - 1.f) * 0.5f);
-  while (a * (a + 1) / 2 > p) --a;
-  while ((a + 1) * (a + 2) / 2 <= p) ++a;
-  b = p - a * (a + 1) / 2;
-}
-
 // part[blockIdx.x][p] = sum of the weights of this workgroup's rows that hold both players of pair p. The threads form
 // groups of (at least) one per pair, which take the rows in turn.
 __global__ __launch_bounds__(kSmallThreads) void small_gram_kernel(const uint64_t* Z, const float* w, int64_t R, int paired, int n,
@@ -1649,66 +1708,6 @@ __global__ __launch_bounds__(kSmallThreads) void small_gram_kernel(const uint64_
 #pragma unroll
   for (int u = 0; u < kSmallPerThread; ++u)
     if (t + u * width < pairs) part[(size_t)blockIdx.x * pairs + t + u * width] = acc[u];
-}
-
-// The system matrix from the parts (as sum_slices_row_mean, stats and build_matrix form it) and its factor: one workgroup.
-__global__ __launch_bounds__(kThreads) void small_system_kernel(const double* part, int parts, int n, int64_t ld, double* M,
-                                                                double* linv, int* flag) {
-  __shared__ double S[kTile][NB + 1];
-  __shared__ double Y[kTile][NB + 1];
-  __shared__ double mean[NB];
-  constexpr int kAhead = 16;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, pairs = n * (n + 1) / 2;
-  for (int p = tid; p < pairs; p += kThreads) {
-    double sum = 0.0;
-    for (int i0 = 0; i0 < parts; i0 += kAhead) {   // (all of a step's loads in flight; past the end the last part is read again)
-      double v[kAhead];
-#pragma unroll
-      for (int u = 0; u < kAhead; ++u) v[u] = part[(size_t)(i0 + u < parts ? i0 + u : parts - 1) * pairs + p];
-#pragma unroll
-      for (int u = 0; u < kAhead; ++u) sum += i0 + u < parts ? v[u] : 0.0;
-    }
-    int a, b;
-    small_pair(p, a, b);
-    S[a][b] = sum;
-    S[b][a] = sum;
-  }
-  __syncthreads();
-  if (tid < n) {
-    double sum = 0.0;
-    for (int b = 0; b < n; ++b) sum += S[tid][b];
-    mean[tid] = sum / (double)n;
-  }
-  __syncthreads();
-  double mu = 0.0, tr = 0.0;
-  for (int i = 0; i < n; ++i) {
-    mu += mean[i];
-    tr += S[i][i];
-  }
-  mu /= (double)n;
-  tr -= (double)n * mu;
-  double gamma = tr / (double)(n > 1 ? n - 1 : 1);
-  if (!(gamma > 0.0)) gamma = 1.0;
-  if (tid == 0) {
-    *flag = 0;
-    *(double*)(flag + 2) = 256.0 * (double)n * 0x1p-52 * ((tr > 0.0 ? tr : 0.0) + gamma) / (double)n;   // see build_matrix_kernel
-    __threadfence_block();
-  }
-  DiagRegs mt;
-#pragma unroll
-  for (int u = 0; u < 3; ++u) {
-    const int t = wave + 4 * u;
-    if (t >= kDiagTiles) break;
-    int r0, c0;
-    diag_subtile(t, r0, c0);
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      const int r = r0 + 4 * r4 + (lane >> 4), c = c0 + (lane & 15);
-      mt.v[u][r4] = r < n && c < n ? S[r][c] - mean[r] - mean[c] + mu + gamma / (double)n : (r == c ? 1.0 : 0.0);
-    }
-  }
-  __syncthreads();   // every wave has read the sums before the block's tile is written
-  chol_diag_body(M, ld, 0, n, linv, flag, nullptr, S, Y, mt);
 }
 
 // cpart[blockIdx.x][a] = sum over this workgroup's rows that hold player a of the right-hand side's coefficients
@@ -1896,7 +1895,8 @@ int ds_gram_begin(ds_ctx* ctx, ds_gram_state* gs, const uint64_t* Z, const float
     hipLaunchKernelGGL(small_gram_kernel, dim3(parts), dim3(kSmallThreads), 0, st, Z, w, R, paired, (int)n, gs->Gp);
     DS_TRY(ds_kernel_mark(ctx, 1, 1));
     DS_TRY(ds_kernel_mark(ctx, 2, 0));
-    hipLaunchKernelGGL(small_system_kernel, dim3(1), dim3(kThreads), 0, st, gs->Gp, (int)parts, (int)n, ld, gs->M, gs->linv, gs->flag);
+    hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(kThreads), 0, st, gs->M, ld, (int64_t)0, (int)n, gs->linv, gs->flag, (const double*)gs->Gp,
+                       (int)parts);
     DS_HIP(ctx, hipGetLastError());
     return ds_kernel_mark(ctx, 2, 1);
   }
@@ -1927,7 +1927,7 @@ int ds_gram_begin(ds_ctx* ctx, ds_gram_state* gs, const uint64_t* Z, const float
   // the first diagonal block does not involve the right-hand side either: factorised here, off the path that waits
   // for the model outputs
   hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(kThreads), 0, st, gs->M, ld, (int64_t)0, (int)(n < NB ? n : NB), gs->linv,
-                     gs->flag);
+                     gs->flag, (const double*)nullptr, 0);
   DS_HIP(ctx, hipGetLastError());
   return DS_OK;
 }
@@ -2002,7 +2002,8 @@ static int gram_factor(ds_ctx* ctx, const ds_gram_state* gs, int64_t rows_total,
     const int nb = (int)(n - j0 < NB ? n - j0 : NB);
     double* li = linv + (size_t)(j0 / NB) * NB * NB;
     // a diagonal block has a launch of its own only if the update before it did not factorise it already
-    if (!diag_done) hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(kThreads), 0, st, M, ld, j0, nb, li, gs->flag);
+    if (!diag_done) hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(kThreads), 0, st, M, ld, j0, nb, li, gs->flag,
+                                       (const double*)nullptr, 0);
     diag_done = false;
     const int64_t rest = rows_total - j0 - nb;
     // One launch per step where its workgroups, one to a compute unit, run in a single round; above that the panel's own

@@ -30,6 +30,7 @@ def ctx_tiny():
     # a wave per pair below that: the most columns of each instance and one more, a workgroup that is not full
     (511, 600, 2, 1), (512, 602, 3, 1), (513, 604, 4, 1), (1024, 700, 5, 1), (1025, 702, 6, 1), (2048, 900, 7, 1), (2049, 902, 8, 1),
     (4095, 2002, 9, 1), (26, 6, 10, 1),
+    (4095, 2002, 6609, 7), (4095, 2002, 6632, 7),   # several keys equal a threshold: the lowest columns go first
 ])
 def test_sampler_bit_exact(ctx_tiny, n, ns, seed, tag):
     ctx, _ = ctx_tiny
