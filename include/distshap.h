@@ -163,7 +163,7 @@ typedef struct ds_tuning {
                                  layer reads more entries than fit on chip). 2, 3 and 4 need 256 rows or more and fall
                                  back to 1 where they do not apply (a test hook: the results agree to rounding) */
   int32_t cgls_dense_div;     /* CGLS on large games: pair rows with more than n / div players stay bit-packed and
-                                 are multiplied on the int8 matrix cores, the sparser ones become (row, column)
+                                 are multiplied on the matrix cores, the sparser ones become (row, column)
                                  entries multiplied through LDS (default 64, the measured optimum; 32..65536) */
   int32_t pair_lists;         /* ds_explain with long mask rows: the sampler also writes the players of every sparse
                                  small member (at most n / div players; 0 = default div 64, a list of half the bit row's

@@ -417,7 +417,7 @@ __global__ void pair_sizes_kernel(const int32_t* sz, int64_t R, int32_t thr, int
 }
 
 // ---- small games: an iteration in two launches ----
-// With a few thousand players and rows an iteration of the loop above is seven launches of 3 to 11 us that each
+// With a few thousand players and rows an iteration of the loop above is six launches of 3 to 11 us that each
 // start by finishing the reduction of the one before, so what bounds it is the chain of launches. Here every
 // workgroup redoes the vector work of all n (R) entries itself, straight into the LDS copy that its products gather
 // from (a few dozen KB per workgroup, from L2), and only the owner of a slice writes it back. What is left is
@@ -816,7 +816,7 @@ int ds_solve_cgls_impl(ds_ctx* ctx, int64_t n, int64_t k, const uint64_t* Z, con
   // ---- storage for the two products ----
   // Paired, size-sorted rows of a large game: the small members with at most n/div players become
   // (row, column) entries in 2-D tiles that serve both products through LDS, the denser tail stays a
-  // bitmap (rows of Z itself, plus a transposed copy) and is multiplied on the int8 matrix cores; both
+  // bitmap (rows of Z itself, plus a transposed copy) and is multiplied on the matrix cores; both
   // in fixed point with exact integer sums. Otherwise: plain bitmap and its transpose, set bits walked
   // one by one in fp64.
   bool hybrid = false;
