@@ -641,11 +641,17 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
     lists.offset = (int64_t*)ds_arena_alloc(ctx, (size_t)(k / 2) * 8);
     if (!lists.entries || !lists.offset) return ds_fail(ctx, DS_EINTERNAL, "explain: arena exhausted");
   }
-  // The shared first transform and the predicted class depend only on the computational graph:
-  // they run on the side stream while the main stream draws the coalitions.
-  DS_HIP(ctx, hipEventRecord(ctx->fork_ev, st));
-  DS_HIP(ctx, hipStreamWaitEvent(ctx->side, ctx->fork_ev, 0));
-  {
+  const bool direct = n >= 2 && (o.solver == DS_SOLVER_GRAM_CHOL || (o.solver == DS_SOLVER_AUTO && n <= 16384));
+  const bool ahead = direct && ds_gram_ahead_applies(n);
+  // The shared first transform and the predicted class depend only on the computational graph: they run on the side stream while the
+  // main stream draws the coalitions. Where the solver factorises ahead the side stream has the longest chain (Gram matrix, factor),
+  // which begins as soon as the coalitions are drawn: they follow the sampler on the main stream then. (1,010 players: 0.752 ms,
+  // now 0.686; queued in front of the Gram kernels 0.69; with sampler, Gram matrix and factor on one stream 0.70 to 0.72, 12 players
+  // 0.21 instead of 0.18: the host takes longer to get the first kernels under way.)
+  const bool model_first = !ahead;
+  if (model_first) {
+    DS_HIP(ctx, hipEventRecord(ctx->fork_ev, st));
+    DS_HIP(ctx, hipStreamWaitEvent(ctx->side, ctx->fork_ev, 0));
     ctx->stream = ctx->side;
     const int prc = ds_prepare_model(ctx, cg);  // its temporaries stay allocated below `mark`
     ctx->stream = st;
@@ -670,8 +676,6 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   // factorised there too, and the right-hand side follows with a forward solve. The inference then takes no more compute
   // units than its rounds of workgroups need, and where that is more than half of them it starts behind the Gram kernels
   // (1,010 players, 157 units: the Gram kernels take 76 us in front of it, 164 beside it, and the factorisation waits for them).
-  const bool direct = n >= 2 && (o.solver == DS_SOLVER_GRAM_CHOL || (o.solver == DS_SOLVER_AUTO && n <= 16384));
-  const bool ahead = direct && ds_gram_ahead_applies(n);
   ds_gram_state gs;
   if (direct) {
     DS_TRY(ds_gram_alloc(ctx, n, k, 1, &gs));   // (stays allocated below `mark2`)
@@ -681,12 +685,13 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
     const int grc = ds_gram_begin(ctx, &gs, Z, w);
     ctx->stream = st;
     DS_TRY(grc);
-    if (ahead && gs.formed && k > (int64_t)ctx->num_cus * 32) DS_HIP(ctx, hipStreamWaitEvent(st, gs.formed, 0));
     if (!ahead) DS_HIP(ctx, hipEventRecord(ctx->join2_ev, ctx->side));
   }
+  if (!model_first) DS_TRY(ds_prepare_model(ctx, cg));   // (its temporaries stay allocated below `mark2`)
+  if (ahead && gs.formed && k > (int64_t)ctx->num_cus * 32) DS_HIP(ctx, hipStreamWaitEvent(st, gs.formed, 0));
   const size_t mark2 = ctx->arena_used;
 
-  DS_HIP(ctx, hipStreamWaitEvent(st, ctx->join_ev, 0));
+  if (model_first) DS_HIP(ctx, hipStreamWaitEvent(st, ctx->join_ev, 0));
   ctx->lists = lists;
   const int erc = ds_eval_impl(ctx, cg, Z, k, o.score, y, DS_EVAL_PAIRED | (ahead ? DS_EVAL_BESIDE : 0), n >= 2 ? sz : nullptr);  // the sampler's rows are complementary pairs
   ctx->lists = ds_pair_lists{};
