@@ -14,6 +14,7 @@
 #include <stdlib.h>
 
 #include "internal.h"
+#include "small_game.h"
 #include "solve_common.h"
 
 namespace {
@@ -1653,23 +1654,18 @@ inline int sparse_divisor(const ds_ctx* ctx) {
 // One mask word per row and one diagonal block: four launches in place of fourteen, each of which costs its start and a
 // trip through memory for a few kilobytes of matrix (an explanation of 12 players, 4,096 coalitions: 324 us; now 232). Sums of the weights themselves
 // in fp64, in a fixed order; a pair of players costs six instructions per row.
-constexpr int kSmallMax = 64;
-constexpr int kSmallThreads = 1024;
-constexpr int kSmallPairs = kSmallMax * (kSmallMax + 1) / 2;
-constexpr int kSmallPerThread = (kSmallPairs + kSmallThreads - 1) / kSmallThreads;
 constexpr int kSmallChunk = 512;    // rows per step
 constexpr int kSmallParts = 64;     // workgroups at most, each with a part of the rows
 
-// part[blockIdx.x][p] = sum of the weights of this workgroup's rows that hold both players of pair p. The threads form
-// groups of (at least) one per pair, which take the rows in turn.
+// part[blockIdx.x][p] = sum of the weights of this workgroup's rows that hold both players of pair p (the threads' shares: small_game.h).
 __global__ __launch_bounds__(kSmallThreads) void small_gram_kernel(const uint64_t* Z, const float* w, int64_t R, int paired, int n,
                                                                    double* part) {
   __shared__ uint64_t zs[kSmallChunk];
   __shared__ double ws[kSmallChunk];
   __shared__ double red[kSmallThreads];
   const int tid = threadIdx.x, pairs = n * (n + 1) / 2;
-  const int width = pairs < kSmallThreads ? (pairs + 63) & ~63 : kSmallThreads;   // threads of a group
-  const int groups = kSmallThreads / width, g = tid / width, t = tid - g * width;
+  const ds_small_share mine = ds_small_share_of(pairs, tid);
+  const int width = mine.width, groups = mine.groups, t = mine.at;
   uint64_t mask[kSmallPerThread];
   double acc[kSmallPerThread];
 #pragma unroll
@@ -1690,8 +1686,8 @@ __global__ __launch_bounds__(kSmallThreads) void small_gram_kernel(const uint64_
       ws[tid] = (double)used_row_weight(w, r0 + tid, paired);
     }
     __syncthreads();
-    if (g < groups)
-      for (int i = g; i < count; i += groups) {
+    if (ds_small_adds(mine))
+      for (int i = mine.group; i < count; i += groups) {
         const uint64_t z = zs[i];
         const double wi = ws[i];
 #pragma unroll
@@ -1702,9 +1698,9 @@ __global__ __launch_bounds__(kSmallThreads) void small_gram_kernel(const uint64_
   if (groups > 1) {
     red[tid] = acc[0];
     __syncthreads();
-    if (g > 0) return;
-    for (int i = 1; i < groups; ++i) acc[0] += red[i * width + t];
   }
+  if (!ds_small_stores(mine)) return;
+  for (int i = 1; i < groups; ++i) acc[0] += red[i * width + t];
 #pragma unroll
   for (int u = 0; u < kSmallPerThread; ++u)
     if (t + u * width < pairs) part[(size_t)blockIdx.x * pairs + t + u * width] = acc[u];

@@ -769,9 +769,10 @@ def test_gram_cholesky_mid_size_crosses_every_factorisation_regime(ctx_tiny):
 
 # Which rows are sparse is decided 64 rows at a time: rows of more than 64 words (copied in two rounds), a last word of a
 # few rows, a single word; and the sizes up to which the sparse rows' tiles ride in the column-wise kernel's launch. Games of
-# at most 64 players: one pair of players per thread and one more, more rows than a workgroup's step holds.
+# at most 64 players: one pair of players per thread and one more, more rows than a workgroup's step holds; two groups of threads
+# exactly (31), one and waves that are left over (32 to 43), a last workgroup of a single row (37, paired).
 @pytest.mark.parametrize("n,ns", [(4161, 17030), (65, 512), (1408, 6000), (1409, 6000), (44, 400),
-                                  (45, 400), (64, 80000), (3, 64)])
+                                  (45, 400), (64, 80000), (3, 64), (31, 386), (32, 386), (36, 386), (37, 8066), (43, 386)])
 def test_gram_row_classes(ctx_tiny, n, ns):
     from paper_2506_22668_amd import Options, DS_SOLVER_GRAM_CHOL
     ctx, _ = ctx_tiny
