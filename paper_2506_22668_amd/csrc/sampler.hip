@@ -156,11 +156,15 @@ struct SampleArgs {
 // 1,010 columns was a chain of barriers around four generator calls a lane: 10,000 pairs 70 us, now 16.
 constexpr int64_t kWaveMax = 4096;   // (from there on the one-pass kernel)
 constexpr int kWavePairs = 4;        // waves, pairs, of a workgroup
+// Workgroups in x direction; the y direction has the rest, as 2^32 threads or more in one direction (2^26 pairs) are refused. (A loop over
+// pairs instead: its invariants stay in scalar registers, of which up to 247 are spilled.)
+constexpr int64_t kWaveGridX = 1 << 16;
 template <int CALLS>
 __global__ __launch_bounds__(64 * kWavePairs) void sample_pairs_wave_kernel(SampleArgs a) {
   const int lane = threadIdx.x & 63;
   const int n = (int)a.n, words32 = 2 * (int)a.W;
-  const int64_t r = a.pair_begin + (int64_t)blockIdx.x * kWavePairs + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t r = a.pair_begin + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kWavePairs +
+                    __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   if (r >= a.pair_end) return;
   const int64_t o = 2 * (r - a.pair_begin);
   uint32_t* const row_small = (uint32_t*)(a.Z + o * a.W);
@@ -849,7 +853,8 @@ int ds_sample_launch(ds_ctx* ctx, const ds_plan& plan, uint64_t seed, uint32_t t
                                        : plan.n <= 1024 ? sample_pairs_wave_kernel<4>
                                        : plan.n <= 2048 ? sample_pairs_wave_kernel<8>
                                                         : sample_pairs_wave_kernel<16>;
-      hipLaunchKernelGGL(kern, dim3((unsigned)((pairs + kWavePairs - 1) / kWavePairs)), dim3(64 * kWavePairs), 0, ctx->stream, a);
+      const int64_t groups = (pairs + kWavePairs - 1) / kWavePairs, gy = (groups + kWaveGridX - 1) / kWaveGridX;
+      hipLaunchKernelGGL(kern, dim3((unsigned)((groups + gy - 1) / gy), (unsigned)gy), dim3(64 * kWavePairs), 0, ctx->stream, a);
     } else {
       if (a.window_cap > 4096) a.window_cap = 4096;
       hipLaunchKernelGGL(sample_pairs_kernel<256>, dim3((unsigned)blocks), dim3(256), (size_t)a.window_cap * 8, ctx->stream, a);

@@ -31,6 +31,7 @@ def ctx_tiny():
     (511, 600, 2, 1), (512, 602, 3, 1), (513, 604, 4, 1), (1024, 700, 5, 1), (1025, 702, 6, 1), (2048, 900, 7, 1), (2049, 902, 8, 1),
     (4095, 2002, 9, 1), (26, 6, 10, 1),
     (4095, 2002, 6609, 7), (4095, 2002, 6632, 7),   # several keys equal a threshold: the lowest columns go first
+    (27, 524288, 10, 1), (27, 524290, 11, 1),   # as many workgroups as one direction of the grid takes, and one more
 ])
 def test_sampler_bit_exact(ctx_tiny, n, ns, seed, tag):
     ctx, _ = ctx_tiny
@@ -85,6 +86,20 @@ def test_sampler_pair_ranges_equal_the_full_run(ctx_tiny):
         assert torch.equal(Zp, Z[2 * r0:2 * r1])
         assert torch.equal(wp, w[2 * r0:2 * r1])
         assert torch.equal(szp, sz[2 * r0:2 * r1])
+
+
+def test_sampler_takes_more_pairs_than_one_direction_of_a_grid(ctx_tiny):
+    """2^26 pairs at four pairs to 256 threads are 2^32 threads."""
+    ctx, _ = ctx_tiny
+    n, ns, seed, tag = 28, 2 ** 27 + 6, 17, 3
+    say(f"sampler n={n} n_samples={ns}")
+    Z, w, sz = ctx.sample(n, ns, seed, tag)
+    K = Z.shape[0] // 2
+    assert K == 2 ** 26 + 3
+    assert bool(((Z[0::2] ^ Z[1::2]) == 2 ** n - 1).all()) and bool((sz[0::2] + sz[1::2] == n).all())
+    for lo, hi in [(0, 300), (K // 2 - 150, K // 2 + 150), (K - 300, K)]:
+        Zr, wr, szr = ctx.sample_range(n, ns, seed, tag, lo, hi)
+        assert torch.equal(Z[2 * lo:2 * hi], Zr) and torch.equal(w[2 * lo:2 * hi], wr) and torch.equal(sz[2 * lo:2 * hi], szr)
 
 
 def test_sampler_rejects_bad_arguments(ctx_tiny):
