@@ -104,6 +104,7 @@ __global__ __launch_bounds__(kWeightThreads) void gram_weights_kernel(const floa
 // read the rows' weights back word by word, and two that cleared and summed for them, it took 42 us at 10,000 rows of 1,010 columns; the
 // two kernels here take 11.)
 constexpr int kClassWaves = 16;
+constexpr int64_t kClassGridX = 1 << 14;   // workgroups in x direction, the rest in y: 2^32 threads in one direction (2^28 rows) are refused
 __global__ __launch_bounds__(64 * kClassWaves) void gram_row_class_kernel(const uint64_t* Z, int64_t R, int64_t W, int64_t n,
                                                                           int64_t row_step, const float* gw, const double* scale,
                                                                           int sparse_divisor, float dense_fraction, uint64_t* Zc,
@@ -112,7 +113,8 @@ __global__ __launch_bounds__(64 * kClassWaves) void gram_row_class_kernel(const 
   constexpr int kRows = 64 / kClassWaves;
   __shared__ int set[64];   // columns set in a row of the word
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t wd = blockIdx.x, r0 = wd * 64 + wave * kRows;
+  const int64_t wd = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, r0 = wd * 64 + wave * kRows;
+  if (wd * 64 >= R) return;
   const double sc = scale[0];
   const uint64_t* zr[kRows];
   int c[kRows];
@@ -1904,7 +1906,8 @@ int ds_gram_begin(ds_ctx* ctx, ds_gram_state* gs, const uint64_t* Z, const float
   // sparse rows: row-wise outer products; the rest (bits in `keep`) column-wise
   const int64_t row_step = paired ? 2 : 1;
   hipLaunchKernelGGL(gram_weights_kernel, dim3(1), dim3(kWeightThreads), 0, st, w, R, paired, gw, gscale);
-  hipLaunchKernelGGL(gram_row_class_kernel, dim3((unsigned)RW), dim3(64 * kClassWaves), 0, st, Z, R, W, n, row_step, gw, gscale,
+  const int64_t class_y = (RW + kClassGridX - 1) / kClassGridX;
+  hipLaunchKernelGGL(gram_row_class_kernel, dim3((unsigned)((RW + class_y - 1) / class_y), (unsigned)class_y), dim3(64 * kClassWaves), 0, st, Z, R, W, n, row_step, gw, gscale,
                      sparse_divisor(ctx), dense_fraction(ctx), Zc, (unsigned long long*)keep, (unsigned long long*)wq, wu, uni);
   const unsigned tiles = nblocks(n, kTile);
   DS_TRY(ds_kernel_mark(ctx, 1, 0));

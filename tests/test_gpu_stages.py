@@ -787,7 +787,8 @@ def test_gram_cholesky_mid_size_crosses_every_factorisation_regime(ctx_tiny):
 # at most 64 players: one pair of players per thread and one more, more rows than a workgroup's step holds; two groups of threads
 # exactly (31), one and waves that are left over (32 to 43), a last workgroup of a single row (37, paired).
 @pytest.mark.parametrize("n,ns", [(4161, 17030), (65, 512), (1408, 6000), (1409, 6000), (44, 400),
-                                  (45, 400), (64, 80000), (3, 64), (31, 386), (32, 386), (36, 386), (37, 8066), (43, 386)])
+                                  (45, 400), (64, 80000), (3, 64), (31, 386), (32, 386), (36, 386), (37, 8066), (43, 386),
+                                  (70, 1048640)])   # unpaired: one word of rows more than the grid takes in one direction
 def test_gram_row_classes(ctx_tiny, n, ns):
     from paper_2506_22668_amd import Options, DS_SOLVER_GRAM_CHOL
     ctx, _ = ctx_tiny
@@ -805,6 +806,24 @@ def test_gram_row_classes(ctx_tiny, n, ns):
                         Options(solver=DS_SOLVER_GRAM_CHOL, paired=paired))[0].cpu().numpy().astype(np.float64)
         # the column-wise sums are fp32 over 2,048 rows, 2^-24 of an entry, times the condition of the system (1e3 here)
         assert np.abs(got - ref).max() <= 1e-4 * np.abs(ref).max()
+
+
+def test_gram_takes_more_rows_than_one_direction_of_a_grid(ctx_tiny):
+    """2^28 rows at sixteen threads to a row are 2^32 threads. A linear game, whose coefficients are the answer."""
+    from paper_2506_22668_amd import Options, DS_SOLVER_GRAM_CHOL
+    ctx, _ = ctx_tiny
+    n, ns = 65, 2 ** 28 + 64
+    say(f"gram n={n} n_samples={ns}")
+    Z, w, _ = ctx.sample(n, ns, 7, 2)
+    a = np.random.default_rng(5).integers(-64, 65, n).astype(np.float32) / 128   # (every sum of them is exact in float32)
+    y = torch.zeros(Z.shape[0], dtype=torch.float32, device="cuda")
+    for j in range(n):
+        for i in range(0, Z.shape[0], 1 << 26):
+            y[i:i + (1 << 26)] += ((Z[i:i + (1 << 26), j >> 6] >> (j & 63)) & 1).float() * float(a[j])
+    phi = ctx.solve(n, Z, w, y, Options(solver=DS_SOLVER_GRAM_CHOL))[0].cpu().numpy()
+    assert np.abs(phi - a).max() <= 1e-6
+    del Z, w, y
+    torch.cuda.empty_cache()
 
 
 # The 128 x 128 tiles of the wide update start at row 512: 2,304 leaves a last row of tiles that holds nothing but the
