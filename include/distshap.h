@@ -107,10 +107,14 @@ typedef struct ds_report {
   double cgls_rel_residual; /* |s_i| / |s_0| at exit */
   double f_empty;         /* f(no edges) = phi_0 */
   double f_full;          /* f(all edges) */
+  /* stages; they add up to ms_total. ms_eval runs from the drawn coalitions to their scores (with what of the shared first
+   * transform and the predicted class is not hidden behind the sampler). Where the direct solver forms its matrix in front of
+   * the inference (65 to 2,304 players, more than 32 rows per compute unit) that time is in ms_solve. */
   float ms_extract, ms_sample, ms_eval, ms_solve, ms_total;
   /* single-kernel durations inside the stages above (0 when the kernel did not run):
    * the masked-inference kernel over all k rows, the popcount Gram kernel, the
-   * Cholesky factorisation launches, and the CGLS loop (all iterations). */
+   * Cholesky factorisation launches, and the CGLS loop (all iterations). The direct solver's run on a second stream: those of
+   * the matrix, and up to 2,304 players of the factorisation, beside the inference, with which they share the GPU. */
   float ms_k_eval, ms_k_gram, ms_k_chol, ms_k_cgls;
   int64_t num_pairs;      /* K: sampled complementary pairs (rows 2..k-1 are K pairs; 2^(n-1) - 1 when enumerated) */
   /* Algorithmic bytes of each stage: what the step has to move whatever the kernel does, the basis of the

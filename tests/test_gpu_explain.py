@@ -317,6 +317,21 @@ def test_factorising_ahead_of_the_scores_equals_solving_with_them(players):
     ctx.close()
 
 
+def test_time_of_the_inference_holds_no_solver_kernels():
+    """1,010 players: the inference waits for the Gram kernels, and the report has that wait in the solver's time."""
+    ctx = make_context(w := make_workload("c2"))
+    say("report: stages")
+    beyond, gram = [], []
+    for _ in range(5):
+        rep = ctx.explain(w.targets[0], w.n_samples, w.seed)[3]
+        assert abs(rep.ms_extract + rep.ms_sample + rep.ms_eval + rep.ms_solve - rep.ms_total) <= 0.02
+        beyond.append(rep.ms_eval - rep.ms_k_eval)
+        gram.append(rep.ms_k_gram)
+    say(f"  ms_eval - ms_k_eval = {min(beyond):.3f}, ms_k_gram = {min(gram):.3f}")
+    assert min(beyond) < 0.5 * min(gram)
+    ctx.close()
+
+
 def test_directed_players_and_wider_extraction():
     """Directed players (one CSR entry each) and a computational graph wider than the receptive
     field: edges joining two nodes beyond L hops are exact null players."""
