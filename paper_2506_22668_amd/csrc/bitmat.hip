@@ -277,8 +277,7 @@ __global__ __launch_bounds__(256) void quantize_kernel(const double* x, int64_t 
 }
 
 // A workgroup's units (a chunk of a row group each) are consecutive, row group by row group: cut evenly (even_units = their
-// total: workgroup b of G takes [b u / G, (b + 1) u / G) and leaves the sums of a row group in the slot that counts the workgroups from the
-// group's first one on; a plan clears the slots that nobody writes), or `groups` to a row group (even_units = 0). The mask words of
+// total: mm_split.h; a plan clears the slots that nobody writes), or `groups` to a row group (even_units = 0). The mask words of
 // the two units ahead are on their way while one is used, across row groups too. Every load is issued unconditionally (behind the last
 // unit, of one cache line): a conditional one would make the wait for the current words a wait for all of them.
 __global__ __launch_bounds__(kMmThreads, 2) void bit_spmv_mm_kernel(const uint64_t* B, int64_t rows, int64_t cols, int64_t stride,
@@ -297,11 +296,11 @@ __global__ __launch_bounds__(kMmThreads, 2) void bit_spmv_mm_kernel(const uint64
   int64_t left;        // units from it on
   int64_t slot = 0;    // where this workgroup's sums of the row group go
   if (even_units > 0) {
-    const int64_t u0 = bid * even_units / G;
-    left = (bid + 1) * even_units / G - u0;
+    const int64_t u0 = ds_mm_even_begin(bid, G, even_units);
+    left = ds_mm_even_begin(bid + 1, G, even_units) - u0;
     rg = u0 / n_chunks;
     c = u0 - rg * n_chunks;
-    slot = bid - ((rg * n_chunks + 1) * G - 1) / even_units;   // (a later row group's first workgroup is this one)
+    slot = bid - ds_mm_even_owner(rg * n_chunks, G, even_units);   // (a later row group's first workgroup is this one)
   } else {
     const int64_t row_groups = G / groups;   // (consecutive workgroups: consecutive row groups of one column group)
     slot = bid / row_groups;

@@ -1,22 +1,26 @@
-// How the matrix-core product of the bit-packed rows (bitmat.hip) is cut into column groups. Host code only.
+// How the matrix-core product of the bit-packed rows (bitmat.hip) is cut into the shares of its workgroups. For host and, the shares of an
+// even cut, device.
 #pragma once
 #include <stdint.h>
+#ifdef __HIPCC__
+#define DS_MM_FN __host__ __device__ inline
+#else
+#define DS_MM_FN inline
+#endif
 
 struct ds_mm_split {
   int64_t cpg, groups;   // chunks per column group; column groups
 };
 
-// Two workgroups fit a compute unit (registers), so a launch runs in rounds of up to 2 x CUs of them. Every split is
-// priced, in us as measured on this card, and the cheapest taken. A round costs, per chunk of its groups, 2.6 with two
+// Column groups: a workgroup per row group and column group. Two workgroups fit a compute unit, so a launch runs in rounds of up
+// to 2 x CUs of them. Every split is priced and the cheapest taken. A round costs, per chunk of its groups, 2.6 us with two
 // workgroups on a unit, also where only some units hold two, and 1.6 with at most one on each: a workgroup waits for the
 // latency of its loads and, where two share a unit, for the other. A group's digit sums (`sum_bytes` a row) are written
-// and read once more by whoever adds them up: 1 us per MB. The three figures are fitted to sweeps of the number of
-// groups over both products of ten games (matrices of 9 MB to 7.2 GB; inside and outside of the Infinity Cache they
-// differ less than the fit is off). us per CGLS iteration, against a price that grew with the number of workgroups in
-// flight and took digit sums for 1.5 times as dear (dense rows x columns of the forward product):
-//   34,267 x 99,981  335.0 -> 322.9 (428 MB; 3 and 1 groups instead of 7 and 5 left a fifth of the places empty)
-//   32,409 x 200,003 558.4 -> 537.7    15,121 x 500,009 618.7 -> 613.4    7,906 x 20,011 76.1 -> 72.7
-//   3,425 x 100,428 86.5 -> 86.9; 57,572 x 1,000,175, 9,424 x 300,007, 18,176 x 50,021 and 10,280 x 99,981: same splits
+// and read once more by whoever adds them up: 1 us per MB. The three figures were fitted to the product on the int8 instruction, with 32
+// bytes of sums a row, and the caller still states 32 where a row has 16. Their order of the splits holds for the present kernel: with
+// the number of groups of either product of eleven games swept, and the even cut below, what is chosen was within 1.5 % of the
+// fastest CGLS iteration but for two (us per iteration; tests/test_mm_split.py has the sweeps):
+//   500,009 x 15,102: 562, one column group 542;  100,428 x 3,414: 75.4, one column group 73.8
 inline double ds_mm_price(int64_t num_cus, int64_t wgs, int64_t chunks, int64_t sums) {
   const int64_t cap = 2 * num_cus, rest = wgs % cap;
   const double per_chunk = 2.6 * (double)(wgs / cap) + (rest == 0 ? 0.0 : rest <= num_cus ? 1.6 : 2.6);
@@ -45,18 +49,21 @@ inline ds_mm_split ds_mm_choose_split(int64_t num_cus, int64_t rows, int64_t row
   return best;
 }
 
-// The same work cut evenly: the chunks of all row groups in one line, row group by row group, workgroup b of `wgs` takes
-// units [b u / wgs, (b + 1) u / wgs) of u. A row group's sums then come from up to `slots` workgroups.
+// The same work cut evenly: the units (a chunk of a row group each) of all row groups in one line, row group by row group; workgroup b of
+// `wgs` takes units ds_mm_even_begin(b) to ds_mm_even_begin(b + 1) of u. A row group's sums then come from up to `slots` workgroups: each
+// leaves its own in the slot that counts the workgroups from the row group's first one on.
 struct ds_mm_even {
   int64_t wgs, slots;    // wgs == 0: the column groups are cheaper
 };
 
+DS_MM_FN int64_t ds_mm_even_begin(int64_t b, int64_t wgs, int64_t units) { return b * units / wgs; }
 // the workgroup that holds unit x
-inline int64_t ds_mm_even_owner(int64_t x, int64_t wgs, int64_t units) { return ((x + 1) * wgs - 1) / units; }
+DS_MM_FN int64_t ds_mm_even_owner(int64_t x, int64_t wgs, int64_t units) { return ((x + 1) * wgs - 1) / units; }
 
-// A workgroup to a compute unit, 1.6 to 1.8 us a unit (with two: 3.2 to 4.1). A workgroup that holds a row group whole meets no more than two others' ends, so that what
-// a cut within row groups costs is the second slot's sums (1 us per MB, as above). Taken where its price is below that of the column groups
-// at the same cost of a unit; no more of one row group than the accumulators hold.
+// A workgroup to a compute unit, 1.6 to 1.8 us a unit (with two: 3.2 to 4.1). A workgroup that holds a row group whole meets no more than
+// two others' ends, so that what a cut within row groups costs is the second slot's sums (1 us per MB, as above). Taken where its price
+// is below that of the column groups at the same cost of a unit; no more of one row group than the accumulators hold. (us per iteration, best
+// number of column groups and even: 34,177 x 99,981 283, 276; 10,253 x 99,981 116.5, 116.3; 9,410 x 300,007 251, 249.)
 inline ds_mm_even ds_mm_choose_even(int64_t num_cus, int64_t rows, int64_t row_groups, int64_t n_chunks, int64_t max_cpg,
                                     int64_t sum_bytes, const ds_mm_split& split) {
   const double unit_us = 1.8;
