@@ -751,6 +751,29 @@ def test_cgls_one_iteration_under_enumeration(ctx_tiny):
     assert rep.cgls_iterations == 1
 
 
+def test_auto_falls_back_where_both_solvers_fill_the_workspace(ctx_tiny):
+    """Many rows, none of which tells the last two players apart: the direct solver's buffers leave no room for those of the iterative one.
+    A linear game, whose minimum-norm solution splits what the two have together."""
+    from paper_2506_22668_amd import Options, DS_SOLVER_CGLS
+    ctx, _ = ctx_tiny
+    n, ns = 4090, 400000
+    say(f"auto fallback n={n} n_samples={ns}")
+    Z, w, _ = ctx.sample(n, ns, 7, 2)
+    last = Z.shape[1] - 1
+    two = (Z[:, last] >> ((n - 2) & 63)) & 1
+    Z[:, last] = (Z[:, last] & ~(1 << ((n - 1) & 63))) | (two << ((n - 1) & 63))
+    a = np.zeros(n, dtype=np.float32)
+    who = np.array([0, 5, 77, 1800, n - 2, n - 1])
+    a[who] = [3.0, -2.0, 0.5, 1.0, 1.5, 0.5]
+    y = torch.zeros(Z.shape[0], dtype=torch.float32, device="cuda")
+    for j in who:
+        y += ((Z[:, j >> 6] >> (int(j) & 63)) & 1).float() * float(a[j])
+    phi, rep, _ = ctx.solve(n, Z, w, y, Options(tol=1e-9))
+    assert rep.solver_used == DS_SOLVER_CGLS
+    a[n - 2:] = 1.0
+    assert np.abs(phi.cpu().numpy() - a).max() <= 1e-5
+
+
 def test_cgls_reports_non_convergence(ctx_tiny):
     from paper_2506_22668_amd import Options, DS_SOLVER_CGLS, DS_ENOTCONV
     ctx, _ = ctx_tiny
