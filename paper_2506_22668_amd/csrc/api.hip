@@ -680,6 +680,11 @@ static int explain_extracted(ds_ctx* ctx, ds_cgraph* cg, int64_t target, int64_t
   // factorised there too, and the right-hand side follows with a forward solve. The inference then takes no more compute
   // units than its rounds of workgroups need, and where that is more than half of them it starts behind the Gram kernels
   // (1,010 players, 157 units: the Gram kernels take 76 us in front of it, 164 beside it, and the factorisation waits for them).
+  // That pays where the factorisation is the longer of the two; us of an explanation, beside and behind the Gram kernels:
+  //   20,000 rows: 600 players 490, 487; 1,010 players 673, 669 (16,000 rows 725, 707); 1,500 players 920, 933; 2,300 players 1,486, 1,436
+  //   40,000 rows: 300 players 571, 612; 600 players 629, 676; 2,300 players 1,787, 1,764
+  //   80,000 rows: 130 players 702, 794; 300 players 828, 962; 1,010 players 1,222, 1,317; 2,300 players 2,361, 2,437
+  // (so with many rows for the players the line has no upper end that it should have).
   ds_gram_state gs;
   if (direct) {
     DS_TRY(ds_gram_alloc(ctx, n, k, 1, &gs));   // (stays allocated below `mark2`)
@@ -824,7 +829,7 @@ int ds_explain_batch(ds_ctx* ctx, const int64_t* targets, int32_t num_targets, i
   if (num_targets == 0) return DS_OK;
   // Several explanations (eight unless the knob says otherwise) are in flight at a time, each on its own worker
   // context and host thread: a single explanation leaves much of the GPU idle in its latency-bound stages.
-  // (Measured on 1,010-player games: 1.53 / 1.21 / 1.00 / 0.96 ms per explanation with 1 / 2 / 4 / 8 in flight; the
+  // (Measured on 1,010-player games: 0.67 / 0.59 / 0.46 / 0.43 ms per explanation with 1 / 2 / 4 / 8 in flight; the
   // launches of all workers go through one runtime, which is what the curve runs into.)
   // A target's place in the outputs depends on the sizes of all targets before it. Every worker extracts its
   // target's computational graph, publishes the size, waits until the sizes before it are known (their workers

@@ -453,8 +453,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 4))
 #pragma unroll
   for (int i = 0; i < 16; ++i) Ts[wi + 8 * (i / 4) + 4 * half + (i % 4)][wj + l32] = accm[i];
   __syncthreads();
-  // slice 0 already holds the sparse rows' part (both triangles): all of a thread's entries are fetched before the
-  // first store (one memory latency instead of sixteen; addresses clamped instead of skipped)
+  // slice 0 already holds the lower tiles of the sparse rows' part, if that had a launch of its own (else it is the last slice): all of a
+  // thread's entries are fetched before the first store (one memory latency instead of sixteen; addresses clamped instead of skipped)
   double prev[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -1015,7 +1015,7 @@ __device__ __forceinline__ void small_pair(int p, int& a, int& b) {
   b = p - a * (a + 1) / 2;
 }
 
-// The system matrix of a game of at most 64 players from the parts of its counts (as sum_slices_row_mean, stats and build_matrix form
+// The system matrix of a game of at most 64 players from the parts of its counts (as sum_slices, row_means, stats and build_matrix form
 // it), one workgroup; S, mean: its LDS. The elimination follows in the same kernel, a launch fewer.
 __device__ __forceinline__ void small_system(const double* part, int parts, int n, int* flag, double (&S)[kTile][NB + 1],
                                              double (&mean)[NB], DiagRegs& mt) {
@@ -1573,7 +1573,7 @@ __global__ __launch_bounds__(kSolveThreads) void chol_forward_kernel(const doubl
 
 // L^T psi = v from the end, phi = psi + (y1 - y0)/n. A wave reads whole rows of a tile (lane = column), and the eight waves'
 // partial sums meet in LDS: lanes that share a column, as in the forward solve, would read 64 bytes of a row each (a launch then
-// takes 20 us instead of 13).
+// takes 20 us instead of 10).
 template <int BLOCKS>
 __global__ __launch_bounds__(kSolveThreads) void chol_back_kernel(const double* M, int64_t ld, int64_t n, int64_t J,
                                                                   const double* linv, double* v, const float* y01, float* phi) {
@@ -1655,7 +1655,12 @@ inline int sparse_divisor(const ds_ctx* ctx) {
 // ---------------- games of at most 64 players ----------------
 // One mask word per row and one diagonal block: four launches in place of fourteen, each of which costs its start and a
 // trip through memory for a few kilobytes of matrix (an explanation of 12 players, 4,096 coalitions: 324 us; now 232). Sums of the weights themselves
-// in fp64, in a fixed order; a pair of players costs six instructions per row.
+// in fp64, in a fixed order; a pair of players costs six instructions per row. A solve alone, us, fourteen launches and four:
+//   13 players    4,096 rows 149, 69    80,000 267, 82     400,000 760, 130     1,600,000 2,560, 317
+//   33 players    4,096 rows 150, 73    80,000 275, 132    400,000 768, 363     1,600,000 2,604, 1,229
+//   64 players    4,096 rows 154, 92    80,000 299, 201    400,000 878, 639     1,600,000 3,020, 2,272
+// The line is drawn by the players alone, as more do not fit one block. Near it and with many rows, the 64 workgroups of these kernels are
+// too few: 65 players, which the general kernels take, 200,000 rows 344 (64 players: 363), 400,000 568 (639), 1,600,000 1,837 (2,273).
 constexpr int kSmallChunk = 512;    // rows per step
 constexpr int kSmallParts = 64;     // workgroups at most, each with a part of the rows
 
